@@ -316,10 +316,9 @@ omc_status omc_transport_open(const void *msg_prefix_host, size_t prefix_bytes, 
  * launch.  Launch order: the full-tile kernels, one per distinct code width among the quantized
  * variables of at least 2048 elements, in ascending width (two for a width whose formats need
  * both rounding variants: formats with man_bits == 23 or a top binade of 2^(105+man_bits) or more
- * use the second), the first of them also serving the fp32 variables as extra workgroups; then
- * up to two kernels for the ragged tails (n % 2048 != 0) of quantized variables; then, only if no
- * full-tile kernel ran, one kernel for the fp32 variables; then the per-variable
- * finalize, if any variable is quantized.  omc_plan_launches gives the count; nevents must be at
+ * use the second), the first of them also serving the ragged tails (n % 2048 != 0) of quantized variables
+ * and the fp32 variables as extra workgroups; only if no full-tile kernel ran, one kernel for the ragged tails
+ * and one for the fp32 variables; then the per-variable finalize, if any variable is quantized.  omc_plan_launches gives the count; nevents must be at
  * least twice that (OMC_ERR_SIZE otherwise).  Results are identical to the plain call.
  * Under OMC_OPT_KEEP_CODES a full-tile kernel may be enqueued as two launches, one event pair around
  * both: packed codes are read and rewritten in place by every step, so when a set holds more than 264 MiB of them, the

@@ -403,15 +403,15 @@ uint64_t omc_plan_aux_elems(const void *plan_host) {
 static uint32_t plan_launches(const PlanHeader *ph) {
     const uint8_t *b = reinterpret_cast<const uint8_t *>(ph);
     const PlanGroup *groups = reinterpret_cast<const PlanGroup *>(b + ph->group_off);
-    uint32_t k = ph->nquant > 0 ? 1u : 0u;
-    bool full = false, fp32 = false;
+    uint32_t full = 0, tails = 0, fp32 = 0;
     for (uint32_t g = 0; g < ph->ngroups; ++g) {
         if (groups[g].nitems == 0) continue;
-        ++k;
-        full = full || groups[g].kind == kGroupFull;
-        fp32 = fp32 || groups[g].kind == kGroupFp32;
+        if (groups[g].kind == kGroupFull) ++full;
+        else if (groups[g].kind == kGroupTail) tails = 1;
+        else fp32 = 1;
     }
-    if (full && fp32) --k;   // the fp32 variables share the first full-tile launch
+    // the ragged tails and the fp32 variables share the first full-tile launch
+    const uint32_t k = (ph->nquant > 0 ? 1u : 0u) + (full > 0 ? full : tails + fp32);
     return k;
 }
 

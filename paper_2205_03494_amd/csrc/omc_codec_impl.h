@@ -12,14 +12,34 @@ struct CodecArgs {
     uint64_t var_off, item_off;
     uint32_t first_item, nitems;
     uint32_t fp32_first, fp32_nitems;   // set calls: copies of fp32 variables appended to the grid
+    uint32_t tail_first, tail_nitems;   // ragged tails, the first workgroups of the grid (set calls: a run of the plan's
+                                        // work items; single variable: 0 or 1, its partial sums go to slot tail_first)
     PlanVar single;
     uint32_t single_tiles;       // single variable: full tiles per work item
-    uint32_t single_tail;        // single variable: 1 = one more workgroup of the full-tile launch serves the ragged tail
     const float *sb_in;          // decompress: (s, b) table / pair, nullptr = (1, 0)
     const float *vin;            // compress: fp32 values, indexed by aux_offset
     float *vout;                 // decompress: fp32 output, indexed by aux_offset
     Partial *ws;
 };
+
+// What rides along with a set's first full-tile launch (the tail groups follow each other in the item list).
+struct SetGroups {
+    uint32_t fp32_first, fp32_nitems, tail_first, tail_nitems;
+};
+inline SetGroups set_groups(const PlanGroup *groups, uint32_t ngroups) {
+    SetGroups sg{};
+    for (uint32_t gi = 0; gi < ngroups; ++gi) {
+        if (groups[gi].nitems == 0) continue;
+        if (groups[gi].kind == kGroupFp32) {
+            sg.fp32_first = groups[gi].first_item;
+            sg.fp32_nitems = groups[gi].nitems;
+        } else if (groups[gi].kind == kGroupTail) {
+            if (sg.tail_nitems == 0) sg.tail_first = groups[gi].first_item;
+            sg.tail_nitems += groups[gi].nitems;
+        }
+    }
+    return sg;
+}
 
 // fp32 variable of a set: plain copy between the aux-indexed array and the arena (16-byte pieces)
 template <int MODE>
@@ -72,34 +92,50 @@ __device__ __forceinline__ void codec_tile_args(const CodecArgs &ca, const PlanV
     }
 }
 
-template <int B, int MODE, int VARIANT>
-__global__ __launch_bounds__(64, (Tuning<MODE, B>::waves)) void codec_kernel(CodecArgs ca) {
-    __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsDwords];
-    if (blockIdx.x >= ca.nitems) {
-        copy_fp32_item<MODE>(ca, ca.fp32_first + (blockIdx.x - ca.nitems));
-        return;
-    }
-    uint32_t item = blockIdx.x, var = 0, chunk = blockIdx.x;
+// A ragged tail as one workgroup; `lds`: kTileElems dwords.
+template <int MODE>
+__device__ __forceinline__ void codec_tail(const CodecArgs &ca, uint32_t index, uint32_t *lds) {
+    const uint32_t item = ca.tail_first + index;
+    uint32_t var = 0;
     PlanVar pv = ca.single;
-    uint32_t tiles = tiles_per_chunk(B);
-    if (!ca.plan) {
-        tiles = ca.single_tiles;
-        if (ca.single_tail && blockIdx.x == ca.nitems - 1) {       // the last workgroup: the variable's ragged tail
-            TileArgs a{};
-            codec_tile_args<MODE>(ca, pv, 0, a);
-            OptConst oc{};
-            do_tail<MODE, variant_wide(VARIANT)>(a, pv.fp, oc, ca.ws + item);   // (a format's rounding kind follows its variant)
-            return;
-        }
-    }
     if (ca.plan) {
         const PlanItem *items = reinterpret_cast<const PlanItem *>(ca.plan + ca.item_off);
         const PlanVar *vars = reinterpret_cast<const PlanVar *>(ca.plan + ca.var_off);
-        item = ca.first_item + blockIdx.x;
+        const PlanItem it = to_scalar_regs(items[item]);
+        pv = to_scalar_regs(vars[it.var]);
+        var = pv.sb_index;
+    }
+    TileArgs a{};
+    codec_tile_args<MODE>(ca, pv, var, a);
+    OptConst oc{};
+    do_tail<MODE>(a, pv.fp, oc, lds, ca.ws + item);
+}
+
+// Grid: ragged tails, then full-tile work items, then copies of fp32 variables.
+template <int B, int MODE, int VARIANT>
+__global__ __launch_bounds__(64, (Tuning<MODE, B>::waves)) void codec_kernel(CodecArgs ca) {
+    __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsDwords];
+    if (blockIdx.x < ca.tail_nitems) {
+        codec_tail<MODE>(ca, blockIdx.x, lds);
+        return;
+    }
+    const uint32_t block = blockIdx.x - ca.tail_nitems;
+    if (block >= ca.nitems) {
+        copy_fp32_item<MODE>(ca, ca.fp32_first + (block - ca.nitems));
+        return;
+    }
+    uint32_t item = block, var = 0, chunk = block;
+    PlanVar pv = ca.single;
+    uint32_t tiles = ca.single_tiles;
+    if (ca.plan) {
+        const PlanItem *items = reinterpret_cast<const PlanItem *>(ca.plan + ca.item_off);
+        const PlanVar *vars = reinterpret_cast<const PlanVar *>(ca.plan + ca.var_off);
+        item = ca.first_item + block;
         const PlanItem it = to_scalar_regs(items[item]);
         chunk = it.chunk;
         pv = to_scalar_regs(vars[it.var]);
         var = pv.sb_index;
+        tiles = tiles_per_chunk(B);
     }
     TileArgs a{};
     codec_tile_args<MODE>(ca, pv, var, a);
@@ -107,22 +143,11 @@ __global__ __launch_bounds__(64, (Tuning<MODE, B>::waves)) void codec_kernel(Cod
     do_chunk<B, MODE, VARIANT>(a, pv.fp, oc, chunk, lds, ca.ws + item, tiles);
 }
 
-template <int MODE, bool WIDE>
+// Tails of a set that has no full tile at all.
+template <int MODE>
 __global__ __launch_bounds__(64) void codec_tail_kernel(CodecArgs ca) {
-    uint32_t item = ca.first_item, var = 0;     // single variable: first_item is the tail's partial slot
-    PlanVar pv = ca.single;
-    if (ca.plan) {
-        const PlanItem *items = reinterpret_cast<const PlanItem *>(ca.plan + ca.item_off);
-        const PlanVar *vars = reinterpret_cast<const PlanVar *>(ca.plan + ca.var_off);
-        item = ca.first_item + blockIdx.x;
-        const PlanItem it = to_scalar_regs(items[item]);
-        pv = to_scalar_regs(vars[it.var]);
-        var = pv.sb_index;
-    }
-    TileArgs a{};
-    codec_tile_args<MODE>(ca, pv, var, a);
-    OptConst oc{};
-    do_tail<MODE, WIDE>(a, pv.fp, oc, ca.ws + item);
+    __shared__ uint32_t lds[kTileElems];
+    codec_tail<MODE>(ca, blockIdx.x, lds);
 }
 
 }  // namespace omc

@@ -48,12 +48,6 @@ static int launch_full(uint32_t bits, uint32_t variant, uint32_t grid, const Cod
     return static_cast<int>(hipGetLastError());
 }
 
-static int launch_tail(bool wide, uint32_t grid, const CodecArgs &ca, hipStream_t st) {
-    if (wide) codec_tail_kernel<kCompress, true><<<dim3(grid), dim3(64), 0, st>>>(ca);
-    else codec_tail_kernel<kCompress, false><<<dim3(grid), dim3(64), 0, st>>>(ca);
-    return static_cast<int>(hipGetLastError());
-}
-
 // Full tiles per work item of a single variable: the plan's figure, doubled until at most kMaxSingleItems work
 // items are left (a 64 M-element variable: 2048 items of 16 tiles), so that all of them are resident at once and the
 // finalize adds a few thousand partial sums at most.  Depends on the size alone.
@@ -80,11 +74,12 @@ int launch_compress(const float *v, const VarArgs &va, int use_pvt, void *codes,
     ca.single.total_dwords = va.total_dwords;
     ca.single.fp = va.fp;
     ca.single_tiles = tiles;
-    ca.single_tail = has_tail ? 1u : 0u;
+    ca.tail_first = nchunks;                               // the ragged tail is the launch's first workgroup
+    ca.tail_nitems = has_tail ? 1u : 0u;
     ca.vin = v;
     ca.ws = ws;
-    ca.nitems = nchunks + (has_tail ? 1u : 0u);            // the ragged tail is the launch's last workgroup
-    int rc = launch_full(va.fp.bits, va.fp.variant, ca.nitems, ca, st);
+    ca.nitems = nchunks;
+    int rc = launch_full(va.fp.bits, va.fp.variant, ca.tail_nitems + ca.nitems, ca, st);
     if (rc != 0) return rc;
     // the width of the reduction depends on the size alone, so results do not depend on the run
     const int exact = variant_exact(va.fp.variant) ? 1 : 0;
@@ -139,42 +134,37 @@ int launch_compress_set(const float *values, const PlanHeader *ph, const void *p
     ca.item_off = ph->item_off;
     ca.vin = values;
     ca.ws = ws;
-    const PlanGroup *fp32_group = nullptr;
-    bool any_full = false;
-    for (uint32_t gi = 0; gi < ph->ngroups; ++gi) {
-        if (groups[gi].kind == kGroupFp32 && groups[gi].nitems > 0) fp32_group = &groups[gi];
-        if (groups[gi].kind == kGroupFull && groups[gi].nitems > 0) any_full = true;
-    }
-    bool fp32_done = (fp32_group == nullptr);
+    // the copies of fp32 variables and the ragged tails ride along with the first full-tile launch
+    const SetGroups sg = set_groups(groups, ph->ngroups);
+    bool rode = false;
     for (uint32_t gi = 0; gi < ph->ngroups; ++gi) {
         const PlanGroup &g = groups[gi];
-        if (g.nitems == 0 || g.kind == kGroupFp32) continue;
+        if (g.nitems == 0 || g.kind != kGroupFull) continue;
         ca.first_item = g.first_item;
         ca.nitems = g.nitems;
-        ca.fp32_first = 0;
-        ca.fp32_nitems = 0;
-        int rc;
-        if (g.kind == kGroupFull) {
-            if (!fp32_done) {                          // the fp32 copies ride along with the first full-tile launch
-                ca.fp32_first = fp32_group->first_item;
-                ca.fp32_nitems = fp32_group->nitems;
-                fp32_done = true;
-            }
-            rc = launch_full(g.bits, g.wide, g.nitems + ca.fp32_nitems, ca, st);
-        } else {
-            rc = launch_tail(g.wide != 0, g.nitems, ca, st);
-        }
+        ca.fp32_first = sg.fp32_first;
+        ca.fp32_nitems = rode ? 0u : sg.fp32_nitems;
+        ca.tail_first = sg.tail_first;
+        ca.tail_nitems = rode ? 0u : sg.tail_nitems;
+        rode = true;
+        const int rc = launch_full(g.bits, g.wide, ca.tail_nitems + ca.nitems + ca.fp32_nitems, ca, st);
         if (rc != 0) return rc;
     }
-    if (!fp32_done) {                                  // no full-tile launch to ride on: a launch of copies alone
-        (void)any_full;
-        ca.first_item = 0;
-        ca.nitems = 0;
-        ca.fp32_first = fp32_group->first_item;
-        ca.fp32_nitems = fp32_group->nitems;
-        codec_kernel<8, kCompress, 0><<<dim3(fp32_group->nitems), dim3(64), 0, st>>>(ca);
-        const int rc = static_cast<int>(hipGetLastError());
-        if (rc != 0) return rc;
+    if (!rode) {                                       // no full tile in the whole set
+        ca.first_item = ca.nitems = 0;
+        ca.fp32_first = sg.fp32_first;
+        ca.fp32_nitems = sg.fp32_nitems;
+        if (sg.fp32_nitems > 0) {
+            codec_kernel<8, kCompress, 0><<<dim3(sg.fp32_nitems), dim3(64), 0, st>>>(ca);
+            const int rc = static_cast<int>(hipGetLastError());
+            if (rc != 0) return rc;
+        }
+        ca.tail_first = sg.tail_first;
+        if (sg.tail_nitems > 0) {
+            codec_tail_kernel<kCompress><<<dim3(sg.tail_nitems), dim3(64), 0, st>>>(ca);
+            const int rc = static_cast<int>(hipGetLastError());
+            if (rc != 0) return rc;
+        }
     }
     if (ph->nquant > 0) {
         finalize_plan_kernel<kFinalizeWaves><<<dim3(ph->nvars), dim3(64 * kFinalizeWaves), 0, st>>>(

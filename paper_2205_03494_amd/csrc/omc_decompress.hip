@@ -28,11 +28,12 @@ int launch_decompress(const void *codes, const VarArgs &va, const float *sb, flo
     ca.single.total_dwords = va.total_dwords;
     ca.single.fp = va.fp;
     ca.single_tiles = tiles;
-    ca.single_tail = has_tail ? 1u : 0u;
+    ca.tail_first = nchunks;                               // the ragged tail is the launch's first workgroup
+    ca.tail_nitems = has_tail ? 1u : 0u;
     ca.sb_in = sb;
     ca.vout = out;
-    ca.nitems = nchunks + (has_tail ? 1u : 0u);            // the ragged tail is the launch's last workgroup
-    return launch_full(va.fp.bits, ca.nitems, ca, st);
+    ca.nitems = nchunks;
+    return launch_full(va.fp.bits, ca.tail_nitems + ca.nitems, ca, st);
 }
 
 int launch_decompress_set(const void *arena, const PlanHeader *ph, const void *plan_dev, const float *sb_table,
@@ -47,38 +48,37 @@ int launch_decompress_set(const void *arena, const PlanHeader *ph, const void *p
     ca.item_off = ph->item_off;
     ca.sb_in = sb_table;
     ca.vout = out;
-    const PlanGroup *fp32_group = nullptr;
-    for (uint32_t gi = 0; gi < ph->ngroups; ++gi)
-        if (groups[gi].kind == kGroupFp32 && groups[gi].nitems > 0) fp32_group = &groups[gi];
-    bool fp32_done = (fp32_group == nullptr);
+    // the copies of fp32 variables and the ragged tails ride along with the first full-tile launch
+    const SetGroups sg = set_groups(groups, ph->ngroups);
+    bool rode = false;
     for (uint32_t gi = 0; gi < ph->ngroups; ++gi) {
         const PlanGroup &g = groups[gi];
-        if (g.nitems == 0 || g.kind == kGroupFp32) continue;
+        if (g.nitems == 0 || g.kind != kGroupFull) continue;
         ca.first_item = g.first_item;
         ca.nitems = g.nitems;
-        ca.fp32_first = 0;
-        ca.fp32_nitems = 0;
-        int rc;
-        if (g.kind == kGroupFull) {
-            if (!fp32_done) {
-                ca.fp32_first = fp32_group->first_item;
-                ca.fp32_nitems = fp32_group->nitems;
-                fp32_done = true;
-            }
-            rc = launch_full(g.bits, g.nitems + ca.fp32_nitems, ca, st);
-        } else {
-            codec_tail_kernel<kDecompress, false><<<dim3(g.nitems), dim3(64), 0, st>>>(ca);
-            rc = static_cast<int>(hipGetLastError());
-        }
+        ca.fp32_first = sg.fp32_first;
+        ca.fp32_nitems = rode ? 0u : sg.fp32_nitems;
+        ca.tail_first = sg.tail_first;
+        ca.tail_nitems = rode ? 0u : sg.tail_nitems;
+        rode = true;
+        const int rc = launch_full(g.bits, ca.tail_nitems + ca.nitems + ca.fp32_nitems, ca, st);
         if (rc != 0) return rc;
     }
-    if (!fp32_done) {
-        ca.first_item = 0;
-        ca.nitems = 0;
-        ca.fp32_first = fp32_group->first_item;
-        ca.fp32_nitems = fp32_group->nitems;
-        codec_kernel<8, kDecompress, 0><<<dim3(fp32_group->nitems), dim3(64), 0, st>>>(ca);
-        return static_cast<int>(hipGetLastError());
+    if (!rode) {                                       // no full tile in the whole set
+        ca.first_item = ca.nitems = 0;
+        ca.fp32_first = sg.fp32_first;
+        ca.fp32_nitems = sg.fp32_nitems;
+        if (sg.fp32_nitems > 0) {
+            codec_kernel<8, kDecompress, 0><<<dim3(sg.fp32_nitems), dim3(64), 0, st>>>(ca);
+            const int rc = static_cast<int>(hipGetLastError());
+            if (rc != 0) return rc;
+        }
+        ca.tail_first = sg.tail_first;
+        if (sg.tail_nitems > 0) {
+            codec_tail_kernel<kDecompress><<<dim3(sg.tail_nitems), dim3(64), 0, st>>>(ca);
+            const int rc = static_cast<int>(hipGetLastError());
+            if (rc != 0) return rc;
+        }
     }
     return 0;
 }

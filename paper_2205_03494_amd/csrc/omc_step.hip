@@ -21,32 +21,11 @@ __global__ __launch_bounds__(64) void step_fp32_kernel(StepArgs sa) {
     do_fp32_item<MODE>(sa, sa.first_item + blockIdx.x);
 }
 
-// Ragged tails of quantized variables, one wave each (code width read from the plan).
-template <int MODE, bool WIDE>
-__global__ __launch_bounds__(64) void step_tail_kernel(StepArgs sa) {
-    const PlanItem *items = reinterpret_cast<const PlanItem *>(sa.plan + sa.item_off);
-    const PlanVar *vars = reinterpret_cast<const PlanVar *>(sa.plan + sa.var_off);
-    const uint32_t item = sa.first_item + blockIdx.x;
-    const PlanItem it = to_scalar_regs(items[item]);
-    const PlanVar pv = to_scalar_regs(vars[it.var]);
-    TileArgs a{};
-    a.codes = reinterpret_cast<uint32_t *>(sa.arena + pv.data_offset);
-    a.total_dwords = pv.total_dwords;
-    a.grad = sa.grads + pv.aux_offset;
-    a.st0 = sa.st0 ? sa.st0 + pv.aux_offset : nullptr;
-    a.st1 = sa.st1 ? sa.st1 + pv.aux_offset : nullptr;
-    a.n = pv.n;
-    a.s = to_scalar_regs(sa.sb_table[2 * static_cast<uint64_t>(pv.sb_index)]);
-    a.b = to_scalar_regs(sa.sb_table[2 * static_cast<uint64_t>(pv.sb_index) + 1]);
-    const FmtParams fp = pv.fp;
-    do_tail<MODE, WIDE>(a, fp, sa.oc, sa.ws + item);
-}
-
+// Ragged tails of a set that has no full tile at all, one wave each.
 template <int MODE>
-static int launch_tail(bool wide, const StepArgs &sa, hipStream_t st) {
-    if (wide) step_tail_kernel<MODE, true><<<dim3(sa.nitems), dim3(64), 0, st>>>(sa);
-    else step_tail_kernel<MODE, false><<<dim3(sa.nitems), dim3(64), 0, st>>>(sa);
-    return static_cast<int>(hipGetLastError());
+__global__ __launch_bounds__(64) void step_tail_kernel(StepArgs sa) {
+    __shared__ uint32_t lds[kTileElems];
+    step_tail<MODE>(sa, blockIdx.x, lds);
 }
 
 int launch_step(void *arena, const PlanHeader *ph, const void *plan_dev, float *sb_table, const float *grads,
@@ -72,14 +51,19 @@ int launch_step(void *arena, const PlanHeader *ph, const void *plan_dev, float *
     sa.ws = ws;
     sa.oc = OptConst{opt.lr, opt.momentum, opt.beta1, opt.beta2, opt.eps, opt.one_minus_beta1,
                      opt.one_minus_beta2, opt.bias_corr1, opt.bias_corr2};
-    // the fp32 variables ride along with the first full-tile launch as extra workgroups
+    // the fp32 variables and the ragged tails ride along with the first full-tile launch as extra workgroups
     const PlanGroup *fp32_group = nullptr;
+    uint32_t tail_first = 0, tail_nitems = 0;              // the tail groups follow each other in the item list
     bool fuse = false;
     for (uint32_t gi = 0; gi < ph->ngroups; ++gi) {
-        if (groups[gi].kind == kGroupFp32 && groups[gi].nitems > 0) fp32_group = &groups[gi];
-        if (groups[gi].kind == kGroupFull && groups[gi].nitems > 0) fuse = true;
+        if (groups[gi].nitems == 0) continue;
+        if (groups[gi].kind == kGroupFp32) fp32_group = &groups[gi];
+        if (groups[gi].kind == kGroupFull) fuse = true;
+        if (groups[gi].kind == kGroupTail) {
+            if (tail_nitems == 0) tail_first = groups[gi].first_item;
+            tail_nitems += groups[gi].nitems;
+        }
     }
-    fuse = fuse && fp32_group != nullptr;
     bool fused_done = false;
     // Packed codes are read and rewritten by every step.  In a training loop a forward and a backward pass lie
     // between two steps and nothing survives in the caches, so by default every code access carries the
@@ -110,24 +94,33 @@ int launch_step(void *arena, const PlanHeader *ph, const void *plan_dev, float *
     for (uint32_t gi = 0; gi < ph->ngroups; ++gi) {
         const PlanGroup &g = groups[gi];
         if (g.nitems == 0) continue;
-        if (fuse && g.kind == kGroupFp32) continue;
+        if (fuse && g.kind != kGroupFull) continue;
+        if (g.kind == kGroupTail && g.first_item != tail_first) continue;   // both tail groups are one launch
         sa.first_item = g.first_item;
         sa.nitems = g.nitems;
         sa.fp32_first = 0;
         sa.fp32_nitems = 0;
         auto ride_along = [&]() {                                          // with the first full-tile launch of the step
-            if (!fuse || fused_done) return;
-            sa.fp32_first = fp32_group->first_item;
-            sa.fp32_nitems = fp32_group->nitems;
-            sa.fp32_keep_items = fp32_keep_items;
+            sa.fp32_nitems = 0;
+            sa.tail_nitems = 0;
+            if (fused_done) return;
+            sa.tail_first = tail_first;
+            sa.tail_nitems = tail_nitems;
+            if (fp32_group) {
+                sa.fp32_first = fp32_group->first_item;
+                sa.fp32_nitems = fp32_group->nitems;
+                sa.fp32_keep_items = fp32_keep_items;
+            }
             fused_done = true;
         };
         int rc = mark(0);
         if (rc != 0) return rc;
         if (g.kind == kGroupTail) {
-            if (opt.kind == OMC_SGD) rc = launch_tail<kStepSgd>(g.wide != 0, sa, st);
-            else if (opt.kind == OMC_MOMENTUM) rc = launch_tail<kStepMomentum>(g.wide != 0, sa, st);
-            else rc = launch_tail<kStepAdam>(g.wide != 0, sa, st);
+            sa.tail_first = tail_first;
+            if (opt.kind == OMC_SGD) step_tail_kernel<kStepSgd><<<dim3(tail_nitems), dim3(64), 0, st>>>(sa);
+            else if (opt.kind == OMC_MOMENTUM) step_tail_kernel<kStepMomentum><<<dim3(tail_nitems), dim3(64), 0, st>>>(sa);
+            else step_tail_kernel<kStepAdam><<<dim3(tail_nitems), dim3(64), 0, st>>>(sa);
+            rc = static_cast<int>(hipGetLastError());
         } else if (g.kind == kGroupFp32) {
             sa.fp32_first = g.first_item;
             sa.fp32_keep_items = fp32_keep_items;
@@ -141,8 +134,6 @@ int launch_step(void *arena, const PlanHeader *ph, const void *plan_dev, float *
                 sa.first_item = g.first_item + (part == 0 ? 0 : kept);
                 sa.nitems = part == 0 ? kept : g.nitems - kept;
                 if (sa.nitems == 0) continue;
-                sa.fp32_first = 0;
-                sa.fp32_nitems = 0;
                 ride_along();
                 if (opt.kind == OMC_SGD) rc = launch_step_group_sgd(g.bits, g.wide, sa, part == 0, st);
                 else if (opt.kind == OMC_MOMENTUM) rc = launch_step_group_momentum(g.bits, g.wide, sa, part == 0, st);

@@ -23,6 +23,7 @@ struct StepArgs {
     uint64_t var_off, item_off;
     uint32_t first_item, nitems;
     uint32_t fp32_first, fp32_nitems;   // work items of fp32 variables appended to this launch's grid
+    uint32_t tail_first, tail_nitems;   // ragged tails, the first workgroups of this launch's grid
     float *sb_table;
     const float *grads;
     float *st0, *st1;
@@ -114,6 +115,32 @@ __device__ __forceinline__ void do_fp32_item(const StepArgs &sa, uint32_t item) 
     else fp32_item_body<MODE, false>(sa, item);
 }
 
+// What the kernels need of one quantized variable.
+__device__ __forceinline__ void step_tile_args(const StepArgs &sa, const PlanVar &pv, TileArgs &a) {
+    a.codes = reinterpret_cast<uint32_t *>(sa.arena + pv.data_offset);
+    a.total_dwords = pv.total_dwords;
+    a.grad = sa.grads + pv.aux_offset;
+    a.st0 = sa.st0 ? sa.st0 + pv.aux_offset : nullptr;
+    a.st1 = sa.st1 ? sa.st1 + pv.aux_offset : nullptr;
+    a.n = pv.n;
+    a.s = to_scalar_regs(sa.sb_table[2 * static_cast<uint64_t>(pv.sb_index)]);
+    a.b = to_scalar_regs(sa.sb_table[2 * static_cast<uint64_t>(pv.sb_index) + 1]);
+}
+
+// A ragged tail as one workgroup (code width read from the plan); `lds`: kTileElems dwords.
+template <int MODE>
+__device__ __forceinline__ void step_tail(const StepArgs &sa, uint32_t index, uint32_t *lds) {
+    const PlanItem *items = reinterpret_cast<const PlanItem *>(sa.plan + sa.item_off);
+    const PlanVar *vars = reinterpret_cast<const PlanVar *>(sa.plan + sa.var_off);
+    const uint32_t item = sa.tail_first + index;
+    const PlanItem it = to_scalar_regs(items[item]);
+    const PlanVar pv = to_scalar_regs(vars[it.var]);
+    TileArgs a{};
+    step_tile_args(sa, pv, a);
+    const FmtParams fp = pv.fp;
+    do_tail<MODE>(a, fp, sa.oc, lds, sa.ws + item);
+}
+
 // KEEP: the launch's work items keep their packed codes cached from step to step; without it the code
 // loads and stores carry the non-temporal hint.
 // Occupancy: the register budget follows Tuning<>::waves (waves per SIMD the compiler must make room for).  The
@@ -134,24 +161,22 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64, 64)))
 __attribute__((amdgpu_waves_per_eu(StepOccupancy<B, MODE, VARIANT>::lo, StepOccupancy<B, MODE, VARIANT>::hi)))
 void step_kernel(StepArgs sa) {
     __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsDwords];
-    if (blockIdx.x >= sa.nitems) {                       // the workgroups past the end serve fp32 variables
-        do_fp32_item<MODE>(sa, sa.fp32_first + (blockIdx.x - sa.nitems));
+    if (blockIdx.x < sa.tail_nitems) {
+        step_tail<MODE>(sa, blockIdx.x, lds);
+        return;
+    }
+    const uint32_t block = blockIdx.x - sa.tail_nitems;
+    if (block >= sa.nitems) {                            // the workgroups past the end serve fp32 variables
+        do_fp32_item<MODE>(sa, sa.fp32_first + (block - sa.nitems));
         return;
     }
     const PlanItem *items = reinterpret_cast<const PlanItem *>(sa.plan + sa.item_off);
     const PlanVar *vars = reinterpret_cast<const PlanVar *>(sa.plan + sa.var_off);
-    const uint32_t item = sa.first_item + blockIdx.x;
+    const uint32_t item = sa.first_item + block;
     const PlanItem it = to_scalar_regs(items[item]);
     const PlanVar pv = to_scalar_regs(vars[it.var]);
     TileArgs a{};
-    a.codes = reinterpret_cast<uint32_t *>(sa.arena + pv.data_offset);
-    a.total_dwords = pv.total_dwords;
-    a.grad = sa.grads + pv.aux_offset;
-    a.st0 = sa.st0 ? sa.st0 + pv.aux_offset : nullptr;
-    a.st1 = sa.st1 ? sa.st1 + pv.aux_offset : nullptr;
-    a.n = pv.n;
-    a.s = to_scalar_regs(sa.sb_table[2 * static_cast<uint64_t>(pv.sb_index)]);
-    a.b = to_scalar_regs(sa.sb_table[2 * static_cast<uint64_t>(pv.sb_index) + 1]);
+    step_tile_args(sa, pv, a);
     const FmtParams fp = pv.fp;
     do_chunk<B, MODE, VARIANT, KEEP>(a, fp, sa.oc, it.chunk, lds, sa.ws + item);
 }
@@ -169,7 +194,7 @@ inline void launch_step_generic_variant(uint32_t variant, dim3 grid, dim3 block,
 
 template <int MODE, bool KEEP>
 inline int launch_step_group_keep(uint32_t bits, uint32_t variant, const StepArgs &sa, hipStream_t st) {
-    const dim3 grid(sa.nitems + sa.fp32_nitems), block(64);
+    const dim3 grid(sa.tail_nitems + sa.nitems + sa.fp32_nitems), block(64);
     // the hardware-conversion variant pays off where the vector ALU is the limit: plain SGD
     if (bits == 8 && variant == 2 && MODE <= OMC_TUNE_OCP_MAXMODE) {
         step_kernel<8, MODE, 2, KEEP><<<grid, block, 0, st>>>(sa);

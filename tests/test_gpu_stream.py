@@ -316,3 +316,32 @@ def test_e2m3_hardware_path_saturation_and_non_finite_values():
             assert np.array_equal(ga, oa)
             assert np.isnan(vs.g_sb.cpu().numpy()).all() and np.isnan(vs.o_sb).all()
     assert mism == 0
+
+
+@pytest.mark.parametrize("full_tile", [False, True])
+@pytest.mark.parametrize("kind,lr", [(0, 0.05), (1, 0.05), (2, 1e-3)])
+def test_tails_of_every_kind_in_one_launch(kind, lr, full_tile):
+    """Ragged tails at the borders of a batch of loads (64 lanes x 8) and of the stream's dwords, in formats of both
+    rounding kinds and of both kinds of fit sums, beside fp32 variables: with a full tile in the set they are workgroups
+    of the first full-tile launch, without one they have a launch of their own."""
+    ns = [1, 63, 64, 65, 511, 512, 513, 2047]
+    formats = [(4, 3), (3, 7), (8, 7), (4, 14), (7, 20), (8, 23)]
+    specs = [synth.VarSpec(f"v{i}", (n,), n, True) for i, n in enumerate(ns * len(formats))]
+    fmts = [formats[i // len(ns)] for i in range(len(specs))]
+    mask = [True] * len(specs)
+    for n in (5, 4097):
+        specs.append(synth.VarSpec(f"vec{n}", (n,), n, False))
+        fmts.append(None)
+        mask.append(False)
+    if full_tile:
+        for n, f in ((2048 + 513, (3, 7)), (4096 + 1, (7, 20))):
+            specs.append(synth.VarSpec(f"w{n}", (n,), n, True))
+            fmts.append(f)
+            mask.append(True)
+    vs = VarSet(specs, mask, fmts, seed=9)
+    assert vs.plan.launches == 3                # two widths, or tails and fp32 variables, and the finalize
+    for t in range(1, 3):
+        g = synth.gradients(vs.lay, 0.05, 30 + t)
+        vs.step_oracle(g, kind, lr, t)
+        vs.step_gpu(to_dev(g), kind, lr, t)
+        assert vs.compare(kind, f"t={t}") == 0
