@@ -970,16 +970,24 @@ __device__ __forceinline__ void do_tail(const TileArgs &a, const FmtParams &fp, 
 }
 
 // ---- finalize: per-variable (s, b) from the partials (paper Sec. 2.3) -----------------------------
-// Called by a whole workgroup of NW waves (blockDim.x == 64 * NW).  Sums the variable's partials
+// Called by a whole workgroup of NW <= 16 waves (blockDim.x == 64 * NW).  Sums the variable's partials
 // (a run of `nparts` from the full-tile kernels and, if `tail` is not null, one more from the tail
 // kernel) with compensated additions in an order fixed by (nparts, NW) alone: thread t takes
-// partials t, t + 64 NW, ...; lanes combine by a butterfly; waves combine in index order.  Then the
+// partials t, t + 64 NW, ...; lanes combine by a butterfly; waves combine by a butterfly.  Then the
 // closed form in fp64, stored as fp32.  `red` is LDS scratch of NW * 10 doubles.  `exact`: the partials
 // carry error words (formats of 16 or more mantissa bits), which are added as well.
+// What bounds it is the chain of dependent fp64 additions of one or a few waves.  The four sums are therefore dealt out
+// on the way: the first exchange of the butterfly leaves a lane with two of them, the second with one, so that six
+// exchanges cost 7 additions of pairs instead of 24.
+__device__ __forceinline__ DD keep_half(bool upper, DD lower_sum, DD upper_sum, int off) {
+    const DD mine = upper ? upper_sum : lower_sum, other = upper ? lower_sum : upper_sum;
+    return dd_add(mine, dd_shfl_xor(other, off));
+}
 template <int NW>
 __device__ __forceinline__ void finalize_variable(const Partial *__restrict__ parts, uint32_t nparts,
                                                   const Partial *__restrict__ tail, uint64_t n, bool use_pvt,
                                                   bool exact, float *sb_out, double *red) {
+    static_assert(NW <= 16 && (NW & (NW - 1)) == 0, "one lane of the first wave per wave and sum");
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     if (!use_pvt) {
         if (tid == 0) { sb_out[0] = 1.0f; sb_out[1] = 0.0f; }
@@ -993,70 +1001,80 @@ __device__ __forceinline__ void finalize_variable(const Partial *__restrict__ pa
     // loads of a batch are in flight together instead of one memory round trip per partial)
     constexpr uint32_t kBatch = 8, kStride = 64 * NW;
     for (uint32_t i0 = tid; i0 < total; i0 += kBatch * kStride) {
-        Partial p[kBatch];
+        double p[kBatch][4], l[kBatch][4];
+        float lo[kBatch], hi[kBatch];
 #pragma unroll
         for (uint32_t u = 0; u < kBatch; ++u) {
             const uint32_t i = i0 + u * kStride;
-            if (i < total) p[u] = (i < nparts) ? parts[i] : *tail;
+            if (i >= total) break;
+            const Partial *q = (i < nparts) ? parts + i : tail;
+            p[u][0] = q->sV; p[u][1] = q->sT; p[u][2] = q->sVT; p[u][3] = q->sTT;
+            lo[u] = q->tmin; hi[u] = q->tmax;
+            if (exact) { l[u][0] = q->lV; l[u][1] = q->lT; l[u][2] = q->lVT; l[u][3] = q->lTT; }
         }
 #pragma unroll
         for (uint32_t u = 0; u < kBatch; ++u) {
             if (i0 + u * kStride >= total) break;
-            finite = finite && isfinite(p[u].sV);
+            finite = finite && isfinite(p[u][0]);
             if (finite) {
-                sV = dd_add(sV, p[u].sV);
-                sT = dd_add(sT, p[u].sT);
-                sVT = dd_add(sVT, p[u].sVT);
-                sTT = dd_add(sTT, p[u].sTT);
-                if (exact) {                        // the error words of the wide-mantissa kernels (zero otherwise)
-                    sV = dd_add(sV, p[u].lV);
-                    sT = dd_add(sT, p[u].lT);
-                    sVT = dd_add(sVT, p[u].lVT);
-                    sTT = dd_add(sTT, p[u].lTT);
+                sV = dd_add(sV, p[u][0]);
+                sT = dd_add(sT, p[u][1]);
+                sVT = dd_add(sVT, p[u][2]);
+                sTT = dd_add(sTT, p[u][3]);
+                if (exact) {                        // the error words of the wide-mantissa kernels
+                    sV = dd_add(sV, l[u][0]);
+                    sT = dd_add(sT, l[u][1]);
+                    sVT = dd_add(sVT, l[u][2]);
+                    sTT = dd_add(sTT, l[u][3]);
                 }
             }
-            tmin = fminf(tmin, p[u].tmin);
-            tmax = fmaxf(tmax, p[u].tmax);
+            tmin = fminf(tmin, lo[u]);
+            tmax = fmaxf(tmax, hi[u]);
         }
     }
+    // lanes 0-15 end with the wave's sum of V, 16-31 of Vt, 32-47 of V Vt, 48-63 of Vt^2
+    const DD two0 = keep_half((lane & 32u) != 0, sV, sVT, 32), two1 = keep_half((lane & 32u) != 0, sT, sTT, 32);
+    DD one = keep_half((lane & 16u) != 0, two0, two1, 16);
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) one = dd_add(one, dd_shfl_xor(one, off));
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
-        sV = dd_add(sV, dd_shfl_xor(sV, off));
-        sT = dd_add(sT, dd_shfl_xor(sT, off));
-        sVT = dd_add(sVT, dd_shfl_xor(sVT, off));
-        sTT = dd_add(sTT, dd_shfl_xor(sTT, off));
         tmin = fminf(tmin, __shfl_xor(tmin, off));
         tmax = fmaxf(tmax, __shfl_xor(tmax, off));
-        finite = __shfl_xor(static_cast<int>(finite), off) && finite;
     }
+    finite = __all(finite);
     if (NW > 1) {
+        double *r = red + wave * 10;
+        if ((lane & 15u) == 0) {
+            r[lane >> 3] = one.hi;
+            r[(lane >> 3) + 1] = one.lo;
+        }
         if (lane == 0) {
-            double *r = red + wave * 10;
-            r[0] = sV.hi; r[1] = sV.lo; r[2] = sT.hi; r[3] = sT.lo; r[4] = sVT.hi; r[5] = sVT.lo;
-            r[6] = sTT.hi; r[7] = sTT.lo;
             r[8] = static_cast<double>(tmin);
             r[9] = finite ? static_cast<double>(tmax) : __builtin_nan("");   // NaN marks a poisoned wave
         }
         __syncthreads();
-        if (tid != 0) return;
-        for (int w = 1; w < NW; ++w) {
-            const double *r = red + w * 10;
-            sV = dd_add(sV, DD{r[0], r[1]});
-            sT = dd_add(sT, DD{r[2], r[3]});
-            sVT = dd_add(sVT, DD{r[4], r[5]});
-            sTT = dd_add(sTT, DD{r[6], r[7]});
-            tmin = fminf(tmin, static_cast<float>(r[8]));
-            if (r[9] != r[9]) finite = false; else tmax = fmaxf(tmax, static_cast<float>(r[9]));
+        if (wave != 0) return;
+        const double *from = red + (lane & (NW - 1)) * 10;
+        one.hi = from[2 * (lane >> 4)];
+        one.lo = from[2 * (lane >> 4) + 1];
+        tmin = static_cast<float>(from[8]);
+        tmax = static_cast<float>(from[9]);
+        finite = __all(from[9] == from[9]);
+#pragma unroll
+        for (int off = NW / 2; off >= 1; off >>= 1) {
+            one = dd_add(one, dd_shfl_xor(one, off));
+            tmin = fminf(tmin, __shfl_xor(tmin, off));
+            tmax = fmaxf(tmax, __shfl_xor(tmax, off));
         }
-    } else if (tid != 0) {
-        return;
     }
+    const double SV = __shfl(one.hi, 0), ST = __shfl(one.hi, 16), SVT = __shfl(one.hi, 32), STT = __shfl(one.hi, 48);
+    if (tid != 0) return;
     if (!finite) {                                   // a non-finite input value poisons the fit
         sb_out[0] = __builtin_nanf("");
         sb_out[1] = __builtin_nanf("");
         return;
     }
-    const double SV = sV.hi, ST = sT.hi, SVT = sVT.hi, STT = sTT.hi;
     const double dn = static_cast<double>(n);
     double s;
     if (tmin == tmax) {                              // all decompressed values equal: degenerate case
