@@ -371,8 +371,8 @@ omc_status omc_aggregate_mean(const void *agg_host, const void *agg_dev, const v
 
 /* ---- forward path ------------------------------------------------------------------------ */
 
-/* Workspace (device bytes) for omc_dequant_gemm / omc_dequant_gemm_dx with M activation rows (a few
- * flag words of a pre-pass over the codes; 0 for M == 0). */
+/* Workspace (device bytes) for omc_dequant_gemm / omc_dequant_gemm_dx with M activation rows (256, whatever
+ * the sizes; 0 for M == 0).  It is checked and reserved; the present kernels do not write to it. */
 size_t omc_dequant_gemm_workspace_bytes(uint32_t M);
 
 /* C[M x N] = A[M x K] * Wbar[K x N], Wbar = decompress(codes, sb)  (Sec. 2.1 forward path: the
@@ -386,9 +386,9 @@ size_t omc_dequant_gemm_workspace_bytes(uint32_t M);
  * Uses  A*(s*Vt + b*1) = s*(A*Vt) + b*rowsum(A)*1^T.  Requires man_bits <= 7 (every Vtilde is then
  * exactly a bfloat16), M % 256 == 0, N % 128 == 0, K % 32 == 0 (OMC_ERR_FORMAT / OMC_ERR_SIZE).
  * Values of the format below 2^-126 (possible only with a bias near 127) may be flushed to zero by
- * the matrix cores.  S1E4M3 with bias 7 is converted by the hardware's FP8 instructions unless a
- * pre-pass over the codes finds the one code (all exponent and mantissa bits set, value 480) that
- * they read differently; results are the same either way. */
+ * the matrix cores.  S1E4M3 with bias 7 is converted by the hardware's FP8 instructions; a tile in which
+ * the one code occurs that they read differently (all exponent and mantissa bits set, value 480) is computed
+ * again without them, so that results are the same either way. */
 omc_status omc_dequant_gemm(const uint16_t *A, const void *codes, omc_format f, const float *sb,
                             float *C, uint32_t M, uint32_t N, uint32_t K, void *ws, size_t ws_bytes,
                             void *stream);

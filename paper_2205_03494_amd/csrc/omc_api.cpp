@@ -702,7 +702,7 @@ omc_status omc_aggregate_mean(const void *agg_host, const void *agg_dev, const v
 }
 
 size_t omc_dequant_gemm_workspace_bytes(uint32_t M) {
-    return M == 0 ? 0 : 256;   // the flag words of the top-code scan (independent of M)
+    return M == 0 ? 0 : 256;   // (part of the interface; the present kernels need no workspace)
 }
 
 omc_status omc_dequant_gemm(const uint16_t *A, const void *codes, omc_format f, const float *sb, float *C,
@@ -716,7 +716,7 @@ omc_status omc_dequant_gemm(const uint16_t *A, const void *codes, omc_format f, 
         return OMC_ERR_ALIGN;
     if (!ws || ws_bytes < omc_dequant_gemm_workspace_bytes(M)) return OMC_ERR_WORKSPACE;
     if (!aligned16(ws)) return OMC_ERR_ALIGN;
-    const int rc = launch_dequant_gemm(A, codes, fp, sb, C, M, N, K, static_cast<float *>(ws), 0, stream);
+    const int rc = launch_dequant_gemm(A, codes, fp, sb, C, M, N, K, 0, stream);
     return rc == 0 ? OMC_OK : OMC_ERR_DEVICE;
 }
 
@@ -760,7 +760,7 @@ omc_status omc_dequant_gemm_dx(const uint16_t *dY, const void *codes, omc_format
     if (!ws || ws_bytes < omc_dequant_gemm_workspace_bytes(M)) return OMC_ERR_WORKSPACE;
     if (!aligned16(ws)) return OMC_ERR_ALIGN;
     // output columns = K (the weights' rows), contraction over N
-    const int rc = launch_dequant_gemm(dY, codes, fp, sb, dX, M, K, N, static_cast<float *>(ws), 1, stream);
+    const int rc = launch_dequant_gemm(dY, codes, fp, sb, dX, M, K, N, 1, stream);
     return rc == 0 ? OMC_OK : OMC_ERR_DEVICE;
 }
 

@@ -1,0 +1,296 @@
+// omc_dequant_gemm / omc_dequant_gemm_dx on S1E4M3 codes with bias 7 (OCP FP8 E4M3 but for the value of the top code).
+//
+// C[M x N] = A[M x K] * (s W + b), W packed as [K x N] (forward) or [N x K] (TRANS, the input gradient).  Both operands go
+// from global memory straight into a ring of S LDS stages of 64 k each, as they are: A as rows of 128 bytes, W as bytes.  A
+// wave takes A fragments with 16-byte reads and W fragments as eight codes per lane -- forward with the transposing 8-bit read
+// (ds_read_b64_tr_b8: of 16 lanes that point at eight k rows x two 8-byte chunks, lane c receives column c's eight k), TRANS
+// with a plain read of eight consecutive codes -- and converts them to bfloat16 in registers, four instructions for eight
+// codes.  Staging costs no vector instruction and W passes through LDS at one byte per weight.
+//
+// 16-byte pieces are XOR-swizzled on their way in (the lane picks the piece, its LDS place is fixed): A pieces by the row,
+// forward W pieces by the k row, TRANS W pieces by half the column, so that the rows of one read lie on different banks.
+//
+// Fragments of a quarter step are read while the quarter before is multiplied; the last quarter is multiplied after the
+// barrier of the next step, under that step's first reads.  Waves start their quarters at different places
+// (WN + WM rotation), which also deals the row sums of A (each column wave sums its own quarters, in every
+// multiplication order the same) and the check for top codes (each row wave checks its own) evenly and without branches.
+//
+// The top code reads as NaN in the hardware conversion, without its sign.  No pass over the codes looks for it beforehand:
+// the waves check what they multiply (five instructions per eight codes, half of the fragments), and a workgroup that
+// saw one computes its tile again with a bit-domain decode.
+//
+// Measured (us, 8192 x 4096 x 1024 / 8192 x 1024 x 4096, fp32 output, new operands each time), against the kernel before (256 x 128 tile,
+// A fragments from global memory, W decoded on the way into LDS, a 5 us pass over the codes for top codes first): 83 / 81 ->
+// 68 / 66.  What bounds it now: LDS bandwidth (24 KB through LDS per 16 k of a 128 x 256 tile, three quarters of what
+// 128 B/clk gives at the matrix cores' rate), power (1150 TFLOP/s at 16384 x 4096 x 2048, random data), and 4 us of C stores
+// that nothing covers.
+#include "omc_mma.h"
+
+#pragma clang fp contract(off)
+
+namespace omc {
+
+// Eight codes as bfloat16.  EXACT: bit-domain decode, right for the top code too.
+template <bool EXACT>
+__device__ __forceinline__ bf16x8 fp8x8_to_bf16(u32x2 c) {
+    u32x4 o;
+    if (EXACT) {
+#pragma unroll
+        for (int d = 0; d < 2; ++d)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t pair = 0;
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const uint32_t code_at_top = c[d] << (24 - 16 * h - 8 * e);
+                    const uint32_t bits = static_cast<uint32_t>(static_cast<int32_t>(code_at_top) >> 4) & 0x87f00000u;
+                    const uint32_t v = __float_as_uint(__uint_as_float(bits) * 0x1p120f);
+                    pair |= e ? (v & 0xffff0000u) : (v >> 16);
+                }
+                o[2 * d + h] = pair;
+            }
+    } else {
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            o[2 * d] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c[d], 1.0f, false));
+            o[2 * d + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c[d], 1.0f, true));
+        }
+    }
+    return __builtin_bit_cast(bf16x8, o);
+}
+
+struct Fp8Args {
+    const uint16_t *A;
+    const uint8_t *codes;
+    const float *sb;
+    float *C;
+    uint32_t N, K, tiles_m, tiles_n;
+};
+
+// WM x WN waves of TM x TN matrix tiles (32 x 32) each, TEAMS times: team t multiplies the steps t, t + TEAMS, ... of the
+// contraction in LDS stages of its own, and team 0 adds up the teams' tiles in order.  S stages, OCC waves per SIMD.
+template <int WM, int WN, int TM, int TN, int TEAMS, int S, int OCC, bool TRANS>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN * TEAMS, 64 * WM * WN * TEAMS))) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
+void gemm_fp8_kernel(Fp8Args ga) {
+    constexpr int NW = WM * WN, BM = 32 * TM * WM, BN = 32 * TN * WN;
+    constexpr int kALoads = BM / 8 / NW, kWLoads = BN / 16 / NW, kLoads = kALoads + kWLoads;   // 1 KB loads per wave and stage
+    constexpr int kPieces = BN / 16;                        // 16-byte pieces in a k row of the forward W tile
+    constexpr uint32_t kABytes = BM * 128, kStage = kABytes + BN * 64;
+    static_assert(WM == 2 && (WN == 2 || WN == 4), "how the quarters are dealt below");
+    static_assert(BM % (8 * NW) == 0 && BN % (16 * NW) == 0 && (64 / kPieces) * NW % kPieces == 0, "whole loads, one swizzle per wave");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_all[TEAMS * S * kStage];
+    const uint32_t team = TEAMS == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
+    uint8_t *lds = lds_all + team * (S * kStage);
+    const uint32_t lds0 = lds_offset(lds);
+    const uint32_t tid = TEAMS == 1 ? threadIdx.x : threadIdx.x % (64 * NW), lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
+    const uint32_t N = ga.N, K = ga.K;
+    uint32_t m0, n0;
+    tile_of_block(ga.tiles_m, ga.tiles_n, m0, n0);
+    m0 *= BM;
+    n0 *= BN;
+
+    // ---- global -> LDS: stage j holds k in [64 j, 64 j + 64); the last one may be half empty (K % 64 == 32), its lanes then
+    // bring the lower half twice instead of reading past the row, and nobody multiplies the upper half
+    const uint32_t full_k = K / 64, stages_k = (K + 63) / 64;
+    const uint32_t full = (full_k + TEAMS - 1 - team) / TEAMS, stages = (stages_k + TEAMS - 1 - team) / TEAMS;   // this team's
+    const uint8_t *a_base = reinterpret_cast<const uint8_t *>(ga.A) + static_cast<uint64_t>(m0) * K * 2;
+    const uint32_t a_row = lane >> 3, a_piece = (lane & 7u) ^ a_row;
+    const uint8_t *w_base = TRANS ? ga.codes + static_cast<uint64_t>(n0) * K : ga.codes + n0;
+    const uint32_t w_row = TRANS ? lane >> 2 : lane / kPieces;
+    const uint32_t w_piece = TRANS ? (lane & 3u) ^ ((lane >> 3) & 3u) : (lane % kPieces) ^ ((wave * (64 / kPieces) + w_row) & (kPieces - 1));
+    auto load_stage = [&](uint32_t at, uint32_t step) {
+        const uint32_t j = team + TEAMS * step;
+        const bool half = j == full_k;
+        const uint32_t a_off = a_row * K * 2 + (half ? a_piece & 3u : a_piece) * 16;
+#pragma unroll
+        for (int i = 0; i < kALoads; ++i) {
+            const uint32_t c = wave + NW * i;                 // rows 8 c ..
+            load_to_lds(a_base + static_cast<uint64_t>(j) * 128 + static_cast<uint64_t>(c) * 16 * K, a_off, lds0 + at + c * 1024);
+        }
+        const uint32_t w_off = TRANS ? w_row * K + (half ? w_piece & 1u : w_piece) * 16 : w_row * N + w_piece * 16;
+#pragma unroll
+        for (int i = 0; i < kWLoads; ++i) {
+            const uint32_t c = wave + NW * i;
+            const uint32_t first = TRANS ? 16 * c : (half ? (c * (64 / kPieces)) & 31u : c * (64 / kPieces));   // column / k row
+            const uint8_t *from = TRANS ? w_base + static_cast<uint64_t>(j) * 64 + static_cast<uint64_t>(first) * K
+                                        : w_base + (static_cast<uint64_t>(j) * 64 + first) * N;
+            load_to_lds(from, w_off, lds0 + at + kABytes + c * 1024);
+        }
+    };
+
+    // ---- LDS -> fragments.  The k of a quarter's two halves may be any, as long as both operands agree: TRANS takes 16 codes of
+    // a column as the same half of two quarters, so that A's pieces follow that order.
+    const uint32_t f_row = lane & 31u, f_half = lane >> 5;
+    auto a_place = [&](uint32_t ks) {
+        const uint32_t row = 32 * TM * wm + f_row;
+        const uint32_t piece = TRANS ? 4 * (ks >> 1) + 2 * f_half + (ks & 1u) : 2 * ks + f_half;
+        return row * 128 + ((piece ^ (row & 7u)) << 4);
+    };
+    auto w_place = [&](uint32_t ks) {
+        if (TRANS) {
+            const uint32_t col = 32 * TN * wn + f_row, piece = 2 * (ks >> 1) + f_half;
+            return kABytes + col * 64 + ((piece ^ ((col >> 1) & 3u)) << 4) + 8 * (ks & 1u);
+        }
+        const uint32_t block = lane >> 4, in = lane & 15u;      // 16 lanes: 16 columns x 8 k
+        const uint32_t row = 16 * ks + 8 * (block >> 1) + (in >> 1), piece = 2 * TN * wn + (block & 1u);
+        return kABytes + row * BN + ((piece ^ (row & (kPieces - 1))) << 4) + 8 * (in & 1u);
+    };
+    uint32_t a_at[4], w_at[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const uint32_t ks = (p + wn + 2 * wm) & 3u;
+        a_at[p] = a_place(ks);
+        w_at[p] = w_place(ks);
+    }
+    struct Frags {
+        bf16x8 a[TM];
+        u32x2 w[TN];
+    };
+    auto read_frags = [&](uint32_t at, uint32_t a_off, uint32_t w_off, Frags &f) {
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi) f.a[mi] = *reinterpret_cast<const bf16x8 *>(lds + at + a_off + 32 * 128 * mi);
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) {
+            if (TRANS) {
+                f.w[ni] = *reinterpret_cast<const u32x2 *>(lds + at + w_off + 32 * 64 * ni);
+            } else {                                        // 32 columns on: two pieces on, before the swizzle
+                const i32x2 t = __builtin_amdgcn_ds_read_tr8_b64_v2i32((OMC_LDS i32x2 *)(lds + at + (w_off ^ (32u * ni))));
+                f.w[ni] = u32x2{static_cast<uint32_t>(t[0]), static_cast<uint32_t>(t[1])};
+            }
+        }
+    };
+
+    f32x16 acc[TM][TN];
+    float rsum[TM];
+    uint32_t top;
+    auto compute = [&](auto exact_tag) {
+        constexpr bool EXACT = decltype(exact_tag)::value;
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi) {
+            rsum[mi] = 0.0f;
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
+        }
+        top = 0;
+        auto multiply = [&](const Frags &f, bool sum, bool check) {
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni) {
+                const bf16x8 w = fp8x8_to_bf16<EXACT>(f.w[ni]);
+                if (!EXACT && check) top |= ((f.w[ni][0] & 0x7f7f7f7fu) + 0x01010101u) | ((f.w[ni][1] & 0x7f7f7f7fu) + 0x01010101u);
+#pragma unroll
+                for (int mi = 0; mi < TM; ++mi) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mi], w, acc[mi][ni], 0, 0, 0);
+            }
+            if (sum) {
+#pragma unroll
+                for (int mi = 0; mi < TM; ++mi) rsum[mi] = add_fragment(f.a[mi], rsum[mi]);
+            }
+        };
+        Frags f0, f1;
+        uint32_t cur = 0, far = (S - 1) * kStage;
+        auto rest_of_step = [&]() {                           // everything but the first quarter's reads and the last one's products
+            read_frags(cur, a_at[1], w_at[1], f1);
+            multiply(f0, true, true);
+            read_frags(cur, a_at[2], w_at[2], f0);
+            multiply(f1, false, true);
+            read_frags(cur, a_at[3], w_at[3], f1);
+            multiply(f0, WN == 2, false);
+            cur = cur == (S - 1) * kStage ? 0 : cur + kStage;
+            far = far == (S - 1) * kStage ? 0 : far + kStage;
+        };
+#pragma unroll
+        for (uint32_t i = 0; i < S - 1; ++i)
+            if (i < stages) load_stage(i * kStage, i);
+        if (full > 0) {
+            wait_stage<S, kLoads>(0, stages);
+            read_frags(cur, a_at[0], w_at[0], f0);
+            if (stages > S - 1) load_stage(far, S - 1);
+            rest_of_step();
+            uint32_t j = 1;
+            for (; j + (S - 1) < stages; ++j) {
+                wait_loads_and_sync<(S - 2) * kLoads>();
+                read_frags(cur, a_at[0], w_at[0], f0);
+                load_stage(far, j + S - 1);
+                multiply(f1, false, false);
+                rest_of_step();
+            }
+            for (; j < full; ++j) {
+                wait_stage<S, kLoads>(j, stages);
+                read_frags(cur, a_at[0], w_at[0], f0);
+                multiply(f1, false, false);
+                rest_of_step();
+            }
+            multiply(f1, false, false);
+        }
+        if (full < stages) {                                  // 32 k more: two quarters
+            wait_loads_and_sync<0>();
+            for (uint32_t ks = 0; ks < 2; ++ks) {
+                read_frags(cur, a_place(ks), w_place(ks), f0);
+                multiply(f0, false, true);
+                if (ks % WN == wn) {
+#pragma unroll
+                    for (int mi = 0; mi < TM; ++mi) rsum[mi] = add_fragment(f0.a[mi], rsum[mi]);
+                }
+            }
+        }
+        for (uint32_t i = stages; i < (stages_k + TEAMS - 1) / TEAMS; ++i) wait_loads_and_sync<0>();   // teams wait for each other
+        wait_loads_and_sync<0>();                             // nobody reads a stage any more
+    };
+
+    float *rowsum = reinterpret_cast<float *>(lds_all);       // [TEAMS * WN][BM], then a flag per wave, then the other teams' tiles
+    uint32_t *tops = reinterpret_cast<uint32_t *>(rowsum + TEAMS * WN * BM);
+    float *parts = reinterpret_cast<float *>(tops + 64);
+    static_assert(4 * (TEAMS * WN * BM + 64 + (TEAMS - 1) * BM * BN) <= TEAMS * S * static_cast<int>(kStage), "fits the stages");
+    compute(BoolTag<false>{});
+    const bool mine = __any((top & 0x80808080u) != 0);
+    if (lane == 0) tops[team * NW + wave] = mine ? 1u : 0u;
+    __syncthreads();
+    uint32_t any_top = 0;
+#pragma unroll
+    for (int w = 0; w < NW * TEAMS; ++w) any_top |= tops[w];
+    __syncthreads();                                          // the flags are read before anything overwrites them
+    if (__builtin_amdgcn_readfirstlane(any_top) != 0) compute(BoolTag<true>{});
+    const float s = ga.sb ? ga.sb[0] : 1.0f, b = ga.sb ? ga.sb[1] : 0.0f;
+    publish_row_sums<WN, BM, TM>(rowsum, rsum, ga.sb != nullptr, team, 32 * TM * wm, wn, lane);
+    if (!add_teams<TEAMS, NW, TM, TN>(parts, acc, team, wave, lane)) return;
+    store_tile<TEAMS * WN, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 32 * TN * wn, N, acc, rowsum, 32 * TM * wm, lane, s, b);
+}
+
+// The first tile has two workgroups of four waves on a compute unit, so that one's C stores pass under the other's products: it
+// wins wherever a unit gets several tiles (8192 x 4096 x 1024, new operands each time: 69 us; 80 with a 256 x 256 tile, one
+// workgroup of eight waves per unit, although that one is the faster without any stores, 63.5 to 65.5).  The second one is the same
+// tile by eight waves with a third stage, better when every unit has one tile (8192 x 1024 x 4096: 66 to 68 us).  The small tiles
+// win where they spread a short product over more units, and several teams where even those leave most of them
+// idle (1024 x 256 x 4096: 48 us with 128 x 256, 38 with 128 x 128, 21 / 16 / 15 with 64 x 64 and 1 / 2 / 4 teams).
+static constexpr GemmTile kFp8Tiles[] = {
+    {128, 256, 1, 2, 4.5, 0.95, 0.92, 1.5}, {128, 256, 1, 1, 4.5, 0.67, 0.90, 3.5}, {128, 128, 1, 2, 3.4, 0.55, 0.46, 1.8},
+    {64, 128, 1, 2, 3.2, 0.33, 0.30, 1.0},  {64, 64, 1, 4, 2.9, 0.275, 0.166, 0.5}, {64, 64, 2, 2, 3.2, 0.40, 0.40, 0.5},
+    {64, 64, 4, 1, 4.0, 0.66, 1.25, 0.5},
+};
+
+template <bool TRANS>
+static int launch_tile(int which, const Fp8Args &ga, uint32_t tiles, hipStream_t st) {
+    switch (which) {
+        case 0: gemm_fp8_kernel<2, 2, 2, 4, 1, 2, 2, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
+        case 1: gemm_fp8_kernel<2, 4, 2, 2, 1, 3, 2, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
+        case 2: gemm_fp8_kernel<2, 2, 2, 2, 1, 3, 2, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
+        case 3: gemm_fp8_kernel<2, 4, 1, 1, 1, 3, 4, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
+        case 4: gemm_fp8_kernel<2, 2, 1, 1, 1, 3, 4, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
+        case 5: gemm_fp8_kernel<2, 2, 1, 1, 2, 3, 4, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
+        case 6: gemm_fp8_kernel<2, 2, 1, 1, 4, 3, 4, TRANS><<<dim3(tiles), dim3(1024), 0, st>>>(ga); break;
+        default: return static_cast<int>(hipErrorInvalidValue);
+    }
+    return static_cast<int>(hipGetLastError());
+}
+
+int launch_gemm_fp8(const uint16_t *A, const void *codes, const float *sb, float *C, uint32_t M, uint32_t N, uint32_t K, int trans, hipStream_t st) {
+    const int which = pick_tile(kFp8Tiles, M, N, K);
+    if (which < 0) return static_cast<int>(hipErrorInvalidValue);
+    const GemmTile &t = kFp8Tiles[which];
+    const Fp8Args ga{A, static_cast<const uint8_t *>(codes), sb, C, N, K, M / t.bm, N / t.bn};
+    return trans ? launch_tile<true>(which, ga, ga.tiles_m * ga.tiles_n, st) : launch_tile<false>(which, ga, ga.tiles_m * ga.tiles_n, st);
+}
+
+}  // namespace omc

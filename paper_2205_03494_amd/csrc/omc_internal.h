@@ -240,6 +240,8 @@ int launch_step(void *arena, const PlanHeader *ph, const void *plan_dev, float *
 int launch_reselect_sb(const uint32_t *actions_dev, uint32_t nvars, const float *sb_old, float *sb_new, void *stream);
 int launch_transport_pack(const PlanHeader *ph, const void *plan_dev, const void *arena, const float *sb_table,
                           void *msg_dev, const TransportHeader &th, void *stream);
+int launch_gemm_fp8(const uint16_t *A, const void *codes, const float *sb, float *C, uint32_t M, uint32_t N, uint32_t K,
+                    int trans, struct ihipStream_t *stream);   // S1E4M3 codes, bias 7
 struct DwConfig {
     uint32_t rows;     // weight rows per tile: 256 or 128
     uint32_t nsplit;   // workgroups per tile along the contraction
@@ -256,6 +258,6 @@ struct AggPointers {
 };
 int launch_aggregate_mean(const AggHeader *ah, const void *agg_dev, const AggPointers &ptrs, float *out, void *stream);
 int launch_dequant_gemm(const uint16_t *A, const void *codes, const FmtParams &fp, const float *sb,
-                        float *C, uint32_t M, uint32_t N, uint32_t K, float *ws, int trans, void *stream);
+                        float *C, uint32_t M, uint32_t N, uint32_t K, int trans, void *stream);
 
 }  // namespace omc

@@ -1,0 +1,176 @@
+// Building blocks of the matrix-core kernels whose operands travel from global memory straight into LDS.
+#pragma once
+#include "omc_stream.h"
+
+namespace omc {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+#define OMC_LDS __attribute__((address_space(3)))
+
+template <bool B>
+struct BoolTag {
+    static constexpr bool value = B;
+};
+
+// LDS byte offset of a __shared__ object, as the direct-to-LDS loads take it.
+__device__ __forceinline__ uint32_t lds_offset(const void *p) {
+    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const OMC_LDS uint8_t *)(p)));
+}
+
+// One wave copies 64 pieces of 16 bytes from global memory into 1 KB of LDS at `dst` (the same in every lane), lane l's
+// piece to dst + 16 l, from base + off (off per lane).  No register is written, so nothing can be overwritten under
+// a load in flight.  Written as asm because the compiler makes every LDS read it cannot tell apart from the target wait for
+// all such loads; the kernels wait for them by count instead (wait_loads_and_sync), which is sound because
+// these are the only vector-memory operations of their loops and return in order.
+__device__ __forceinline__ void load_to_lds(const uint8_t *base, uint32_t off, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "memory", "m0");
+}
+
+// Waits until at most LATER of this wave's vector-memory operations are in flight and its LDS accesses are done, then for
+// the whole workgroup: what the older loads of all waves brought is in LDS, and what was read before may be overwritten.
+template <int LATER>
+__device__ __forceinline__ void wait_loads_and_sync() {
+    static_assert(LATER >= 0 && LATER <= 63, "the counter has six bits");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LATER) : "memory");
+}
+
+// The ring of S stages: waits for stage j of `total` when up to S - 1 of them have been asked for; PER = loads per stage.
+template <int S, int PER>
+__device__ __forceinline__ void wait_stage(uint32_t j, uint32_t total) {
+    static_assert(S >= 2 && S <= 5, "cases below");
+    const uint32_t later = total - 1 - j;
+    if (later >= S - 2) wait_loads_and_sync<(S - 2) * PER>();
+    else if (S > 4 && later == 2) wait_loads_and_sync<(S > 4 ? 2 : 0) * PER>();
+    else if (S > 3 && later == 1) wait_loads_and_sync<(S > 3 ? 1 : 0) * PER>();
+    else wait_loads_and_sync<0>();
+}
+
+// Host: which of a kernel's tile sizes to launch for an M x N result over K.  All figures are measured, in us: `base` is a launch
+// with one tile per compute unit and nothing to multiply, `step` a step of 64 k (of TEAMS times as many with several teams) when
+// every compute unit has at most `resident` workgroups, `loaded` what a step costs per workgroup and unit when all 256 units
+// are busy (matrix cores, LDS and power), `stores` the C stores of 256 tiles.  Estimates lie within 15 % of what was measured over M
+// 256 - 16384, N 128 - 4096, K 256 - 4096, the chosen tile within 7 % of the best one.
+struct GemmTile {
+    uint32_t bm, bn, teams, resident;
+    double base, step, loaded, stores;
+};
+template <int COUNT>
+inline int pick_tile(const GemmTile (&tiles)[COUNT], uint32_t M, uint32_t N, uint32_t K) {
+    int best = -1;
+    double best_cost = 0.0;
+    for (int i = 0; i < COUNT; ++i) {
+        const GemmTile &t = tiles[i];
+        if (M % t.bm != 0 || N % t.bn != 0) continue;
+        const uint64_t count = static_cast<uint64_t>(M / t.bm) * (N / t.bn);
+        if (count > 0x7fffffffull) continue;
+        const double per_unit = static_cast<double>(count) / 256.0;
+        const double alone = t.step * static_cast<double>((count + 256ull * t.resident - 1) / (256ull * t.resident));
+        const double busy = t.loaded * per_unit;
+        const uint64_t steps = (static_cast<uint64_t>(K) + 64ull * t.teams - 1) / (64ull * t.teams);
+        const double cost = t.base + t.stores * per_unit + static_cast<double>(steps) * (alone > busy ? alone : busy);
+        if (best < 0 || cost < best_cost) {
+            best = i;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// Tile of this workgroup in a grid of tiles_m x tiles_n (one-dimensional launch).  Workgroups go to the 8 dies in turn and
+// each die has an L2 of its own, so every die gets a contiguous run of the tile order, in which groups of eight tile rows
+// share their columns.
+__device__ __forceinline__ void tile_of_block(uint32_t tiles_m, uint32_t tiles_n, uint32_t &tm, uint32_t &tn) {
+    const uint32_t total = tiles_m * tiles_n, q = total / 8, r = total % 8, die = blockIdx.x % 8;
+    const uint32_t id = die * q + (die < r ? die : r) + blockIdx.x / 8;
+    const uint32_t rows = tiles_m < 8 ? tiles_m : 8u;
+    const uint32_t group = id / (rows * tiles_n), first = group * rows;
+    const uint32_t height = tiles_m - first < rows ? tiles_m - first : rows;
+    const uint32_t in = id - group * rows * tiles_n;
+    tm = first + in % height;
+    tn = in / height;
+}
+
+// acc += sum of the 8 bfloat16 values of a fragment
+__device__ __forceinline__ float add_fragment(bf16x8 f, float acc) {
+    const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+    const u32x4 x = __builtin_bit_cast(u32x4, f);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t w = x[i];
+        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, acc, false);
+    }
+    return acc;
+}
+
+// A wave's share of the row sums of A to LDS, [team * WN + column wave][BM]; without an offset they must not enter the result,
+// whatever they are.
+template <int WN, int BM, int TM>
+__device__ __forceinline__ void publish_row_sums(float *rowsum, const float (&rsum)[TM], bool wanted, uint32_t team, uint32_t row0,
+                                                 uint32_t wn, uint32_t lane) {
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi) {
+        const float t = rsum[mi] + __shfl_xor(rsum[mi], 32);
+        if (lane < 32) rowsum[(team * WN + wn) * BM + row0 + 32 * mi + lane] = wanted ? t : 0.0f;
+    }
+}
+
+// Team 0's waves add the other teams' tiles to theirs, in order; true for team 0.  `parts`: LDS for (TEAMS - 1) tiles.
+// The barrier also makes the row sums visible.
+template <int TEAMS, int NW, int TM, int TN>
+__device__ __forceinline__ bool add_teams(float *parts, f32x16 (&acc)[TM][TN], uint32_t team, uint32_t wave, uint32_t lane) {
+    constexpr uint32_t kWaveFloats = TM * TN * 16 * 64;
+    if (TEAMS > 1 && team > 0) {
+        float *to = parts + ((team - 1) * NW + wave) * kWaveFloats + lane;
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) to[((mi * TN + ni) * 16 + v) * 64] = acc[mi][ni][v];
+    }
+    __syncthreads();
+    if (TEAMS > 1 && team > 0) return false;
+#pragma unroll
+    for (int t = 1; t < TEAMS; ++t) {
+        const float *from = parts + ((t - 1) * NW + wave) * kWaveFloats + lane;
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[mi][ni][v] += from[((mi * TN + ni) * 16 + v) * 64];
+    }
+    return true;
+}
+
+// C tile = s * acc + b * row sums.  Several waves (PARTS) have each summed a part of the
+// contraction: `rowsum` in LDS, [PARTS][BM].  A lane's accumulators are one column of each 32-column block, so a store instruction of a wave writes two rows
+// of 128 contiguous bytes.  The result is
+// read by another kernel at the earliest: with ordinary stores it displaces the operands, 71.2 instead of 66.4 us and 84 instead
+// of 80 (8192 x 1024 x 4096 and 8192 x 4096 x 1024, new operands each time).
+template <int PARTS, int BM, int TM, int TN>
+__device__ __forceinline__ void store_tile(float *__restrict__ C, uint32_t ldc, const f32x16 (&acc)[TM][TN], const float *rowsum,
+                                           uint32_t row0, uint32_t lane, float s, float b) {
+    const uint32_t f_row = lane & 31u, f_half = lane >> 5;
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const uint32_t row = row0 + 32 * mi + 8 * (v >> 2) + 4 * f_half + (v & 3);
+            float sum = rowsum[row];
+#pragma unroll
+            for (int q = 1; q < PARTS; ++q) sum += rowsum[q * BM + row];
+            const float add = b * sum;
+            float *to = C + static_cast<uint64_t>(row) * ldc + f_row;
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni) __builtin_nontemporal_store(s * acc[mi][ni][v] + add, to + 32 * ni);
+        }
+    }
+}
+
+}  // namespace omc

@@ -185,3 +185,53 @@ def test_large_offset_makes_the_row_sum_term_count(shape):
     dX = run_gemm_dx(dY, packed, gf, sb, M, N, K) if K % 128 == 0 else None
     if dX is not None:
         check(dX, orc.dequant_gemm_dx(dY, packed, of, sb, M, N, K, threads=8), (0, M))
+
+
+def both_directions(EM, M, N, K, rows, sb=None, seed=0):
+    """A [M x K] times W stored [K x N] and times the transpose of W stored [N x K]: the same tiles in both directions."""
+    of, gf = pair(*EM)
+    A = synth.to_bf16_bits(synth.normal_f32(M * K, 1.0, seed + 1) + np.float32(0.25))
+    packed, fitted = orc.compress(synth.normal_f32(K * N, 1 / np.sqrt(K), seed + 2), of)
+    sb = fitted if sb is None else sb
+    sub = np.ascontiguousarray(A.reshape(M, K)[rows]).ravel()
+    worst = check_rows(run_gemm(A, packed, gf, sb, M, N, K), orc.dequant_gemm(sub, packed, of, sb, rows.size, N, K, threads=8), rows)
+    dX = run_gemm_dx(A, packed, gf, sb, M, K, N)            # the same stream read as a weight matrix of N rows, K columns
+    ref = orc.dequant_gemm_dx(sub, packed, of, sb, rows.size, K, N, threads=8)
+    return max(worst, check_rows(dX, ref, rows))
+
+
+@pytest.mark.parametrize("EM", [(1, 0), (2, 0), (2, 1), (3, 1), (3, 2), (2, 3), (3, 3), (4, 3), (5, 2), (4, 4), (2, 7), (3, 7),
+                                (4, 7), (5, 7), (6, 7), (7, 7), (8, 7)])
+@pytest.mark.parametrize("shape", [(256, 128, 96), (256, 256, 1056)])
+def test_every_code_width_half_steps_and_teams(EM, shape):
+    """All widths 2 .. 16 (odd ones start a thread's codes in the middle of a dword), contractions that end on half a step, and
+    workgroups of one team and of several.  1e-5: fp32 sums of 1056 products, each within 2^-24 of the last partial sum."""
+    M, N, K = shape
+    assert both_directions(EM, M, N, K, np.arange(M), sb=np.array([0.75, 0.125], np.float32)) < 1e-5
+
+
+@pytest.mark.parametrize("EM", [(4, 3), (3, 7)])
+@pytest.mark.parametrize("shape", [(256, 256, 2080), (2304, 896, 544), (4096, 1024, 288), (4096, 2048, 96), (4096, 4096, 288), (8192, 1024, 2080)])
+def test_every_tile_size_ends_on_half_a_step(EM, shape):
+    """One shape per tile of the two dispatch tables, 64 x 64 by four teams up to 256 x 256, rows of every tile."""
+    M, N, K = shape
+    assert both_directions(EM, M, N, K, tile_sample_rows(M, seed=K, per_quarter=4)) < 1e-5
+
+
+@pytest.mark.parametrize("shape", [(4096, 2048, 160), (256, 256, 544)])
+def test_top_codes_in_some_tiles_only(shape):
+    """A tile that meets the code that the FP8 conversion reads as NaN is computed again; its neighbours are not."""
+    of, gf = pair(4, 3)
+    M, N, K = shape
+    A = np.zeros((M, K), np.float32)
+    pick = (np.arange(M) * 7 + 3) % K
+    A[np.arange(M), pick] = 1.0
+    codes = ((np.arange(K * N, dtype=np.int64) * 37 + 11) % 254).astype(np.uint32)
+    codes = np.where(codes >= 127, codes + 1, codes)
+    codes[3 * N + 5] = 0x7F                                 # the first tile's columns, an early k
+    codes[(K - 1) * N + N - 1] = 0xFF                       # the last tile's, the last k
+    W = orc.decode(codes, of)
+    packed = orc.pack(codes, 8)
+    assert np.array_equal(run_gemm(synth.to_bf16_bits(A.ravel()), packed, gf, None, M, N, K), W.reshape(K, N)[pick])
+    got = run_gemm_dx(synth.to_bf16_bits(A.ravel()), packed, gf, None, M, K, N)
+    assert np.array_equal(got, W.reshape(N, K)[:, pick].T)
