@@ -5,7 +5,7 @@
 
 namespace omc {
 
-constexpr int kMetaThreads = 256;
+constexpr int kMetaThreads = 1024;
 
 // One workgroup: walks the plan's variable table in order, gives every variable its 16-byte aligned place
 // in the payload (a running sum of the sizes), writes the message's variable table and (s, b) table, and
@@ -13,14 +13,12 @@ constexpr int kMetaThreads = 256;
 __global__ __launch_bounds__(kMetaThreads) void transport_meta_kernel(const uint8_t *__restrict__ plan, uint64_t var_off,
                                                                        const float *__restrict__ sb_table,
                                                                        uint8_t *__restrict__ msg, TransportHeader th) {
-    __shared__ uint64_t scan[kMetaThreads];
-    __shared__ uint64_t carry;
-    const uint32_t tid = threadIdx.x;
+    __shared__ uint64_t wave_sum[kMetaThreads / 64];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const PlanVar *vars = reinterpret_cast<const PlanVar *>(plan + var_off);
     TransportVar *out = reinterpret_cast<TransportVar *>(msg + sizeof(TransportHeader));
     float *sb_out = reinterpret_cast<float *>(msg + th.sb_off);
-    if (tid == 0) carry = 0;
-    __syncthreads();
+    uint64_t carry = 0;                                         // the same in every thread
     uint64_t hash_sum = 0;
     for (uint32_t base = 0; base < th.nvars; base += kMetaThreads) {
         const uint32_t i = base + tid;
@@ -30,17 +28,23 @@ __global__ __launch_bounds__(kMetaThreads) void transport_meta_kernel(const uint
             pv = vars[i];
             bytes = (pv.flags & OMC_VAR_QUANTIZED) ? pv.total_dwords * 4 : (4 * pv.n + 15) / 16 * 16;
         }
-        scan[tid] = bytes;
-        __syncthreads();
-        for (int off = 1; off < kMetaThreads; off <<= 1) {       // inclusive scan of the sizes
-            const uint64_t add = tid >= static_cast<uint32_t>(off) ? scan[tid - off] : 0;
-            __syncthreads();
-            scan[tid] += add;
-            __syncthreads();
+        uint64_t upto = bytes;                                   // inclusive scan of the sizes: within the wave ...
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint64_t add = __shfl_up(upto, off);
+            if (lane >= static_cast<uint32_t>(off)) upto += add;
         }
+        __syncthreads();                                         // (the sums of the round before are read)
+        if (lane == 63) wave_sum[wave] = upto;
+        __syncthreads();
+        uint64_t total = 0;                                      // ... and over the waves before it
+        for (uint32_t w = 0; w < kMetaThreads / 64; ++w) {
+            if (w == wave) upto += carry + total;
+            total += wave_sum[w];
+        }
+        carry += total;
         if (i < th.nvars) {
             TransportVar tv;
-            tv.payload_offset = carry + scan[tid] - bytes;
+            tv.payload_offset = upto - bytes;
             tv.aux_offset = pv.aux_offset;
             tv.n = pv.n;
             const bool q = (pv.flags & OMC_VAR_QUANTIZED) != 0;
@@ -53,18 +57,15 @@ __global__ __launch_bounds__(kMetaThreads) void transport_meta_kernel(const uint
             sb_out[2 * static_cast<uint64_t>(i)] = q ? sb_table[2 * static_cast<uint64_t>(pv.sb_index)] : 1.0f;
             sb_out[2 * static_cast<uint64_t>(i) + 1] = q ? sb_table[2 * static_cast<uint64_t>(pv.sb_index) + 1] : 0.0f;
         }
-        __syncthreads();
-        if (tid == kMetaThreads - 1) carry += scan[tid];
-        __syncthreads();
     }
-    scan[tid] = hash_sum;
+    for (int off = 32; off >= 1; off >>= 1) hash_sum += __shfl_xor(hash_sum, off);
     __syncthreads();
-    for (int off = kMetaThreads / 2; off >= 1; off >>= 1) {
-        if (tid < static_cast<uint32_t>(off)) scan[tid] += scan[tid + off];
-        __syncthreads();
-    }
+    if (lane == 0) wave_sum[wave] = hash_sum;
+    __syncthreads();
+    hash_sum = 0;
+    for (uint32_t w = 0; w < kMetaThreads / 64; ++w) hash_sum += wave_sum[w];
     if (tid == 0) {
-        th.checksum = transport_header_hash(th, scan[0]);
+        th.checksum = transport_header_hash(th, hash_sum);
         *reinterpret_cast<TransportHeader *>(msg) = th;
     }
 }
