@@ -92,7 +92,7 @@ __device__ __forceinline__ void codec_tile_args(const CodecArgs &ca, const PlanV
     }
 }
 
-// A ragged tail as one workgroup; `lds`: kTileElems dwords.
+// A ragged tail as one workgroup; `lds`: kLdsDwords dwords.
 template <int MODE>
 __device__ __forceinline__ void codec_tail(const CodecArgs &ca, uint32_t index, uint32_t *lds) {
     const uint32_t item = ca.tail_first + index;
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(64, (Tuning<MODE, B>::waves)) void codec_kernel(Cod
 // Tails of a set that has no full tile at all.
 template <int MODE>
 __global__ __launch_bounds__(64) void codec_tail_kernel(CodecArgs ca) {
-    __shared__ uint32_t lds[kTileElems];
+    __shared__ uint32_t lds[kLdsDwords];
     codec_tail<MODE>(ca, blockIdx.x, lds);
 }
 

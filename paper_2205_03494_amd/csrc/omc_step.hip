@@ -24,7 +24,7 @@ __global__ __launch_bounds__(64) void step_fp32_kernel(StepArgs sa) {
 // Ragged tails of a set that has no full tile at all, one wave each.
 template <int MODE>
 __global__ __launch_bounds__(64) void step_tail_kernel(StepArgs sa) {
-    __shared__ uint32_t lds[kTileElems];
+    __shared__ uint32_t lds[kLdsDwords];
     step_tail<MODE>(sa, blockIdx.x, lds);
 }
 

@@ -127,7 +127,7 @@ __device__ __forceinline__ void step_tile_args(const StepArgs &sa, const PlanVar
     a.b = to_scalar_regs(sa.sb_table[2 * static_cast<uint64_t>(pv.sb_index) + 1]);
 }
 
-// A ragged tail as one workgroup (code width read from the plan); `lds`: kTileElems dwords.
+// A ragged tail as one workgroup (code width read from the plan); `lds`: kLdsDwords dwords.
 template <int MODE>
 __device__ __forceinline__ void step_tail(const StepArgs &sa, uint32_t index, uint32_t *lds) {
     const PlanItem *items = reinterpret_cast<const PlanItem *>(sa.plan + sa.item_off);

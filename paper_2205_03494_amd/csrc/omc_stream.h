@@ -884,15 +884,16 @@ __device__ __forceinline__ void do_chunk(const TileArgs &a, const FmtParams &fp,
 // ---- the ragged tail of a variable ----------------------------------------------------------------------
 // Elements [e0, n) with e0 a multiple of 2048 and n - e0 < 2048, by one wave.  Same arithmetic as a full tile, but the
 // code width is a run-time value and every access is bounds-checked.  A lane takes every 64th element, so that all
-// streams are coalesced, in batches of kTailBatch whose loads are issued together; the new codes meet in LDS
-// (one dword per element), and each lane then assembles every 64th dword of the packed stream, up to the end of the
-// (16-byte padded) buffer.  What bounds it is latency: a wave on its own needs 4 rounds of loads.  A tail is a workgroup
-// of the full-tile launch (the first ones of the grid), where those rounds pass beside the tiles.  With 32 consecutive elements per lane, one
+// streams are coalesced, in batches whose loads are issued together; the new codes meet in LDS (one dword per element, one
+// spare every 32), and each lane then packs 32 consecutive ones, B whole dwords.  What bounds it is latency, that of the
+// loads first: values to compress are all asked for at once and wait in LDS, the streams of the other modes come in
+// batches of eight (a longer batch costs registers of the whole kernel).  A tail is a workgroup of the full-tile launch (the first
+// ones of the grid), where it passes beside the tiles.  With 32 consecutive elements per lane, one
 // load after the other, and a launch of its own the 89 tails of a 13-bit momentum set (8 blocks of 243 x 971, 90 % packed)
-// took 18.3 us behind a full-tile kernel of 40.6 us: the whole step 65.8 -> 49.1 us; a 9.4 M-element 19-bit variable
-// with a tail, compressed and decompressed: 44.8 -> 39.5 us.
+// took 18.3 us behind a full-tile kernel of 40.6 us: the whole step 65.8 -> 49.1 us.  A 9.4 M-element variable whose tail
+// is almost a tile is compressed in 19.9 us (25.8 with batches of eight values and dwords assembled one by one).
 // The sums of the fit are kept with their rounding errors for the formats whose full-tile kernels do so (fp.variant).
-// `lds`: kTileElems dwords.
+// `lds`: kLdsDwords dwords.
 constexpr uint32_t kTailBatch = 8;
 template <int MODE>
 __device__ __forceinline__ void do_tail(const TileArgs &a, const FmtParams &fp, const OptConst &oc, uint32_t *lds,
@@ -907,18 +908,37 @@ __device__ __forceinline__ void do_tail(const TileArgs &a, const FmtParams &fp, 
     const bool exact = variant_exact(fp.variant);
     FitAcc acc;
     acc.clear();
-    for (uint32_t i0 = lane; i0 < count; i0 += 64u * kTailBatch) {
-        uint32_t lo[kTailBatch], hi[kTailBatch];
-        float x[kTailBatch], g[kTailBatch], m[kTailBatch], v[kTailBatch];
+    // the rounded value's code and its share of the sums
+    auto round_one = [&](uint32_t i, float x) {
+        uint32_t code;
+        float tq;
+        if (fp.wide) encode<true>(x, fp, code, tq); else encode<false>(x, fp, code, tq);
+        acc.seed(tq);
+        if (exact) acc.add<true>(x, tq); else acc.add<false>(x, tq);
+        lds[i + (i >> 5)] = code;
+    };
+    if constexpr (MODE == kCompress) {
+        float x[kLaneElems];
 #pragma unroll
-        for (uint32_t u = 0; u < kTailBatch; ++u) {
+        for (uint32_t u = 0; u < kLaneElems; ++u) x[u] = lane + 64u * u < count ? a.vin[e0 + lane + 64u * u] : 0.0f;
+#pragma unroll
+        for (uint32_t u = 0; u < kLaneElems; ++u) {
+            const uint32_t i = lane + 64u * u;
+            lds[i + (i >> 5)] = __float_as_uint(x[u]);
+        }
+        for (uint32_t i = lane; i < count; i += 64u) round_one(i, __uint_as_float(lds[i + (i >> 5)]));
+    }
+    for (uint32_t i0 = lane; MODE != kCompress && i0 < count; i0 += 64u * kTailBatch) {
+        constexpr uint32_t kBatch = kTailBatch;
+        uint32_t lo[kBatch], hi[kBatch];
+        float x[kBatch], g[kBatch], m[kBatch], v[kBatch];
+#pragma unroll
+        for (uint32_t u = 0; u < kBatch; ++u) {
             const uint32_t i = i0 + 64u * u;
             const bool live = i < count;
             lo[u] = hi[u] = 0u;
             x[u] = g[u] = m[u] = v[u] = 0.0f;
-            if (MODE == kCompress) {
-                if (live) x[u] = a.vin[e0 + i];
-            } else if (live) {
+            if (live) {
                 const uint32_t d = (i * B) >> 5;
                 lo[u] = a.codes[dw0 + d];
                 if (d + 1 < dwords) hi[u] = a.codes[dw0 + d + 1];
@@ -928,16 +948,14 @@ __device__ __forceinline__ void do_tail(const TileArgs &a, const FmtParams &fp, 
             if (MODE == kStepAdam && live) v[u] = a.st1[e0 + i];
         }
 #pragma unroll
-        for (uint32_t u = 0; u < kTailBatch; ++u) {
+        for (uint32_t u = 0; u < kBatch; ++u) {
             const uint32_t i = i0 + 64u * u;
             if (i >= count) break;
-            if (MODE != kCompress) {
-                const uint64_t both = (static_cast<uint64_t>(hi[u]) << 32) | lo[u];
-                const uint32_t code = static_cast<uint32_t>(both >> ((i * B) & 31u)) & cmask;
-                const float vt = decode_top(code << (32u - B), fp);
-                const float sv = a.s * vt;
-                x[u] = sv + a.b;
-            }
+            const uint64_t both = (static_cast<uint64_t>(hi[u]) << 32) | lo[u];
+            const uint32_t old = static_cast<uint32_t>(both >> ((i * B) & 31u)) & cmask;
+            const float vt = decode_top(old << (32u - B), fp);
+            const float sv = a.s * vt;
+            x[u] = sv + a.b;
             if (MODE == kDecompress) {
                 a.vout[e0 + i] = x[u];
                 continue;
@@ -947,24 +965,26 @@ __device__ __forceinline__ void do_tail(const TileArgs &a, const FmtParams &fp, 
                 if (MODE >= kStepMomentum) a.st0[e0 + i] = m[u];
                 if (MODE == kStepAdam) a.st1[e0 + i] = v[u];
             }
-            uint32_t code;
-            float tq;
-            if (fp.wide) encode<true>(x[u], fp, code, tq); else encode<false>(x[u], fp, code, tq);
-            acc.seed(tq);
-            if (exact) acc.add<true>(x[u], tq); else acc.add<false>(x[u], tq);
-            lds[i] = code;
+            round_one(i, x[u]);
         }
     }
     if (MODE == kDecompress) return;
     lds_fence();                                             // every code of the tail is read and every new one in LDS
-    for (uint32_t d = lane; d < dwords; d += 64u) {
-        const uint32_t bit0 = 32u * d;
-        uint32_t out = 0;
-        for (uint32_t i = bit0 / B; i < count && i * B < bit0 + 32u; ++i) {      // padding past the last element stays zero
-            const uint32_t at = i * B;
-            out |= at >= bit0 ? lds[i] << (at - bit0) : lds[i] >> (bit0 - at);
+    // a lane's 32 codes as B dwords (elements past the last one are zero bits), and what is left of the padding
+    uint64_t bits = 0;
+    uint32_t fill = 0, d = lane * B;
+#pragma unroll 8
+    for (uint32_t k = 0; k < kLaneElems; ++k) {
+        const uint32_t i = lane * kLaneElems + k;
+        const uint32_t code = i < count ? lds[i + lane] : 0u;
+        bits |= static_cast<uint64_t>(code) << fill;
+        fill += B;
+        if (fill >= 32u) {                                    // the same in every lane
+            if (d < dwords) a.codes[dw0 + d] = static_cast<uint32_t>(bits);
+            bits >>= 32;
+            fill -= 32u;
+            ++d;
         }
-        a.codes[dw0 + d] = out;
     }
     if (exact) acc.reduce_and_store<true>(partial_out); else acc.reduce_and_store<false>(partial_out);
 }
@@ -997,9 +1017,9 @@ __device__ __forceinline__ void finalize_variable(const Partial *__restrict__ pa
     float tmin = __builtin_huge_valf(), tmax = -__builtin_huge_valf();
     bool finite = true;
     const uint32_t total = nparts + (tail ? 1u : 0u);
-    // a lane's partials are fetched eight at a time before they are added (same order of additions; the
+    // a lane's partials are fetched a few at a time before they are added (same order of additions; the
     // loads of a batch are in flight together instead of one memory round trip per partial)
-    constexpr uint32_t kBatch = 8, kStride = 64 * NW;
+    constexpr uint32_t kBatch = NW > 8 ? 2 : 8, kStride = 64 * NW;   // (16 waves share the registers: eight would spill)
     for (uint32_t i0 = tid; i0 < total; i0 += kBatch * kStride) {
         double p[kBatch][4], l[kBatch][4];
         float lo[kBatch], hi[kBatch];
