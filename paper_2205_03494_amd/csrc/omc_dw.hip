@@ -1,12 +1,11 @@
 // omc_dw_update_recompress: the backward pass of a linear layer on a compressed weight matrix
 // (paper Sec. 2.1, backward propagation: decompress the layer's parameters, apply the gradients,
-// compress, discard).  The weight gradient dW = X^T dY is formed on the matrix cores and consumed in
-// the epilogue of the same kernel: the tile's codes are read, decoded and transformed (Sec. 2.2,
-// 2.3), updated with the accumulators as gradient, rounded and written back, and the sums of the fit
-// are taken on the way.  With an 8-bit format and enough tiles for the chip the fp32 gradient never exists
-// in memory (unless the caller asks for a copy); on the other routes -- contraction split between
-// workgroups, code widths other than 8, the 16-wave kernel -- the accumulators pass through the workspace
-// once and a second kernel consumes them.
+// compress, discard).  The weight gradient dW = X^T dY is formed on the matrix cores and consumed at once.  Two routes
+// (dw_route): the gradient passes through the workspace once as partial sums and a second kernel runs the cycle on them, for
+// any code width; or, for 8-bit formats with enough tiles for the chip or a contraction too short to share out, in the kernel
+// below, whose epilogue reads the tile's codes, decodes and transforms them (Sec. 2.2, 2.3), updates them with the accumulators as
+// gradient, rounds, writes them back and takes the sums of the fit: the fp32 gradient then never exists in memory (unless the
+// caller asks for a copy).
 //
 // Tiling.  Workgroup = 4 waves, tile of W = 256 rows (k) x 128 columns (n), contraction over the M rows of
 // X and dY in steps of 32.  Both operands are contraction-strided in memory, so threads load 4 x 4
@@ -217,20 +216,18 @@ __global__ __launch_bounds__(256, ROWS == 256 ? 2 : 3) void dw_update_kernel(DwA
     };
 
     // the loads of step ms + 2 are issued right after the barrier that ends round ms
-    // this workgroup's share of the contraction: rows [m_begin, m_begin + nm * 32) of X and dY
-    const uint32_t nm = a.M / kDwStep / a.nsplit;
-    const uint32_t m_begin = blockIdx.z * nm * kDwStep;
-    load_stage(m_begin);
+    const uint32_t nm = a.M / kDwStep;
+    load_stage(0);
     store_stage(lds);
     __syncthreads();
-    if (nm > 1) load_stage(m_begin + kDwStep);
+    if (nm > 1) load_stage(kDwStep);
     uint32_t ms = 0;
     for (; ms + 2 < nm; ++ms) {
         const uint32_t cur = (ms & 1u) * kDwStageBytes;
         multiply_stage(lds + cur);
         store_stage(lds + (kDwStageBytes - cur));
         __syncthreads();
-        load_stage(m_begin + (ms + 2) * kDwStep);
+        load_stage((ms + 2) * kDwStep);
     }
     for (; ms < nm; ++ms) {
         const uint32_t cur = (ms & 1u) * kDwStageBytes;
@@ -242,160 +239,7 @@ __global__ __launch_bounds__(256, ROWS == 256 ? 2 : 3) void dw_update_kernel(DwA
     }
 
     const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x;     // tile index
-    // ---- park the accumulators (accumulator layout, 16 bytes per lane and row): several splits of the
-    // contraction, or a code width other than 8; the slab kernels add them up in split order and do the rest
-    if (a.park) {
-        constexpr uint32_t kTileFloats = ROWS * kDwCols;
-        float *mine = a.partials + (static_cast<uint64_t>(block) * a.nsplit + blockIdx.z) * kTileFloats;
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                __builtin_nontemporal_store(f32x4{acc[mi][0][v], acc[mi][1][v], acc[mi][2][v], acc[mi][3][v]},
-                                            reinterpret_cast<f32x4 *>(mine) + ((mi * 16 + v) * 256 + tid));
-        return;
-    }
-
     dw_finish_wave<ROWS, MODE>(a, acc, k0t, n0, lane, wave, block);
-}
-
-// ---- wave-specialised variant (at most one tile per compute unit, long contraction) ---------------
-// 16 waves: waves 0-7 only multiply (64 x 64 of the tile each), waves 8-15 only stage: each thread of
-// them brings in one 4 x 4 patch of X per step, the threads of waves 12-15 also one patch of dY.  Three LDS
-// stages; stage j is complete at barrier j, its fragments are read during round j + 1 and multiplied
-// during round j + 2; global loads run three steps ahead.  Tile columns sit in LDS so that a multiplying
-// wave's 64 columns are consecutive slots (column 64 h + 2 q + i at slot 64 h + 32 i + q).  The accumulators
-// are always parked, in the layout of the four-wave kernel, and the slab kernels do the update.
-constexpr int kDwWsStages = 3;
-constexpr int kDwWsStageBytes = 4 * 256 * 16 + 4 * kDwBChunk;
-
-__global__ __launch_bounds__(1024, 1) void dw_update_ws_kernel(DwArgs a) {
-    constexpr int kDwAChunk = 256 * 16;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kDwWsStages * kDwWsStageBytes];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t k0t = blockIdx.x * 256, n0 = blockIdx.y * kDwCols;
-    const uint32_t K = a.K, N = a.N;
-    const uint32_t nm = a.M / kDwStep / a.nsplit;           // this workgroup's share of the contraction, in steps
-    const uint32_t m_begin = blockIdx.z * nm * kDwStep;
-
-    if (wave < 8) {
-        const uint32_t wm = wave >> 1, wh = wave & 1u;
-        const uint32_t f_row = lane & 31u, f_half = lane >> 5;
-        f32x16 acc[2][2];
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
-        struct Frags {
-            bf16x8 a[2], b[2];
-        };
-        auto read_frags = [&](const uint8_t *st, int ks, Frags &f) {
-            const uint32_t chunk = 2 * ks + f_half;
-#pragma unroll
-            for (int mi = 0; mi < 2; ++mi) {
-                const uint32_t row = 64 * wm + 32 * mi + f_row;
-                f.a[mi] = *reinterpret_cast<const bf16x8 *>(st + chunk * kDwAChunk + (dw_a_slot(row, chunk) << 4));
-            }
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni)
-                f.b[ni] = *reinterpret_cast<const bf16x8 *>(st + 4 * kDwAChunk + chunk * kDwBChunk +
-                                                            ((64u * wh + 32u * ni + f_row) << 4));
-        };
-        auto multiply_frags = [&](const Frags &f) {
-#pragma unroll
-            for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < 2; ++ni)
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mi], f.b[ni], acc[mi][ni], 0, 0, 0);
-        };
-        Frags f0, f1;
-        __syncthreads();                                    // barrier 0: stage 0 is complete
-        read_frags(lds, 0, f0);
-        read_frags(lds, 1, f1);
-        __syncthreads();                                    // barrier 1
-        uint32_t nxt = kDwWsStageBytes;                     // LDS offset of stage j - 1
-        for (uint32_t j = 2; j < nm + 2; ++j) {
-            const bool more = j - 1 < nm;
-            multiply_frags(f0);
-            if (more) read_frags(lds + nxt, 0, f0);
-            multiply_frags(f1);
-            if (more) read_frags(lds + nxt, 1, f1);
-            nxt = (nxt == (kDwWsStages - 1) * kDwWsStageBytes) ? 0u : nxt + kDwWsStageBytes;
-            __syncthreads();                                // barrier j
-        }
-        // park: element (tile row, column c) goes where the four-wave kernel's lane (row's wave, c / 4) puts it
-        const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x;
-        constexpr uint32_t kTileFloats = 256 * kDwCols;
-        float *mine = a.partials + (static_cast<uint64_t>(block) * a.nsplit + blockIdx.z) * kTileFloats;
-        const uint32_t owner = 64 * wm + 32 * f_half + 16 * wh + (f_row >> 1);
-        const uint32_t sub = 2 * (f_row & 1u);
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                __builtin_nontemporal_store(f32x2{acc[mi][0][v], acc[mi][1][v]},
-                                            reinterpret_cast<f32x2 *>(mine + (static_cast<uint32_t>(mi * 16 + v) * 256 + owner) * 4 + sub));
-        return;
-    }
-
-    // ---- staging waves ---------------------------------------------------------------------------------
-    const uint32_t pt = tid - 512u;
-    const bool does_y = wave >= 12;
-    const uint32_t x_kq = (pt >> 1) & 63u, x_mg = 2 * (pt >> 7) + (pt & 1u);
-    const uint32_t wt = tid & 255u;
-    const uint32_t y_nq = wt & 31u, y_mg = wt >> 5;
-    struct Regs {
-        u32x2 x[4], y[4];
-    };
-    Regs r[kDwWsStages];
-    auto load_stage = [&](Regs &g, uint32_t m0) {
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr)
-            g.x[rr] = *reinterpret_cast<const u32x2 *>(a.X + static_cast<uint64_t>(m0 + 4 * x_mg + rr) * K + k0t + 4 * x_kq);
-        if (!does_y) return;
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr)
-            g.y[rr] = *reinterpret_cast<const u32x2 *>(a.dY + static_cast<uint64_t>(m0 + 4 * y_mg + rr) * N + n0 + 4 * y_nq);
-    };
-    auto store_stage = [&](const Regs &g, uint8_t *st) {
-        const uint32_t xc = x_mg >> 1;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t row = 64 * i + x_kq;
-            *reinterpret_cast<u32x2 *>(st + xc * kDwAChunk + (dw_a_slot(row, xc) << 4) + 8u * (x_mg & 1u)) = patch_column(g.x, i);
-        }
-        if (!does_y) return;
-        const uint32_t yc = y_mg >> 1;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t c = 4 * y_nq + i;
-            const uint32_t slot = (c & 64u) + 32u * (c & 1u) + ((c & 63u) >> 1);
-            *reinterpret_cast<u32x2 *>(st + 4 * kDwAChunk + yc * kDwBChunk + (slot << 4) + 8u * (y_mg & 1u)) = patch_column(g.y, i);
-        }
-    };
-#pragma unroll
-    for (int u = 0; u < kDwWsStages; ++u)
-        if (static_cast<uint32_t>(u) < nm) load_stage(r[u], m_begin + u * kDwStep);
-    uint32_t j = 0;
-    for (; j + kDwWsStages <= nm; j += kDwWsStages) {
-#pragma unroll
-        for (int u = 0; u < kDwWsStages; ++u) {
-            store_stage(r[u], lds + u * kDwWsStageBytes);
-            if (j + u + kDwWsStages < nm) load_stage(r[u], m_begin + (j + u + kDwWsStages) * kDwStep);
-            __syncthreads();                                // barrier j + u
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < kDwWsStages - 1; ++u)
-        if (j + u < nm) {
-            store_stage(r[u], lds + u * kDwWsStageBytes);
-            __syncthreads();
-        }
-    __syncthreads();                                        // barriers nm and nm + 1: the multiplying waves drain
-    __syncthreads();
 }
 
 template <int NW>
@@ -405,47 +249,44 @@ __global__ __launch_bounds__(64 * NW) void dw_finalize_kernel(const Partial *__r
     finalize_variable<NW>(ws, nparts, nullptr, n, use_pvt != 0, exact != 0, sb, red);
 }
 
-// one Partial per 16-row x 128-column slab (the finest grain any of the update kernels uses)
+// one Partial per 2048 elements (the finest grain any of the update kernels uses)
 static size_t dw_fit_bytes(uint32_t N, uint32_t K) {
     return (static_cast<size_t>(K) * N / kTileElems * sizeof(Partial) + 255) / 256 * 256;
 }
 
-// Tile height and number of contraction splits for a problem size: 256-row tiles and no split when
-// that already gives two workgroups per compute unit; otherwise split the M rows (each split at least
-// 512 rows, at most 8 splits) and, if that is still not enough, take 128-row tiles.
-DwConfig dw_config(uint32_t M, uint32_t N, uint32_t K) {
-    DwConfig c{256, 1, 0};
-    const uint64_t tiles256 = static_cast<uint64_t>(K / 256) * (N / kDwCols);
-    // At most one workgroup per compute unit with at least 2048 rows of the contraction each, and at least
-    // half of the compute units busy: the wave-specialised kernel.
-    if (K % 256 == 0 && tiles256 <= 256) {
+// The route of a call, by its sizes and code width alone (so that the workspace follows from them): 8-bit codes whose
+// tiles fill the chip without sharing out the contraction, or whose contraction is too short to share out, are updated in
+// the epilogue of the matrix-core kernel and need no room for a gradient; every other call gets room for `splits` partial sums.
+struct DwRoute {
+    uint32_t rows;     // weight rows per tile of the one-kernel route: 256 or 128
+    uint32_t splits;   // partial sums of the gradient that the workspace holds; 0: one kernel
+};
+static DwRoute dw_route(uint32_t bits, uint32_t M, uint32_t N, uint32_t K) {
+    const uint64_t tiles = static_cast<uint64_t>(K / 256) * (N / kDwCols);
+    if (tiles <= 256) {                                       // at most one 256 x 128 tile per compute unit and a long contraction
         uint32_t sp = 1;
-        while (tiles256 * (2 * sp) <= 256 && sp < 8 && M % (2 * sp * kDwStep) == 0 && M / (2 * sp) >= 2048) sp *= 2;
-        if (M / sp >= 2048 && tiles256 * sp >= 128) return DwConfig{256, sp, 1};
+        while (tiles * (2 * sp) <= 256 && sp < 8 && M % (2 * sp * kDwStep) == 0 && M / (2 * sp) >= 2048) sp *= 2;
+        if (M / sp >= 2048 && tiles * sp >= 128) return DwRoute{256, sp};
     }
-    auto splits_for = [&](uint64_t tiles) {
+    auto splits_for = [&](uint64_t count) {
         uint32_t sp = 1;
-        while (tiles * sp < 512 && sp < 8 && M % (2 * sp * kDwStep) == 0 && M / (2 * sp) >= 512) sp *= 2;
+        while (count * sp < 512 && sp < 8 && M % (2 * sp * kDwStep) == 0 && M / (2 * sp) >= 512) sp *= 2;
         return sp;
     };
-    c.nsplit = splits_for(tiles256);
-    if (tiles256 * c.nsplit < 512) {
-        c.rows = 128;
-        c.nsplit = splits_for(2 * tiles256);
-    }
-    return c;
+    DwRoute r{256, splits_for(tiles)};
+    if (tiles * r.splits < 512) r = DwRoute{128, splits_for(2 * tiles)};
+    if (bits == 8 && r.splits == 1) r.splits = 0;
+    return r;
 }
 
 int launch_dw_update(const uint16_t *X, const uint16_t *dY, void *codes, const FmtParams &fp, float *sb, int use_pvt,
                      float *state0, float *state1, const omc_opt &opt, float *dW_out, uint32_t M, uint32_t N,
                      uint32_t K, void *ws, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const DwConfig cfg = dw_config(M, N, K);
-    const uint32_t tiles = (K / cfg.rows) * (N / kDwCols);
-    // workspace: the fit's partials (one per 16-row slab at most) | parked accumulators
+    const DwRoute route = dw_route(fp.bits, M, N, K);
+    // workspace: the fit's partials | the gradient's partial sums
     uint8_t *w8 = static_cast<uint8_t *>(ws);
-    const size_t fit_bytes = dw_fit_bytes(N, K);
-    const bool byte_codes = fp.bits == 8;
+    float *sums = reinterpret_cast<float *>(w8 + dw_fit_bytes(N, K));
     DwArgs a{};
     a.X = X;
     a.dY = dY;
@@ -455,38 +296,37 @@ int launch_dw_update(const uint16_t *X, const uint16_t *dY, void *codes, const F
     a.st1 = opt.kind == OMC_ADAM ? state1 : nullptr;
     a.dW_out = dW_out;
     a.ws = reinterpret_cast<Partial *>(w8);
-    a.partials = reinterpret_cast<float *>(w8 + fit_bytes);
-    a.park = (cfg.nsplit > 1 || !byte_codes || cfg.ws) ? 1u : 0u;
-    a.nsplit = cfg.nsplit;
+    a.partials = sums;
     a.fp = fp;
     a.oc = OptConst{opt.lr, opt.momentum, opt.beta1, opt.beta2, opt.eps, opt.one_minus_beta1,
                     opt.one_minus_beta2, opt.bias_corr1, opt.bias_corr2};
     a.M = M;
     a.N = N;
     a.K = K;
-    const dim3 grid(K / cfg.rows, N / kDwCols, cfg.nsplit);
+    uint32_t nparts;
+    int rc;
+    if (route.splits == 0) {
+        const dim3 grid(K / route.rows, N / kDwCols);
+        nparts = 4u * grid.x * grid.y;
 #define OMC_DW_LAUNCH(ROWS)                                                                      \
     do {                                                                                         \
         if (opt.kind == OMC_SGD) dw_update_kernel<ROWS, kStepSgd><<<grid, dim3(256), 0, st>>>(a); \
         else if (opt.kind == OMC_MOMENTUM) dw_update_kernel<ROWS, kStepMomentum><<<grid, dim3(256), 0, st>>>(a); \
         else dw_update_kernel<ROWS, kStepAdam><<<grid, dim3(256), 0, st>>>(a);                    \
     } while (0)
-    if (cfg.ws) dw_update_ws_kernel<<<grid, dim3(1024), 0, st>>>(a);
-    else if (cfg.rows == 128) OMC_DW_LAUNCH(128);
-    else OMC_DW_LAUNCH(256);
+        if (route.rows == 128) OMC_DW_LAUNCH(128);
+        else OMC_DW_LAUNCH(256);
 #undef OMC_DW_LAUNCH
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return static_cast<int>(e);
-    uint32_t nparts = 4u * tiles;
-    if (a.park) {                                          // the slab kernels do the update, whatever the code width
-        const uint32_t tx = K / cfg.rows;
-        int rc;
-        if (opt.kind == OMC_SGD) rc = launch_dw_generic_sgd(fp.bits, fp.variant == 2 || fp.variant == 3 ? 0u : fp.variant, cfg.rows, a, tiles, tx, st);
-        else if (opt.kind == OMC_MOMENTUM) rc = launch_dw_generic_momentum(fp.bits, fp.variant == 2 || fp.variant == 3 ? 0u : fp.variant, cfg.rows, a, tiles, tx, st);
-        else rc = launch_dw_generic_adam(fp.bits, fp.variant == 2 || fp.variant == 3 ? 0u : fp.variant, cfg.rows, a, tiles, tx, st);
-        if (rc != 0) return rc;
+        rc = static_cast<int>(hipGetLastError());
+    } else {
         nparts = static_cast<uint32_t>(static_cast<uint64_t>(K) * N / kTileElems);
+        rc = launch_dw_product(X, dY, sums, M, N, K, route.splits, &a.nsplit, st);
+        if (rc != 0) return rc;
+        if (opt.kind == OMC_SGD) rc = launch_dw_update_sgd(a, st);
+        else if (opt.kind == OMC_MOMENTUM) rc = launch_dw_update_momentum(a, st);
+        else rc = launch_dw_update_adam(a, st);
     }
+    if (rc != 0) return rc;
     const uint64_t n = static_cast<uint64_t>(K) * N;
     // the width of the reduction depends on the sizes alone, so results do not depend on the run
     const int exact = variant_exact(fp.variant) ? 1 : 0;
@@ -497,10 +337,7 @@ int launch_dw_update(const uint16_t *X, const uint16_t *dY, void *codes, const F
 }
 
 size_t dw_workspace_bytes(uint32_t bits, uint32_t M, uint32_t N, uint32_t K) {
-    const DwConfig cfg = dw_config(M, N, K);
-    const bool park = cfg.nsplit > 1 || bits != 8 || cfg.ws;
-    const size_t partial_bytes = park ? static_cast<size_t>(cfg.nsplit) * K * N * sizeof(float) : 0;
-    return dw_fit_bytes(N, K) + partial_bytes;
+    return dw_fit_bytes(N, K) + static_cast<size_t>(dw_route(bits, M, N, K).splits) * K * N * sizeof(float);
 }
 
 }  // namespace omc

@@ -1,4 +1,4 @@
-// Shared by the weight-gradient kernels (omc_dw.hip) and their any-code-width update kernels.
+// Shared by the kernels of omc_dw_update_recompress.
 #pragma once
 #include "omc_stream.h"
 
@@ -13,21 +13,20 @@ struct DwArgs {
     float *st0, *st1;
     float *dW_out;
     Partial *ws;
-    float *partials;         // split contraction: [tile][split][ROWS * 128] accumulators
-    uint32_t nsplit;         // workgroups per tile along the contraction (gridDim.z)
-    uint32_t park;           // 1: the matrix-core kernel only parks its accumulators (several splits, or a code
-                             // width other than 8, whose update runs in a kernel of its own)
+    const float *partials;   // two-kernel route: [nsplit][K * N] partial sums of the gradient
+    uint32_t nsplit;
     FmtParams fp;
     OptConst oc;
     uint32_t M, N, K;
 };
 
-// Second kernel of omc_dw_update_recompress for code widths other than 8: one launcher per optimizer.
-int launch_dw_generic_sgd(uint32_t bits, uint32_t variant, uint32_t rows, const DwArgs &a, uint32_t tiles, uint32_t tiles_x,
-                          hipStream_t st);
-int launch_dw_generic_momentum(uint32_t bits, uint32_t variant, uint32_t rows, const DwArgs &a, uint32_t tiles, uint32_t tiles_x,
-                               hipStream_t st);
-int launch_dw_generic_adam(uint32_t bits, uint32_t variant, uint32_t rows, const DwArgs &a, uint32_t tiles, uint32_t tiles_x,
-                           hipStream_t st);
+// First kernel of the two-kernel route: the gradient as *nsplit <= most_splits partial sums.
+int launch_dw_product(const uint16_t *X, const uint16_t *dY, float *partials, uint32_t M, uint32_t N, uint32_t K, uint32_t most_splits,
+                      uint32_t *nsplit, hipStream_t st);
+
+// Second kernel: adds them up and runs the cycle; one launcher per optimizer.
+int launch_dw_update_sgd(const DwArgs &a, hipStream_t st);
+int launch_dw_update_momentum(const DwArgs &a, hipStream_t st);
+int launch_dw_update_adam(const DwArgs &a, hipStream_t st);
 
 }  // namespace omc

@@ -1,0 +1,202 @@
+// The weight gradient dW[K x N] = X^T dY of omc_dw_update_recompress, as `nsplit` partial sums over runs of the M rows, row-major
+// in the workspace; the update kernels add them in order.
+//
+// Both operands lie along the contraction, X as [M x K] and dY as [M x N], and go from global memory straight into a ring of S LDS
+// stages of 32 rows, as they are.  The transposing 16-bit read (ds_read_b64_tr_b16) makes matrix fragments of them: of 16 lanes
+// that point at four rows x 16 columns, lane c receives column c's four rows.  Staging costs no vector instruction.  The
+// 64-byte groups of a row are XOR-swizzled by f(row) = (row & 3) + 4 * (bit 3 of the row), as far as the row has groups, on the way in
+// (the lane picks the piece, its LDS place is fixed): the eight rows of one read then lie on different banks.
+//
+// A weight matrix gives few tiles (4 M weights = 128 of 256 x 128) and the contraction is long, so it is shared out twice: between
+// TEAMS of waves of a workgroup, which add up their tiles through LDS, and between workgroups (nsplit).
+//
+// What bounds it: LDS bandwidth (36 KB per 16 rows of a 256 x 128 tile: 12 % more than 128 B/clk carry at the matrix cores' rate).
+#include "omc_dw_args.h"
+#include "omc_mma.h"
+
+namespace omc {
+
+struct ProductArgs {
+    const uint16_t *X, *dY;
+    float *partials;                     // [nsplit][K][N]
+    uint32_t N, K, steps, nsplit;        // steps of 32 rows in all
+    uint32_t tiles_k, tiles_n;
+};
+
+// WM x WN waves of TM x TN matrix tiles (32 x 32) each, TEAMS times; S stages, OCC waves per SIMD.
+template <int WM, int WN, int TM, int TN, int TEAMS, int S, int OCC>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN * TEAMS, 64 * WM * WN * TEAMS))) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
+void dw_product_kernel(ProductArgs pa) {
+    constexpr int NW = WM * WN, BK = 32 * TM * WM, BN = 32 * TN * WN;
+    constexpr int kXLoads = BK / 16 / NW, kYLoads = BN / 16 / NW, kLoads = kXLoads + kYLoads;   // 1 KB loads per wave and stage
+    constexpr uint32_t kXBytes = BK * 64, kStage = kXBytes + BN * 64;
+    static_assert(BK % (16 * NW) == 0 && BN % (16 * NW) == 0, "whole loads");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_all[TEAMS * S * kStage];
+    const uint32_t team = TEAMS == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
+    uint8_t *lds = lds_all + team * (S * kStage);
+    const uint32_t lds0 = lds_offset(lds);
+    const uint32_t tid = TEAMS == 1 ? threadIdx.x : threadIdx.x % (64 * NW), lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
+    const uint32_t N = pa.N, K = pa.K;
+    uint32_t k0, n0;
+    tile_of_block(pa.tiles_k, pa.tiles_n, k0, n0);
+    k0 *= BK;
+    n0 *= BN;
+    // this workgroup's steps, and its teams' shares of them: team t takes t, t + TEAMS, ...
+    const uint32_t split = blockIdx.y;
+    const uint32_t begin = static_cast<uint32_t>(static_cast<uint64_t>(pa.steps) * split / pa.nsplit);
+    const uint32_t end = static_cast<uint32_t>(static_cast<uint64_t>(pa.steps) * (split + 1) / pa.nsplit);
+    const uint32_t mine = (end - begin + TEAMS - 1 - team) / TEAMS, most = (end - begin + TEAMS - 1) / TEAMS;
+
+    // ---- global -> LDS
+    auto f = [](uint32_t row) { return (row & 3u) | ((row >> 1) & 4u); };
+    auto load_operand = [&](auto width, const uint16_t *base, uint32_t ld, uint32_t col0, uint32_t at, uint32_t j) {
+        constexpr uint32_t W = decltype(width)::value, kRows = 512 / W, kSlots = W / 8;
+        const uint8_t *from = reinterpret_cast<const uint8_t *>(base) + (static_cast<uint64_t>(j) * 32 * ld + col0) * 2;
+#pragma unroll
+        for (uint32_t i = 0; i < W / 16 / NW; ++i) {
+            const uint32_t c = wave + NW * i, in = lane / kSlots, row = c * kRows + in, slot = lane % kSlots;
+            const uint32_t piece = (((slot >> 2) ^ (f(row) & (W / 32 - 1))) << 2) | (slot & 3u);
+            load_to_lds(from + static_cast<uint64_t>(c) * kRows * ld * 2, in * ld * 2 + piece * 16, lds0 + at + c * 1024);
+        }
+    };
+    auto load_stage = [&](uint32_t at, uint32_t i) {
+        const uint32_t j = begin + team + TEAMS * i;
+        load_operand(UintTag<BK>{}, pa.X, K, k0, at, j);
+        load_operand(UintTag<BN>{}, pa.dY, N, n0, at + kXBytes, j);
+    };
+
+    // ---- LDS -> fragments of 16 rows: 32 columns x 8 rows of either half
+    const uint32_t row = 8 * (lane >> 5) + ((lane & 15u) >> 2), piece = 2 * ((lane >> 4) & 1u) + ((lane >> 1) & 1u), byte = 8 * (lane & 1u);
+    uint32_t x_at[TM], y_at[TN];
+#pragma unroll
+    for (uint32_t mi = 0; mi < TM; ++mi) x_at[mi] = row * (2 * BK) + (((TM * wm + mi) ^ (f(row) & (BK / 32 - 1))) * 4 + piece) * 16 + byte;
+#pragma unroll
+    for (uint32_t ni = 0; ni < TN; ++ni) y_at[ni] = kXBytes + row * (2 * BN) + (((TN * wn + ni) ^ (f(row) & (BN / 32 - 1))) * 4 + piece) * 16 + byte;
+    auto read_one = [&](uint32_t at, uint32_t four_rows) {
+        typedef short s16x8 __attribute__((ext_vector_type(8)));
+        uint8_t *q = lds + at;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((OMC_LDS s16x4 *)(q));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((OMC_LDS s16x4 *)(q + four_rows));
+        const s16x8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        return __builtin_bit_cast(bf16x8, both);
+    };
+    struct Frags {
+        bf16x8 x[TM], y[TN];
+    };
+    auto read_frags = [&](uint32_t at, uint32_t half, Frags &t) {
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi) t.x[mi] = read_one(at + x_at[mi] + half * 16 * (2 * BK), 4 * 2 * BK);
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) t.y[ni] = read_one(at + y_at[ni] + half * 16 * (2 * BN), 4 * 2 * BN);
+    };
+    f32x16 acc[TM][TN];
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
+    auto multiply = [&](const Frags &t) {
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+            for (int mi = 0; mi < TM; ++mi) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(t.x[mi], t.y[ni], acc[mi][ni], 0, 0, 0);
+    };
+
+    Frags f0, f1;
+    uint32_t cur = 0, far = (S - 1) * kStage;
+    auto rest_of_step = [&]() {
+        read_frags(cur, 1, f1);
+        multiply(f0);
+        cur = cur == (S - 1) * kStage ? 0 : cur + kStage;
+        far = far == (S - 1) * kStage ? 0 : far + kStage;
+    };
+#pragma unroll
+    for (uint32_t i = 0; i < S - 1; ++i)
+        if (i < mine) load_stage(i * kStage, i);
+    if (mine > 0) {
+        wait_stage<S, kLoads>(0, mine);
+        read_frags(cur, 0, f0);
+        if (mine > S - 1) load_stage(far, S - 1);
+        rest_of_step();
+        uint32_t i = 1;
+        for (; i + (S - 1) < mine; ++i) {
+            wait_loads_and_sync<(S - 2) * kLoads>();
+            read_frags(cur, 0, f0);
+            load_stage(far, i + S - 1);
+            multiply(f1);
+            rest_of_step();
+        }
+        for (; i < mine; ++i) {
+            wait_stage<S, kLoads>(i, mine);
+            read_frags(cur, 0, f0);
+            multiply(f1);
+            rest_of_step();
+        }
+        multiply(f1);
+    }
+    for (uint32_t i = mine; i < most; ++i) wait_loads_and_sync<0>();   // teams wait for each other
+    wait_loads_and_sync<0>();                                 // nobody reads a stage any more
+    static_assert((TEAMS - 1) * BK * BN * 4 <= TEAMS * S * static_cast<int>(kStage), "the other teams' tiles fit the stages");
+    if (!add_teams<TEAMS, NW, TM, TN>(reinterpret_cast<float *>(lds_all), acc, team, wave, lane)) return;
+    float *to = pa.partials + static_cast<uint64_t>(split) * K * N + static_cast<uint64_t>(k0 + 32 * TM * wm + 4 * (lane >> 5)) * N +
+                n0 + 32 * TN * wn + (lane & 31u);
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni) to[static_cast<uint64_t>(32 * mi + 8 * (v >> 2) + (v & 3)) * N + 32 * ni] = acc[mi][ni][v];
+}
+
+// Tiles: their figures are for steps of 32 rows (of TEAMS times as many with several teams), see GemmTile.
+static constexpr GemmTile kProductTiles[] = {
+    {256, 128, 2, 1, 6.2, 0.64, 0.93, 0.0}, {128, 128, 1, 2, 3.5, 0.25, 0.28, 0.0}, {128, 128, 2, 1, 4.7, 0.355, 0.57, 0.0},
+    {64, 64, 1, 4, 3.2, 0.13, 0.126, 0.0},  {64, 64, 2, 2, 3.4, 0.20, 0.245, 0.0},  {64, 64, 4, 1, 4.0, 0.40, 0.53, 0.0},
+};
+
+// Any number of splits up to `most_splits` (what the workspace holds) with any tile, by the estimate that pick_tile makes;
+// a split costs its partial sums, written here and read by the update (4 bytes each way at 5 TB/s, half of the writing
+// covered).  8192 rows, 4096 x 1024 weights, us: two splits of 256 x 128 by two teams 74, one of 128 x 128 by two teams 78, one
+// of 128 x 128 81, four of 256 x 128 82, 64 x 64 124 - 133.  2048 rows, 512 x 2048 weights: 10 with 64 x 64, 12 - 19 with the others.
+int launch_dw_product(const uint16_t *X, const uint16_t *dY, float *partials, uint32_t M, uint32_t N, uint32_t K, uint32_t most_splits,
+                      uint32_t *nsplit, hipStream_t st) {
+    ProductArgs pa{X, dY, partials, N, K, M / 32, 1, 0, 0};
+    int which = -1;
+    double best_cost = 0.0;
+    for (int i = 0; i < static_cast<int>(sizeof(kProductTiles) / sizeof(kProductTiles[0])); ++i) {
+        const GemmTile &t = kProductTiles[i];
+        if (K % t.bm != 0 || N % t.bn != 0) continue;
+        const uint64_t tiles = static_cast<uint64_t>(K / t.bm) * (N / t.bn);
+        if (tiles > 0x7fffffffull) continue;
+        for (uint32_t splits = 1; splits <= most_splits && splits <= pa.steps; ++splits) {
+            const double per_unit = static_cast<double>(tiles * splits) / 256.0;
+            const double alone = t.step * static_cast<double>((tiles * splits + 256ull * t.resident - 1) / (256ull * t.resident));
+            const double busy = t.loaded * per_unit;
+            const uint32_t steps = ((pa.steps + splits - 1) / splits + t.teams - 1) / t.teams;
+            const double cost = t.base + steps * (alone > busy ? alone : busy) + splits * 6.0 * K * N / 5e6;
+            if (which < 0 || cost < best_cost) {
+                which = i;
+                best_cost = cost;
+                pa.nsplit = splits;
+            }
+        }
+    }
+    if (which < 0) return static_cast<int>(hipErrorInvalidValue);
+    pa.tiles_k = K / kProductTiles[which].bm;
+    pa.tiles_n = N / kProductTiles[which].bn;
+    *nsplit = pa.nsplit;
+    const dim3 grid(pa.tiles_k * pa.tiles_n, pa.nsplit);
+    switch (which) {
+        case 0: dw_product_kernel<2, 2, 4, 2, 2, 3, 2><<<grid, dim3(512), 0, st>>>(pa); break;
+        case 1: dw_product_kernel<2, 2, 2, 2, 1, 4, 2><<<grid, dim3(256), 0, st>>>(pa); break;
+        case 2: dw_product_kernel<2, 2, 2, 2, 2, 4, 2><<<grid, dim3(512), 0, st>>>(pa); break;
+        case 3: dw_product_kernel<2, 2, 1, 1, 1, 4, 4><<<grid, dim3(256), 0, st>>>(pa); break;
+        case 4: dw_product_kernel<2, 2, 1, 1, 2, 4, 4><<<grid, dim3(512), 0, st>>>(pa); break;
+        default: dw_product_kernel<2, 2, 1, 1, 4, 4, 4><<<grid, dim3(1024), 0, st>>>(pa); break;
+    }
+    return static_cast<int>(hipGetLastError());
+}
+
+}  // namespace omc

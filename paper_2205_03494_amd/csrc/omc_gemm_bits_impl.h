@@ -283,7 +283,7 @@ void gemm_bits_kernel(BitsArgs ga) {
 // 2048 x 512 x 2048: 50 us with 256 x 256, 27 with 128 x 128, 19 / 14 / 13 with 64 x 64 and 1 / 2 / 4 teams.
 static constexpr GemmTile kBitsTiles[] = {
     {256, 256, 1, 1, 7.0, 1.30, 1.80, 10.0}, {128, 256, 1, 1, 4.7, 1.00, 1.18, 5.0}, {128, 128, 1, 2, 3.0, 0.76, 0.66, 2.6},
-    {64, 64, 1, 4, 2.2, 0.54, 0.263, 0.65},  {64, 64, 2, 2, 2.9, 0.70, 0.575, 0.65}, {64, 64, 4, 1, 3.6, 1.15, 1.62, 0.65},
+    {64, 64, 1, 4, 2.2, 0.54, 0.263, 0.65},  {64, 64, 2, 2, 1.0, 0.70, 0.50, 1.6}, {64, 64, 4, 1, 1.0, 1.15, 1.15, 3.2},
 };
 
 template <int B, bool TRANS>

@@ -266,8 +266,8 @@ void gemm_fp8_kernel(Fp8Args ga) {
 // idle (1024 x 256 x 4096: 48 us with 128 x 256, 38 with 128 x 128, 21 / 16 / 15 with 64 x 64 and 1 / 2 / 4 teams).
 static constexpr GemmTile kFp8Tiles[] = {
     {128, 256, 1, 2, 4.5, 0.95, 0.92, 1.5}, {128, 256, 1, 1, 4.5, 0.67, 0.90, 3.5}, {128, 128, 1, 2, 3.4, 0.55, 0.46, 1.8},
-    {64, 128, 1, 2, 3.2, 0.33, 0.30, 1.0},  {64, 64, 1, 4, 2.9, 0.275, 0.166, 0.5}, {64, 64, 2, 2, 3.2, 0.40, 0.40, 0.5},
-    {64, 64, 4, 1, 4.0, 0.66, 1.25, 0.5},
+    {64, 128, 1, 2, 3.2, 0.33, 0.30, 1.0},  {64, 64, 1, 4, 2.9, 0.275, 0.166, 0.5}, {64, 64, 2, 2, 2.0, 0.40, 0.30, 1.5},
+    {64, 64, 4, 1, 1.5, 0.70, 0.70, 3.1},
 };
 
 template <bool TRANS>

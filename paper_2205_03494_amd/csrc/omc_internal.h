@@ -242,12 +242,6 @@ int launch_transport_pack(const PlanHeader *ph, const void *plan_dev, const void
                           void *msg_dev, const TransportHeader &th, void *stream);
 int launch_gemm_fp8(const uint16_t *A, const void *codes, const float *sb, float *C, uint32_t M, uint32_t N, uint32_t K,
                     int trans, struct ihipStream_t *stream);   // S1E4M3 codes, bias 7
-struct DwConfig {
-    uint32_t rows;     // weight rows per tile: 256 or 128
-    uint32_t nsplit;   // workgroups per tile along the contraction
-    uint32_t ws;       // 1: the 16-wave kernel with separate multiplying and staging waves (rows = 256, always parks)
-};
-DwConfig dw_config(uint32_t M, uint32_t N, uint32_t K);
 size_t dw_workspace_bytes(uint32_t bits, uint32_t M, uint32_t N, uint32_t K);
 int launch_dw_update(const uint16_t *X, const uint16_t *dY, void *codes, const FmtParams &fp, float *sb, int use_pvt,
                      float *state0, float *state1, const omc_opt &opt, float *dW_out, uint32_t M, uint32_t N,

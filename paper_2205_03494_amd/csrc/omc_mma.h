@@ -17,6 +17,11 @@ struct BoolTag {
     static constexpr bool value = B;
 };
 
+template <uint32_t V>
+struct UintTag {
+    static constexpr uint32_t value = V;
+};
+
 // LDS byte offset of a __shared__ object, as the direct-to-LDS loads take it.
 __device__ __forceinline__ uint32_t lds_offset(const void *p) {
     return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const OMC_LDS uint8_t *)(p)));
@@ -53,7 +58,8 @@ __device__ __forceinline__ void wait_stage(uint32_t j, uint32_t total) {
 // Host: which of a kernel's tile sizes to launch for an M x N result over K.  All figures are measured, in us: `base` is a launch
 // with one tile per compute unit and nothing to multiply, `step` a step of 64 k (of TEAMS times as many with several teams) when
 // every compute unit has at most `resident` workgroups, `loaded` what a step costs per workgroup and unit when all 256 units
-// are busy (matrix cores, LDS and power), `stores` the C stores of 256 tiles.  Estimates lie within 15 % of what was measured over M
+// are busy (matrix cores, LDS and power), `stores` the C stores of 256 tiles (with several teams, also
+// what a round of workgroups loses before its first and after its last step).  Estimates lie within 15 % of what was measured over M
 // 256 - 16384, N 128 - 4096, K 256 - 4096, the chosen tile within 7 % of the best one.
 struct GemmTile {
     uint32_t bm, bn, teams, resident;
