@@ -4,8 +4,6 @@
 
 namespace omc {
 
-constexpr int kDwCols = 128, kDwStep = 32;
-
 struct DwArgs {
     const uint16_t *X, *dY;
     uint32_t *codes;
@@ -20,9 +18,12 @@ struct DwArgs {
     uint32_t M, N, K;
 };
 
-// First kernel of the two-kernel route: the gradient as *nsplit <= most_splits partial sums.
-int launch_dw_product(const uint16_t *X, const uint16_t *dY, float *partials, uint32_t M, uint32_t N, uint32_t K, uint32_t most_splits,
-                      uint32_t *nsplit, hipStream_t st);
+// First kernel of the two-kernel route: the gradient as *nsplit <= room partial sums.
+int launch_dw_product(const DwArgs &a, float *partials, uint32_t room, uint32_t *nsplit, hipStream_t st);
+// The one-kernel route (8-bit codes); *nparts: how many partial sums of the fit it leaves.  `room`: how many copies of the
+// gradient the workspace holds, 0 or more; none is written.
+int launch_dw_one_kernel(const DwArgs &a, uint32_t room, int opt_kind, uint32_t *nparts, hipStream_t st);
+bool dw_one_kernel_is_faster(uint32_t M, uint32_t N, uint32_t K, uint32_t room);
 
 // Second kernel: adds them up and runs the cycle; one launcher per optimizer.
 int launch_dw_update_sgd(const DwArgs &a, hipStream_t st);

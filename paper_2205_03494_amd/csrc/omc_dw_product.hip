@@ -1,5 +1,9 @@
-// The weight gradient dW[K x N] = X^T dY of omc_dw_update_recompress, as `nsplit` partial sums over runs of the M rows, row-major
-// in the workspace; the update kernels add them in order.
+// The weight gradient dW[K x N] = X^T dY of omc_dw_update_recompress (paper Sec. 2.1, backward propagation: decompress the layer's
+// parameters, apply the gradients, compress, discard), either as `nsplit` partial sums over runs of the M rows, row-major in the
+// workspace, which the update kernels add in order; or, for 8-bit codes, consumed in the epilogue: the tile of the gradient
+// goes to LDS, a thread takes four consecutive weights of a row at a time, one dword of codes, decodes and transforms them
+// (Sec. 2.2, 2.3), updates, rounds, stores them back and takes the sums of the fit, and the fp32 gradient is nowhere in memory
+// (unless the caller asks for a copy).
 //
 // Both operands lie along the contraction, X as [M x K] and dY as [M x N], and go from global memory straight into a ring of S LDS
 // stages of 32 rows, as they are.  The transposing 16-bit read (ds_read_b64_tr_b16) makes matrix fragments of them: of 16 lanes
@@ -23,15 +27,70 @@ struct ProductArgs {
     uint32_t tiles_k, tiles_n;
 };
 
-// WM x WN waves of TM x TN matrix tiles (32 x 32) each, TEAMS times; S stages, OCC waves per SIMD.
-template <int WM, int WN, int TM, int TN, int TEAMS, int S, int OCC>
+// Epilogue of the one-kernel route on a tile [ROWS][COLS] of the gradient in LDS, by all THREADS of the workgroup.
+template <int ROWS, int COLS, int THREADS, int MODE, bool WIDE>
+__device__ __forceinline__ void update_tile(const DwArgs &a, const float *grad, uint32_t k0, uint32_t n0, FitAcc &fit) {
+    constexpr int kPieces = ROWS * COLS / 4 / THREADS, kMost = MODE == kStepAdam ? 2 : 4, kBatch = kPieces < kMost ? kPieces : kMost;
+    static_assert(kPieces * 4 * THREADS == ROWS * COLS && kPieces % kBatch == 0, "whole batches of whole pieces");
+    const float s = to_scalar_regs(a.sb[0]), b = to_scalar_regs(a.sb[1]);
+    const FmtParams fp = a.fp;
+    for (int i = 0; i < kPieces; i += kBatch) {
+        uint32_t cw[kBatch];
+        f32x4 g4[kBatch], m4[kBatch], v4[kBatch];
+        uint64_t e[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t q = (i + u) * THREADS + threadIdx.x;
+            e[u] = static_cast<uint64_t>(k0 + q / (COLS / 4)) * a.N + n0 + 4 * (q % (COLS / 4));
+            cw[u] = a.codes[e[u] >> 2];
+            if (MODE >= kStepMomentum) m4[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(a.st0 + e[u]));
+            if (MODE == kStepAdam) v4[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(a.st1 + e[u]));
+            g4[u] = reinterpret_cast<const f32x4 *>(grad)[q];
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            pin(cw[u]);
+            uint32_t out = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float vt = decode_top(cw[u] << (24 - 8 * c), fp);
+                const float sv = s * vt;
+                float x = sv + b;
+                float mm = MODE >= kStepMomentum ? m4[u][c] : 0.0f, vv = MODE == kStepAdam ? v4[u][c] : 0.0f;
+                x = apply_update<MODE>(x, g4[u][c], mm, vv, a.oc);
+                if (MODE >= kStepMomentum) m4[u][c] = mm;
+                if (MODE == kStepAdam) v4[u][c] = vv;
+                uint32_t code;
+                float tq;
+                encode<WIDE>(x, fp, code, tq);
+                fit.seed(tq);
+                fit.add(x, tq);
+                out |= code << (8 * c);
+            }
+            // keep the pieces in program order: the arithmetic must not pile up above the serial fp64 accumulation
+            fit.pin_sums();
+            pin(out);
+            a.codes[e[u] >> 2] = out;
+            if (MODE >= kStepMomentum) __builtin_nontemporal_store(m4[u], reinterpret_cast<f32x4 *>(a.st0 + e[u]));
+            if (MODE == kStepAdam) __builtin_nontemporal_store(v4[u], reinterpret_cast<f32x4 *>(a.st1 + e[u]));
+            if (a.dW_out) __builtin_nontemporal_store(g4[u], reinterpret_cast<f32x4 *>(a.dW_out + e[u]));
+        }
+    }
+}
+
+// WM x WN waves of TM x TN matrix tiles (32 x 32) each, TEAMS times; S stages, OCC waves per SIMD.  MODE: kPark for partial sums, else
+// the optimizer of the one-kernel route.
+constexpr int kPark = -1;
+template <int WM, int WN, int TM, int TN, int TEAMS, int S, int OCC, int MODE>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN * TEAMS, 64 * WM * WN * TEAMS))) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
-void dw_product_kernel(ProductArgs pa) {
+void dw_product_kernel(ProductArgs pa, DwArgs a) {
     constexpr int NW = WM * WN, BK = 32 * TM * WM, BN = 32 * TN * WN;
     constexpr int kXLoads = BK / 16 / NW, kYLoads = BN / 16 / NW, kLoads = kXLoads + kYLoads;   // 1 KB loads per wave and stage
     constexpr uint32_t kXBytes = BK * 64, kStage = kXBytes + BN * 64;
     static_assert(BK % (16 * NW) == 0 && BN % (16 * NW) == 0, "whole loads");
-    __shared__ __attribute__((aligned(1024))) uint8_t lds_all[TEAMS * S * kStage];
+    // (the one-kernel route's sums lie behind its tile)
+    constexpr int kExtra = MODE != kPark && BK * BN * 4 + 16 * static_cast<int>(sizeof(Partial)) > TEAMS * S * static_cast<int>(kStage) ? 16 * static_cast<int>(sizeof(Partial)) : 0;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_all[TEAMS * S * kStage + kExtra];
     const uint32_t team = TEAMS == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
     uint8_t *lds = lds_all + team * (S * kStage);
     const uint32_t lds0 = lds_offset(lds);
@@ -139,64 +198,130 @@ void dw_product_kernel(ProductArgs pa) {
     for (uint32_t i = mine; i < most; ++i) wait_loads_and_sync<0>();   // teams wait for each other
     wait_loads_and_sync<0>();                                 // nobody reads a stage any more
     static_assert((TEAMS - 1) * BK * BN * 4 <= TEAMS * S * static_cast<int>(kStage), "the other teams' tiles fit the stages");
-    if (!add_teams<TEAMS, NW, TM, TN>(reinterpret_cast<float *>(lds_all), acc, team, wave, lane)) return;
-    float *to = pa.partials + static_cast<uint64_t>(split) * K * N + static_cast<uint64_t>(k0 + 32 * TM * wm + 4 * (lane >> 5)) * N +
-                n0 + 32 * TN * wn + (lane & 31u);
+    const bool lead = add_teams<TEAMS, NW, TM, TN>(reinterpret_cast<float *>(lds_all), acc, team, wave, lane);
+    if constexpr (MODE == kPark) {
+        if (!lead) return;
+        float *to = pa.partials + static_cast<uint64_t>(split) * K * N + static_cast<uint64_t>(k0 + 32 * TM * wm + 4 * (lane >> 5)) * N +
+                    n0 + 32 * TN * wn + (lane & 31u);
 #pragma unroll
-    for (int mi = 0; mi < TM; ++mi)
+        for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
+            for (int v = 0; v < 16; ++v)
 #pragma unroll
-            for (int ni = 0; ni < TN; ++ni) to[static_cast<uint64_t>(32 * mi + 8 * (v >> 2) + (v & 3)) * N + 32 * ni] = acc[mi][ni][v];
+                for (int ni = 0; ni < TN; ++ni) to[static_cast<uint64_t>(32 * mi + 8 * (v >> 2) + (v & 3)) * N + 32 * ni] = acc[mi][ni][v];
+    } else {
+        static_assert(BK * BN * 4 + 16 * static_cast<int>(sizeof(Partial)) <= TEAMS * S * static_cast<int>(kStage) + kExtra, "the tile fits the stages");
+        float *tile = reinterpret_cast<float *>(lds_all);
+        Partial *sums = reinterpret_cast<Partial *>(lds_all + BK * BN * 4);
+        if (TEAMS > 1) __syncthreads();                       // the other teams' tiles are read
+        if (lead) {
+            float *to = tile + (32 * TM * wm + 4 * (lane >> 5)) * BN + 32 * TN * wn + (lane & 31u);
+#pragma unroll
+            for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+#pragma unroll
+                    for (int ni = 0; ni < TN; ++ni) to[(32 * mi + 8 * (v >> 2) + (v & 3)) * BN + 32 * ni] = acc[mi][ni][v];
+        }
+        __syncthreads();
+        FitAcc fit;
+        fit.clear();
+        if (a.fp.wide) update_tile<BK, BN, 64 * NW * TEAMS, MODE, true>(a, tile, k0, n0, fit);
+        else update_tile<BK, BN, 64 * NW * TEAMS, MODE, false>(a, tile, k0, n0, fit);
+        fit.reduce_and_store<false>(sums + team * NW + wave);  // 8-bit formats: plain fp64 sums
+        __syncthreads();
+        if (threadIdx.x == 0) {                               // one partial per tile, the waves in order
+            Partial p = sums[0];
+#pragma unroll
+            for (int w = 1; w < NW * TEAMS; ++w) {
+                p.sV += sums[w].sV;
+                p.sT += sums[w].sT;
+                p.sVT += sums[w].sVT;
+                p.sTT += sums[w].sTT;
+                p.tmin = fminf(p.tmin, sums[w].tmin);
+                p.tmax = fmaxf(p.tmax, sums[w].tmax);
+            }
+            a.ws[blockIdx.x] = p;
+        }
+    }
 }
 
 // Tiles: their figures are for steps of 32 rows (of TEAMS times as many with several teams), see GemmTile.
+constexpr double kUpdateLaunchUs = 2.0;
 static constexpr GemmTile kProductTiles[] = {
-    {256, 128, 2, 1, 6.2, 0.64, 0.93, 0.0}, {128, 128, 1, 2, 3.5, 0.25, 0.28, 0.0}, {128, 128, 2, 1, 4.7, 0.355, 0.57, 0.0},
+    {256, 128, 2, 1, 6.2, 0.64, 0.93, 0.0}, {128, 128, 1, 2, 3.5, 0.30, 0.28, 0.0}, {128, 128, 2, 1, 4.7, 0.355, 0.57, 0.0},
     {64, 64, 1, 4, 3.2, 0.13, 0.126, 0.0},  {64, 64, 2, 2, 3.4, 0.20, 0.245, 0.0},  {64, 64, 4, 1, 4.0, 0.40, 0.53, 0.0},
 };
 
-// Any number of splits up to `most_splits` (what the workspace holds) with any tile, by the estimate that pick_tile makes;
-// a split costs its partial sums, written here and read by the update (4 bytes each way at 5 TB/s, half of the writing
-// covered).  8192 rows, 4096 x 1024 weights, us: two splits of 256 x 128 by two teams 74, one of 128 x 128 by two teams 78, one
+// The tile, number of splits and estimated time (us) of a product, by the estimate that pick_tile makes, over any number of splits up
+// to what the workspace has room for, or none.  The contraction is cut into at least `room` parts, by splits and teams together:
+// so that no fp32 sum runs over more products than M / room, which keeps its error where a workspace of that size puts it (2e-7 for 4096
+// products, 3e-7 for 8192).  A split costs its partial sums, written here and read by the update (4 bytes each way at 5 TB/s, half of the
+// writing covered).  8192 rows, 4096 x 1024 weights: two splits of 256 x 128 by two teams 74, one of 128 x 128 by two teams 78, one
 // of 128 x 128 81, four of 256 x 128 82, 64 x 64 124 - 133.  2048 rows, 512 x 2048 weights: 10 with 64 x 64, 12 - 19 with the others.
-int launch_dw_product(const uint16_t *X, const uint16_t *dY, float *partials, uint32_t M, uint32_t N, uint32_t K, uint32_t most_splits,
-                      uint32_t *nsplit, hipStream_t st) {
-    ProductArgs pa{X, dY, partials, N, K, M / 32, 1, 0, 0};
-    int which = -1;
-    double best_cost = 0.0;
+struct ProductChoice {
+    int tile;
+    uint32_t splits;
+    double us;
+};
+static ProductChoice choose_product(uint32_t M, uint32_t N, uint32_t K, uint32_t room, bool parked) {
+    const uint32_t most_splits = parked ? room : 1;
+    ProductChoice best{-1, 1, 0.0};
+    const uint32_t all_steps = M / 32;
     for (int i = 0; i < static_cast<int>(sizeof(kProductTiles) / sizeof(kProductTiles[0])); ++i) {
         const GemmTile &t = kProductTiles[i];
         if (K % t.bm != 0 || N % t.bn != 0) continue;
         const uint64_t tiles = static_cast<uint64_t>(K / t.bm) * (N / t.bn);
         if (tiles > 0x7fffffffull) continue;
-        for (uint32_t splits = 1; splits <= most_splits && splits <= pa.steps; ++splits) {
+        for (uint32_t splits = 1; splits <= most_splits && splits <= all_steps; ++splits) {
+            if (splits * t.teams < room) continue;
             const double per_unit = static_cast<double>(tiles * splits) / 256.0;
             const double alone = t.step * static_cast<double>((tiles * splits + 256ull * t.resident - 1) / (256ull * t.resident));
             const double busy = t.loaded * per_unit;
-            const uint32_t steps = ((pa.steps + splits - 1) / splits + t.teams - 1) / t.teams;
-            const double cost = t.base + steps * (alone > busy ? alone : busy) + splits * 6.0 * K * N / 5e6;
-            if (which < 0 || cost < best_cost) {
-                which = i;
-                best_cost = cost;
-                pa.nsplit = splits;
-            }
+            const uint32_t steps = ((all_steps + splits - 1) / splits + t.teams - 1) / t.teams;
+            const double us = t.base + steps * (alone > busy ? alone : busy) + (parked ? splits * 6.0 * K * N / 5e6 : 0.0);
+            if (best.tile < 0 || us < best.us) best = ProductChoice{i, splits, us};
         }
     }
-    if (which < 0) return static_cast<int>(hipErrorInvalidValue);
-    pa.tiles_k = K / kProductTiles[which].bm;
-    pa.tiles_n = N / kProductTiles[which].bn;
-    *nsplit = pa.nsplit;
+    return best;
+}
+
+template <int MODE>
+static int launch_product(int tile, ProductArgs pa, const DwArgs &a, hipStream_t st) {
+    if (tile < 0) return static_cast<int>(hipErrorInvalidValue);
+    pa.tiles_k = pa.K / kProductTiles[tile].bm;
+    pa.tiles_n = pa.N / kProductTiles[tile].bn;
     const dim3 grid(pa.tiles_k * pa.tiles_n, pa.nsplit);
-    switch (which) {
-        case 0: dw_product_kernel<2, 2, 4, 2, 2, 3, 2><<<grid, dim3(512), 0, st>>>(pa); break;
-        case 1: dw_product_kernel<2, 2, 2, 2, 1, 4, 2><<<grid, dim3(256), 0, st>>>(pa); break;
-        case 2: dw_product_kernel<2, 2, 2, 2, 2, 4, 2><<<grid, dim3(512), 0, st>>>(pa); break;
-        case 3: dw_product_kernel<2, 2, 1, 1, 1, 4, 4><<<grid, dim3(256), 0, st>>>(pa); break;
-        case 4: dw_product_kernel<2, 2, 1, 1, 2, 4, 4><<<grid, dim3(512), 0, st>>>(pa); break;
-        default: dw_product_kernel<2, 2, 1, 1, 4, 4, 4><<<grid, dim3(1024), 0, st>>>(pa); break;
+    switch (tile) {
+        case 0: dw_product_kernel<2, 2, 4, 2, 2, 3, 2, MODE><<<grid, dim3(512), 0, st>>>(pa, a); break;
+        case 1: dw_product_kernel<2, 2, 2, 2, 1, 4, 2, MODE><<<grid, dim3(256), 0, st>>>(pa, a); break;
+        case 2: dw_product_kernel<2, 2, 2, 2, 2, 4, 2, MODE><<<grid, dim3(512), 0, st>>>(pa, a); break;
+        case 3: dw_product_kernel<2, 2, 1, 1, 1, 4, 4, MODE><<<grid, dim3(256), 0, st>>>(pa, a); break;
+        case 4: dw_product_kernel<2, 2, 1, 1, 2, 4, 4, MODE><<<grid, dim3(512), 0, st>>>(pa, a); break;
+        default: dw_product_kernel<2, 2, 1, 1, 4, 4, 4, MODE><<<grid, dim3(1024), 0, st>>>(pa, a); break;
     }
     return static_cast<int>(hipGetLastError());
+}
+
+int launch_dw_product(const DwArgs &a, float *partials, uint32_t room, uint32_t *nsplit, hipStream_t st) {
+    const ProductChoice c = choose_product(a.M, a.N, a.K, room, true);
+    *nsplit = c.splits;
+    return launch_product<kPark>(c.tile, ProductArgs{a.X, a.dY, partials, a.N, a.K, a.M / 32, c.splits, 0, 0}, a, st);
+}
+
+// The epilogue takes longer than parking a tile, but the update kernel's launch and its pass over the partial sums go.
+bool dw_one_kernel_is_faster(uint32_t M, uint32_t N, uint32_t K, uint32_t room) {
+    const ProductChoice one = choose_product(M, N, K, room, false), two = choose_product(M, N, K, room, true);
+    return one.tile >= 0 && (two.tile < 0 || one.us <= two.us + kUpdateLaunchUs);
+}
+
+int launch_dw_one_kernel(const DwArgs &a, uint32_t room, int opt_kind, uint32_t *nparts, hipStream_t st) {
+    const ProductChoice c = choose_product(a.M, a.N, a.K, room, false);
+    if (c.tile >= 0) *nparts = (a.K / kProductTiles[c.tile].bm) * (a.N / kProductTiles[c.tile].bn);
+    const ProductArgs pa{a.X, a.dY, nullptr, a.N, a.K, a.M / 32, 1, 0, 0};
+    if (opt_kind == OMC_SGD) return launch_product<kStepSgd>(c.tile, pa, a, st);
+    if (opt_kind == OMC_MOMENTUM) return launch_product<kStepMomentum>(c.tile, pa, a, st);
+    return launch_product<kStepAdam>(c.tile, pa, a, st);
 }
 
 }  // namespace omc

@@ -148,3 +148,21 @@ def test_long_contraction_on_a_small_grid_takes_the_sixteen_wave_kernel(EM, kind
     """64 tiles and 4096 rows: two workgroups of 16 waves per tile (eight multiplying, eight staging), each over
     2048 rows; the accumulators pass through the workspace in the four-wave kernel's layout."""
     run_case(EM, 4096, 2048, 1024, kind, lr, steps=2, rows=(0, 16, 320, 1008))
+
+
+@pytest.mark.parametrize("EM", [(4, 3), (3, 7)])
+@pytest.mark.parametrize("shape", [(160, 2048, 1024), (2080, 1024, 512), (2048, 2048, 512), (1056, 2048, 1024), (544, 4096, 2048),
+                                   (1056, 4096, 4096), (4128, 384, 512)])
+def test_every_tile_of_the_product_and_uneven_shares(EM, shape):
+    """Tiles of 64 x 64 (one, two and four teams of waves), 128 x 128 (one and two) and 256 x 128, in the kernel that updates 8-bit
+    codes in its epilogue and in the one that leaves partial sums; 65 or 33 steps of 32 rows do not share out evenly."""
+    M, N, K = shape
+    run_case(EM, M, N, K, 1, 0.05, steps=1, rows=None if K * N <= 1 << 20 else (0, 16, K // 2 - 16, K - 16))
+
+
+@pytest.mark.parametrize("kind,lr", [(0, 0.05), (2, 1e-3)])
+@pytest.mark.parametrize("shape", [(8192, 1024, 4096), (4096, 128, 256)])
+def test_contraction_in_two_and_in_eight_parts(kind, lr, shape):
+    """Room for two copies of the gradient: 8-bit codes are updated by two teams of waves in one kernel; for eight: teams and splits."""
+    M, N, K = shape
+    run_case((4, 3), M, N, K, kind, lr, steps=1, rows=(0, K - 16))
