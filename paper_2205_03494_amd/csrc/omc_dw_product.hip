@@ -14,7 +14,8 @@
 // A weight matrix gives few tiles (4 M weights = 128 of 256 x 128) and the contraction is long, so it is shared out twice: between
 // TEAMS of waves of a workgroup, which add up their tiles through LDS, and between workgroups (nsplit).
 //
-// What bounds it: LDS bandwidth (36 KB per 16 rows of a 256 x 128 tile: 12 % more than 128 B/clk carry at the matrix cores' rate).
+// What bounds it: the loads (48 bytes per clock and compute unit at the matrix cores' rate; with all of them hitting the L2 the 8192-row product
+// of 4096 x 1024 weights takes 64 instead of 71 us), not the LDS reads: plain or 16-byte reads in their place change nothing.
 #include "omc_dw_args.h"
 #include "omc_mma.h"
 
@@ -98,7 +99,7 @@ void dw_product_kernel(ProductArgs pa, DwArgs a) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
     const uint32_t N = pa.N, K = pa.K;
     uint32_t k0, n0;
-    tile_of_block(pa.tiles_k, pa.tiles_n, k0, n0);
+    tile_of_block<BK == 256 ? 2 : 8>(pa.tiles_k, pa.tiles_n, k0, n0);
     k0 *= BK;
     n0 *= BN;
     // this workgroup's steps, and its teams' shares of them: team t takes t, t + TEAMS, ...
@@ -247,18 +248,17 @@ void dw_product_kernel(ProductArgs pa, DwArgs a) {
 }
 
 // Tiles: their figures are for steps of 32 rows (of TEAMS times as many with several teams), see GemmTile.
-constexpr double kUpdateLaunchUs = 2.0;
 static constexpr GemmTile kProductTiles[] = {
-    {256, 128, 2, 1, 6.2, 0.64, 0.93, 0.0}, {128, 128, 1, 2, 3.5, 0.30, 0.28, 0.0}, {128, 128, 2, 1, 4.7, 0.355, 0.57, 0.0},
-    {64, 64, 1, 4, 3.2, 0.13, 0.126, 0.0},  {64, 64, 2, 2, 3.4, 0.20, 0.245, 0.0},  {64, 64, 4, 1, 4.0, 0.40, 0.53, 0.0},
+    {256, 128, 2, 1, 6.2, 0.64, 0.88, 0.0}, {128, 128, 1, 2, 3.5, 0.30, 0.28, 0.0}, {128, 128, 2, 1, 4.7, 0.355, 0.57, 0.0},
+    {64, 64, 1, 4, 3.2, 0.13, 0.126, 0.0},  {64, 64, 2, 2, 1.0, 0.20, 0.215, 3.0},  {64, 64, 4, 1, 1.0, 0.40, 0.46, 3.0},
 };
 
 // The tile, number of splits and estimated time (us) of a product, by the estimate that pick_tile makes, over any number of splits up
 // to what the workspace has room for, or none.  The contraction is cut into at least `room` parts, by splits and teams together:
 // so that no fp32 sum runs over more products than M / room, which keeps its error where a workspace of that size puts it (2e-7 for 4096
 // products, 3e-7 for 8192).  A split costs its partial sums, written here and read by the update (4 bytes each way at 5 TB/s, half of the
-// writing covered).  8192 rows, 4096 x 1024 weights: two splits of 256 x 128 by two teams 74, one of 128 x 128 by two teams 78, one
-// of 128 x 128 81, four of 256 x 128 82, 64 x 64 124 - 133.  2048 rows, 512 x 2048 weights: 10 with 64 x 64, 12 - 19 with the others.
+// writing covered).  8192 rows, 4096 x 1024 weights: two splits of 256 x 128 by two teams 71, one of 128 x 128 by two teams 78, one
+// of 128 x 128 81, four of 256 x 128 80, 64 x 64 124 - 133.  2048 rows, 512 x 2048 weights: 10 with 64 x 64, 12 - 19 with the others.
 struct ProductChoice {
     int tile;
     uint32_t splits;
@@ -279,7 +279,7 @@ static ProductChoice choose_product(uint32_t M, uint32_t N, uint32_t K, uint32_t
             const double alone = t.step * static_cast<double>((tiles * splits + 256ull * t.resident - 1) / (256ull * t.resident));
             const double busy = t.loaded * per_unit;
             const uint32_t steps = ((all_steps + splits - 1) / splits + t.teams - 1) / t.teams;
-            const double us = t.base + steps * (alone > busy ? alone : busy) + (parked ? splits * 6.0 * K * N / 5e6 : 0.0);
+            const double us = t.base + t.stores * per_unit + steps * (alone > busy ? alone : busy) + (parked ? splits * 6.0 * K * N / 5e6 : 0.0);
             if (best.tile < 0 || us < best.us) best = ProductChoice{i, splits, us};
         }
     }
@@ -309,10 +309,12 @@ int launch_dw_product(const DwArgs &a, float *partials, uint32_t room, uint32_t 
     return launch_product<kPark>(c.tile, ProductArgs{a.X, a.dY, partials, a.N, a.K, a.M / 32, c.splits, 0, 0}, a, st);
 }
 
-// The epilogue takes longer than parking a tile, but the update kernel's launch and its pass over the partial sums go.
+// What the update kernel costs besides reading the partial sums: its launch, and codes and state, which the one-kernel route's
+// epilogue moves mostly under other workgroups' products (8192 rows, 4096 x 1024 weights, 8 bits, momentum: one kernel 79 us,
+// product and update 71 + 17).
 bool dw_one_kernel_is_faster(uint32_t M, uint32_t N, uint32_t K, uint32_t room) {
     const ProductChoice one = choose_product(M, N, K, room, false), two = choose_product(M, N, K, room, true);
-    return one.tile >= 0 && (two.tile < 0 || one.us <= two.us + kUpdateLaunchUs);
+    return one.tile >= 0 && (two.tile < 0 || one.us <= two.us + 3.0 + 6.0 * K * N / 5e6);
 }
 
 int launch_dw_one_kernel(const DwArgs &a, uint32_t room, int opt_kind, uint32_t *nparts, hipStream_t st) {

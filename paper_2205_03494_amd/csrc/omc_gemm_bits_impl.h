@@ -14,7 +14,7 @@
 // What bounds it: LDS bandwidth (64 KB per 16 k of a 256 x 256 tile: all that 128 B/clk allows at the matrix cores' rate) and the
 // decode, about five vector instructions per code.  Measured on 11-bit codes against the kernels before (256 x 128 or 128 x 128 tile,
 // A staged through registers, a patch of 4 x 4 codes per thread with run-time shifts; 256 x 128 by 16 waves for long contractions):
-// forward 8192 x 4096 x 1024 104 -> 89 us, 2048 x 2048 x 512 18.6 -> 11.4, input gradient 2048 x 512 x 2048 53.6 -> 13.
+// forward 8192 x 4096 x 1024 104 -> 82 us, 2048 x 2048 x 512 18.6 -> 11.4, input gradient 2048 x 512 x 2048 53.6 -> 13.
 #pragma once
 #include "omc_mma.h"
 
@@ -105,7 +105,7 @@ void gemm_bits_kernel(BitsArgs ga) {
     const uint32_t N = ga.N, K = ga.K;
     const FmtParams fp = ga.fp;
     uint32_t m0, n0;
-    tile_of_block(ga.tiles_m, ga.tiles_n, m0, n0);
+    tile_of_block<BM == 256 ? 4 : 8>(ga.tiles_m, ga.tiles_n, m0, n0);
     m0 *= BM;
     n0 *= BN;
 
@@ -279,10 +279,10 @@ void gemm_bits_kernel(BitsArgs ga) {
     store_tile<TEAMS * WN, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 32 * TN * wn, N, acc, rowsum, 32 * TM * wm, lane, s, b);
 }
 
-// (11-bit codes; the other widths differ in the decode alone.)  8192 x 4096 x 1024: 83 us with 256 x 256, 108 with 128 x 128;
+// (11-bit codes; the other widths differ in the decode alone.)  8192 x 4096 x 1024: 82 us with 256 x 256, 107 with 128 x 128;
 // 2048 x 512 x 2048: 50 us with 256 x 256, 27 with 128 x 128, 19 / 14 / 13 with 64 x 64 and 1 / 2 / 4 teams.
 static constexpr GemmTile kBitsTiles[] = {
-    {256, 256, 1, 1, 7.0, 1.30, 1.80, 10.0}, {128, 256, 1, 1, 4.7, 1.00, 1.18, 5.0}, {128, 128, 1, 2, 3.0, 0.76, 0.66, 2.6},
+    {256, 256, 1, 1, 7.0, 1.30, 1.855, 8.0}, {128, 256, 1, 1, 4.7, 1.00, 1.18, 5.0}, {128, 128, 1, 2, 3.0, 0.76, 0.66, 2.6},
     {64, 64, 1, 4, 2.2, 0.54, 0.263, 0.65},  {64, 64, 2, 2, 1.0, 0.70, 0.50, 1.6}, {64, 64, 4, 1, 1.0, 1.15, 1.15, 3.2},
 };
 

@@ -12,18 +12,17 @@
 //
 // Fragments of a quarter step are read while the quarter before is multiplied; the last quarter is multiplied after the
 // barrier of the next step, under that step's first reads.  Waves start their quarters at different places
-// (WN + WM rotation), which also deals the row sums of A (each column wave sums its own quarters, in every
-// multiplication order the same) and the check for top codes (each row wave checks its own) evenly and without branches.
+// (WN + WM rotation), which also deals the row sums of A evenly and without branches: each column wave sums its own quarters.
 //
-// The top code reads as NaN in the hardware conversion, without its sign.  No pass over the codes looks for it beforehand:
-// the waves check what they multiply (five instructions per eight codes, half of the fragments), and a workgroup that
-// saw one computes its tile again with a bit-domain decode.
+// The top code reads as NaN in the hardware conversion, without its sign.  No pass over the codes looks for it beforehand, and no
+// instruction in the loop: it makes every row of its column NaN, so a wave looks at one row of its sums, and a workgroup that finds
+// one computes its tile again with a bit-domain decode (as it does, to the same result, where A itself is not finite).
 //
 // Measured (us, 8192 x 4096 x 1024 / 8192 x 1024 x 4096, fp32 output, new operands each time), against the kernel before (256 x 128 tile,
 // A fragments from global memory, W decoded on the way into LDS, a 5 us pass over the codes for top codes first): 83 / 81 ->
-// 68 / 66.  What bounds it now: LDS bandwidth (24 KB through LDS per 16 k of a 128 x 256 tile, three quarters of what
-// 128 B/clk gives at the matrix cores' rate), power (1150 TFLOP/s at 16384 x 4096 x 2048, random data), and 4 us of C stores
-// that nothing covers.
+// 65 / 60.  What bounds it now: LDS bandwidth (24 KB through LDS per 16 k of a 128 x 256 tile, three quarters of what
+// 128 B/clk gives at the matrix cores' rate) and power (1300 TFLOP/s at 8192 x 4096 x 4096, random data), and the C stores where
+// nothing covers them.
 #include "omc_mma.h"
 
 #pragma clang fp contract(off)
@@ -86,7 +85,7 @@ void gemm_fp8_kernel(Fp8Args ga) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
     const uint32_t N = ga.N, K = ga.K;
     uint32_t m0, n0;
-    tile_of_block(ga.tiles_m, ga.tiles_n, m0, n0);
+    tile_of_block<BM == 256 ? 4 : 8>(ga.tiles_m, ga.tiles_n, m0, n0);
     m0 *= BM;
     n0 *= BN;
 
@@ -163,7 +162,6 @@ void gemm_fp8_kernel(Fp8Args ga) {
 
     f32x16 acc[TM][TN];
     float rsum[TM];
-    uint32_t top;
     auto compute = [&](auto exact_tag) {
         constexpr bool EXACT = decltype(exact_tag)::value;
 #pragma unroll
@@ -174,12 +172,10 @@ void gemm_fp8_kernel(Fp8Args ga) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
         }
-        top = 0;
-        auto multiply = [&](const Frags &f, bool sum, bool check) {
+        auto multiply = [&](const Frags &f, bool sum) {
 #pragma unroll
             for (int ni = 0; ni < TN; ++ni) {
                 const bf16x8 w = fp8x8_to_bf16<EXACT>(f.w[ni]);
-                if (!EXACT && check) top |= ((f.w[ni][0] & 0x7f7f7f7fu) + 0x01010101u) | ((f.w[ni][1] & 0x7f7f7f7fu) + 0x01010101u);
 #pragma unroll
                 for (int mi = 0; mi < TM; ++mi) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mi], w, acc[mi][ni], 0, 0, 0);
             }
@@ -192,11 +188,11 @@ void gemm_fp8_kernel(Fp8Args ga) {
         uint32_t cur = 0, far = (S - 1) * kStage;
         auto rest_of_step = [&]() {                           // everything but the first quarter's reads and the last one's products
             read_frags(cur, a_at[1], w_at[1], f1);
-            multiply(f0, true, true);
+            multiply(f0, true);
             read_frags(cur, a_at[2], w_at[2], f0);
-            multiply(f1, false, true);
+            multiply(f1, false);
             read_frags(cur, a_at[3], w_at[3], f1);
-            multiply(f0, WN == 2, false);
+            multiply(f0, WN == 2);
             cur = cur == (S - 1) * kStage ? 0 : cur + kStage;
             far = far == (S - 1) * kStage ? 0 : far + kStage;
         };
@@ -213,22 +209,22 @@ void gemm_fp8_kernel(Fp8Args ga) {
                 wait_loads_and_sync<(S - 2) * kLoads>();
                 read_frags(cur, a_at[0], w_at[0], f0);
                 load_stage(far, j + S - 1);
-                multiply(f1, false, false);
+                multiply(f1, false);
                 rest_of_step();
             }
             for (; j < full; ++j) {
                 wait_stage<S, kLoads>(j, stages);
                 read_frags(cur, a_at[0], w_at[0], f0);
-                multiply(f1, false, false);
+                multiply(f1, false);
                 rest_of_step();
             }
-            multiply(f1, false, false);
+            multiply(f1, false);
         }
         if (full < stages) {                                  // 32 k more: two quarters
             wait_loads_and_sync<0>();
             for (uint32_t ks = 0; ks < 2; ++ks) {
                 read_frags(cur, a_place(ks), w_place(ks), f0);
-                multiply(f0, false, true);
+                multiply(f0, false);
                 if (ks % WN == wn) {
 #pragma unroll
                     for (int mi = 0; mi < TM; ++mi) rsum[mi] = add_fragment(f0.a[mi], rsum[mi]);
@@ -244,7 +240,10 @@ void gemm_fp8_kernel(Fp8Args ga) {
     float *parts = reinterpret_cast<float *>(tops + 64);
     static_assert(4 * (TEAMS * WN * BM + 64 + (TEAMS - 1) * BM * BN) <= TEAMS * S * static_cast<int>(kStage), "fits the stages");
     compute(BoolTag<false>{});
-    const bool mine = __any((top & 0x80808080u) != 0);
+    bool bad = false;                                         // one row of every column tells
+#pragma unroll
+    for (int ni = 0; ni < TN; ++ni) bad = bad || acc[0][ni][0] != acc[0][ni][0];
+    const bool mine = __any(bad);
     if (lane == 0) tops[team * NW + wave] = mine ? 1u : 0u;
     __syncthreads();
     uint32_t any_top = 0;
@@ -258,28 +257,30 @@ void gemm_fp8_kernel(Fp8Args ga) {
     store_tile<TEAMS * WN, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 32 * TN * wn, N, acc, rowsum, 32 * TM * wm, lane, s, b);
 }
 
-// The first tile has two workgroups of four waves on a compute unit, so that one's C stores pass under the other's products: it
-// wins wherever a unit gets several tiles (8192 x 4096 x 1024, new operands each time: 69 us; 80 with a 256 x 256 tile, one
-// workgroup of eight waves per unit, although that one is the faster without any stores, 63.5 to 65.5).  The second one is the same
-// tile by eight waves with a third stage, better when every unit has one tile (8192 x 1024 x 4096: 66 to 68 us).  The small tiles
-// win where they spread a short product over more units, and several teams where even those leave most of them
-// idle (1024 x 256 x 4096: 48 us with 128 x 256, 38 with 128 x 128, 21 / 16 / 15 with 64 x 64 and 1 / 2 / 4 teams).
+// 128 x 256 by four waves has two workgroups on a compute unit, so that one's C stores pass under the other's products: it
+// wins wherever a unit gets several tiles of a contraction that is not very long (8192 x 4096 x 1024, new operands each time: 66 us; 70
+// with 256 x 256, one workgroup of eight waves per unit, whose loop is the fastest but whose stores nothing covers: 213 to 224 us at
+// K = 4096).  The third one is the same tile by eight waves with a third stage, better when every unit has one tile
+// (8192 x 1024 x 4096: 60 to 62 us).  The small tiles win where they spread a short product over more units, and several teams where
+// even those leave most of them idle (2048 x 512 x 2048: 25 us with 128 x 256, 19 with 128 x 128, 12 with 64 x 128, 11.6 / 10.1 / 10.1
+// with 64 x 64 and 1 / 2 / 4 teams).
 static constexpr GemmTile kFp8Tiles[] = {
-    {128, 256, 1, 2, 4.5, 0.95, 0.92, 1.5}, {128, 256, 1, 1, 4.5, 0.67, 0.90, 3.5}, {128, 128, 1, 2, 3.4, 0.55, 0.46, 1.8},
-    {64, 128, 1, 2, 3.2, 0.33, 0.30, 1.0},  {64, 64, 1, 4, 2.9, 0.275, 0.166, 0.5}, {64, 64, 2, 2, 2.0, 0.40, 0.30, 1.5},
-    {64, 64, 4, 1, 1.5, 0.70, 0.70, 3.1},
+    {256, 256, 1, 1, 6.5, 1.13, 1.48, 8.3}, {128, 256, 1, 2, 4.5, 0.88, 0.81, 2.2}, {128, 256, 1, 1, 4.3, 0.66, 0.84, 4.0},
+    {128, 128, 1, 2, 3.8, 0.46, 0.46, 1.5},  {64, 128, 1, 2, 3.5, 0.285, 0.24, 1.2}, {64, 64, 1, 4, 3.0, 0.27, 0.178, 0.3},
+    {64, 64, 2, 2, 2.9, 0.40, 0.34, 0.8},    {64, 64, 4, 1, 1.5, 0.70, 0.70, 3.0},
 };
 
 template <bool TRANS>
 static int launch_tile(int which, const Fp8Args &ga, uint32_t tiles, hipStream_t st) {
     switch (which) {
-        case 0: gemm_fp8_kernel<2, 2, 2, 4, 1, 2, 2, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
-        case 1: gemm_fp8_kernel<2, 4, 2, 2, 1, 3, 2, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
-        case 2: gemm_fp8_kernel<2, 2, 2, 2, 1, 3, 2, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
-        case 3: gemm_fp8_kernel<2, 4, 1, 1, 1, 3, 4, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
-        case 4: gemm_fp8_kernel<2, 2, 1, 1, 1, 3, 4, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
-        case 5: gemm_fp8_kernel<2, 2, 1, 1, 2, 3, 4, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
-        case 6: gemm_fp8_kernel<2, 2, 1, 1, 4, 3, 4, TRANS><<<dim3(tiles), dim3(1024), 0, st>>>(ga); break;
+        case 0: gemm_fp8_kernel<2, 4, 4, 2, 1, 3, 2, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
+        case 1: gemm_fp8_kernel<2, 2, 2, 4, 1, 2, 2, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
+        case 2: gemm_fp8_kernel<2, 4, 2, 2, 1, 3, 2, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
+        case 3: gemm_fp8_kernel<2, 2, 2, 2, 1, 3, 2, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
+        case 4: gemm_fp8_kernel<2, 4, 1, 1, 1, 3, 4, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
+        case 5: gemm_fp8_kernel<2, 2, 1, 1, 1, 3, 4, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
+        case 6: gemm_fp8_kernel<2, 2, 1, 1, 2, 3, 4, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
+        case 7: gemm_fp8_kernel<2, 2, 1, 1, 4, 3, 4, TRANS><<<dim3(tiles), dim3(1024), 0, st>>>(ga); break;
         default: return static_cast<int>(hipErrorInvalidValue);
     }
     return static_cast<int>(hipGetLastError());
