@@ -70,42 +70,68 @@ __global__ __launch_bounds__(kMetaThreads) void transport_meta_kernel(const uint
     }
 }
 
-// Workgroup (i, y) copies runs of 1024 16-byte pieces, y, y + gridDim.y, ..., of variable i from the arena to
-// the place the meta kernel gave it (read back from the message's own table).
-constexpr uint32_t kPackSlices = 64;
-__global__ __launch_bounds__(256) void transport_pack_kernel(const uint8_t *__restrict__ plan, uint64_t var_off,
-                                                             const uint8_t *__restrict__ arena, uint8_t *__restrict__ msg,
-                                                             uint64_t payload_off) {
-    const PlanVar *vars = reinterpret_cast<const PlanVar *>(plan + var_off);
-    const uint32_t i = blockIdx.x;
-    const PlanVar pv = to_scalar_regs(vars[i]);
-    const TransportVar *tvs = reinterpret_cast<const TransportVar *>(msg + sizeof(TransportHeader));
-    const uint64_t dst_off = to_scalar_regs(tvs[i].payload_offset);
-    const bool q = (pv.flags & OMC_VAR_QUANTIZED) != 0;
-    const uint64_t bytes = q ? pv.total_dwords * 4 : 4 * pv.n;
-    const uint64_t full = bytes / 16;
-    const u32x4 *src = reinterpret_cast<const u32x4 *>(arena + pv.data_offset);
-    u32x4 *dst = reinterpret_cast<u32x4 *>(msg + payload_off + dst_off);
-    // four pieces per thread in flight; a slice's run of 4 * 256 pieces is contiguous
-    constexpr uint32_t kBatch = 4;
-    for (uint64_t p0 = static_cast<uint64_t>(blockIdx.y) * (256 * kBatch); p0 < full; p0 += 256ull * kBatch * gridDim.y) {
-        u32x4 x[kBatch];
+// The payload in runs of 32 KB, one workgroup each: eight 16-byte pieces per thread, all in flight together.  A run is found in the
+// message's own table, which the meta kernel has written: the threads look at one entry in every `stride`, then at the
+// entries between, two dependent loads.  A run that lies in one variable is copied by all threads; in the others each wave
+// takes one variable after the other.  Bound by memory (both streams are touched once and carry the hint): 190.7 MB of 599 variables
+// 67 us; with 64 workgroups per variable, whatever its size, and four pieces per thread 88 us.
+constexpr uint32_t kPackThreads = 256, kPackBatch = 8;
+constexpr uint64_t kPackRun = 16ull * kPackThreads * kPackBatch;
+
+// pieces [p0, p1) of a variable by THREADS threads, `t` being this one; `bytes` is the variable's size in the arena
+template <uint32_t THREADS>
+__device__ __forceinline__ void pack_pieces(const uint8_t *src8, uint8_t *dst8, uint64_t bytes, uint64_t p0, uint64_t p1, uint32_t t) {
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(src8);
+    u32x4 *dst = reinterpret_cast<u32x4 *>(dst8);
+    const uint64_t full = bytes / 16, end = p1 < full ? p1 : full;
+    for (uint64_t p = p0 + t; p < end; p += THREADS * kPackBatch) {
+        u32x4 x[kPackBatch];
 #pragma unroll
-        for (uint32_t u = 0; u < kBatch; ++u) {
-            const uint64_t p = p0 + u * 256 + threadIdx.x;
-            if (p < full) x[u] = __builtin_nontemporal_load(src + p);
-        }
+        for (uint32_t u = 0; u < kPackBatch; ++u)
+            if (p + u * THREADS < end) x[u] = __builtin_nontemporal_load(src + p + u * THREADS);
 #pragma unroll
-        for (uint32_t u = 0; u < kBatch; ++u) {
-            const uint64_t p = p0 + u * 256 + threadIdx.x;
-            if (p < full) __builtin_nontemporal_store(x[u], dst + p);
-        }
+        for (uint32_t u = 0; u < kPackBatch; ++u)
+            if (p + u * THREADS < end) __builtin_nontemporal_store(x[u], dst + p + u * THREADS);
     }
-    if (blockIdx.y == 0 && threadIdx.x == 0 && bytes % 16) {      // an fp32 variable whose size is no multiple of four
+    if (t == 0 && p0 <= full && full < p1 && bytes % 16) {        // an fp32 variable whose size is no multiple of four
         const uint32_t *s = reinterpret_cast<const uint32_t *>(src + full);
         uint32_t *d = reinterpret_cast<uint32_t *>(dst + full);
         const uint32_t left = static_cast<uint32_t>(bytes % 16) / 4;
         for (uint32_t k = 0; k < 4; ++k) d[k] = k < left ? s[k] : 0u;
+    }
+}
+
+__global__ __launch_bounds__(kPackThreads) void transport_pack_kernel(const uint8_t *__restrict__ plan, uint64_t var_off,
+                                                                      const uint8_t *__restrict__ arena, uint8_t *__restrict__ msg,
+                                                                      uint64_t payload_off, uint64_t payload_bytes, uint32_t nvars) {
+    const PlanVar *vars = reinterpret_cast<const PlanVar *>(plan + var_off);
+    const TransportVar *tvs = reinterpret_cast<const TransportVar *>(msg + sizeof(TransportHeader));
+    const uint32_t tid = threadIdx.x;
+    const uint64_t lo = static_cast<uint64_t>(blockIdx.x) * kPackRun, hi = lo + kPackRun < payload_bytes ? lo + kPackRun : payload_bytes;
+    // the last variable that starts at or before lo (variable 0 starts at 0)
+    uint32_t first = 0;
+    for (uint32_t span = nvars; span > 1;) {
+        const uint32_t stride = (span + kPackThreads - 1) / kPackThreads, at = first + tid * stride;
+        const bool below = tid * stride < span && tvs[at].payload_offset <= lo;
+        const uint32_t steps = static_cast<uint32_t>(__syncthreads_count(below)) - 1;   // offsets ascend; entry `first` is below
+        const uint32_t rest = span - steps * stride;
+        first += steps * stride;
+        span = rest < stride ? rest : stride;
+    }
+    auto bytes_of = [&](const PlanVar &pv) { return (pv.flags & OMC_VAR_QUANTIZED) ? pv.total_dwords * 4 : 4 * pv.n; };
+    const PlanVar pv = to_scalar_regs(vars[first]);
+    const uint64_t off = to_scalar_regs(tvs[first].payload_offset);
+    uint8_t *payload = msg + payload_off;
+    if (off + (bytes_of(pv) + 15) / 16 * 16 >= hi) {
+        pack_pieces<kPackThreads>(arena + pv.data_offset, payload + off, bytes_of(pv), (lo - off) / 16, (hi - off) / 16, tid);
+        return;
+    }
+    for (uint32_t i = first + (tid >> 6); i < nvars; i += kPackThreads / 64) {
+        const uint64_t o = to_scalar_regs(tvs[i].payload_offset);
+        if (o >= hi) return;
+        const PlanVar v = to_scalar_regs(vars[i]);
+        const uint64_t end = o + (bytes_of(v) + 15) / 16 * 16;
+        pack_pieces<64>(arena + v.data_offset, payload + o, bytes_of(v), lo > o ? (lo - o) / 16 : 0, ((end < hi ? end : hi) - o) / 16, tid & 63u);
     }
 }
 
@@ -116,9 +142,11 @@ int launch_transport_pack(const PlanHeader *ph, const void *plan_dev, const void
                                                                   static_cast<uint8_t *>(msg_dev), th);
     int rc = static_cast<int>(hipGetLastError());
     if (rc != 0) return rc;
-    transport_pack_kernel<<<dim3(ph->nvars, kPackSlices), dim3(256), 0, st>>>(
+    const uint64_t runs = (th.payload_bytes + kPackRun - 1) / kPackRun;
+    if (runs > 0x7fffffffull) return static_cast<int>(hipErrorInvalidValue);
+    transport_pack_kernel<<<dim3(static_cast<uint32_t>(runs)), dim3(kPackThreads), 0, st>>>(
         static_cast<const uint8_t *>(plan_dev), ph->var_off, static_cast<const uint8_t *>(arena),
-        static_cast<uint8_t *>(msg_dev), th.payload_off);
+        static_cast<uint8_t *>(msg_dev), th.payload_off, th.payload_bytes, ph->nvars);
     return static_cast<int>(hipGetLastError());
 }
 

@@ -251,3 +251,40 @@ def test_message_is_validated_on_open():
     with pytest.raises(omc.OmcError) as e:
         omc.omc_transport_pack(vs.plan, vs.g_arena, vs.g_sb, msg[:nbytes - 16])
     assert e.value.status == 3
+
+
+@pytest.mark.parametrize("count", [1, 2, 255, 257, 1030])
+def test_transport_payload_of_many_sizes(count):
+    """Runs of 32 KB of the payload that start and end inside variables, hold dozens of small ones or lie in one large one, and sets of
+    one variable up to more than 1024 (the table's scan takes a second round); fp32 sizes that are no multiple of four, whose
+    padding in the message is zero whatever the arena holds there."""
+    rng = np.random.default_rng(count)
+    ns = rng.integers(1, 3000, count)
+    ns[rng.random(count) < 0.02] = 70001
+    ns[0] = 50003
+    mask = rng.random(count) < 0.5
+    bits, off, aux, table, want = 11, 0, 0, [], []
+    for n, q in zip(ns.tolist(), mask.tolist()):
+        nbytes = omc.omc_packed_bytes(omc.fmt(3, 7), n) if q else 4 * n
+        off += 16 * int(rng.integers(0, 3))                 # gaps in the arena
+        table.append(dict(data_offset=off, aux_offset=aux, n=n, fmt=omc.fmt(3, 7), quantized=q))
+        want.append((off, nbytes))
+        off += (nbytes + 15) // 16 * 16
+        aux += (n + 3) // 4 * 4
+    plan = omc.omc_plan_build(omc.make_var_table(table))
+    arena = rng.integers(0, 256, off, dtype=np.uint8)
+    sb = rng.standard_normal((count, 2)).astype(np.float32)
+    nbytes = omc.omc_transport_bytes(plan)
+    msg = torch.full((nbytes + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    omc.omc_transport_pack(plan, to_dev(arena), to_dev(sb), msg)
+    torch.cuda.synchronize()
+    assert bool((msg[nbytes:] == 0xA5).all())
+    host = msg[:nbytes].cpu().numpy()
+    got, nvars, sb_off, payload, _, _ = open_message(host)
+    assert nvars == count
+    for i, (o, b) in enumerate(want):
+        at = payload + got[i].data_offset
+        assert np.array_equal(host[at:at + b], arena[o:o + b]), i
+        assert not host[at + b:at + (b + 15) // 16 * 16].any(), i
+    table_sb = host[sb_off:sb_off + 8 * count].view(np.float32).reshape(count, 2)
+    assert np.array_equal(table_sb, np.where(mask[:, None], sb, np.array([1.0, 0.0], np.float32)))
