@@ -150,7 +150,7 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream):
-    if stream is None:   # the current stream's handle, without a Stream object built for it: a 65 536-element step 12.6 -> 10.2 us
+    if stream is None:   # the current stream's handle, without a Stream object built for it: a step on 512 x 512 weights 12.6 -> 10.2 us
         return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream
 
