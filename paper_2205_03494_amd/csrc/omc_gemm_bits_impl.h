@@ -1,7 +1,7 @@
 // omc_dequant_gemm / omc_dequant_gemm_dx on codes of any width B (2 .. 16 bits; S1E4M3 with bias 7 has a kernel of its own).
 //
 // C[M x N] = A[M x K] * (s W + b), W packed as [K x N] (forward) or [N x K] (TRANS).  Steps of 64 k, two LDS stages.  A goes from
-// global memory straight into LDS as rows of 128 bytes (16-byte pieces XOR-swizzled by the row).  W passes through
+// global memory straight into LDS as rows of 128 bytes (16-byte pieces XOR-swizzled by half the row: 64 banks hold two rows).  W passes through
 // registers: a thread takes 32 consecutive codes = B whole dwords, so that every shift is a compile-time constant,
 // decodes them in the bit domain and stores 32 bfloat16 values: forward as a part of a k row [k][BN] that the transposing
 // 16-bit read turns into fragments, TRANS as half of a column's 64 k, laid out like A.  Each code is decoded once per
@@ -11,8 +11,7 @@
 // groups, and its four pieces are rotated by g / 2: the eight k rows of a transposing read and the eight lanes of a store then
 // lie on different banks.
 //
-// What bounds it: LDS bandwidth (64 KB per 16 k of a 256 x 256 tile: all that 128 B/clk allows at the matrix cores' rate) and the
-// decode, about five vector instructions per code.  Measured on 11-bit codes against the kernels before (256 x 128 or 128 x 128 tile,
+// What bounds it: the decode, about five vector instructions per code, beside 64 KB through LDS per 16 k of a 256 x 256 tile.  Measured on 11-bit codes against the kernels before (256 x 128 or 128 x 128 tile,
 // A staged through registers, a patch of 4 x 4 codes per thread with run-time shifts; 256 x 128 by 16 waves for long contractions):
 // forward 8192 x 4096 x 1024 104 -> 82 us, 2048 x 2048 x 512 18.6 -> 11.4, input gradient 2048 x 512 x 2048 53.6 -> 13.
 #pragma once
@@ -114,7 +113,7 @@ void gemm_bits_kernel(BitsArgs ga) {
     const uint32_t full_k = K / 64, steps_k = (K + 63) / 64;
     const uint32_t full = (full_k + TEAMS - 1 - team) / TEAMS, steps = (steps_k + TEAMS - 1 - team) / TEAMS;   // this team's
     const uint8_t *a_base = reinterpret_cast<const uint8_t *>(ga.A) + static_cast<uint64_t>(m0) * K * 2;
-    const uint32_t a_row = lane >> 3, a_piece = (lane & 7u) ^ a_row;
+    const uint32_t a_row = lane >> 3, a_piece = (lane & 7u) ^ ((a_row >> 1) + 4 * (wave & 1u));
     auto load_a = [&](uint32_t at, uint32_t i) {
         const uint32_t j = team + TEAMS * i;
         const uint32_t a_off = a_row * K * 2 + (j == full_k ? a_piece & 3u : a_piece) * 16;
@@ -140,7 +139,7 @@ void gemm_bits_kernel(BitsArgs ga) {
 #pragma unroll
     for (uint32_t i = 0; i < kPieces; ++i) {
         const uint32_t piece = u_part * kPieces + i, group = piece / 4;
-        u_at[i] = kABytes + (TRANS ? u_row * 128 + ((piece ^ (u_row & 7u)) << 4)
+        u_at[i] = kABytes + (TRANS ? u_row * 128 + ((piece ^ ((u_row >> 1) & 7u)) << 4)
                                    : u_row * (2 * BN) + ((group ^ swizzle_f(u_row)) * 4 + ((piece & 3u) ^ ((group >> 1) & 3u))) * 16);
     }
     auto store_piece = [&](uint32_t at, const Unit<B, U> &u, int i) {
@@ -151,7 +150,7 @@ void gemm_bits_kernel(BitsArgs ga) {
     const uint32_t f_row = lane & 31u, f_half = lane >> 5;
     auto a_place = [&](uint32_t ks) {
         const uint32_t row = 32 * TM * wm + f_row;
-        return row * 128 + (((2 * ks + f_half) ^ (row & 7u)) << 4);
+        return row * 128 + (((2 * ks + f_half) ^ ((row >> 1) & 7u)) << 4);
     };
     const uint32_t block = lane >> 4, in = lane & 15u;          // forward: 16 lanes point at 4 k rows x 16 columns
     uint32_t w_base[TN];                                        // forward: quarter 0's place per column block
@@ -163,7 +162,7 @@ void gemm_bits_kernel(BitsArgs ga) {
     auto w_place = [&](uint32_t ks) {                           // TRANS: place of column block 0; forward: step to quarter ks
         if (!TRANS) return ks * 16 * (2 * BN);
         const uint32_t col = 32 * TN * wn + f_row;
-        return kABytes + col * 128 + (((2 * ks + f_half) ^ (col & 7u)) << 4);
+        return kABytes + col * 128 + (((2 * ks + f_half) ^ ((col >> 1) & 7u)) << 4);
     };
     uint32_t a_at[4], w_at[4];
 #pragma unroll

@@ -7,8 +7,10 @@
 // with a plain read of eight consecutive codes -- and converts them to bfloat16 in registers, four instructions for eight
 // codes.  Staging costs no vector instruction and W passes through LDS at one byte per weight.
 //
-// 16-byte pieces are XOR-swizzled on their way in (the lane picks the piece, its LDS place is fixed): A pieces by the row,
-// forward W pieces by the k row, TRANS W pieces by half the column, so that the rows of one read lie on different banks.
+// 16-byte pieces are XOR-swizzled on their way in (the lane picks the piece, its LDS place is fixed): A pieces by half the row,
+// forward W pieces by twice the k row, TRANS W pieces by a quarter of the column, so that the 16 pieces that one read takes at
+// a time lie on different ones of the 64 banks (A by the whole row: 8.1 clocks a read instead of 4.4, W 4.2 instead of 3.2 and
+// 8.0 instead of 4.2, all forward bank conflicts gone).
 //
 // Fragments of a quarter step are read while the quarter before is multiplied; the last quarter is multiplied after the
 // barrier of the next step, under that step's first reads.  Waves start their quarters at different places
@@ -20,9 +22,8 @@
 //
 // Measured (us, 8192 x 4096 x 1024 / 8192 x 1024 x 4096, fp32 output, new operands each time), against the kernel before (256 x 128 tile,
 // A fragments from global memory, W decoded on the way into LDS, a 5 us pass over the codes for top codes first): 83 / 81 ->
-// 65 / 60.  What bounds it now: LDS bandwidth (24 KB through LDS per 16 k of a 128 x 256 tile, three quarters of what
-// 128 B/clk gives at the matrix cores' rate) and power (1300 TFLOP/s at 8192 x 4096 x 4096, random data), and the C stores where
-// nothing covers them.
+// 65 / 60.  What bounds it now: power (1300 TFLOP/s at 8192 x 4096 x 4096, random data) and the C stores where nothing covers
+// them; not the LDS (67.6 -> 67.1 us at the first shape without its bank conflicts).
 #include "omc_mma.h"
 
 #pragma clang fp contract(off)
@@ -75,7 +76,7 @@ void gemm_fp8_kernel(Fp8Args ga) {
     constexpr int kALoads = BM / 8 / NW, kWLoads = BN / 16 / NW, kLoads = kALoads + kWLoads;   // 1 KB loads per wave and stage
     constexpr int kPieces = BN / 16;                        // 16-byte pieces in a k row of the forward W tile
     constexpr uint32_t kABytes = BM * 128, kStage = kABytes + BN * 64;
-    static_assert(WM == 2 && (WN == 2 || WN == 4), "how the quarters are dealt below");
+    static_assert(WM == 2 && (WN == 2 || WN == 4), "how the quarters are dealt below; with an even number of waves a wave's loads bring one half of 16 rows");
     static_assert(BM % (8 * NW) == 0 && BN % (16 * NW) == 0 && (64 / kPieces) * NW % kPieces == 0, "whole loads, one swizzle per wave");
     __shared__ __attribute__((aligned(1024))) uint8_t lds_all[TEAMS * S * kStage];
     const uint32_t team = TEAMS == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
@@ -94,10 +95,11 @@ void gemm_fp8_kernel(Fp8Args ga) {
     const uint32_t full_k = K / 64, stages_k = (K + 63) / 64;
     const uint32_t full = (full_k + TEAMS - 1 - team) / TEAMS, stages = (stages_k + TEAMS - 1 - team) / TEAMS;   // this team's
     const uint8_t *a_base = reinterpret_cast<const uint8_t *>(ga.A) + static_cast<uint64_t>(m0) * K * 2;
-    const uint32_t a_row = lane >> 3, a_piece = (lane & 7u) ^ a_row;
+    const uint32_t a_row = lane >> 3, a_piece = (lane & 7u) ^ ((a_row >> 1) + 4 * (wave & 1u));
     const uint8_t *w_base = TRANS ? ga.codes + static_cast<uint64_t>(n0) * K : ga.codes + n0;
     const uint32_t w_row = TRANS ? lane >> 2 : lane / kPieces;
-    const uint32_t w_piece = TRANS ? (lane & 3u) ^ ((lane >> 3) & 3u) : (lane % kPieces) ^ ((wave * (64 / kPieces) + w_row) & (kPieces - 1));
+    auto w_swizzle = [](uint32_t k_row) { return k_row * kPieces / 8 & (kPieces - 2u); };
+    const uint32_t w_piece = TRANS ? (lane & 3u) ^ (lane >> 4) : (lane % kPieces) ^ w_swizzle(wave * (64 / kPieces) + w_row);
     auto load_stage = [&](uint32_t at, uint32_t step) {
         const uint32_t j = team + TEAMS * step;
         const bool half = j == full_k;
@@ -124,16 +126,16 @@ void gemm_fp8_kernel(Fp8Args ga) {
     auto a_place = [&](uint32_t ks) {
         const uint32_t row = 32 * TM * wm + f_row;
         const uint32_t piece = TRANS ? 4 * (ks >> 1) + 2 * f_half + (ks & 1u) : 2 * ks + f_half;
-        return row * 128 + ((piece ^ (row & 7u)) << 4);
+        return row * 128 + ((piece ^ ((row >> 1) & 7u)) << 4);
     };
     auto w_place = [&](uint32_t ks) {
         if (TRANS) {
             const uint32_t col = 32 * TN * wn + f_row, piece = 2 * (ks >> 1) + f_half;
-            return kABytes + col * 64 + ((piece ^ ((col >> 1) & 3u)) << 4) + 8 * (ks & 1u);
+            return kABytes + col * 64 + ((piece ^ ((col >> 2) & 3u)) << 4) + 8 * (ks & 1u);
         }
         const uint32_t block = lane >> 4, in = lane & 15u;      // 16 lanes: 16 columns x 8 k
         const uint32_t row = 16 * ks + 8 * (block >> 1) + (in >> 1), piece = 2 * TN * wn + (block & 1u);
-        return kABytes + row * BN + ((piece ^ (row & (kPieces - 1))) << 4) + 8 * (in & 1u);
+        return kABytes + row * BN + ((piece ^ w_swizzle(row)) << 4) + 8 * (in & 1u);
     };
     uint32_t a_at[4], w_at[4];
 #pragma unroll
