@@ -414,7 +414,7 @@ omc_status omc_dequant_gemm_dx(const uint16_t *dY, const void *codes, omc_format
 /* Workspace (device bytes) for omc_dw_update_recompress with M rows of X / dY on a K x N weight matrix
  * stored in format f; 0 for unsupported formats or sizes.  When the matrix alone gives too few tiles
  * to fill the chip, the M rows are split between workgroups and the workspace holds their partial
- * accumulators (up to 8 * 4*K*N bytes); for code widths other than 8 it always holds one such copy. */
+ * gradients (up to 8 * 4*K*N bytes); for code widths other than 8 it always holds one such copy. */
 size_t omc_dw_update_workspace_bytes(omc_format f, uint32_t M, uint32_t N, uint32_t K);
 
 /* The whole backward step of a linear layer Y = X * Wbar on its compressed weights (Sec. 2.1, backward
@@ -431,9 +431,9 @@ size_t omc_dw_update_workspace_bytes(omc_format f, uint32_t M, uint32_t N, uint3
  *   dW_out   device, K*N floats, or NULL; receives the gradient exactly as the update consumed it
  *   ws       device workspace of omc_dw_update_workspace_bytes(f, M, N, K) bytes
  * Requires K % 256 == 0, N % 128 == 0, M % 32 == 0 (OMC_ERR_SIZE).  With an 8-bit format and enough
- * tiles the update runs in the GEMM kernel's epilogue (a lane of the accumulator layout owns whole
- * dwords of codes) and the gradient never reaches memory; otherwise the accumulators pass through
- * the workspace once and a second kernel does the update.  Result: identical to
+ * tiles the update runs in the GEMM kernel's epilogue (a thread takes four weights of a row, one
+ * dword of codes) and the gradient never reaches memory; otherwise partial gradients pass through
+ * the workspace once and a second kernel adds them and does the update.  Result: identical to
  * omc_step_update_recompress on this variable with dW_out as its gradient; the gradient's summation
  * order is fixed by the sizes alone, so repeated calls give identical bits. */
 omc_status omc_dw_update_recompress(const uint16_t *X, const uint16_t *dY, void *codes, omc_format f,
