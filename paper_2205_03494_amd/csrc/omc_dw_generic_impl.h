@@ -36,8 +36,9 @@ __global__ __launch_bounds__(64, (Tuning<MODE, B>::waves)) void dw_reduce_update
     fit.template reduce_and_store<variant_exact(VARIANT)>(a.ws + blockIdx.x);
 }
 
-// FmtParams::variant: 0 / 1 rounding by add-subtract / ldexp; 4 / 5 the same with error-carrying sums, which only code widths of
-// 18 bits and more can ask for; the hardware conversions (2 / 3) serve plain SGD.
+// FmtParams::variant: 0 / 1 rounding by add-subtract / ldexp (7 exponent bits, so 8 bits in all, are the fewest that reach the
+// binades of the latter); 4 / 5 the same with error-carrying sums, which only code widths of 18 bits and more can ask for; the
+// hardware conversions (2 / 3) serve plain SGD.
 template <int BITS, int MODE>
 inline void launch_dw_update_width(dim3 grid, const DwArgs &a, hipStream_t st) {
     const uint32_t variant = a.fp.variant;
@@ -51,7 +52,7 @@ inline void launch_dw_update_width(dim3 grid, const DwArgs &a, hipStream_t st) {
     if constexpr (BITS == 6 && MODE == kStepSgd) {
         if (variant == 3) { dw_reduce_update_kernel<6, MODE, 3><<<grid, dim3(64), 0, st>>>(a); return; }
     }
-    if constexpr (BITS >= 9) {
+    if constexpr (BITS >= 8) {
         if (variant == 1) { dw_reduce_update_kernel<BITS, MODE, 1><<<grid, dim3(64), 0, st>>>(a); return; }
     }
     dw_reduce_update_kernel<BITS, MODE, 0><<<grid, dim3(64), 0, st>>>(a);

@@ -17,11 +17,11 @@ from test_gpu_gemm import check
 pytestmark = pytest.mark.gpu
 
 
-def run_case(EM, M, N, K, kind, lr, use_pvt=True, steps=2, grad_scale=1.0, rows=None):
+def run_case(EM, M, N, K, kind, lr, use_pvt=True, steps=2, grad_scale=1.0, rows=None, w_scale=0.05):
     want_dw = True
     of, gf = pair(*EM)
     n = K * N
-    W = synth.normal_f32(n, 0.05, 2)
+    W = synth.normal_f32(n, w_scale, 2)
     packed, sb = orc.compress(W, of, use_pvt=use_pvt)
     st0 = np.zeros(n, np.float32) if kind >= 1 else None
     st1 = np.zeros(n, np.float32) if kind == 2 else None
@@ -166,3 +166,11 @@ def test_contraction_in_two_and_in_eight_parts(kind, lr, shape):
     """Room for two copies of the gradient: 8-bit codes are updated by two teams of waves in one kernel; for eight: teams and splits."""
     M, N, K = shape
     run_case((4, 3), M, N, K, kind, lr, steps=1, rows=(0, K - 16))
+
+
+@pytest.mark.parametrize("kind,lr", [(0, 2.0 ** 45), (1, 2.0 ** 45), (2, 0.6 * 2.0 ** 105)])
+@pytest.mark.parametrize("M", [96, 4096])
+def test_eight_bit_format_whose_top_binades_need_the_wide_rounding(M, kind, lr):
+    """S1E7M0 with a bias below 23 holds values above 2^105, which the rounding by add and subtract cannot reach.  96 rows: updated
+    in the product's epilogue; 4096: by the second kernel, from partial sums."""
+    run_case((7, 0, 10), M, 128, 256, kind, lr, steps=1, grad_scale=2.0 ** 60, w_scale=2.0 ** 107)
