@@ -63,7 +63,8 @@ int launch_dw_update(const uint16_t *X, const uint16_t *dY, void *codes, const F
     a.K = K;
     uint32_t nparts = 0;
     int rc;
-    if (fp.bits == 8 && dw_one_kernel_is_faster(M, N, K, room)) {
+    const bool one_kernel = fp.bits == 8 && dw_one_kernel_is_faster(M, N, K, room);
+    if (one_kernel) {
         rc = launch_dw_one_kernel(a, room, opt.kind, &nparts, st);
     } else {
         nparts = static_cast<uint32_t>(static_cast<uint64_t>(K) * N / kTileElems);
@@ -76,7 +77,7 @@ int launch_dw_update(const uint16_t *X, const uint16_t *dY, void *codes, const F
     if (rc != 0) return rc;
     const uint64_t n = static_cast<uint64_t>(K) * N;
     // the width of the reduction depends on the sizes alone, so results do not depend on the run
-    const int exact = variant_exact(fp.variant) ? 1 : 0;
+    const int exact = one_kernel || variant_exact(fp.variant) ? 1 : 0;   // the partials carry error words
     if (nparts <= 256) dw_finalize_kernel<1><<<dim3(1), dim3(64), 0, st>>>(a.ws, nparts, n, use_pvt, exact, sb);
     else if (nparts <= 2048) dw_finalize_kernel<4><<<dim3(1), dim3(256), 0, st>>>(a.ws, nparts, n, use_pvt, exact, sb);
     else dw_finalize_kernel<16><<<dim3(1), dim3(1024), 0, st>>>(a.ws, nparts, n, use_pvt, exact, sb);

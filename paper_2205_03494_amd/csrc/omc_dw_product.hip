@@ -229,20 +229,29 @@ void dw_product_kernel(ProductArgs pa, DwArgs a) {
         fit.clear();
         if (a.fp.wide) update_tile<BK, BN, 64 * NW * TEAMS, MODE, true>(a, tile, k0, n0, fit);
         else update_tile<BK, BN, 64 * NW * TEAMS, MODE, false>(a, tile, k0, n0, fit);
-        fit.reduce_and_store<false>(sums + team * NW + wave);  // 8-bit formats: plain fp64 sums
+        fit.reduce_and_store<false>(sums + team * NW + wave);  // (8-bit formats: plain fp64 sums within a wave)
         __syncthreads();
-        if (threadIdx.x == 0) {                               // one partial per tile, the waves in order
-            Partial p = sums[0];
+        if (threadIdx.x < 64) {                               // one partial per tile: the waves' sums, each addition's error kept
+            constexpr uint32_t kWaves = NW * TEAMS;
+            static_assert(kWaves <= 16 && (kWaves & (kWaves - 1)) == 0, "one lane of the first wave per wave and sum");
+            const Partial *from = sums + (lane & (kWaves - 1));
+            DD one{(&from->sV)[lane >> 4], 0.0};              // 16 lanes a sum: V, Vt, V Vt, Vt^2
+            float tmin = from->tmin, tmax = from->tmax;
 #pragma unroll
-            for (int w = 1; w < NW * TEAMS; ++w) {
-                p.sV += sums[w].sV;
-                p.sT += sums[w].sT;
-                p.sVT += sums[w].sVT;
-                p.sTT += sums[w].sTT;
-                p.tmin = fminf(p.tmin, sums[w].tmin);
-                p.tmax = fmaxf(p.tmax, sums[w].tmax);
+            for (int off = kWaves / 2; off >= 1; off >>= 1) {
+                one = dd_add(one, dd_shfl_xor(one, off));
+                tmin = fminf(tmin, __shfl_xor(tmin, off));
+                tmax = fmaxf(tmax, __shfl_xor(tmax, off));
             }
-            a.ws[blockIdx.x] = p;
+            Partial *out = a.ws + blockIdx.x;
+            if ((lane & 15u) == 0) {
+                (&out->sV)[lane >> 4] = one.hi;
+                (&out->lV)[lane >> 4] = one.lo;
+            }
+            if (lane == 0) {
+                out->tmin = tmin;
+                out->tmax = tmax;
+            }
         }
     }
 }

@@ -53,7 +53,7 @@ constexpr uint32_t kVariants = 6;
 
 // Per-chunk partial sums of the least-squares fit (paper Sec. 2.3).  The four sums are unevaluated
 // pairs s + l: the kernels of formats with fewer than 16 mantissa bits leave l = 0, the others carry
-// the rounding errors of their additions there (see FitAcc).
+// the rounding errors of their additions there (see FitAcc), as does whoever adds up several waves' sums.
 struct Partial {
     double sV, sT, sVT, sTT;
     double lV, lT, lVT, lTT;

@@ -174,3 +174,23 @@ def test_eight_bit_format_whose_top_binades_need_the_wide_rounding(M, kind, lr):
     """S1E7M0 with a bias below 23 holds values above 2^105, which the rounding by add and subtract cannot reach.  96 rows: updated
     in the product's epilogue; 4096: by the second kernel, from partial sums."""
     run_case((7, 0, 10), M, 128, 256, kind, lr, steps=1, grad_scale=2.0 ** 60, w_scale=2.0 ** 107)
+
+
+def test_epilogue_combines_its_waves_sums_without_rounding():
+    """Two weights of +-2^80 in rows of two waves of a 64-row tile, ones in the rows of the wave between them: whoever adds the waves' sums in
+    plain fp64 loses the ones, and with them their share of b.  V = Vt + 0.25 for the ones and V = Vt elsewhere (the zeros
+    become codes of 0.25), so that what a wave loses beside +-2^80 it loses from both sums: s = 1, b = 0.25 x share of the ones, exactly."""
+    of, gf = pair(7, 0, 40)
+    M, N, K = 32, 128, 256
+    ones = (np.arange(K) % 8) >= 4                          # rows of waves 1 and 3; the others hold zeros
+    codes = np.where(ones[:, None], 40, 0) * np.ones((1, N), np.int64)
+    codes[0, 0], codes[8, 0] = 120, 0x80 | 120
+    packed, sb = orc.pack(codes.ravel().astype(np.uint32), 8), np.array([1.0, 0.25], np.float32)
+    codes_d, sb_d = to_dev(packed), to_dev(sb)
+    X, dY = torch.zeros((M, K), dtype=torch.int16, device="cuda"), torch.zeros((M, N), dtype=torch.int16, device="cuda")
+    ws = torch.empty(omc.omc_dw_update_workspace_bytes(gf, M, N, K), dtype=torch.uint8, device="cuda")
+    omc.omc_dw_update_recompress(X, dY, codes_d, gf, sb_d, True, None, None, omc.opt(0, 0.0), None, M, N, K, ws)
+    orc.step_quantized(packed, K * N, of, sb, np.zeros(K * N, np.float32), None, None, orc.Opt(kind=0, lr=0.0))
+    assert sb.tolist() == [1.0, 0.125]                      # (half of the rows)
+    assert np.array_equal(codes_d.cpu().numpy(), packed)
+    assert bits_equal(sb_d.cpu().numpy(), sb), (sb_d.cpu().numpy(), sb)
