@@ -18,7 +18,12 @@
 //
 // The top code reads as NaN in the hardware conversion, without its sign.  No pass over the codes looks for it beforehand, and no
 // instruction in the loop: it makes every row of its column NaN, so a wave looks at one row of its sums, and a workgroup that finds
-// one computes its tile again with a bit-domain decode (as it does, to the same result, where A itself is not finite).
+// one computes its tile again with a conversion that is right for it (as it does, to the same result, where A itself is not finite).
+// The large tiles also look once after an eighth of a long contraction, and stop there: where top codes are all over the matrix, the
+// second pass is then nearly all it costs.  8192 x 4096 x 1024 / 8192 x 1024 x 4096, us: one code in 1000 a top code 90 / 89 (154 / 150 where
+// the second pass decoded in the bit domain and the first one always ran to its end; 95 / 109 with a pass over the codes first and a
+// kernel of other formats behind it); a top code in one column of 64, in the last row of k, 134 / 135 (156 / 154; 95 / 108); none 65 / 58
+// either way.  Looking more often costs up to 9 % where there is none, and so does looking in small tiles (up to 4 %).
 //
 // Measured (us, 8192 x 4096 x 1024 / 8192 x 1024 x 4096, fp32 output, new operands each time), against the kernel before (256 x 128 tile,
 // A fragments from global memory, W decoded on the way into LDS, a 5 us pass over the codes for top codes first): 83 / 81 ->
@@ -30,30 +35,25 @@
 
 namespace omc {
 
-// Eight codes as bfloat16.  EXACT: bit-domain decode, right for the top code too.
+// Eight codes as bfloat16.  EXACT: right for the top code too.  It is converted as the code below it, 448 = 0x43e0 in bfloat16, and
+// gets the bit that is missing to 480 = 0x43f0 afterwards: 24 instructions for eight codes instead of four (the bit-domain
+// decode of the other formats takes 44).
 template <bool EXACT>
 __device__ __forceinline__ bf16x8 fp8x8_to_bf16(u32x2 c) {
     u32x4 o;
-    if (EXACT) {
 #pragma unroll
-        for (int d = 0; d < 2; ++d)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t pair = 0;
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const uint32_t code_at_top = c[d] << (24 - 16 * h - 8 * e);
-                    const uint32_t bits = static_cast<uint32_t>(static_cast<int32_t>(code_at_top) >> 4) & 0x87f00000u;
-                    const uint32_t v = __float_as_uint(__uint_as_float(bits) * 0x1p120f);
-                    pair |= e ? (v & 0xffff0000u) : (v >> 16);
-                }
-                o[2 * d + h] = pair;
-            }
-    } else {
-#pragma unroll
-        for (int d = 0; d < 2; ++d) {
-            o[2 * d] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c[d], 1.0f, false));
-            o[2 * d + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c[d], 1.0f, true));
+    for (int d = 0; d < 2; ++d) {
+        uint32_t codes = c[d], top = 0;
+        if (EXACT) {
+            top = ((codes & 0x7f7f7f7fu) + 0x01010101u) & 0x80808080u;   // bit 7 of the bytes that hold it
+            codes -= top >> 7;
+            top >>= 3;
+        }
+        o[2 * d] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(codes, 1.0f, false));
+        o[2 * d + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(codes, 1.0f, true));
+        if (EXACT) {
+            o[2 * d] |= __builtin_amdgcn_perm(0u, top, 0x0c010c00u);
+            o[2 * d + 1] |= __builtin_amdgcn_perm(0u, top, 0x0c030c02u);
         }
     }
     return __builtin_bit_cast(bf16x8, o);
@@ -76,9 +76,11 @@ void gemm_fp8_kernel(Fp8Args ga) {
     constexpr int kALoads = BM / 8 / NW, kWLoads = BN / 16 / NW, kLoads = kALoads + kWLoads;   // 1 KB loads per wave and stage
     constexpr int kPieces = BN / 16;                        // 16-byte pieces in a k row of the forward W tile
     constexpr uint32_t kABytes = BM * 128, kStage = kABytes + BN * 64;
+    constexpr bool kLookEarly = BM * BN >= 128 * 256;
     static_assert(WM == 2 && (WN == 2 || WN == 4), "how the quarters are dealt below; with an even number of waves a wave's loads bring one half of 16 rows");
     static_assert(BM % (8 * NW) == 0 && BN % (16 * NW) == 0 && (64 / kPieces) * NW % kPieces == 0, "whole loads, one swizzle per wave");
     __shared__ __attribute__((aligned(1024))) uint8_t lds_all[TEAMS * S * kStage];
+    __shared__ uint32_t top_met;
     const uint32_t team = TEAMS == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
     uint8_t *lds = lds_all + team * (S * kStage);
     const uint32_t lds0 = lds_offset(lds);
@@ -164,6 +166,13 @@ void gemm_fp8_kernel(Fp8Args ga) {
 
     f32x16 acc[TM][TN];
     float rsum[TM];
+    auto holds_nan = [&]() {                                  // one row of every column tells
+        bool bad = false;
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) bad = bad || acc[0][ni][0] != acc[0][ni][0];
+        return __any(bad);
+    };
+    // Without EXACT it may stop on the way, in all waves of the workgroup alike, with a NaN in some wave's sums.
     auto compute = [&](auto exact_tag) {
         constexpr bool EXACT = decltype(exact_tag)::value;
 #pragma unroll
@@ -186,6 +195,9 @@ void gemm_fp8_kernel(Fp8Args ga) {
                 for (int mi = 0; mi < TM; ++mi) rsum[mi] = add_fragment(f.a[mi], rsum[mi]);
             }
         };
+        const uint32_t shortest = stages_k / TEAMS;
+        uint32_t steady_end = stages > S - 1 ? stages - (S - 1) : 0, full_end = full, slots = (stages_k + TEAMS - 1) / TEAMS;
+        bool half = full < stages;
         Frags f0, f1;
         uint32_t cur = 0, far = (S - 1) * kStage;
         auto rest_of_step = [&]() {                           // everything but the first quarter's reads and the last one's products
@@ -198,6 +210,7 @@ void gemm_fp8_kernel(Fp8Args ga) {
             cur = cur == (S - 1) * kStage ? 0 : cur + kStage;
             far = far == (S - 1) * kStage ? 0 : far + kStage;
         };
+        if (!EXACT && kLookEarly && threadIdx.x == 0) top_met = 0;
 #pragma unroll
         for (uint32_t i = 0; i < S - 1; ++i)
             if (i < stages) load_stage(i * kStage, i);
@@ -207,14 +220,24 @@ void gemm_fp8_kernel(Fp8Args ga) {
             if (stages > S - 1) load_stage(far, S - 1);
             rest_of_step();
             uint32_t j = 1;
-            for (; j + (S - 1) < stages; ++j) {
+            auto steady_step = [&]() {
                 wait_loads_and_sync<(S - 2) * kLoads>();
                 read_frags(cur, a_at[0], w_at[0], f0);
                 load_stage(far, j + S - 1);
                 multiply(f1, false);
                 rest_of_step();
+            };
+            if (!EXACT && kLookEarly && shortest >= 16) {     // (every team gets this far)
+                for (const uint32_t look = shortest / 8; j < look; ++j) steady_step();
+                if (holds_nan() && lane == 0) top_met = 1;
+                sync_lds();
+                if (__builtin_amdgcn_readfirstlane(top_met) != 0) {
+                    steady_end = full_end = slots = 0;        // the same in all waves: nothing more is multiplied in this pass
+                    half = false;
+                }
             }
-            for (; j < full; ++j) {
+            for (; j < steady_end; ++j) steady_step();
+            for (; j < full_end; ++j) {
                 wait_stage<S, kLoads>(j, stages);
                 read_frags(cur, a_at[0], w_at[0], f0);
                 multiply(f1, false);
@@ -222,7 +245,7 @@ void gemm_fp8_kernel(Fp8Args ga) {
             }
             multiply(f1, false);
         }
-        if (full < stages) {                                  // 32 k more: two quarters
+        if (half) {                                           // 32 k more: two quarters
             wait_loads_and_sync<0>();
             for (uint32_t ks = 0; ks < 2; ++ks) {
                 read_frags(cur, a_place(ks), w_place(ks), f0);
@@ -233,7 +256,7 @@ void gemm_fp8_kernel(Fp8Args ga) {
                 }
             }
         }
-        for (uint32_t i = stages; i < (stages_k + TEAMS - 1) / TEAMS; ++i) wait_loads_and_sync<0>();   // teams wait for each other
+        for (uint32_t i = stages; i < slots; ++i) wait_loads_and_sync<0>();   // teams wait for each other
         wait_loads_and_sync<0>();                             // nobody reads a stage any more
     };
 
@@ -242,10 +265,7 @@ void gemm_fp8_kernel(Fp8Args ga) {
     float *parts = reinterpret_cast<float *>(tops + 64);
     static_assert(4 * (TEAMS * WN * BM + 64 + (TEAMS - 1) * BM * BN) <= TEAMS * S * static_cast<int>(kStage), "fits the stages");
     compute(BoolTag<false>{});
-    bool bad = false;                                         // one row of every column tells
-#pragma unroll
-    for (int ni = 0; ni < TN; ++ni) bad = bad || acc[0][ni][0] != acc[0][ni][0];
-    const bool mine = __any(bad);
+    const bool mine = holds_nan();
     if (lane == 0) tops[team * NW + wave] = mine ? 1u : 0u;
     __syncthreads();
     uint32_t any_top = 0;

@@ -44,6 +44,11 @@ __device__ __forceinline__ void wait_loads_and_sync() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LATER) : "memory");
 }
 
+// A barrier that waits for this wave's LDS accesses and leaves its loads in flight.
+__device__ __forceinline__ void sync_lds() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // The ring of S stages: waits for stage j of `total` when up to S - 1 of them have been asked for; PER = loads per stage.
 template <int S, int PER>
 __device__ __forceinline__ void wait_stage(uint32_t j, uint32_t total) {

@@ -235,3 +235,26 @@ def test_top_codes_in_some_tiles_only(shape):
     assert np.array_equal(run_gemm(synth.to_bf16_bits(A.ravel()), packed, gf, None, M, N, K), W.reshape(K, N)[pick])
     got = run_gemm_dx(synth.to_bf16_bits(A.ravel()), packed, gf, None, M, K, N)
     assert np.array_equal(got, W.reshape(N, K)[:, pick].T)
+
+
+@pytest.mark.parametrize("where", ["early", "late", "everywhere"])
+@pytest.mark.parametrize("shape", [(3584, 3584, 2976), (7936, 1024, 1056), (1536, 4352, 1312), (1280, 2944, 1056), (256, 2816, 1056), (256, 128, 1056)])
+def test_top_codes_along_a_long_contraction(shape, where):
+    """The large tiles (256 x 256 and both of 128 x 256, the first three shapes) look for top codes after an eighth of the steps too and stop
+    there; whether they do, find one at the end, or find none, every weight has its exact value."""
+    of, gf = pair(4, 3)
+    M, N, K = shape
+    A = np.zeros((M, K), np.float32)
+    pick = (np.arange(M) * 7 + 3) % K
+    A[np.arange(M), pick] = 1.0
+    A = synth.to_bf16_bits(A.ravel())
+    codes = ((np.arange(K * N, dtype=np.int64) * 37 + 11) % 254).astype(np.uint32)
+    codes = np.where(codes >= 127, codes + 1, codes)
+    rows = {"early": slice(3, 11, 7), "late": slice(K - 8, K, 7), "everywhere": slice(0, K, 97)}[where]
+    for trans in (False, True):                             # stored [K x N], or [N x K] for the input gradient
+        W = codes.reshape(N, K).T.copy() if trans else codes.reshape(K, N).copy()
+        W[rows, 5::1408] = 0x7F
+        W[rows, N - 1] = 0xFF
+        packed = orc.pack(np.ascontiguousarray(W.T if trans else W).ravel(), 8)
+        got = run_gemm_dx(A, packed, gf, None, M, K, N) if trans else run_gemm(A, packed, gf, None, M, N, K)
+        assert np.array_equal(got, orc.decode(np.ascontiguousarray(W).ravel(), of).reshape(K, N)[pick])
