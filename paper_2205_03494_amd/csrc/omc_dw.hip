@@ -37,6 +37,13 @@ static uint32_t gradient_room(uint32_t bits, uint32_t M, uint32_t N, uint32_t K)
     return bits == 8 && sp == 1 ? 0u : sp;
 }
 
+// Host only, not part of the interface: which kernels a call of these sizes takes, 10000 for the one-kernel route + 100 * tile + splits.
+extern "C" uint32_t omc_internal_dw_route(uint32_t bits, uint32_t M, uint32_t N, uint32_t K) {
+    const uint32_t room = gradient_room(bits, M, N, K);
+    const bool one_kernel = bits == 8 && dw_one_kernel_is_faster(M, N, K, room);
+    return (one_kernel ? 10000u : 0u) + dw_tile_and_splits(M, N, K, room, !one_kernel);
+}
+
 int launch_dw_update(const uint16_t *X, const uint16_t *dY, void *codes, const FmtParams &fp, float *sb, int use_pvt,
                      float *state0, float *state1, const omc_opt &opt, float *dW_out, uint32_t M, uint32_t N,
                      uint32_t K, void *ws, void *stream) {

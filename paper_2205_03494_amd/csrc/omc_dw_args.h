@@ -24,6 +24,8 @@ int launch_dw_product(const DwArgs &a, float *partials, uint32_t room, uint32_t 
 // gradient the workspace holds, 0 or more; none is written.
 int launch_dw_one_kernel(const DwArgs &a, uint32_t room, int opt_kind, uint32_t *nparts, hipStream_t st);
 bool dw_one_kernel_is_faster(uint32_t M, uint32_t N, uint32_t K, uint32_t room);
+// 100 * tile + splits of a route.
+uint32_t dw_tile_and_splits(uint32_t M, uint32_t N, uint32_t K, uint32_t room, bool parked);
 
 // Second kernel: adds them up and runs the cycle; one launcher per optimizer.
 int launch_dw_update_sgd(const DwArgs &a, hipStream_t st);

@@ -25,7 +25,7 @@ struct ProductArgs {
     const uint16_t *X, *dY;
     float *partials;                     // [nsplit][K][N]
     uint32_t N, K, steps, nsplit;        // steps of 32 rows in all
-    uint32_t tiles_k, tiles_n;
+    uint32_t tiles_k, tiles_n, group_rows;
 };
 
 // Epilogue of the one-kernel route on a tile [ROWS][COLS] of the gradient in LDS, by all THREADS of the workgroup.
@@ -99,7 +99,7 @@ void dw_product_kernel(ProductArgs pa, DwArgs a) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
     const uint32_t N = pa.N, K = pa.K;
     uint32_t k0, n0;
-    tile_of_block<BK == 256 ? 2 : 8>(pa.tiles_k, pa.tiles_n, k0, n0);
+    tile_of_block(pa.group_rows, pa.tiles_k, pa.tiles_n, k0, n0);
     k0 *= BK;
     n0 *= BN;
     // this workgroup's steps, and its teams' shares of them: team t takes t, t + TEAMS, ...
@@ -262,12 +262,22 @@ static constexpr GemmTile kProductTiles[] = {
     {64, 64, 1, 4, 3.2, 0.13, 0.126, 0.0},  {64, 64, 2, 2, 1.0, 0.20, 0.215, 3.0},  {64, 64, 4, 1, 1.0, 0.40, 0.46, 3.0},
 };
 
+// What the one-kernel route's epilogue takes, in us per workgroup of a compute unit, under momentum (under SGD 0.6 of it, under
+// Adam 2: the sizes alone decide, so that the gradient's bits depend on them alone).
+static constexpr double kEpilogue[] = {13.7, 6.9, 9.3, 2.0, 1.5, 4.0};
+
 // The tile, number of splits and estimated time (us) of a product, by the estimate that pick_tile makes, over any number of splits up
 // to what the workspace has room for, or none.  The contraction is cut into at least `room` parts, by splits and teams together:
 // so that no fp32 sum runs over more products than M / room, which keeps its error where a workspace of that size puts it (2e-7 for 4096
 // products, 3e-7 for 8192).  A split costs its partial sums, written here and read by the update (4 bytes each way at 5 TB/s, half of the
 // writing covered).  8192 rows, 4096 x 1024 weights: two splits of 256 x 128 by two teams 71, one of 128 x 128 by two teams 78, one
 // of 128 x 128 81, four of 256 x 128 80, 64 x 64 124 - 133.  2048 rows, 512 x 2048 weights: 10 with 64 x 64, 12 - 19 with the others.
+// On matrices of more than one 256 x 128 tile per compute unit that leave no room for partial sums, the epilogue, codes and state, is no
+// small part of the call and is counted.  Where a unit has one workgroup at a time nothing runs beside it; where it has several, half of
+// the shorter of epilogue and product passes under the longer one.  8-bit codes, 128 rows on 8192 x 8192 weights, SGD / momentum / Adam:
+// 96 / 142 / 250 with 128 x 128, 119 / 155 / 278 with 256 x 128 by two teams, which the products alone would choose, 125 / 162 / 271 with
+// 64 x 64.  (Smaller ones: over 100 random sizes the chosen tile is 3 % off the best one with and without it.)
+static bool fills_several_times(uint32_t N, uint32_t K) { return static_cast<uint64_t>(K) * N > 256ull * 256 * 128; }
 struct ProductChoice {
     int tile;
     uint32_t splits;
@@ -284,15 +294,39 @@ static ProductChoice choose_product(uint32_t M, uint32_t N, uint32_t K, uint32_t
         if (tiles > 0x7fffffffull) continue;
         for (uint32_t splits = 1; splits <= most_splits && splits <= all_steps; ++splits) {
             if (splits * t.teams < room) continue;
-            const double per_unit = static_cast<double>(tiles * splits) / 256.0;
-            const double alone = t.step * static_cast<double>((tiles * splits + 256ull * t.resident - 1) / (256ull * t.resident));
+            const uint64_t count = tiles * splits;
+            const double per_unit = static_cast<double>(count) / 256.0;
+            const double alone = t.step * static_cast<double>((count + 256ull * t.resident - 1) / (256ull * t.resident));
             const double busy = t.loaded * per_unit;
             const uint32_t steps = ((all_steps + splits - 1) / splits + t.teams - 1) / t.teams;
-            const double us = t.base + t.stores * per_unit + steps * (alone > busy ? alone : busy) + (parked ? splits * 6.0 * K * N / 5e6 : 0.0);
+            const double product = steps * (alone > busy ? alone : busy);
+            double us = t.base + t.stores * per_unit;
+            if (room > 0 || !fills_several_times(N, K)) {
+                us += product;
+                if (parked) us += splits * 6.0 * K * N / 5e6;
+            } else {
+                const double epilogue = kEpilogue[i] * (t.resident > 1 ? per_unit : static_cast<double>((count + 255) / 256));
+                const double longer = product > epilogue ? product : epilogue, shorter = product > epilogue ? epilogue : product;
+                us += longer + (t.resident > 1 ? 0.5 : 1.0) * shorter;
+            }
             if (best.tile < 0 || us < best.us) best = ProductChoice{i, splits, us};
         }
     }
     return best;
+}
+
+// Tile rows in a group of the tile order.  For the operands' sake eight, or two of the 256-row tiles.  The epilogue also moves codes and state
+// of the tiles that are under way at one time, and with eight tile rows of a matrix whose rows are a multiple of 8 KB long these lie in
+// a part of every such stretch only, as if in a part of the memory's channels: 32 rows on 4096 x 4096 weights, momentum 48 us, Adam 65 - 99
+// depending on where the buffers lie.  Where the product is short enough not to miss the shared operands, the tiles under way on a die
+// therefore cover whole rows of the weights: 38 and 65 us; 1024 rows 73 -> 65 and 97 - 121 -> 93.  (Smaller matrices have all their tiles under
+// way at once; rows of 5120 weights take 108 us under Adam as it is, 115 so.)
+static uint32_t tile_group(const GemmTile &t, uint32_t tiles_n, uint32_t M, uint32_t N, uint32_t K, bool moves_state) {
+    const uint32_t usual = t.bm == 256 ? 2 : 8;
+    if (!moves_state || t.bn < 128 || M > 1024 || N % 2048 != 0 || !fills_several_times(N, K)) return usual;
+    const uint32_t whole = 32 * t.resident / tiles_n;         // 32 compute units on a die
+    if (whole < 2) return M <= 256 ? 1 : usual;
+    return whole < usual ? whole : usual;
 }
 
 template <int MODE>
@@ -300,6 +334,7 @@ static int launch_product(int tile, ProductArgs pa, const DwArgs &a, hipStream_t
     if (tile < 0) return static_cast<int>(hipErrorInvalidValue);
     pa.tiles_k = pa.K / kProductTiles[tile].bm;
     pa.tiles_n = pa.N / kProductTiles[tile].bn;
+    pa.group_rows = tile_group(kProductTiles[tile], pa.tiles_n, 32 * pa.steps, pa.N, pa.K, MODE >= kStepMomentum);
     const dim3 grid(pa.tiles_k * pa.tiles_n, pa.nsplit);
     switch (tile) {
         case 0: dw_product_kernel<2, 2, 4, 2, 2, 3, 2, MODE><<<grid, dim3(512), 0, st>>>(pa, a); break;
@@ -315,7 +350,7 @@ static int launch_product(int tile, ProductArgs pa, const DwArgs &a, hipStream_t
 int launch_dw_product(const DwArgs &a, float *partials, uint32_t room, uint32_t *nsplit, hipStream_t st) {
     const ProductChoice c = choose_product(a.M, a.N, a.K, room, true);
     *nsplit = c.splits;
-    return launch_product<kPark>(c.tile, ProductArgs{a.X, a.dY, partials, a.N, a.K, a.M / 32, c.splits, 0, 0}, a, st);
+    return launch_product<kPark>(c.tile, ProductArgs{a.X, a.dY, partials, a.N, a.K, a.M / 32, c.splits, 0, 0, 0}, a, st);
 }
 
 // What the update kernel costs besides reading the partial sums: its launch, and codes and state, which the one-kernel route's
@@ -326,10 +361,15 @@ bool dw_one_kernel_is_faster(uint32_t M, uint32_t N, uint32_t K, uint32_t room) 
     return one.tile >= 0 && (two.tile < 0 || one.us <= two.us + 3.0 + 6.0 * K * N / 5e6);
 }
 
+uint32_t dw_tile_and_splits(uint32_t M, uint32_t N, uint32_t K, uint32_t room, bool parked) {
+    const ProductChoice c = choose_product(M, N, K, room, parked);
+    return static_cast<uint32_t>(c.tile) * 100 + c.splits;
+}
+
 int launch_dw_one_kernel(const DwArgs &a, uint32_t room, int opt_kind, uint32_t *nparts, hipStream_t st) {
     const ProductChoice c = choose_product(a.M, a.N, a.K, room, false);
     if (c.tile >= 0) *nparts = (a.K / kProductTiles[c.tile].bm) * (a.N / kProductTiles[c.tile].bn);
-    const ProductArgs pa{a.X, a.dY, nullptr, a.N, a.K, a.M / 32, 1, 0, 0};
+    const ProductArgs pa{a.X, a.dY, nullptr, a.N, a.K, a.M / 32, 1, 0, 0, 0};
     if (opt_kind == OMC_SGD) return launch_product<kStepSgd>(c.tile, pa, a, st);
     if (opt_kind == OMC_MOMENTUM) return launch_product<kStepMomentum>(c.tile, pa, a, st);
     return launch_product<kStepAdam>(c.tile, pa, a, st);

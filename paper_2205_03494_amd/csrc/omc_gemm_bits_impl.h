@@ -104,7 +104,7 @@ void gemm_bits_kernel(BitsArgs ga) {
     const uint32_t N = ga.N, K = ga.K;
     const FmtParams fp = ga.fp;
     uint32_t m0, n0;
-    tile_of_block<BM == 256 ? 4 : 8>(ga.tiles_m, ga.tiles_n, m0, n0);
+    tile_of_block(BM == 256 ? 4 : 8, ga.tiles_m, ga.tiles_n, m0, n0);
     m0 *= BM;
     n0 *= BN;
 

@@ -88,7 +88,7 @@ void gemm_fp8_kernel(Fp8Args ga) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
     const uint32_t N = ga.N, K = ga.K;
     uint32_t m0, n0;
-    tile_of_block<BM == 256 ? 4 : 8>(ga.tiles_m, ga.tiles_n, m0, n0);
+    tile_of_block(BM == 256 ? 4 : 8, ga.tiles_m, ga.tiles_n, m0, n0);
     m0 *= BM;
     n0 *= BN;
 

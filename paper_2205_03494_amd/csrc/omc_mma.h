@@ -93,15 +93,14 @@ inline int pick_tile(const GemmTile (&tiles)[COUNT], uint32_t M, uint32_t N, uin
 }
 
 // Tile of this workgroup in a grid of tiles_m x tiles_n (one-dimensional launch).  Workgroups go to the 8 dies in turn and
-// each die has an L2 of its own, so every die gets a contiguous run of the tile order, in which groups of ROWS tile rows
+// each die has an L2 of its own, so every die gets a contiguous run of the tile order, in which groups of `group_rows` tile rows
 // share their columns.  The tiles of a die at one time should need as many bytes of the one operand as of the other: eight rows for
 // tiles whose two sides weigh the same, fewer for 256-row tiles (256 x 256 of bf16 by bytes, 8192 x 4096 x 1024: 70 us with 4 rows, 79
 // with 8, 82 with 16; 11-bit codes 82, 89, 93; weight gradient in 256 x 128, 8192 rows, 4096 x 1024: 71 with 2, 72 with 4, 75 with 8).
-template <uint32_t ROWS>
-__device__ __forceinline__ void tile_of_block(uint32_t tiles_m, uint32_t tiles_n, uint32_t &tm, uint32_t &tn) {
+__device__ __forceinline__ void tile_of_block(uint32_t group_rows, uint32_t tiles_m, uint32_t tiles_n, uint32_t &tm, uint32_t &tn) {
     const uint32_t total = tiles_m * tiles_n, q = total / 8, r = total % 8, die = blockIdx.x % 8;
     const uint32_t id = die * q + (die < r ? die : r) + blockIdx.x / 8;
-    const uint32_t rows = tiles_m < ROWS ? tiles_m : ROWS;
+    const uint32_t rows = tiles_m < group_rows ? tiles_m : group_rows;
     const uint32_t group = id / (rows * tiles_n), first = group * rows;
     const uint32_t height = tiles_m - first < rows ? tiles_m - first : rows;
     const uint32_t in = id - group * rows * tiles_n;

@@ -396,3 +396,20 @@ def test_reselect_plan_and_transport_reject_bad_arguments():
     assert pk(msg=0x200008) == 4
     bad = po.copy(); bad[200] ^= 1
     assert pk(ph=bad.ctypes.data) == 8
+
+
+def dw_route(bits, M, N, K):
+    """(one kernel?, tile, splits) of a weight-gradient call; tiles 256 x 128 by two teams, 128 x 128 by one and two, 64 x 64 by one, two, four."""
+    fn = C.CDLL(omc.LIB_PATH).omc_internal_dw_route
+    fn.restype, fn.argtypes = C.c_uint32, [C.c_uint32] * 4
+    r = fn(bits, M, N, K)
+    return r >= 10000, r % 10000 // 100, r % 100
+
+
+def test_weight_gradient_tile_counts_its_epilogue():
+    """Large weight matrices, few rows: the update is most of the work, and 128 x 128 tiles, two on a compute unit, pass it fastest."""
+    for K, N in ((4096, 4096), (8192, 8192), (5120, 5120), (2048, 8192), (8192, 2048), (5120, 4096)):
+        for M in (32, 128, 256, 512, 1024):
+            assert dw_route(8, M, N, K) == (True, 1, 1), (M, N, K)
+    assert dw_route(8, 8192, 1024, 4096) == (True, 2, 1)      # a long contraction: two teams to a tile
+    assert dw_route(11, 8192, 1024, 4096) == (False, 0, 2)    # other widths leave partial sums
