@@ -5,7 +5,7 @@
 
 namespace omc {
 
-constexpr int kMetaThreads = 1024;
+constexpr int kMetaThreads = 1024;   // at most: one wave for every 64 variables up to there
 
 // One workgroup: walks the plan's variable table in order, gives every variable its 16-byte aligned place
 // in the payload (a running sum of the sizes), writes the message's variable table and (s, b) table, and
@@ -14,13 +14,13 @@ __global__ __launch_bounds__(kMetaThreads) void transport_meta_kernel(const uint
                                                                        const float *__restrict__ sb_table,
                                                                        uint8_t *__restrict__ msg, TransportHeader th) {
     __shared__ uint64_t wave_sum[kMetaThreads / 64];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, threads = blockDim.x, waves = threads / 64;
     const PlanVar *vars = reinterpret_cast<const PlanVar *>(plan + var_off);
     TransportVar *out = reinterpret_cast<TransportVar *>(msg + sizeof(TransportHeader));
     float *sb_out = reinterpret_cast<float *>(msg + th.sb_off);
     uint64_t carry = 0;                                         // the same in every thread
     uint64_t hash_sum = 0;
-    for (uint32_t base = 0; base < th.nvars; base += kMetaThreads) {
+    for (uint32_t base = 0; base < th.nvars; base += threads) {
         const uint32_t i = base + tid;
         uint64_t bytes = 0;
         PlanVar pv{};
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kMetaThreads) void transport_meta_kernel(const uint
         if (lane == 63) wave_sum[wave] = upto;
         __syncthreads();
         uint64_t total = 0;                                      // ... and over the waves before it
-        for (uint32_t w = 0; w < kMetaThreads / 64; ++w) {
+        for (uint32_t w = 0; w < waves; ++w) {
             if (w == wave) upto += carry + total;
             total += wave_sum[w];
         }
@@ -63,20 +63,27 @@ __global__ __launch_bounds__(kMetaThreads) void transport_meta_kernel(const uint
     if (lane == 0) wave_sum[wave] = hash_sum;
     __syncthreads();
     hash_sum = 0;
-    for (uint32_t w = 0; w < kMetaThreads / 64; ++w) hash_sum += wave_sum[w];
+    for (uint32_t w = 0; w < waves; ++w) hash_sum += wave_sum[w];
     if (tid == 0) {
         th.checksum = transport_header_hash(th, hash_sum);
         *reinterpret_cast<TransportHeader *>(msg) = th;
     }
 }
 
-// The payload in runs of 32 KB, one workgroup each: eight 16-byte pieces per thread, all in flight together.  A run is found in the
-// message's own table, which the meta kernel has written: the threads look at one entry in every `stride`, then at the
-// entries between, two dependent loads.  A run that lies in one variable is copied by all threads; in the others each wave
-// takes one variable after the other.  Bound by memory (both streams are touched once and carry the hint): 190.7 MB of 599 variables
-// 67 us; with 64 workgroups per variable, whatever its size, and four pieces per thread 88 us.
+// The payload in runs of 32 KB (of less, down to 2 KB, where that would be fewer than 1024), one workgroup each: up to eight 16-byte pieces
+// per thread, all in flight together.  A run is found in the message's own table, which the meta kernel has written: of a set of up to 256
+// variables every thread takes one entry to LDS; of a larger one the threads look at one entry in every `stride`, then at the entries
+// between, two dependent loads.  A run that lies in one variable is copied by all threads; in the others each wave takes one variable
+// after the other.  Large messages are bound by memory (both streams are touched once and carry the hint): 190.7 MB of 599 variables 60 us; with
+// 64 workgroups per variable, whatever its size, and four pieces per thread 71 us.  Small ones are bound by dependent loads, above all
+// by the variables that a wave takes one after the other: 100 variables of 1000 11-bit codes 5.8 us, 11.2 with runs of 32 KB and a table
+// made by 1024 threads; 3000 variables of 300 codes 18 us, 33 so.
 constexpr uint32_t kPackThreads = 256, kPackBatch = 8;
-constexpr uint64_t kPackRun = 16ull * kPackThreads * kPackBatch;
+constexpr uint64_t kPackLongest = 16ull * kPackThreads * kPackBatch, kPackShortest = 2048, kPackRuns = 1024;
+inline uint64_t pack_run(uint64_t payload_bytes) {
+    const uint64_t even = (payload_bytes / kPackRuns + kPackShortest - 1) / kPackShortest * kPackShortest;
+    return even < kPackShortest ? kPackShortest : even > kPackLongest ? kPackLongest : even;
+}
 
 // pieces [p0, p1) of a variable by THREADS threads, `t` being this one; `bytes` is the variable's size in the arena
 template <uint32_t THREADS>
@@ -103,50 +110,63 @@ __device__ __forceinline__ void pack_pieces(const uint8_t *src8, uint8_t *dst8, 
 
 __global__ __launch_bounds__(kPackThreads) void transport_pack_kernel(const uint8_t *__restrict__ plan, uint64_t var_off,
                                                                       const uint8_t *__restrict__ arena, uint8_t *__restrict__ msg,
-                                                                      uint64_t payload_off, uint64_t payload_bytes, uint32_t nvars) {
+                                                                      uint64_t payload_off, uint64_t payload_bytes, uint32_t nvars,
+                                                                      uint64_t run) {
     const PlanVar *vars = reinterpret_cast<const PlanVar *>(plan + var_off);
     const TransportVar *tvs = reinterpret_cast<const TransportVar *>(msg + sizeof(TransportHeader));
     const uint32_t tid = threadIdx.x;
-    const uint64_t lo = static_cast<uint64_t>(blockIdx.x) * kPackRun, hi = lo + kPackRun < payload_bytes ? lo + kPackRun : payload_bytes;
+    const uint64_t lo = static_cast<uint64_t>(blockIdx.x) * run, hi = lo + run < payload_bytes ? lo + run : payload_bytes;
+    struct Entry {
+        uint64_t to, from, bytes;                             // place in the payload, place in the arena, size there
+    };
+    auto look_up = [&](uint32_t i) {
+        const PlanVar &pv = vars[i];
+        return Entry{tvs[i].payload_offset, pv.data_offset, (pv.flags & OMC_VAR_QUANTIZED) ? pv.total_dwords * 4 : 4 * pv.n};
+    };
+    __shared__ Entry table[kPackThreads];                     // of a set that it holds: one round trip for all of it
+    const bool in_table = nvars > 1 && nvars <= kPackThreads;
+    auto entry = [&](uint32_t i) { return in_table ? table[i] : look_up(i); };
     // the last variable that starts at or before lo (variable 0 starts at 0)
     uint32_t first = 0;
-    for (uint32_t span = nvars; span > 1;) {
+    if (in_table) {
+        Entry mine{};
+        if (tid < nvars) table[tid] = mine = look_up(tid);
+        first = static_cast<uint32_t>(__syncthreads_count(tid < nvars && mine.to <= lo)) - 1;   // offsets ascend
+    }
+    for (uint32_t span = in_table ? 1 : nvars; span > 1;) {
         const uint32_t stride = (span + kPackThreads - 1) / kPackThreads, at = first + tid * stride;
         const bool below = tid * stride < span && tvs[at].payload_offset <= lo;
-        const uint32_t steps = static_cast<uint32_t>(__syncthreads_count(below)) - 1;   // offsets ascend; entry `first` is below
+        const uint32_t steps = static_cast<uint32_t>(__syncthreads_count(below)) - 1;   // entry `first` is below
         const uint32_t rest = span - steps * stride;
         first += steps * stride;
         span = rest < stride ? rest : stride;
     }
-    auto bytes_of = [&](const PlanVar &pv) { return (pv.flags & OMC_VAR_QUANTIZED) ? pv.total_dwords * 4 : 4 * pv.n; };
-    const PlanVar pv = to_scalar_regs(vars[first]);
-    const uint64_t off = to_scalar_regs(tvs[first].payload_offset);
+    const Entry e = to_scalar_regs(entry(first));
     uint8_t *payload = msg + payload_off;
-    if (off + (bytes_of(pv) + 15) / 16 * 16 >= hi) {
-        pack_pieces<kPackThreads>(arena + pv.data_offset, payload + off, bytes_of(pv), (lo - off) / 16, (hi - off) / 16, tid);
+    if (e.to + (e.bytes + 15) / 16 * 16 >= hi) {
+        pack_pieces<kPackThreads>(arena + e.from, payload + e.to, e.bytes, (lo - e.to) / 16, (hi - e.to) / 16, tid);
         return;
     }
     for (uint32_t i = first + (tid >> 6); i < nvars; i += kPackThreads / 64) {
-        const uint64_t o = to_scalar_regs(tvs[i].payload_offset);
-        if (o >= hi) return;
-        const PlanVar v = to_scalar_regs(vars[i]);
-        const uint64_t end = o + (bytes_of(v) + 15) / 16 * 16;
-        pack_pieces<64>(arena + v.data_offset, payload + o, bytes_of(v), lo > o ? (lo - o) / 16 : 0, ((end < hi ? end : hi) - o) / 16, tid & 63u);
+        const Entry w = to_scalar_regs(entry(i));
+        if (w.to >= hi) return;
+        const uint64_t end = w.to + (w.bytes + 15) / 16 * 16;
+        pack_pieces<64>(arena + w.from, payload + w.to, w.bytes, lo > w.to ? (lo - w.to) / 16 : 0, ((end < hi ? end : hi) - w.to) / 16, tid & 63u);
     }
 }
 
 int launch_transport_pack(const PlanHeader *ph, const void *plan_dev, const void *arena, const float *sb_table,
                           void *msg_dev, const TransportHeader &th, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    transport_meta_kernel<<<dim3(1), dim3(kMetaThreads), 0, st>>>(static_cast<const uint8_t *>(plan_dev), ph->var_off, sb_table,
+    transport_meta_kernel<<<dim3(1), dim3(ph->nvars < kMetaThreads ? (ph->nvars + 63) / 64 * 64 : kMetaThreads), 0, st>>>(static_cast<const uint8_t *>(plan_dev), ph->var_off, sb_table,
                                                                   static_cast<uint8_t *>(msg_dev), th);
     int rc = static_cast<int>(hipGetLastError());
     if (rc != 0) return rc;
-    const uint64_t runs = (th.payload_bytes + kPackRun - 1) / kPackRun;
+    const uint64_t run = pack_run(th.payload_bytes), runs = (th.payload_bytes + run - 1) / run;
     if (runs > 0x7fffffffull) return static_cast<int>(hipErrorInvalidValue);
     transport_pack_kernel<<<dim3(static_cast<uint32_t>(runs)), dim3(kPackThreads), 0, st>>>(
         static_cast<const uint8_t *>(plan_dev), ph->var_off, static_cast<const uint8_t *>(arena),
-        static_cast<uint8_t *>(msg_dev), th.payload_off, th.payload_bytes, ph->nvars);
+        static_cast<uint8_t *>(msg_dev), th.payload_off, th.payload_bytes, ph->nvars, run);
     return static_cast<int>(hipGetLastError());
 }
 

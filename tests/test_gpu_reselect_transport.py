@@ -253,11 +253,12 @@ def test_message_is_validated_on_open():
     assert e.value.status == 3
 
 
-@pytest.mark.parametrize("count", [1, 2, 255, 257, 1030])
+@pytest.mark.parametrize("count", [1, 2, 64, 65, 255, 256, 257, 1030])
 def test_transport_payload_of_many_sizes(count):
-    """Runs of 32 KB of the payload that start and end inside variables, hold dozens of small ones or lie in one large one, and sets of
-    one variable up to more than 1024 (the table's scan takes a second round); fp32 sizes that are no multiple of four, whose
-    padding in the message is zero whatever the arena holds there."""
+    """Runs of the payload (2 KB of a small one, 4 KB of 1030 variables) that start and end inside variables, hold several small ones or lie
+    in one large one; sets of one variable up to more than 1024, around the 64 variables of a wave of the table's scan, the 256 that the copy holds in
+    LDS and the 1024 after which the scan takes a second round; fp32 sizes that are no multiple of four, whose padding in the message
+    is zero whatever the arena holds there."""
     rng = np.random.default_rng(count)
     ns = rng.integers(1, 3000, count)
     ns[rng.random(count) < 0.02] = 70001
