@@ -413,3 +413,25 @@ def test_weight_gradient_tile_counts_its_epilogue():
             assert dw_route(8, M, N, K) == (True, 1, 1), (M, N, K)
     assert dw_route(8, 8192, 1024, 4096) == (True, 2, 1)      # a long contraction: two teams to a tile
     assert dw_route(11, 8192, 1024, 4096) == (False, 0, 2)    # other widths leave partial sums
+
+
+def test_binding_works_without_torchs_private_stream_lookup(monkeypatch):
+    """The current stream's raw handle comes from a function that is not part of torch's public interface."""
+    import importlib.util
+    import types
+
+    import torch
+
+    class Current:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: Current)
+    without = types.SimpleNamespace(**{k: getattr(torch._C, k) for k in dir(torch._C) if not k.startswith("__") and k != "_cuda_getCurrentRawStream"})
+    monkeypatch.setattr(torch, "_C", without)
+    spec = importlib.util.spec_from_file_location("omc_without_raw_stream", omc.__file__)
+    module = importlib.util.module_from_spec(spec)
+    monkeypatch.setitem(__import__("sys").modules, spec.name, module)
+    spec.loader.exec_module(module)
+    assert module._stream(None) == 0x1234
+    assert module._stream(types.SimpleNamespace(cuda_stream=7)) == 7
