@@ -9,6 +9,10 @@
 
 namespace omc {
 
+// Host only, not part of the interface: index of the tile that a product of these sizes takes (columns N of the result, contraction K), in
+// the table of the FP8 kernel or of the other formats' kernel.
+extern "C" int omc_internal_gemm_tile(int fp8, uint32_t M, uint32_t N, uint32_t K) { return fp8 ? gemm_fp8_tile(M, N, K) : pick_tile(kBitsTiles, M, N, K); }
+
 // C[M x N] = A[M x K] * W (trans == 0, W packed as [K x N]) or A * W^T (trans != 0, W packed as [N x K])
 int launch_dequant_gemm(const uint16_t *A, const void *codes, const FmtParams &fp, const float *sb, float *C,
                         uint32_t M, uint32_t N, uint32_t K, int trans, void *stream) {

@@ -308,8 +308,10 @@ static int launch_tile(int which, const Fp8Args &ga, uint32_t tiles, hipStream_t
     return static_cast<int>(hipGetLastError());
 }
 
+int gemm_fp8_tile(uint32_t M, uint32_t N, uint32_t K) { return pick_tile(kFp8Tiles, M, N, K); }
+
 int launch_gemm_fp8(const uint16_t *A, const void *codes, const float *sb, float *C, uint32_t M, uint32_t N, uint32_t K, int trans, hipStream_t st) {
-    const int which = pick_tile(kFp8Tiles, M, N, K);
+    const int which = gemm_fp8_tile(M, N, K);
     if (which < 0) return static_cast<int>(hipErrorInvalidValue);
     const GemmTile &t = kFp8Tiles[which];
     const Fp8Args ga{A, static_cast<const uint8_t *>(codes), sb, C, N, K, M / t.bm, N / t.bn};

@@ -1,4 +1,6 @@
 """Helpers for the GPU parity tests: run the same seeded inputs through libomc and the oracle."""
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -13,6 +15,23 @@ def to_dev(a):
 def pair(E, M, bias=None):
     """The same format for both sides."""
     return orc.Format(E, M, bias), omc.fmt(E, M, omc.OMC_BIAS_DEFAULT if bias is None else bias)
+
+
+def gemm_tile(EM, M, N, K):
+    """Index of the tile that A [M x K] times K x N (or transposed N x K) weights takes: 256 x 256, 128 x 256 by four waves and by eight,
+    128 x 128, 64 x 128, 64 x 64 by one, two and four teams of waves for S1E4M3; 256 x 256, 128 x 256, 128 x 128, 64 x 64 by one, two, four
+    for the other formats."""
+    fn = omc._lib.omc_internal_gemm_tile
+    fn.restype, fn.argtypes = C.c_int, [C.c_int] + [C.c_uint32] * 3
+    return fn(int(tuple(EM) == (4, 3)), M, N, K)
+
+
+def dw_route(bits, M, N, K):
+    """(one kernel?, tile, splits) of a weight-gradient call; tiles 256 x 128 by two teams, 128 x 128 by one and two, 64 x 64 by one, two, four."""
+    fn = omc._lib.omc_internal_dw_route
+    fn.restype, fn.argtypes = C.c_uint32, [C.c_uint32] * 4
+    r = fn(bits, M, N, K)
+    return r >= 10000, r % 10000 // 100, r % 100
 
 
 def bits_equal(a, b):

@@ -9,6 +9,7 @@ import pytest
 
 from oracle import omc_oracle as orc
 from paper_2205_03494_amd import omc, synth
+from gpu_util import dw_route, gemm_tile
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -398,14 +399,6 @@ def test_reselect_plan_and_transport_reject_bad_arguments():
     assert pk(ph=bad.ctypes.data) == 8
 
 
-def dw_route(bits, M, N, K):
-    """(one kernel?, tile, splits) of a weight-gradient call; tiles 256 x 128 by two teams, 128 x 128 by one and two, 64 x 64 by one, two, four."""
-    fn = C.CDLL(omc.LIB_PATH).omc_internal_dw_route
-    fn.restype, fn.argtypes = C.c_uint32, [C.c_uint32] * 4
-    r = fn(bits, M, N, K)
-    return r >= 10000, r % 10000 // 100, r % 100
-
-
 def test_weight_gradient_tile_counts_its_epilogue():
     """Large weight matrices, few rows: the update is most of the work, and 128 x 128 tiles, two on a compute unit, pass it fastest."""
     for K, N in ((4096, 4096), (8192, 8192), (5120, 5120), (2048, 8192), (8192, 2048), (5120, 4096)):
@@ -435,3 +428,20 @@ def test_binding_works_without_torchs_private_stream_lookup(monkeypatch):
     spec.loader.exec_module(module)
     assert module._stream(None) == 0x1234
     assert module._stream(types.SimpleNamespace(cuda_stream=7)) == 7
+
+
+def test_gpu_tests_reach_every_tile():
+    """The tiles are chosen by measured constants; the sizes in the GPU tests have to reach each of them, whatever the constants."""
+    import test_gpu_dw
+    import test_gpu_gemm
+
+    for EM, tiles in (((4, 3), 8), ((3, 7), 6)):
+        reached = {gemm_tile(EM, *shape) for shape in test_gpu_gemm.HALF_STEP_SHAPES[EM]}
+        assert reached == set(range(tiles)), (EM, reached)
+        assert all(K % 64 == 32 for _, _, K in test_gpu_gemm.HALF_STEP_SHAPES[EM])
+    assert {gemm_tile((4, 3), *shape) for shape in test_gpu_gemm.TOP_CODE_SHAPES} == set(range(8))
+    routes = {dw_route(1 + sum(EM), *shape) for EM, shape in test_gpu_dw.ROUTES}
+    assert {tile for one, tile, _ in routes if one} == set(range(6))
+    assert {tile for one, tile, _ in routes if not one} == set(range(6))
+    assert {splits for one, _, splits in routes if not one} == set(range(1, 9))
+    assert any(tile == 0 and splits > 1 for one, tile, splits in routes if not one)

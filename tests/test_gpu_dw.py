@@ -11,7 +11,7 @@ import torch
 
 from oracle import omc_oracle as orc
 from paper_2205_03494_amd import omc, synth
-from gpu_util import bits_equal, pair, to_dev
+from gpu_util import bits_equal, dw_route, pair, to_dev
 from test_gpu_gemm import check
 
 pytestmark = pytest.mark.gpu
@@ -194,3 +194,24 @@ def test_epilogue_combines_its_waves_sums_without_rounding():
     assert sb.tolist() == [1.0, 0.125]                      # (half of the rows)
     assert np.array_equal(codes_d.cpu().numpy(), packed)
     assert bits_equal(sb_d.cpu().numpy(), sb), (sb_d.cpu().numpy(), sb)
+
+
+# in one kernel or through partial sums, tile, splits
+ROUTES = {
+    ((4, 3), (1024, 1408, 3840)): (True, 0, 1), ((4, 3), (96, 768, 4352)): (True, 1, 1), ((4, 3), (384, 896, 2816)): (True, 2, 1),
+    ((4, 3), (32, 2944, 256)): (True, 3, 1), ((4, 3), (32, 128, 256)): (True, 4, 1), ((4, 3), (2048, 128, 1024)): (True, 5, 1),
+    ((4, 3), (4096, 256, 4352)): (False, 0, 5), ((4, 3), (8192, 256, 4352)): (False, 1, 4), ((4, 3), (4096, 128, 4096)): (False, 2, 5),
+    ((4, 3), (4096, 128, 2048)): (False, 5, 3), ((3, 7), (4096, 256, 4352)): (False, 0, 5), ((3, 7), (96, 768, 4352)): (False, 1, 1),
+    ((3, 7), (384, 896, 2816)): (False, 2, 1), ((3, 7), (32, 2944, 256)): (False, 3, 1), ((3, 7), (4096, 128, 2048)): (False, 5, 3),
+    ((3, 7), (1024, 128, 256)): (False, 4, 2), ((3, 7), (2048, 128, 1280)): (False, 4, 3), ((3, 7), (2048, 128, 256)): (False, 4, 4),
+    ((3, 7), (4096, 128, 1024)): (False, 4, 5), ((3, 7), (4096, 128, 768)): (False, 4, 6), ((3, 7), (4352, 128, 512)): (False, 4, 7),
+    ((3, 7), (4096, 128, 256)): (False, 4, 8), ((3, 7), (8192, 4096, 1024)): (False, 0, 2),
+}
+
+
+@pytest.mark.parametrize("EM,shape,route", [(EM, shape, route) for (EM, shape), route in ROUTES.items()])
+def test_every_tile_in_both_routes_and_every_number_of_splits(EM, shape, route):
+    """Tiles of both routes, and one to eight partial sums, also such as cut the steps into runs of unequal length (3, 5, 6, 7) under two teams."""
+    M, N, K = shape
+    assert dw_route(1 + sum(EM), M, N, K) == route
+    run_case(EM, M, N, K, 1, 0.05, steps=1, rows=None if M * N * K <= 1 << 28 else (0, 16, K // 2 - 16, K - 16))

@@ -210,10 +210,17 @@ def test_every_code_width_half_steps_and_teams(EM, shape):
     assert both_directions(EM, M, N, K, np.arange(M), sb=np.array([0.75, 0.125], np.float32)) < 1e-5
 
 
-@pytest.mark.parametrize("EM", [(4, 3), (3, 7)])
-@pytest.mark.parametrize("shape", [(256, 256, 2080), (2304, 896, 544), (4096, 1024, 288), (4096, 2048, 96), (4096, 4096, 288), (8192, 1024, 2080)])
+HALF_STEP = [(256, 256, 2080), (2304, 896, 544), (4096, 1024, 288), (4096, 2048, 96), (4096, 4096, 288), (8192, 1024, 2080)]
+HALF_STEP_SHAPES = {                                        # every tile of the two dispatch tables
+    (4, 3): HALF_STEP + [(3584, 3584, 2976), (1536, 4352, 1312), (512, 4864, 544), (256, 2816, 224), (256, 128, 1056)],
+    (3, 7): HALF_STEP + [(2560, 3328, 1056), (1536, 4608, 1056), (512, 3968, 1056), (256, 1408, 1056)],
+}
+
+
+@pytest.mark.parametrize("EM,shape", [(EM, shape) for EM, shapes in HALF_STEP_SHAPES.items() for shape in shapes])
 def test_every_tile_size_ends_on_half_a_step(EM, shape):
-    """One shape per tile of the two dispatch tables, 64 x 64 by four teams up to 256 x 256, rows of every tile."""
+    """At least one shape per tile of the two dispatch tables (a test without a GPU holds that), 64 x 64 by four teams up to 256 x 256, rows of
+    every tile."""
     M, N, K = shape
     assert both_directions(EM, M, N, K, tile_sample_rows(M, seed=K, per_quarter=4)) < 1e-5
 
@@ -237,8 +244,12 @@ def test_top_codes_in_some_tiles_only(shape):
     assert np.array_equal(got, W.reshape(N, K)[:, pick].T)
 
 
+TOP_CODE_SHAPES = [(3584, 3584, 2976), (7936, 1024, 1056), (1536, 4352, 1312), (1280, 2944, 1056), (768, 2688, 1056), (512, 2816, 1056),
+                   (256, 2816, 1056), (256, 128, 1056)]     # every tile in turn
+
+
 @pytest.mark.parametrize("where", ["early", "late", "everywhere"])
-@pytest.mark.parametrize("shape", [(3584, 3584, 2976), (7936, 1024, 1056), (1536, 4352, 1312), (1280, 2944, 1056), (256, 2816, 1056), (256, 128, 1056)])
+@pytest.mark.parametrize("shape", TOP_CODE_SHAPES)
 def test_top_codes_along_a_long_contraction(shape, where):
     """The large tiles (256 x 256 and both of 128 x 256, the first three shapes) look for top codes after an eighth of the steps too and stop
     there; whether they do, find one at the end, or find none, every weight has its exact value."""
