@@ -388,7 +388,7 @@ size_t omc_dequant_gemm_workspace_bytes(uint32_t M);
  * Values of the format below 2^-126 (possible only with a bias near 127) may be flushed to zero by
  * the matrix cores.  S1E4M3 with bias 7 is converted by the hardware's FP8 instructions; a tile in which
  * the one code occurs that they read differently (all exponent and mantissa bits set, value 480) is computed
- * again without them, so that results are the same either way. */
+ * again with that code put right, so that results are the same either way. */
 omc_status omc_dequant_gemm(const uint16_t *A, const void *codes, omc_format f, const float *sb,
                             float *C, uint32_t M, uint32_t N, uint32_t K, void *ws, size_t ws_bytes,
                             void *stream);
@@ -435,7 +435,7 @@ size_t omc_dw_update_workspace_bytes(omc_format f, uint32_t M, uint32_t N, uint3
  * dword of codes) and the gradient never reaches memory; otherwise partial gradients pass through
  * the workspace once and a second kernel adds them and does the update.  Result: identical to
  * omc_step_update_recompress on this variable with dW_out as its gradient; the gradient's summation
- * order is fixed by the sizes alone, so repeated calls give identical bits. */
+ * order is fixed by the sizes and the code width alone, so repeated calls give identical bits. */
 omc_status omc_dw_update_recompress(const uint16_t *X, const uint16_t *dY, void *codes, omc_format f,
                                     float *sb, int use_pvt, float *state0, float *state1,
                                     const omc_opt *opt, float *dW_out, uint32_t M, uint32_t N, uint32_t K,

@@ -18,9 +18,10 @@ static size_t dw_fit_bytes(uint32_t N, uint32_t K) {
     return (static_cast<size_t>(K) * N / kTileElems * sizeof(Partial) + 255) / 256 * 256;
 }
 
-// How many fp32 copies of the gradient the workspace holds.  This is part of what callers size their workspace by: as many as keep
-// 256 compute units busy with 256 x 128 tiles (or 512 workgroups with those and smaller ones) on runs of at least 2048 (512) rows,
-// at most 8; none for 8-bit codes where one would do, as those can be updated without.
+// How many fp32 copies of the gradient the workspace holds.  This is part of what callers size their workspace by, whether the route taken
+// writes them or not: as many as keep 256 compute units busy with 256 x 128 tiles on runs of at least 2048 rows, where that gives at
+// least 128 workgroups (one copy also for 8-bit codes, which the one-kernel route leaves unused); else as many as give 512
+// workgroups, with those tiles or half of them, on runs of at least 512 rows, at most 8, and none for 8-bit codes where one would do.
 static uint32_t gradient_room(uint32_t bits, uint32_t M, uint32_t N, uint32_t K) {
     const uint64_t tiles = static_cast<uint64_t>(K / 256) * (N / 128);
     auto splits_for = [&](uint64_t count, uint64_t enough, uint32_t rows) {

@@ -15,7 +15,8 @@
 // TEAMS of waves of a workgroup, which add up their tiles through LDS, and between workgroups (nsplit).
 //
 // What bounds it: the loads (48 bytes per clock and compute unit at the matrix cores' rate; with all of them hitting the L2 the 8192-row product
-// of 4096 x 1024 weights takes 64 instead of 71 us), not the LDS reads: plain or 16-byte reads in their place change nothing.
+// of 4096 x 1024 weights takes 64 instead of 71 us), not the LDS reads: plain or 16-byte reads in their place change nothing.  The
+// matrix cores are busy in 41 - 47 % of the cycles, the waves wait in 35 - 47 % of theirs.
 #include "omc_dw_args.h"
 #include "omc_mma.h"
 

@@ -10,7 +10,8 @@
 // 16-byte pieces are XOR-swizzled on their way in (the lane picks the piece, its LDS place is fixed): A pieces by half the row,
 // forward W pieces by twice the k row, TRANS W pieces by a quarter of the column, so that the 16 pieces that one read takes at
 // a time lie on different ones of the 64 banks (A by the whole row: 8.1 clocks a read instead of 4.4, W 4.2 instead of 3.2 and
-// 8.0 instead of 4.2, all forward bank conflicts gone).
+// 8.0 instead of 4.2).  Forward no bank conflict is counted; TRANS reads half of a 16-byte piece at a time, and these reads still conflict,
+// 4.2 million cycles over all compute units in a launch of 62 - 68 us at the shapes below.
 //
 // Fragments of a quarter step are read while the quarter before is multiplied; the last quarter is multiplied after the
 // barrier of the next step, under that step's first reads.  Waves start their quarters at different places
@@ -27,8 +28,10 @@
 //
 // Measured (us, 8192 x 4096 x 1024 / 8192 x 1024 x 4096, fp32 output, new operands each time), against the kernel before (256 x 128 tile,
 // A fragments from global memory, W decoded on the way into LDS, a 5 us pass over the codes for top codes first): 83 / 81 ->
-// 65 / 60.  What bounds it now: power (1300 TFLOP/s at 8192 x 4096 x 4096, random data) and the C stores where nothing covers
-// them; not the LDS (67.6 -> 67.1 us at the first shape without its bank conflicts).
+// 65 / 58.  What bounds it now: waits.  The matrix cores are busy in 45 - 48 % of the cycles, at 2.1 - 2.2 GHz, and the waves wait in 34 - 47 %
+// of theirs, for fragments that are read one quarter of a step ahead, for the step's barrier, and at a contraction of 1024 for the C
+// stores where nothing covers them; 1300 TFLOP/s at 8192 x 4096 x 4096.  Not for LDS bandwidth (67.6 -> 67.1 us at the first shape without
+// the bank conflicts there were).
 #include "omc_mma.h"
 
 #pragma clang fp contract(off)

@@ -63,9 +63,10 @@ __device__ __forceinline__ void wait_stage(uint32_t j, uint32_t total) {
 // Host: which of a kernel's tile sizes to launch for an M x N result over K.  All figures are measured, in us: `base` is a launch
 // with one tile per compute unit and nothing to multiply, `step` a step of 64 k (of TEAMS times as many with several teams) when
 // every compute unit has at most `resident` workgroups, `loaded` what a step costs per workgroup and unit when all 256 units
-// are busy (matrix cores, LDS and power), `stores` the C stores of 256 tiles (with several teams, also
-// what a round of workgroups loses before its first and after its last step).  Estimates lie within 15 % of what was measured over M
-// 256 - 16384, N 128 - 4096, K 256 - 4096, the chosen tile within 7 % of the best one.
+// are busy (matrix cores, LDS and memory together), `stores` the C stores of 256 tiles (with several teams, also
+// what a round of workgroups loses before its first and after its last step).  Over 160 random sizes (M 256 - 16384, N 128 - 4096, K 256 - 4096,
+// both directions) the chosen tile takes 2.9 % longer than the best one on average and more than 7 % longer in 25 of them, at
+// worst 37 % (8-bit codes other than S1E4M3, 5376 x 3584 x 256: 30.9 us with 256 x 256, 22.5 with 128 x 128).
 struct GemmTile {
     uint32_t bm, bn, teams, resident;
     double base, step, loaded, stores;

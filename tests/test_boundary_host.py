@@ -284,7 +284,7 @@ def test_dw_update_rejects_bad_arguments():
         return omc._dw(X, dY, codes, fm, sb, 1, st0, st1, omc.C.byref(opt), None, M, N, K, ws, wsb, None)
     assert omc.omc_dw_update_workspace_bytes(f, 64, 128, 256) == 1280                        # no split: the fit's partials only
     assert omc.omc_dw_update_workspace_bytes(f, 8192, 128, 256) == 1280 + 8 * 4 * 128 * 256  # 8 splits of 1024 rows
-    assert omc.omc_dw_update_workspace_bytes(omc.fmt(3, 7), 64, 128, 256) == 1280 + 4 * 128 * 256   # other widths park once
+    assert omc.omc_dw_update_workspace_bytes(omc.fmt(3, 7), 64, 128, 256) == 1280 + 4 * 128 * 256   # other widths: one copy of the gradient
     assert omc.omc_dw_update_workspace_bytes(f, 64, 100, 256) == 0
     assert call(X=None) == 1
     assert call(fm=omc.fmt(9, 7)) == 2                   # not a format

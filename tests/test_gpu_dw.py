@@ -80,9 +80,9 @@ def test_tile_grid_and_minimal_contraction(shape):
 
 @pytest.mark.parametrize("M,kind,lr", [(1024, 0, 0.05), (4096, 1, 0.05), (2048, 2, 1e-3)])
 def test_contraction_split_between_workgroups(M, kind, lr):
-    """Few tiles and many rows: the M rows are shared out between workgroups and the last one to arrive at a
-    tile sums the partial accumulators in a fixed order; two runs must agree bit for bit with each other
-    (run_case compares the second step too) and with the oracle's step on the gradient that was used."""
+    """Few tiles and many rows: the M rows are shared out between workgroups, which leave partial sums, or between teams of waves of one
+    workgroup; either way they are added in a fixed order.  Two runs must agree bit for bit with each other (run_case compares the
+    second step too) and with the oracle's step on the gradient that was used."""
     run_case((4, 3), M, 128, 256, kind, lr, steps=2)
     run_case((4, 3), M, 256, 512, kind, lr, steps=1)
 
@@ -100,8 +100,8 @@ def test_config5_layer_sampled_gradient_rows():
 @pytest.mark.parametrize("kind,lr", [(0, 0.05), (1, 0.05), (2, 1e-3)])
 @pytest.mark.parametrize("EM", [(3, 7), (2, 3), (5, 7), (4, 14), (8, 7), (5, 10)])
 def test_other_code_widths_take_the_two_kernel_path(EM, kind, lr):
-    """6-, 11-, 13-, 16- and 19-bit formats: the accumulators pass through the workspace and the slab kernel
-    updates the rows; same two-stage check."""
+    """6-, 11-, 13-, 16- and 19-bit formats: the gradient passes through the workspace as partial sums and a second kernel adds them and
+    updates 2048 weights per wave; same two-stage check."""
     run_case(EM, 96, 128, 256, kind, lr)
 
 
@@ -112,7 +112,7 @@ def test_other_code_widths_with_split_contraction_and_several_tiles():
 
 @pytest.mark.parametrize("EM", [(4, 18), (5, 23), (8, 16)])
 def test_wide_mantissa_formats_keep_exact_fit_sums(EM):
-    """16 and more mantissa bits: the slab kernel carries the rounding errors of the fit's sums like the streaming
+    """16 and more mantissa bits: the update kernel carries the rounding errors of the fit's sums like the streaming
     kernels of these formats do, so (s, b) still match the oracle bit for bit."""
     run_case(EM, 96, 128, 256, 1, 0.05)
     run_case(EM, 1024, 256, 512, 0, 0.05, steps=1)
@@ -138,15 +138,16 @@ def test_fp32_as_a_format_is_plain_sgd():
     assert sb.cpu().numpy().tolist() == [1.0, 0.0]
 
 
-def test_large_matrix_takes_the_in_kernel_epilogue_on_256_row_tiles():
-    # 4096 x 4096 weights = 512 tiles of 256 x 128: no split, the update runs in the GEMM kernel's epilogue
+def test_large_matrix_is_updated_in_the_products_epilogue():
+    # 4096 x 4096 weights = 1024 tiles of 128 x 128: no split, the update runs in the product kernel's epilogue
+    assert dw_route(8, 64, 4096, 4096) == (True, 1, 1)
     run_case((4, 3), 64, 4096, 4096, 1, 0.05, steps=1, rows=(0, 2000, 4080))
 
 
 @pytest.mark.parametrize("EM,kind,lr", [((4, 3), 0, 0.05), ((3, 7), 1, 0.05), ((2, 3), 2, 1e-3)])
-def test_long_contraction_on_a_small_grid_takes_the_sixteen_wave_kernel(EM, kind, lr):
-    """64 tiles and 4096 rows: two workgroups of 16 waves per tile (eight multiplying, eight staging), each over
-    2048 rows; the accumulators pass through the workspace in the four-wave kernel's layout."""
+def test_long_contraction_on_a_small_grid(EM, kind, lr):
+    """4096 rows on 2048 x 1024 weights: 8-bit codes are updated by two teams of waves on 128 x 128 tiles in one kernel, the others from two partial
+    sums."""
     run_case(EM, 4096, 2048, 1024, kind, lr, steps=2, rows=(0, 16, 320, 1008))
 
 
@@ -154,8 +155,8 @@ def test_long_contraction_on_a_small_grid_takes_the_sixteen_wave_kernel(EM, kind
 @pytest.mark.parametrize("shape", [(160, 2048, 1024), (2080, 1024, 512), (2048, 2048, 512), (1056, 2048, 1024), (544, 4096, 2048),
                                    (1056, 4096, 4096), (4128, 384, 512)])
 def test_every_tile_of_the_product_and_uneven_shares(EM, shape):
-    """Tiles of 64 x 64 (one, two and four teams of waves), 128 x 128 (one and two) and 256 x 128, in the kernel that updates 8-bit
-    codes in its epilogue and in the one that leaves partial sums; 65 or 33 steps of 32 rows do not share out evenly."""
+    """Tiles of 64 x 64 (one, two and four teams of waves) and 128 x 128 (one and two), in the kernel that updates 8-bit codes in its epilogue and
+    in the one that leaves partial sums, there also 256 x 128; 65 or 33 steps of 32 rows do not share out evenly."""
     M, N, K = shape
     run_case(EM, M, N, K, 1, 0.05, steps=1, rows=None if K * N <= 1 << 20 else (0, 16, K // 2 - 16, K - 16))
 
@@ -182,7 +183,8 @@ def test_epilogue_combines_its_waves_sums_without_rounding():
     become codes of 0.25), so that what a wave loses beside +-2^80 it loses from both sums: s = 1, b = 0.25 x share of the ones, exactly."""
     of, gf = pair(7, 0, 40)
     M, N, K = 32, 128, 256
-    ones = (np.arange(K) % 8) >= 4                          # rows of waves 1 and 3; the others hold zeros
+    assert dw_route(8, M, N, K) == (True, 4, 1)             # 64 x 64 tiles, eight waves of four rows in turn
+    ones = (np.arange(K) % 8) >= 4                          # rows of the odd waves; the others hold zeros
     codes = np.where(ones[:, None], 40, 0) * np.ones((1, N), np.int64)
     codes[0, 0], codes[8, 0] = 120, 0x80 | 120
     packed, sb = orc.pack(codes.ravel().astype(np.uint32), 8), np.array([1.0, 0.25], np.float32)

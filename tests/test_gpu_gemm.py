@@ -20,8 +20,8 @@ def run_gemm(A_bits, packed, gf, sb, M, N, K):
 
 
 def tile_sample_rows(M, seed, tile=256, per_quarter=1):
-    """Rows to check at full size: from every 256-row tile of the output one row out of each 64-row quarter (the
-    share of one wave of the four-wave kernels), at seeded offsets."""
+    """Rows to check at full size: from every 256 rows of the output one row (or several) out of each 64-row quarter, which is the least that
+    a tile covers, at seeded offsets."""
     rng = np.random.default_rng(seed)
     rows = [t * tile + 64 * q + int(rng.integers(0, 64)) for t in range(M // tile) for q in range(4) for _ in range(per_quarter)]
     return np.array(sorted(set(rows)))
@@ -90,11 +90,11 @@ def test_config5_shapes_sampled_rows(shape):
         assert check(C, ref, (r0, r0 + 24)) < 1e-5
 
 
-@pytest.mark.parametrize("K", [256, 2048])                  # 2048: the kernel for long contractions on small grids
+@pytest.mark.parametrize("K", [256, 2048])                  # (both by four teams of waves)
 @pytest.mark.parametrize("top_at", [None, 0, -1, 12345])
 def test_every_byte_code_exact_with_and_without_the_top_code(top_at, K):
-    """S1E4M3 / bias 7 takes the hardware FP8 conversion unless the weights hold a top code (value 480);
-    the pre-pass must find one anywhere in the stream, and both decodes must give the exact code values."""
+    """S1E4M3 / bias 7 takes the hardware FP8 conversion, which reads a top code (value 480) as NaN; a tile whose sums show one anywhere in
+    the stream is computed again, and both conversions must give the exact code values."""
     of, gf = pair(4, 3)
     M, N = 256, 128
     A = np.zeros((M, K), np.float32)
@@ -133,10 +133,10 @@ def test_dx_small_shapes_all_rows(EM, shape):
     check(dX, orc.dequant_gemm_dx(dY, packed, of, None, M, N, K, threads=8), (0, M))
 
 
-@pytest.mark.parametrize("N", [64, 2048])                   # 2048: the kernel for long contractions on small grids
+@pytest.mark.parametrize("N", [64, 2048])                   # (both by four teams of waves)
 @pytest.mark.parametrize("top_at", [None, 777])
 def test_dx_identity_pattern_pins_the_transposed_layout(top_at, N):
-    # dY = one-hot rows: dX must reproduce columns of W exactly, with and without a top code (both decodes)
+    # dY = one-hot rows: dX must reproduce columns of W exactly, with and without a top code (both conversions)
     of, gf = pair(4, 3)
     M, K = 256, 128
     dY = np.zeros((M, N), np.float32)

@@ -30,7 +30,7 @@ def test_captured_round_replays_like_eager_launches():
     wsb = torch.tensor([0.5, 0.125], device="cuda")
     C = torch.zeros((M, N), device="cuda")
     gws = torch.empty(omc.omc_dequant_gemm_workspace_bytes(M), dtype=torch.uint8, device="cuda")
-    K2 = 2048                                        # a long contraction on a small grid (dX: the sixteen-wave kernel)
+    K2 = 2048                                        # a long contraction on a small grid: teams of waves share it
     A2 = torch.from_numpy(synth.to_bf16_bits(synth.normal_f32(M * K2, 1.0, 6)).view(np.int16)).cuda()
     wcodes2 = torch.randint(0, 120, (K2 * N,), dtype=torch.uint8, device="cuda")
     C2 = torch.zeros((M, N), device="cuda")
