@@ -11,90 +11,207 @@
 
 namespace omc {
 
-#ifndef OMC_AGG_WAVES
-#define OMC_AGG_WAVES 4
-#endif
+// Loads of a batch of clients are in flight together.  Byte codes: eight clients at three waves per SIMD 291 us, four at four 301, two at
+// six 304 (115 M elements, 8 clients; one at eight 311).  The other widths hold a client in 32 registers, and more waves are worth more than
+// more clients: 10 layers of 397 x 1191 in 11 bits, 4 clients, one client at four waves 66 us, two at three 71, four at two 80.
+constexpr uint32_t kByteBatch = 8, kByteWaves = 3, kTileWaves = 4, kFlatBatch = 8, kTailBatchClients = 4;
+constexpr uint32_t kTailPart = 256;       // elements of a ragged tail that one workgroup takes: four per lane
+constexpr uint32_t kTailParts = kTileElems / kTailPart;
+constexpr uint32_t kFlatParts = 4;        // workgroups that share an all-fp32 item
+// A work item is shared by several workgroups until there are this many: about what the chip holds at a time (same sets: 4096 74 us,
+// 8192 and more 71).
+constexpr uint32_t kEnoughBlocks = 8192;
 
 struct AggArgs {
     const uint8_t *plan;                 // device copy of the aggregation plan blob
     uint64_t var_off, src_off, item_off;
-    uint32_t first_item, nitems;
-    uint32_t flat_first, flat_nitems;    // items of all-fp32 variables appended to a full-tile launch
+    uint32_t first_item;
+    uint32_t tail_first, tail_blocks;    // ragged tails: kTailParts workgroups an item, the first ones of the launch
+    uint32_t full_blocks, parts;         // full tiles: `parts` workgroups an item
+    uint32_t flat_first;                 // items of all-fp32 variables: kFlatParts workgroups an item, the last ones of the launch
     uint32_t nreplicas;
     float count;                         // R as a float
     AggPointers p;
     float *out;
 };
 
-// Variables that are fp32 at every client: 16-byte pieces, coalesced, bounds-checked at the end.
-__device__ __forceinline__ void aggregate_flat_item(const AggArgs &aa, uint32_t item) {
+// The variable of a work item and where its copies lie: lane r holds client r's.  All clients' descriptors take three dependent
+// loads together; fetched one client after the other, where they were needed, they were two for each.
+struct AggView {
+    AggVar av;
+    uint32_t chunk;
+    uint32_t addr_lo, addr_hi, quantized;
+    float s, b;
+    __device__ __forceinline__ const uint8_t *copy(uint32_t r) const {
+        return reinterpret_cast<const uint8_t *>((static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(addr_hi, r))) << 32) |
+                                                 static_cast<uint32_t>(__builtin_amdgcn_readlane(addr_lo, r)));
+    }
+    __device__ __forceinline__ bool is_quantized(uint32_t r) const { return __builtin_amdgcn_readlane(quantized, r) != 0; }
+    __device__ __forceinline__ float scale(uint32_t r) const { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), r)); }
+    __device__ __forceinline__ float offset(uint32_t r) const { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(b), r)); }
+};
+__device__ __forceinline__ AggView load_view(const AggArgs &aa, uint32_t item) {
+    AggView v{};
     const PlanItem it = to_scalar_regs(reinterpret_cast<const PlanItem *>(aa.plan + aa.item_off)[item]);
-    const AggVar av = to_scalar_regs(reinterpret_cast<const AggVar *>(aa.plan + aa.var_off)[it.var]);
-    const AggSrc *src = reinterpret_cast<const AggSrc *>(aa.plan + aa.src_off) + static_cast<uint64_t>(it.var) * aa.nreplicas;
+    v.chunk = it.chunk;
+    const uint32_t r = threadIdx.x;
+    if (r < aa.nreplicas) {
+        const AggSrc src = (reinterpret_cast<const AggSrc *>(aa.plan + aa.src_off) + static_cast<uint64_t>(it.var) * aa.nreplicas)[r];
+        const uint64_t addr = reinterpret_cast<uint64_t>(aa.p.arena[r]) + src.data_offset;
+        v.addr_lo = static_cast<uint32_t>(addr);
+        v.addr_hi = static_cast<uint32_t>(addr >> 32);
+        v.quantized = src.quantized;
+        const float *sb = aa.p.sb[r] + 2 * static_cast<uint64_t>(it.var);
+        v.s = sb[0];
+        v.b = sb[1];
+    }
+    v.av = to_scalar_regs(reinterpret_cast<const AggVar *>(aa.plan + aa.var_off)[it.var]);
+    return v;
+}
+
+// Variables that are fp32 at every client: 16-byte pieces, coalesced, bounds-checked at the end.
+__device__ __forceinline__ void aggregate_flat_part(const AggArgs &aa, uint32_t block) {
+    const AggView v = load_view(aa, aa.flat_first + block / kFlatParts);
     const uint32_t lane = threadIdx.x;
-    float *dst = aa.out + av.aux_offset;
-    const uint64_t begin = static_cast<uint64_t>(it.chunk) * kChunkElems;
-    for (int j = 0; j < kChunkElems / 256; ++j) {
+    float *dst = aa.out + v.av.aux_offset;
+    const uint64_t begin = static_cast<uint64_t>(v.chunk) * kChunkElems;
+    for (uint32_t j = block % kFlatParts; j < kChunkElems / 256; j += kFlatParts) {
         const uint64_t e = begin + (static_cast<uint64_t>(j) * 64 + lane) * 4;
-        if (e >= av.n) break;
-        const bool full = e + 4 <= av.n;
-        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (uint32_t r = 0; r < aa.nreplicas; ++r) {
-            const float *v = reinterpret_cast<const float *>(aa.p.arena[r] + to_scalar_regs(src[r].data_offset));
-            float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (full) {
-                const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(v + e));
-                x[0] = t.x; x[1] = t.y; x[2] = t.z; x[3] = t.w;
-            } else {
-                for (int c = 0; c < 4; ++c)
-                    if (e + c < av.n) x[c] = v[e + c];
+        if (begin + static_cast<uint64_t>(j) * 256 >= v.av.n) break;
+        const uint32_t left = e >= v.av.n ? 0u : v.av.n - e < 4 ? static_cast<uint32_t>(v.av.n - e) : 4u;   // this lane's elements
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (uint32_t r0 = 0; r0 < aa.nreplicas; r0 += kFlatBatch) {
+            f32x4 x[kFlatBatch];
+#pragma unroll
+            for (uint32_t g = 0; g < kFlatBatch; ++g) {
+                x[g] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (r0 + g >= aa.nreplicas) continue;
+                const float *from = reinterpret_cast<const float *>(v.copy(r0 + g));
+                if (left == 4) x[g] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(from + e));
+                else
+                    for (uint32_t c = 0; c < 3; ++c)
+                        if (c < left) x[g][c] = from[e + c];
             }
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[c] = (r == 0) ? x[c] : acc[c] + x[c];
+            for (uint32_t g = 0; g < kFlatBatch; ++g)
+                if (r0 + g < aa.nreplicas)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[c] = (r0 + g == 0) ? x[g][c] : acc[c] + x[g][c];
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[c] = acc[c] / aa.count;
-        if (full) {
-            __builtin_nontemporal_store(f32x4{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<f32x4 *>(dst + e));
-        } else {
-            for (int c = 0; c < 4; ++c)
-                if (e + c < av.n) dst[e + c] = acc[c];
+        if (left == 4) __builtin_nontemporal_store(acc, reinterpret_cast<f32x4 *>(dst + e));
+        else
+            for (uint32_t c = 0; c < 3; ++c)
+                if (c < left) dst[e + c] = acc[c];
+    }
+}
+
+// Ragged tails of variables that at least one client quantized: run-time code width, every access checked.  A workgroup takes 256
+// elements, a lane every 64th of them, and asks for those of four clients at a time.  What bounds it is latency: with 32 consecutive
+// elements per lane, one client's after the other's, and a launch behind the full tiles, sets of odd sizes took, 8 clients of 4 blocks of
+// 134 x 273 (41 MB) 128 us, now 12; 6 clients of 15 blocks of 100 x 305 in 16 bits (70 MB) 138, now 22.
+__device__ __forceinline__ void aggregate_tail_part(const AggArgs &aa, uint32_t block) {
+    const AggView v = load_view(aa, aa.tail_first + block / kTailParts);
+    const FmtParams fp = v.av.fp;
+    const uint32_t B = fp.bits, lane = threadIdx.x;
+    const uint32_t cmask = (B == 32) ? 0xffffffffu : ((1u << B) - 1u);
+    const uint64_t e0 = (v.av.n / kTileElems) * kTileElems;
+    const uint32_t count = static_cast<uint32_t>(v.av.n - e0), begin = block % kTailParts * kTailPart;
+    if (begin >= count) return;
+    const uint64_t dw0 = (e0 >> 5) * B;                      // the tail's first dword
+    const uint32_t dwords = static_cast<uint32_t>(v.av.total_dwords - dw0);
+    constexpr uint32_t kEach = kTailPart / 64, G = kTailBatchClients;
+    float acc[kEach] = {};
+    for (uint32_t r0 = 0; r0 < aa.nreplicas; r0 += G) {
+        uint32_t lo[G][kEach], hi[G][kEach];
+#pragma unroll
+        for (uint32_t g = 0; g < G; ++g) {
+#pragma unroll
+            for (uint32_t u = 0; u < kEach; ++u) lo[g][u] = hi[g][u] = 0u;
+            if (r0 + g >= aa.nreplicas) continue;
+            const uint8_t *copy = v.copy(r0 + g);
+            if (v.is_quantized(r0 + g)) {
+                const uint32_t *codes = reinterpret_cast<const uint32_t *>(copy) + dw0;
+#pragma unroll
+                for (uint32_t u = 0; u < kEach; ++u) {
+                    const uint32_t i = begin + lane + 64u * u, d = (i * B) >> 5;
+                    if (i < count) lo[g][u] = codes[d];
+                    if (i < count && d + 1 < dwords) hi[g][u] = codes[d + 1];
+                }
+            } else {
+                const uint32_t *values = reinterpret_cast<const uint32_t *>(copy) + e0;
+#pragma unroll
+                for (uint32_t u = 0; u < kEach; ++u) {
+                    const uint32_t i = begin + lane + 64u * u;
+                    if (i < count) lo[g][u] = values[i];
+                }
+            }
+        }
+#pragma unroll
+        for (uint32_t g = 0; g < G; ++g) {
+            if (r0 + g >= aa.nreplicas) continue;
+            const bool quantized = v.is_quantized(r0 + g);
+            const float s = v.scale(r0 + g), b = v.offset(r0 + g);
+#pragma unroll
+            for (uint32_t u = 0; u < kEach; ++u) {
+                float x = __uint_as_float(lo[g][u]);
+                if (quantized) {
+                    const uint32_t i = begin + lane + 64u * u;
+                    const uint64_t both = (static_cast<uint64_t>(hi[g][u]) << 32) | lo[g][u];
+                    const uint32_t code = static_cast<uint32_t>(both >> ((i * B) & 31u)) & cmask;
+                    const float vt = decode_top(code << (32u - B), fp);
+                    const float sv = s * vt;
+                    x = sv + b;
+                }
+                acc[u] = (r0 + g == 0) ? x : acc[u] + x;
+            }
         }
     }
+#pragma unroll
+    for (uint32_t u = 0; u < kEach; ++u) {
+        const uint32_t i = begin + lane + 64u * u;
+        if (i < count) aa.out[v.av.aux_offset + e0 + i] = acc[u] / aa.count;
+    }
+}
+
+// The workgroups of a launch that take tails (the first ones) and all-fp32 items (the last ones); true if this is one of them.
+__device__ __forceinline__ bool aggregate_rest(const AggArgs &aa) {
+    if (blockIdx.x < aa.tail_blocks) {
+        aggregate_tail_part(aa, blockIdx.x);
+        return true;
+    }
+    if (blockIdx.x >= aa.tail_blocks + aa.full_blocks) {
+        aggregate_flat_part(aa, blockIdx.x - aa.tail_blocks - aa.full_blocks);
+        return true;
+    }
+    return false;
 }
 
 // Full tiles of a variable that at least one client quantized (code width B).  A lane owns 32
 // consecutive elements; a client's tile reaches that layout through LDS from coalesced 16-byte
 // pieces, whether it holds codes or fp32 values.
 template <int B>
-__global__ __launch_bounds__(64, OMC_AGG_WAVES) void aggregate_kernel(AggArgs aa) {
+__global__ __launch_bounds__(64, kTileWaves) void aggregate_kernel(AggArgs aa) {
     __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsDwords];
-    if (blockIdx.x >= aa.nitems) {
-        aggregate_flat_item(aa, aa.flat_first + (blockIdx.x - aa.nitems));
-        return;
-    }
-    const uint32_t lane = threadIdx.x;
-    const uint32_t item = aa.first_item + blockIdx.x;
-    const PlanItem it = to_scalar_regs(reinterpret_cast<const PlanItem *>(aa.plan + aa.item_off)[item]);
-    const AggVar av = to_scalar_regs(reinterpret_cast<const AggVar *>(aa.plan + aa.var_off)[it.var]);
-    const AggSrc *src = reinterpret_cast<const AggSrc *>(aa.plan + aa.src_off) + static_cast<uint64_t>(it.var) * aa.nreplicas;
-    const FmtParams fp = av.fp;
-    const uint64_t first_tile = static_cast<uint64_t>(it.chunk) * tiles_per_chunk(B);
-    const uint64_t full_tiles = av.n / kTileElems;
+    if (aggregate_rest(aa)) return;
+    const uint32_t lane = threadIdx.x, block = blockIdx.x - aa.tail_blocks;
+    const AggView v = load_view(aa, aa.first_item + block / aa.parts);
+    const FmtParams fp = v.av.fp;
+    const uint64_t first_tile = static_cast<uint64_t>(v.chunk) * tiles_per_chunk(B);
+    const uint64_t full_tiles = v.av.n / kTileElems;
     const uint32_t ntiles = static_cast<uint32_t>(
         (full_tiles - first_tile < tiles_per_chunk(B)) ? full_tiles - first_tile : tiles_per_chunk(B));
-    for (uint32_t t = 0; t < ntiles; ++t) {
+    for (uint32_t t = block % aa.parts; t < ntiles; t += aa.parts) {
         const uint64_t e0 = (first_tile + t) * kTileElems;
         float acc[32];
         for (uint32_t r = 0; r < aa.nreplicas; ++r) {
-            const AggSrc s = to_scalar_regs(src[r]);
+            const uint8_t *copy = v.copy(r);
             float val[32];
-            if (s.quantized) {
-                const uint32_t *codes = reinterpret_cast<const uint32_t *>(aa.p.arena[r] + s.data_offset);
-                const float sc = to_scalar_regs(aa.p.sb[r][2 * static_cast<uint64_t>(it.var)]);
-                const float of = to_scalar_regs(aa.p.sb[r][2 * static_cast<uint64_t>(it.var) + 1]);
+            if (v.is_quantized(r)) {
+                const float sc = v.scale(r), of = v.offset(r);
                 u32x4 cq[CodePieces<B>::rounds];
-                load_code_pieces<B, OMC_TUNE_AGG_NT != 0>(codes + (e0 >> 5) * B, lane, cq);
+                load_code_pieces<B, OMC_TUNE_AGG_NT != 0>(reinterpret_cast<const uint32_t *>(copy) + (e0 >> 5) * B, lane, cq);
                 uint32_t w[B];
                 code_pieces_to_lanes<B>(cq, w, lds, lane);
 #pragma unroll
@@ -104,24 +221,18 @@ __global__ __launch_bounds__(64, OMC_AGG_WAVES) void aggregate_kernel(AggArgs aa
                     val[i] = sv + of;
                 }
             } else {
-                const float *v = reinterpret_cast<const float *>(aa.p.arena[r] + s.data_offset);
                 f32x4 g[8];
-                load_f32_pieces<true>(v + e0, lane, g);
+                load_f32_pieces<true>(reinterpret_cast<const float *>(copy) + e0, lane, g);
                 pieces_to_lanes(g, val, lds, lane);
             }
-            if (r == 0) {
 #pragma unroll
-                for (int i = 0; i < 32; ++i) acc[i] = val[i];
-            } else {
-#pragma unroll
-                for (int i = 0; i < 32; ++i) acc[i] = acc[i] + val[i];
-            }
+            for (int i = 0; i < 32; ++i) acc[i] = (r == 0) ? val[i] : acc[i] + val[i];
         }
 #pragma unroll
         for (int i = 0; i < 32; ++i) acc[i] = acc[i] / aa.count;
         f32x4 o[8];
         lanes_to_pieces(acc, o, lds, lane);
-        store_f32_pieces<true>(aa.out + av.aux_offset + e0, lane, o);
+        store_f32_pieces<true>(aa.out + v.av.aux_offset + e0, lane, o);
     }
 }
 
@@ -129,73 +240,74 @@ __global__ __launch_bounds__(64, OMC_AGG_WAVES) void aggregate_kernel(AggArgs aa
 // its 16-byte pieces of the fp32 copies and of the output (slab of 1024 elements: piece j of lane l =
 // elements 256 j + 4 l ..).  Everything stays coalesced and LDS is not used.  S1E4M3 / bias 7 is
 // decoded by the hardware's FP8 conversion; its one deviating code (the top code reads as NaN) leaves a
-// NaN in the sum, and such a slab is redone with the generic decode.
+// NaN in the sums, and such a slab is redone with the generic decode.
 template <bool HW>
-__device__ __forceinline__ void aggregate_byte_slab(const AggArgs &aa, const AggSrc *src, uint32_t var, const FmtParams &fp,
-                                                    uint64_t e0, uint32_t lane, f32x4 (&acc)[4]) {
-    // (fetching the code dwords of all copies before the first decode, to have more loads in flight,
-    // was measured: 499 us instead of 334 us on the benchmark set; one copy at a time it is)
-    for (uint32_t r = 0; r < aa.nreplicas; ++r) {
-        const AggSrc s = to_scalar_regs(src[r]);
-        f32x4 val[4];
-        if (s.quantized) {
-            const uint32_t *c = reinterpret_cast<const uint32_t *>(aa.p.arena[r] + s.data_offset) + (e0 >> 2);
-            const float sc = to_scalar_regs(aa.p.sb[r][2 * static_cast<uint64_t>(var)]);
-            const float of = to_scalar_regs(aa.p.sb[r][2 * static_cast<uint64_t>(var) + 1]);
-            uint32_t w[4];
+__device__ __forceinline__ void aggregate_byte_slab(const AggArgs &aa, const AggView &v, const FmtParams &fp, uint64_t e0,
+                                                    uint32_t lane, f32x4 (&acc)[4]) {
+    for (uint32_t r0 = 0; r0 < aa.nreplicas; r0 += kByteBatch) {
+        f32x4 in[kByteBatch][4];                              // four codes (in the first element) or values
 #pragma unroll
-            for (int j = 0; j < 4; ++j) w[j] = OMC_TUNE_AGG_NT ? __builtin_nontemporal_load(c + (64 * j + lane)) : c[64 * j + lane];
+        for (uint32_t g = 0; g < kByteBatch; ++g) {
+            if (r0 + g >= aa.nreplicas) continue;
+            const uint8_t *copy = v.copy(r0 + g);
+            if (v.is_quantized(r0 + g)) {
+                const uint32_t *c = reinterpret_cast<const uint32_t *>(copy) + (e0 >> 2);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float vt[4];
-                if (HW) {
-                    const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(w[j]), false);
-                    const f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(w[j]), true);
-                    vt[0] = lo[0]; vt[1] = lo[1]; vt[2] = hi[0]; vt[3] = hi[1];
-                } else {
+                for (int j = 0; j < 4; ++j) in[g][j][0] = __uint_as_float(OMC_TUNE_AGG_NT ? __builtin_nontemporal_load(c + (64 * j + lane)) : c[64 * j + lane]);
+            } else {
+                const f32x4 *x = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(copy) + e0);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) vt[i] = decode_top(w[j] << (24 - 8 * i), fp);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float sv = sc * vt[i];
-                    val[j][i] = sv + of;
-                }
+                for (int j = 0; j < 4; ++j) in[g][j] = __builtin_nontemporal_load(x + (64 * j + lane));
             }
-        } else {
-            const f32x4 *v = reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(aa.p.arena[r] + s.data_offset) + e0);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) val[j] = __builtin_nontemporal_load(v + (64 * j + lane));
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (uint32_t g = 0; g < kByteBatch; ++g) {
+            if (r0 + g >= aa.nreplicas) continue;
+            const bool quantized = v.is_quantized(r0 + g);
+            const float sc = v.scale(r0 + g), of = v.offset(r0 + g);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[j][i] = (r == 0) ? val[j][i] : acc[j][i] + val[j][i];
+            for (int j = 0; j < 4; ++j) {
+                f32x4 val = in[g][j];
+                if (quantized) {
+                    const uint32_t w = __float_as_uint(in[g][j][0]);
+                    float vt[4];
+                    if (HW) {
+                        const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(w), false);
+                        const f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(w), true);
+                        vt[0] = lo[0]; vt[1] = lo[1]; vt[2] = hi[0]; vt[3] = hi[1];
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) vt[i] = decode_top(w << (24 - 8 * i), fp);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float sv = sc * vt[i];
+                        val[i] = sv + of;
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[j][i] = (r0 + g == 0) ? val[i] : acc[j][i] + val[i];
+            }
+        }
     }
 }
 
-__global__ __launch_bounds__(64, 8) void aggregate_byte_kernel(AggArgs aa) {
-    if (blockIdx.x >= aa.nitems) {
-        aggregate_flat_item(aa, aa.flat_first + (blockIdx.x - aa.nitems));
-        return;
-    }
-    const uint32_t lane = threadIdx.x;
-    const uint32_t item = aa.first_item + blockIdx.x;
-    const PlanItem it = to_scalar_regs(reinterpret_cast<const PlanItem *>(aa.plan + aa.item_off)[item]);
-    const AggVar av = to_scalar_regs(reinterpret_cast<const AggVar *>(aa.plan + aa.var_off)[it.var]);
-    const AggSrc *src = reinterpret_cast<const AggSrc *>(aa.plan + aa.src_off) + static_cast<uint64_t>(it.var) * aa.nreplicas;
-    const FmtParams fp = av.fp;
-    const uint64_t first_tile = static_cast<uint64_t>(it.chunk) * tiles_per_chunk(8);
-    const uint64_t full_tiles = av.n / kTileElems;
+__global__ __launch_bounds__(64, kByteWaves) void aggregate_byte_kernel(AggArgs aa) {
+    if (aggregate_rest(aa)) return;
+    const uint32_t lane = threadIdx.x, block = blockIdx.x - aa.tail_blocks;
+    const AggView v = load_view(aa, aa.first_item + block / aa.parts);
+    const FmtParams fp = v.av.fp;
+    const uint64_t first_tile = static_cast<uint64_t>(v.chunk) * tiles_per_chunk(8);
+    const uint64_t full_tiles = v.av.n / kTileElems;
     const uint32_t ntiles = static_cast<uint32_t>(
         (full_tiles - first_tile < tiles_per_chunk(8)) ? full_tiles - first_tile : tiles_per_chunk(8));
     const bool hw = fp.variant == 2;
-    for (uint32_t sl = 0; sl < 2 * ntiles; ++sl) {
+    for (uint32_t sl = block % aa.parts; sl < 2 * ntiles; sl += aa.parts) {
         const uint64_t e0 = first_tile * kTileElems + static_cast<uint64_t>(sl) * 1024;
         f32x4 acc[4];
         bool done = false;
         if (hw) {
-            aggregate_byte_slab<true>(aa, src, it.var, fp, e0, lane, acc);
+            aggregate_byte_slab<true>(aa, v, fp, e0, lane, acc);
             bool bad = false;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -203,8 +315,8 @@ __global__ __launch_bounds__(64, 8) void aggregate_byte_kernel(AggArgs aa) {
                 for (int i = 0; i < 4; ++i) bad = bad || (acc[j][i] != acc[j][i]);
             done = !__any(bad);
         }
-        if (!done) aggregate_byte_slab<false>(aa, src, it.var, fp, e0, lane, acc);
-        f32x4 *dst = reinterpret_cast<f32x4 *>(aa.out + av.aux_offset + e0);
+        if (!done) aggregate_byte_slab<false>(aa, v, fp, e0, lane, acc);
+        f32x4 *dst = reinterpret_cast<f32x4 *>(aa.out + v.av.aux_offset + e0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             f32x4 o;
@@ -215,49 +327,15 @@ __global__ __launch_bounds__(64, 8) void aggregate_byte_kernel(AggArgs aa) {
     }
 }
 
-// Ragged tails of those variables: one wave each, run-time code width, every access checked.
-__global__ __launch_bounds__(64) void aggregate_tail_kernel(AggArgs aa) {
-    const uint32_t lane = threadIdx.x;
-    const uint32_t item = aa.first_item + blockIdx.x;
-    const PlanItem it = to_scalar_regs(reinterpret_cast<const PlanItem *>(aa.plan + aa.item_off)[item]);
-    const AggVar av = to_scalar_regs(reinterpret_cast<const AggVar *>(aa.plan + aa.var_off)[it.var]);
-    const AggSrc *src = reinterpret_cast<const AggSrc *>(aa.plan + aa.src_off) + static_cast<uint64_t>(it.var) * aa.nreplicas;
-    const FmtParams fp = av.fp;
-    const uint32_t B = fp.bits;
-    const uint32_t cmask = (B == 32) ? 0xffffffffu : ((1u << B) - 1u);
-    const uint64_t e0 = (av.n / kTileElems) * kTileElems;
-    const uint64_t lane_e0 = e0 + static_cast<uint64_t>(lane) * kLaneElems;
-    const uint64_t lane_dw0 = (lane_e0 >> 5) * B;
-    for (uint32_t i = 0; i < kLaneElems; ++i) {
-        const uint64_t e = lane_e0 + i;
-        if (e >= av.n) break;
-        float acc = 0.0f;
-        for (uint32_t r = 0; r < aa.nreplicas; ++r) {
-            const AggSrc s = to_scalar_regs(src[r]);
-            float x;
-            if (s.quantized) {
-                const uint32_t *codes = reinterpret_cast<const uint32_t *>(aa.p.arena[r] + s.data_offset);
-                const uint32_t bit = i * B, idx = bit >> 5, off = bit & 31u;
-                const uint64_t d = lane_dw0 + idx;
-                const uint32_t lo = (d < av.total_dwords) ? codes[d] : 0u;
-                const uint32_t hi = (idx + 1 < B && d + 1 < av.total_dwords) ? codes[d + 1] : 0u;
-                const uint64_t both = (static_cast<uint64_t>(hi) << 32) | lo;
-                const uint32_t code = static_cast<uint32_t>(both >> off) & cmask;
-                const float vt = decode_top(code << (32u - B), fp);
-                const float sv = aa.p.sb[r][2 * static_cast<uint64_t>(it.var)] * vt;
-                x = sv + aa.p.sb[r][2 * static_cast<uint64_t>(it.var) + 1];
-            } else {
-                x = reinterpret_cast<const float *>(aa.p.arena[r] + s.data_offset)[e];
-            }
-            acc = (r == 0) ? x : acc + x;
-        }
-        aa.out[av.aux_offset + e] = acc / aa.count;
-    }
-}
+// tails and all-fp32 items alone (no full-tile launch to ride on)
+__global__ __launch_bounds__(64) void aggregate_rest_kernel(AggArgs aa) { aggregate_rest(aa); }
 
-// flat items alone (no full-tile launch to ride on)
-__global__ __launch_bounds__(64) void aggregate_flat_kernel(AggArgs aa) {
-    aggregate_flat_item(aa, aa.flat_first + blockIdx.x);
+// Workgroups that share a work item: its slabs of byte codes or its tiles, where the items alone are too few to fill the chip.
+static uint32_t parts_of(uint32_t bits, uint32_t nitems) {
+    const uint32_t most = bits == 8 ? 2 * tiles_per_chunk(8) : tiles_per_chunk(bits);
+    uint32_t parts = 1;
+    while (parts < most && nitems * static_cast<uint64_t>(parts) < kEnoughBlocks) parts *= 2;
+    return parts;
 }
 
 int launch_aggregate_mean(const AggHeader *ah, const void *agg_dev, const AggPointers &ptrs, float *out,
@@ -273,32 +351,35 @@ int launch_aggregate_mean(const AggHeader *ah, const void *agg_dev, const AggPoi
     aa.count = static_cast<float>(ah->nreplicas);
     aa.p = ptrs;
     aa.out = out;
-    const PlanGroup *flat = nullptr;
-    for (uint32_t gi = 0; gi < ah->ngroups; ++gi)
+    // the tails and the all-fp32 items ride on the first full-tile launch
+    const PlanGroup *flat = nullptr, *tail = nullptr;
+    for (uint32_t gi = 0; gi < ah->ngroups; ++gi) {
         if (groups[gi].kind == kGroupFp32 && groups[gi].nitems > 0) flat = &groups[gi];
-    bool flat_done = (flat == nullptr);
+        if (groups[gi].kind == kGroupTail && groups[gi].nitems > 0) tail = &groups[gi];
+    }
+    uint64_t rest_blocks = 0;
+    if (tail) {
+        aa.tail_first = tail->first_item;
+        rest_blocks += static_cast<uint64_t>(tail->nitems) * kTailParts;
+    }
+    if (flat) {
+        aa.flat_first = flat->first_item;
+        rest_blocks += static_cast<uint64_t>(flat->nitems) * kFlatParts;
+    }
+    if (rest_blocks > 0x7fffffffull) return static_cast<int>(hipErrorInvalidValue);
+    aa.tail_blocks = tail ? tail->nitems * kTailParts : 0;
     for (uint32_t gi = 0; gi < ah->ngroups; ++gi) {
         const PlanGroup &g = groups[gi];
-        if (g.nitems == 0 || g.kind == kGroupFp32) continue;
+        if (g.nitems == 0 || g.kind != kGroupFull) continue;
         aa.first_item = g.first_item;
-        aa.nitems = g.nitems;
-        aa.flat_first = 0;
-        aa.flat_nitems = 0;
-        if (g.kind == kGroupTail) {
-            aggregate_tail_kernel<<<dim3(g.nitems), dim3(64), 0, st>>>(aa);
+        aa.parts = parts_of(g.bits, g.nitems);
+        const uint64_t blocks = static_cast<uint64_t>(g.nitems) * aa.parts + rest_blocks;
+        if (blocks > 0x7fffffffull) return static_cast<int>(hipErrorInvalidValue);
+        aa.full_blocks = g.nitems * aa.parts;
+        const dim3 grid(static_cast<uint32_t>(blocks));
+        if (g.bits == 8) {
+            aggregate_byte_kernel<<<grid, dim3(64), 0, st>>>(aa);
         } else {
-            if (!flat_done) {
-                aa.flat_first = flat->first_item;
-                aa.flat_nitems = flat->nitems;
-                flat_done = true;
-            }
-            const dim3 grid(g.nitems + aa.flat_nitems);
-            if (g.bits == 8) {
-                aggregate_byte_kernel<<<grid, dim3(64), 0, st>>>(aa);
-                const hipError_t e8 = hipGetLastError();
-                if (e8 != hipSuccess) return static_cast<int>(e8);
-                continue;
-            }
             switch (g.bits) {
 #define X(BITS) case BITS: aggregate_kernel<BITS><<<grid, dim3(64), 0, st>>>(aa); break;
                 OMC_FOR_EACH_BITS(X)
@@ -308,11 +389,12 @@ int launch_aggregate_mean(const AggHeader *ah, const void *agg_dev, const AggPoi
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return static_cast<int>(e);
+        rest_blocks = 0;
+        aa.tail_blocks = 0;
     }
-    if (!flat_done) {
-        aa.flat_first = flat->first_item;
-        aa.flat_nitems = flat->nitems;
-        aggregate_flat_kernel<<<dim3(flat->nitems), dim3(64), 0, st>>>(aa);
+    if (rest_blocks > 0) {
+        aa.full_blocks = 0;
+        aggregate_rest_kernel<<<dim3(static_cast<uint32_t>(rest_blocks)), dim3(64), 0, st>>>(aa);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return static_cast<int>(e);
     }

@@ -121,3 +121,15 @@ def test_top_codes_and_non_finite_copies_in_the_byte_path():
         assert np.array_equal(np.isnan(got), nan)
         assert bits_equal(got[~nan], want[~nan])
     assert np.isnan(o[int(lays[0].aux_offset[0]) + 12345])
+
+
+@pytest.mark.parametrize("R", [1, 4, 5, 8, 9])
+@pytest.mark.parametrize("EM", [(4, 3), (3, 9)])
+def test_parts_of_tails_and_batches_of_clients(R, EM):
+    """Ragged tails around the 256 elements that one workgroup takes of them, all-fp32 variables around the 256 of one of their
+    pieces, and numbers of clients around the batches whose loads are in flight together."""
+    sizes = [1, 31, 255, 256, 257, 2047, 2048, 2049, 2048 + 511, 2 * 2048 + 1793, 5 * 2048]
+    specs = [synth.VarSpec("w%d" % n, (n,), n, True) for n in sizes] + [synth.VarSpec("b%d" % n, (n,), n, False) for n in (1, 3, 255, 257, 1030, 4099)]
+    rng = np.random.default_rng(R)
+    masks = [np.array([s.is_matrix and (r == R - 1 or rng.random() < 0.6) for s in specs]) for r in range(R)]
+    run_case(specs, [EM] * len(specs), masks)
