@@ -41,20 +41,28 @@ inline SetGroups set_groups(const PlanGroup *groups, uint32_t ngroups) {
     return sg;
 }
 
+#ifndef OMC_TUNE_COPY_PARTS
+#define OMC_TUNE_COPY_PARTS 4
+#endif
+// Four waves to an item, each with all its loads in flight at once and no load behind its own stores: conversions of 115 M elements 199 -> 195
+// us, a change of a tenth of the 11-bit variables and the message 150 -> 143; eight waves 195 and 147.
+constexpr uint32_t kCopyParts = OMC_TUNE_COPY_PARTS;
+constexpr uint32_t kFewCopyItems = 1024;
+constexpr int kCopyPartElems = kChunkElems / static_cast<int>(kCopyParts);
 // fp32 variable of a set: plain copy between the aux-indexed array and the arena (16-byte pieces)
 template <int MODE>
-__device__ __forceinline__ void copy_fp32_item(const CodecArgs &ca, uint32_t item) {
+__device__ __forceinline__ void copy_fp32_item(const CodecArgs &ca, uint32_t item, uint32_t part) {
     const PlanItem *items = reinterpret_cast<const PlanItem *>(ca.plan + ca.item_off);
     const PlanVar *vars = reinterpret_cast<const PlanVar *>(ca.plan + ca.var_off);
     const PlanItem it = to_scalar_regs(items[item]);
     const PlanVar pv = to_scalar_regs(vars[it.var]);
-    const uint32_t lane = threadIdx.x;
+    const uint32_t lane = threadIdx.x & 63u;
     float *in_arena = reinterpret_cast<float *>(ca.arena + pv.data_offset);
     const float *src = (MODE == kCompress) ? ca.vin + pv.aux_offset : in_arena;
     float *dst = (MODE == kCompress) ? in_arena : ca.vout + pv.aux_offset;
-    const uint64_t begin = static_cast<uint64_t>(it.chunk) * kChunkElems;
-    constexpr int kBatch = 8;                              // pieces per lane in flight; both streams are touched once
-    for (int j0 = 0; j0 < kChunkElems / 256; j0 += kBatch) {
+    const uint64_t begin = static_cast<uint64_t>(it.chunk) * kChunkElems + part * kCopyPartElems;
+    constexpr int kBatch = kCopyPartElems / 256 < 8 ? kCopyPartElems / 256 : 8;   // pieces per lane in flight; both streams are touched once
+    for (int j0 = 0; j0 < kCopyPartElems / 256; j0 += kBatch) {
         const uint64_t e0 = begin + (static_cast<uint64_t>(j0) * 64 + lane) * 4;
         if (begin + static_cast<uint64_t>(j0 + kBatch) * 256 <= pv.n) {   // the whole batch is inside: wave-uniform
             f32x4 x[kBatch];
@@ -66,10 +74,26 @@ __device__ __forceinline__ void copy_fp32_item(const CodecArgs &ca, uint32_t ite
                 __builtin_nontemporal_store(x[u], reinterpret_cast<f32x4 *>(dst + e0 + static_cast<uint64_t>(u) * 256));
             continue;
         }
-        for (int u = 0; u < kBatch; ++u) {                   // the variable ends in this batch
+        if (begin + static_cast<uint64_t>(j0) * 256 >= pv.n) return;
+        f32x4 x[kBatch];                                     // the variable ends in this batch: whole pieces where there are any
+        uint32_t live[kBatch];                               // this lane's elements of a piece
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
             const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
-            for (int c = 0; c < 4; ++c)
-                if (e + c < pv.n) dst[e + c] = src[e + c];
+            live[u] = e >= pv.n ? 0u : pv.n - e < 4 ? static_cast<uint32_t>(pv.n - e) : 4u;
+            x[u] = f32x4{0, 0, 0, 0};
+            if (live[u] == 4) x[u] = *reinterpret_cast<const f32x4 *>(src + e);
+            else
+                for (uint32_t c = 0; c < 3; ++c)
+                    if (c < live[u]) x[u][c] = src[e + c];
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
+            if (live[u] == 4) *reinterpret_cast<f32x4 *>(dst + e) = x[u];
+            else
+                for (uint32_t c = 0; c < 3; ++c)
+                    if (c < live[u]) dst[e + c] = x[u][c];
         }
     }
 }
@@ -113,15 +137,18 @@ __device__ __forceinline__ void codec_tail(const CodecArgs &ca, uint32_t index, 
 
 // Grid: ragged tails, then full-tile work items, then copies of fp32 variables.
 template <int B, int MODE, int VARIANT>
-__global__ __launch_bounds__(64, (Tuning<MODE, B>::waves)) void codec_kernel(CodecArgs ca) {
-    __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsDwords];
+__global__ __launch_bounds__((64 * Tuning<MODE, B>::item_waves), (Tuning<MODE, B>::waves)) void codec_kernel(CodecArgs ca) {
+    constexpr int NW = Tuning<MODE, B>::item_waves;
+    __shared__ __attribute__((aligned(16))) uint32_t lds[NW * kLdsDwords];
     if (blockIdx.x < ca.tail_nitems) {
-        codec_tail<MODE>(ca, blockIdx.x, lds);
+        if (NW == 1 || threadIdx.x < 64) codec_tail<MODE>(ca, blockIdx.x, lds);
         return;
     }
     const uint32_t block = blockIdx.x - ca.tail_nitems;
     if (block >= ca.nitems) {
-        copy_fp32_item<MODE>(ca, ca.fp32_first + (block - ca.nitems));
+        const uint32_t part = (block - ca.nitems) * NW + (NW == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+        const bool many = ca.fp32_nitems > kFewCopyItems;    // (of few items, mostly vectors, the parts that are often empty come last)
+        copy_fp32_item<MODE>(ca, ca.fp32_first + (many ? part / kCopyParts : part % ca.fp32_nitems), many ? part % kCopyParts : part / ca.fp32_nitems);
         return;
     }
     uint32_t item = block, var = 0, chunk = block;
@@ -140,7 +167,15 @@ __global__ __launch_bounds__(64, (Tuning<MODE, B>::waves)) void codec_kernel(Cod
     TileArgs a{};
     codec_tile_args<MODE>(ca, pv, var, a);
     OptConst oc{};
-    do_chunk<B, MODE, VARIANT>(a, pv.fp, oc, chunk, lds, ca.ws + item, tiles);
+    do_chunk<B, MODE, VARIANT, true, NW>(a, pv.fp, oc, chunk, lds, ca.ws + item, tiles);
+}
+
+// Tails, the quantized variables' items and the parts of the copies.
+template <int B, int MODE, int VARIANT>
+inline void launch_codec(const CodecArgs &ca, hipStream_t st) {
+    constexpr uint32_t NW = Tuning<MODE, B>::item_waves;
+    static_assert(kCopyParts % NW == 0, "an fp32 item is whole workgroups");
+    codec_kernel<B, MODE, VARIANT><<<dim3(ca.tail_nitems + ca.nitems + ca.fp32_nitems * (kCopyParts / NW)), dim3(64 * NW), 0, st>>>(ca);
 }
 
 // Tails of a set that has no full tile at all.

@@ -16,29 +16,29 @@ __global__ __launch_bounds__(64 * NW) void finalize_single_kernel(const Partial 
 // Variants 0 / 1 (add-subtract or ldexp rounding) and, for code widths that can hold 16 mantissa bits,
 // 4 / 5 (the same with error-carrying sums).
 template <int BITS>
-static void launch_generic_variant(uint32_t variant, uint32_t grid, const CodecArgs &ca, hipStream_t st) {
+static void launch_generic_variant(uint32_t variant, const CodecArgs &ca, hipStream_t st) {
     if constexpr (BITS >= 18) {
-        if (variant == 4) { codec_kernel<BITS, kCompress, 4><<<dim3(grid), dim3(64), 0, st>>>(ca); return; }
-        if (variant == 5) { codec_kernel<BITS, kCompress, 5><<<dim3(grid), dim3(64), 0, st>>>(ca); return; }
+        if (variant == 4) { launch_codec<BITS, kCompress, 4>(ca, st); return; }
+        if (variant == 5) { launch_codec<BITS, kCompress, 5>(ca, st); return; }
     }
-    if (variant == 1) codec_kernel<BITS, kCompress, 1><<<dim3(grid), dim3(64), 0, st>>>(ca);
-    else codec_kernel<BITS, kCompress, 0><<<dim3(grid), dim3(64), 0, st>>>(ca);
+    if (variant == 1) launch_codec<BITS, kCompress, 1>(ca, st);
+    else launch_codec<BITS, kCompress, 0>(ca, st);
 }
 
-// One full-tile launch: `grid` workgroups of the kernel for (bits, variant).
-static int launch_full(uint32_t bits, uint32_t variant, uint32_t grid, const CodecArgs &ca, hipStream_t st) {
+// One full-tile launch of the kernel for (bits, variant).
+static int launch_full(uint32_t bits, uint32_t variant, const CodecArgs &ca, hipStream_t st) {
     if (bits == 8 && variant == 2) {
-        codec_kernel<8, kCompress, 2><<<dim3(grid), dim3(64), 0, st>>>(ca);
+        launch_codec<8, kCompress, 2>(ca, st);
         return static_cast<int>(hipGetLastError());
     }
     if (bits == 6 && variant == 3) {
-        codec_kernel<6, kCompress, 3><<<dim3(grid), dim3(64), 0, st>>>(ca);
+        launch_codec<6, kCompress, 3>(ca, st);
         return static_cast<int>(hipGetLastError());
     }
     switch (bits) {
 #define X(BITS)                                                                                  \
     case BITS:                                                                                   \
-        launch_generic_variant<BITS>(variant, grid, ca, st);                                     \
+        launch_generic_variant<BITS>(variant, ca, st);                                     \
         break;
         OMC_FOR_EACH_BITS(X)
 #undef X
@@ -79,7 +79,7 @@ int launch_compress(const float *v, const VarArgs &va, int use_pvt, void *codes,
     ca.vin = v;
     ca.ws = ws;
     ca.nitems = nchunks;
-    int rc = launch_full(va.fp.bits, va.fp.variant, ca.tail_nitems + ca.nitems, ca, st);
+    int rc = launch_full(va.fp.bits, va.fp.variant, ca, st);
     if (rc != 0) return rc;
     // the width of the reduction depends on the size alone, so results do not depend on the run
     const int exact = variant_exact(va.fp.variant) ? 1 : 0;
@@ -147,15 +147,16 @@ int launch_compress_set(const float *values, const PlanHeader *ph, const void *p
         ca.tail_first = sg.tail_first;
         ca.tail_nitems = rode ? 0u : sg.tail_nitems;
         rode = true;
-        const int rc = launch_full(g.bits, g.wide, ca.tail_nitems + ca.nitems + ca.fp32_nitems, ca, st);
+        const int rc = launch_full(g.bits, g.wide, ca, st);
         if (rc != 0) return rc;
     }
     if (!rode) {                                       // no full tile in the whole set
         ca.first_item = ca.nitems = 0;
         ca.fp32_first = sg.fp32_first;
         ca.fp32_nitems = sg.fp32_nitems;
+        ca.tail_nitems = 0;
         if (sg.fp32_nitems > 0) {
-            codec_kernel<8, kCompress, 0><<<dim3(sg.fp32_nitems), dim3(64), 0, st>>>(ca);
+            launch_codec<8, kCompress, 0>(ca, st);
             const int rc = static_cast<int>(hipGetLastError());
             if (rc != 0) return rc;
         }

@@ -3,11 +3,11 @@
 
 namespace omc {
 
-static int launch_full(uint32_t bits, uint32_t grid, const CodecArgs &ca, hipStream_t st) {
+static int launch_full(uint32_t bits, const CodecArgs &ca, hipStream_t st) {
     switch (bits) {
 #define X(BITS)                                                                       \
     case BITS:                                                                        \
-        codec_kernel<BITS, kDecompress, 0><<<dim3(grid), dim3(64), 0, st>>>(ca);      \
+        launch_codec<BITS, kDecompress, 0>(ca, st);      \
         break;
         OMC_FOR_EACH_BITS(X)
 #undef X
@@ -33,7 +33,7 @@ int launch_decompress(const void *codes, const VarArgs &va, const float *sb, flo
     ca.sb_in = sb;
     ca.vout = out;
     ca.nitems = nchunks;
-    return launch_full(va.fp.bits, ca.tail_nitems + ca.nitems, ca, st);
+    return launch_full(va.fp.bits, ca, st);
 }
 
 int launch_decompress_set(const void *arena, const PlanHeader *ph, const void *plan_dev, const float *sb_table,
@@ -61,15 +61,16 @@ int launch_decompress_set(const void *arena, const PlanHeader *ph, const void *p
         ca.tail_first = sg.tail_first;
         ca.tail_nitems = rode ? 0u : sg.tail_nitems;
         rode = true;
-        const int rc = launch_full(g.bits, ca.tail_nitems + ca.nitems + ca.fp32_nitems, ca, st);
+        const int rc = launch_full(g.bits, ca, st);
         if (rc != 0) return rc;
     }
     if (!rode) {                                       // no full tile in the whole set
         ca.first_item = ca.nitems = 0;
         ca.fp32_first = sg.fp32_first;
         ca.fp32_nitems = sg.fp32_nitems;
+        ca.tail_nitems = 0;
         if (sg.fp32_nitems > 0) {
-            codec_kernel<8, kDecompress, 0><<<dim3(sg.fp32_nitems), dim3(64), 0, st>>>(ca);
+            launch_codec<8, kDecompress, 0>(ca, st);
             const int rc = static_cast<int>(hipGetLastError());
             if (rc != 0) return rc;
         }

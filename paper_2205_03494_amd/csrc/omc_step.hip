@@ -18,7 +18,7 @@ namespace omc {
 
 template <int MODE>
 __global__ __launch_bounds__(64) void step_fp32_kernel(StepArgs sa) {
-    do_fp32_item<MODE>(sa, sa.first_item + blockIdx.x);
+    do_fp32_item<MODE>(sa, sa.first_item + blockIdx.x / kFp32Parts, blockIdx.x % kFp32Parts);
 }
 
 // Ragged tails of a set that has no full tile at all, one wave each.
@@ -124,9 +124,9 @@ int launch_step(void *arena, const PlanHeader *ph, const void *plan_dev, float *
         } else if (g.kind == kGroupFp32) {
             sa.fp32_first = g.first_item;
             sa.fp32_keep_items = fp32_keep_items;
-            if (opt.kind == OMC_SGD) step_fp32_kernel<kStepSgd><<<dim3(g.nitems), dim3(64), 0, st>>>(sa);
-            else if (opt.kind == OMC_MOMENTUM) step_fp32_kernel<kStepMomentum><<<dim3(g.nitems), dim3(64), 0, st>>>(sa);
-            else step_fp32_kernel<kStepAdam><<<dim3(g.nitems), dim3(64), 0, st>>>(sa);
+            if (opt.kind == OMC_SGD) step_fp32_kernel<kStepSgd><<<dim3(g.nitems * kFp32Parts), dim3(64), 0, st>>>(sa);
+            else if (opt.kind == OMC_MOMENTUM) step_fp32_kernel<kStepMomentum><<<dim3(g.nitems * kFp32Parts), dim3(64), 0, st>>>(sa);
+            else step_fp32_kernel<kStepAdam><<<dim3(g.nitems * kFp32Parts), dim3(64), 0, st>>>(sa);
             rc = static_cast<int>(hipGetLastError());
         } else {
             const uint32_t kept = take(g.nitems, static_cast<uint64_t>(tiles_per_chunk(g.bits)) * kTileElems * g.bits / 8);

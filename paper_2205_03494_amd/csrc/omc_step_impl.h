@@ -40,10 +40,19 @@ struct StepArgs {
 #define OMC_TUNE_FP32_NT 1
 #endif
 #ifndef OMC_TUNE_FP32_BATCH
-#define OMC_TUNE_FP32_BATCH 4
+#define OMC_TUNE_FP32_BATCH 2
 #endif
+#ifndef OMC_TUNE_FP32_PARTS
+#define OMC_TUNE_FP32_PARTS 8
+#endif
+// An fp32 item goes to eight waves, each with all its loads in flight at once: a wave that goes on to a second batch waits for the stores
+// of the first, as stores and loads share a counter.  Half of 115 M elements in fp32, 2 waves of two batches of four pieces / 4 of
+// one / 8 of one batch of two, us: Adam 569 / 556 / 538, momentum 366 / 356 / 352, SGD 195 / 190 / 184 (one wave, four batches: 591, 374, 201).
+constexpr uint32_t kFp32Parts = OMC_TUNE_FP32_PARTS;
+constexpr uint32_t kFewFp32Items = 1024;
+constexpr int kFp32PartElems = kChunkElems / static_cast<int>(kFp32Parts);
 template <int MODE, bool KEEPW>
-__device__ __forceinline__ void fp32_item_body(const StepArgs &sa, uint32_t item) {
+__device__ __forceinline__ void fp32_item_body(const StepArgs &sa, uint32_t item, uint32_t part) {
     constexpr bool NT = OMC_TUNE_FP32_NT != 0;
     constexpr bool NTW = NT && !KEEPW;                   // the values themselves: read and rewritten by every step
     constexpr int kFp32Batch = OMC_TUNE_FP32_BATCH;
@@ -51,14 +60,14 @@ __device__ __forceinline__ void fp32_item_body(const StepArgs &sa, uint32_t item
     const PlanVar *vars = reinterpret_cast<const PlanVar *>(sa.plan + sa.var_off);
     const PlanItem it = to_scalar_regs(items[item]);
     const PlanVar pv = to_scalar_regs(vars[it.var]);
-    const uint32_t lane = threadIdx.x;
+    const uint32_t lane = threadIdx.x & 63u;
     float *__restrict__ w = reinterpret_cast<float *>(sa.arena + pv.data_offset);
     const float *__restrict__ g = sa.grads + pv.aux_offset;
     float *__restrict__ m = sa.st0 ? sa.st0 + pv.aux_offset : nullptr;
     float *__restrict__ v = sa.st1 ? sa.st1 + pv.aux_offset : nullptr;
     const uint64_t n = pv.n;
-    const uint64_t begin = static_cast<uint64_t>(it.chunk) * kChunkElems;
-    constexpr int kIters = kChunkElems / 256;
+    const uint64_t begin = static_cast<uint64_t>(it.chunk) * kChunkElems + part * kFp32PartElems;
+    constexpr int kIters = kFp32PartElems / 256;
     static_assert(kIters % kFp32Batch == 0, "batches tile the chunk");
     auto ld = [&](const float *p, bool nt = NT) {
         const f32x4 *q = reinterpret_cast<const f32x4 *>(p);
@@ -96,23 +105,54 @@ __device__ __forceinline__ void fp32_item_body(const StepArgs &sa, uint32_t item
             }
             continue;
         }
-        for (int u = 0; u < kFp32Batch; ++u) {                                     // the variable ends in this batch
+        if (begin + static_cast<uint64_t>(j0) * 256 >= n) return;
+        // the variable ends in this batch: whole pieces where there are any, all loads in flight together
+        f32x4 xw[kFp32Batch], xg[kFp32Batch], xm[kFp32Batch], xv[kFp32Batch];
+        uint32_t live[kFp32Batch];                                                 // this lane's elements of a piece
+        auto ld_live = [&](const float *p, uint32_t count) {
+            f32x4 x = {0, 0, 0, 0};
+            if (count == 4) x = ld(p);
+            else
+                for (uint32_t c = 0; c < 3; ++c)
+                    if (c < count) x[c] = p[c];
+            return x;
+        };
+        auto st_live = [&](float *p, const f32x4 &x, uint32_t count) {
+            if (count == 4) st(p, x);
+            else
+                for (uint32_t c = 0; c < 3; ++c)
+                    if (c < count) p[c] = x[c];
+        };
+#pragma unroll
+        for (int u = 0; u < kFp32Batch; ++u) {
             const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
+            live[u] = e >= n ? 0u : n - e < 4 ? static_cast<uint32_t>(n - e) : 4u;
+            xw[u] = ld_live(w + e, live[u]);
+            xg[u] = ld_live(g + e, live[u]);
+            xm[u] = (MODE >= kStepMomentum) ? ld_live(m + e, live[u]) : f32x4{0, 0, 0, 0};
+            xv[u] = (MODE == kStepAdam) ? ld_live(v + e, live[u]) : f32x4{0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int u = 0; u < kFp32Batch; ++u) {
+            const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
+#pragma unroll
             for (int c = 0; c < 4; ++c) {
-                if (e + c >= n) break;
-                float tm = (MODE >= kStepMomentum) ? m[e + c] : 0.0f, tv = (MODE == kStepAdam) ? v[e + c] : 0.0f;
-                w[e + c] = apply_update<MODE>(w[e + c], g[e + c], tm, tv, sa.oc);
-                if (MODE >= kStepMomentum) m[e + c] = tm;
-                if (MODE == kStepAdam) v[e + c] = tv;
+                float tm = xm[u][c], tv = xv[u][c];
+                xw[u][c] = apply_update<MODE>(xw[u][c], xg[u][c], tm, tv, sa.oc);
+                xm[u][c] = tm;
+                xv[u][c] = tv;
             }
+            st_live(w + e, xw[u], live[u]);
+            if (MODE >= kStepMomentum) st_live(m + e, xm[u], live[u]);
+            if (MODE == kStepAdam) st_live(v + e, xv[u], live[u]);
         }
     }
 }
 
 template <int MODE>
-__device__ __forceinline__ void do_fp32_item(const StepArgs &sa, uint32_t item) {
-    if (item - sa.fp32_first < sa.fp32_keep_items) fp32_item_body<MODE, true>(sa, item);
-    else fp32_item_body<MODE, false>(sa, item);
+__device__ __forceinline__ void do_fp32_item(const StepArgs &sa, uint32_t item, uint32_t part) {
+    if (item - sa.fp32_first < sa.fp32_keep_items) fp32_item_body<MODE, true>(sa, item, part);
+    else fp32_item_body<MODE, false>(sa, item, part);
 }
 
 // What the kernels need of one quantized variable.
@@ -157,17 +197,22 @@ struct StepOccupancy {
     static constexpr int hi = capped ? OMC_TUNE_SGD8_MAX_WAVES : 8;
 };
 template <int B, int MODE, int VARIANT, bool KEEP>
-__global__ __attribute__((amdgpu_flat_work_group_size(64, 64)))
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * Tuning<MODE, B>::item_waves, 64 * Tuning<MODE, B>::item_waves)))
 __attribute__((amdgpu_waves_per_eu(StepOccupancy<B, MODE, VARIANT>::lo, StepOccupancy<B, MODE, VARIANT>::hi)))
 void step_kernel(StepArgs sa) {
-    __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsDwords];
+    constexpr int NW = Tuning<MODE, B>::item_waves;
+    __shared__ __attribute__((aligned(16))) uint32_t lds[NW * kLdsDwords];
     if (blockIdx.x < sa.tail_nitems) {
-        step_tail<MODE>(sa, blockIdx.x, lds);
+        if (NW == 1 || threadIdx.x < 64) step_tail<MODE>(sa, blockIdx.x, lds);
         return;
     }
     const uint32_t block = blockIdx.x - sa.tail_nitems;
-    if (block >= sa.nitems) {                            // the workgroups past the end serve fp32 variables
-        do_fp32_item<MODE>(sa, sa.fp32_first + (block - sa.nitems));
+    if (block >= sa.nitems) {                            // the workgroups past the end serve fp32 variables, a wave a part of an item
+        const uint32_t part = (block - sa.nitems) * NW + (NW == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+        // Many items are the matrices left in fp32: neighbouring parts at the same time.  Few are mostly vectors, whose later parts are
+        // empty: those come last (6 layers of 200 x 800 in 8 bits, SGD 22.2 -> 20.8 us; half of 115 M elements in fp32, SGD 184 -> 209).
+        const bool many = sa.fp32_nitems > kFewFp32Items;
+        do_fp32_item<MODE>(sa, sa.fp32_first + (many ? part / kFp32Parts : part % sa.fp32_nitems), many ? part % kFp32Parts : part / sa.fp32_nitems);
         return;
     }
     const PlanItem *items = reinterpret_cast<const PlanItem *>(sa.plan + sa.item_off);
@@ -178,12 +223,21 @@ void step_kernel(StepArgs sa) {
     TileArgs a{};
     step_tile_args(sa, pv, a);
     const FmtParams fp = pv.fp;
-    do_chunk<B, MODE, VARIANT, KEEP>(a, fp, sa.oc, it.chunk, lds, sa.ws + item);
+    do_chunk<B, MODE, VARIANT, KEEP, NW>(a, fp, sa.oc, it.chunk, lds, sa.ws + item);
+}
+
+// Tails, the quantized variables' items and the parts of the fp32 ones.
+template <int BITS, int MODE>
+inline dim3 step_grid(const StepArgs &sa) {
+    constexpr uint32_t kPartsPerBlock = Tuning<MODE, BITS>::item_waves;
+    static_assert(kFp32Parts % kPartsPerBlock == 0, "an fp32 item is whole workgroups");
+    return dim3(sa.tail_nitems + sa.nitems + sa.fp32_nitems * (kFp32Parts / kPartsPerBlock));
 }
 
 // Variants 0 / 1 and, for code widths that can hold 16 mantissa bits, 4 / 5 (error-carrying sums).
 template <int BITS, int MODE, bool KEEP>
-inline void launch_step_generic_variant(uint32_t variant, dim3 grid, dim3 block, const StepArgs &sa, hipStream_t st) {
+inline void launch_step_generic_variant(uint32_t variant, const StepArgs &sa, hipStream_t st) {
+    const dim3 grid = step_grid<BITS, MODE>(sa), block(64 * Tuning<MODE, BITS>::item_waves);
     if constexpr (BITS >= 18) {
         if (variant == 4) { step_kernel<BITS, MODE, 4, KEEP><<<grid, block, 0, st>>>(sa); return; }
         if (variant == 5) { step_kernel<BITS, MODE, 5, KEEP><<<grid, block, 0, st>>>(sa); return; }
@@ -194,20 +248,19 @@ inline void launch_step_generic_variant(uint32_t variant, dim3 grid, dim3 block,
 
 template <int MODE, bool KEEP>
 inline int launch_step_group_keep(uint32_t bits, uint32_t variant, const StepArgs &sa, hipStream_t st) {
-    const dim3 grid(sa.tail_nitems + sa.nitems + sa.fp32_nitems), block(64);
     // the hardware-conversion variant pays off where the vector ALU is the limit: plain SGD
     if (bits == 8 && variant == 2 && MODE <= OMC_TUNE_OCP_MAXMODE) {
-        step_kernel<8, MODE, 2, KEEP><<<grid, block, 0, st>>>(sa);
+        step_kernel<8, MODE, 2, KEEP><<<step_grid<8, MODE>(sa), dim3(64 * Tuning<MODE, 8>::item_waves), 0, st>>>(sa);
         return static_cast<int>(hipGetLastError());
     }
     if (bits == 6 && variant == 3 && MODE <= OMC_TUNE_FP6_MAXMODE) {
-        step_kernel<6, MODE, 3, KEEP><<<grid, block, 0, st>>>(sa);
+        step_kernel<6, MODE, 3, KEEP><<<step_grid<6, MODE>(sa), dim3(64 * Tuning<MODE, 6>::item_waves), 0, st>>>(sa);
         return static_cast<int>(hipGetLastError());
     }
     switch (bits) {
 #define X(BITS)                                                              \
     case BITS:                                                               \
-        launch_step_generic_variant<BITS, MODE, KEEP>(variant, grid, block, sa, st); \
+        launch_step_generic_variant<BITS, MODE, KEEP>(variant, sa, st); \
         break;
         OMC_FOR_EACH_BITS(X)
 #undef X

@@ -70,10 +70,16 @@ struct Tuning {
     // per SIMD, which measures 2 % slower there)
     static constexpr bool direct = (B % 8 == 0) && (OMC_TUNE_DIRECT != 0) && !(MODE == kStepMomentum && B == 8);
     static constexpr bool adam_wide = MODE == kStepAdam && B >= OMC_TUNE_ADAM_WIDE_BITS;
+    // Two waves take a work item together, a tile each, where there is state to write back.  A wave's stores and loads share a counter, so one
+    // that goes on to a second tile waits for its own stores before it can use what it loads.  115 M elements, one wave -> two, us:
+    // Adam 8 bits 481 -> 463, 11 bits 494 -> 475, 6 bits 486 -> 464; momentum 8 bits 292 -> 287, 13 bits 326 -> 318, 6 bits 291 -> 276; 604 M
+    // elements in 11 bits, momentum 1596 -> 1574.  Plain SGD prefers one (11 bits 139 -> 150, 8 bits under its cap 118 -> 138), and wide Adam,
+    // whose next tile's loads are in flight early, does not care.
+    static constexpr int item_waves = (MODE == kStepMomentum || (MODE == kStepAdam && !adam_wide)) ? 2 : 1;
     static constexpr int waves = adam_wide ? 1 : (MODE == kStepAdam) ? OMC_TUNE_WAVES_ADAM
                                  : (MODE == kStepMomentum) ? OMC_TUNE_WAVES_MOMENTUM : light;
-    // momentum: measured with every stream coming from HBM, the next tile's loads in flight during the arithmetic
-    // are worth 0.3 - 1.4 % at every code width (11 bit: 303 -> 300 us on 115 M elements)
+    // (momentum: where a wave has a second tile, that is 6-bit items of four; measured on items of one wave with every stream coming from
+    // HBM, the next tile's loads in flight during the arithmetic are worth 0.3 - 1.4 % at every code width)
     static constexpr bool prefetch = (MODE <= kStepSgd) ? (OMC_TUNE_PREFETCH != 0)
                                      : (adam_wide || MODE == kStepMomentum || OMC_TUNE_PREFETCH_HEAVY != 0);
 };
@@ -130,7 +136,12 @@ __device__ __forceinline__ uint32_t piece_slot_own(uint32_t k, uint32_t lane) {
     return lane * 8u + (k ^ (lane & 7u));
 }
 
-__device__ __forceinline__ void lds_fence() { __syncthreads(); }  // one wave per workgroup
+// Between one wave's LDS writes and its reads of what other lanes wrote (and the other way round).  The waves of a workgroup have
+// regions of their own, and a wave's LDS accesses are carried out in order, so only the compiler has to be held.
+__device__ __forceinline__ void lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 // ---- global <-> registers, coalesced, full tiles only --------------------------------------------
 // Streams that are read once per step are loaded with the non-temporal hint: the lines are not
@@ -787,7 +798,7 @@ __device__ __forceinline__ bool cycle_mx_fp6(const TileArgs &a, const OptConst &
 template <int B, int MODE, int VARIANT, bool PREFETCH, bool KEEP>
 __device__ __forceinline__ void finish_tile(const TileArgs &a, const FmtParams &fp, const OptConst &oc,
                                             uint64_t e0, uint32_t lane, uint32_t *lds, Stage<B, MODE> &st,
-                                            FitAcc &acc) {
+                                            FitAcc &acc, uint32_t to_next = kTileElems) {
     // hand every lane its 32 elements: consecutive ones, or (byte-multiple code widths) the four
     // consecutive elements of each of its eight 16-byte pieces, which the fp32 loads delivered already
     constexpr bool kDirect = Tuning<MODE, B>::direct;
@@ -810,7 +821,7 @@ __device__ __forceinline__ void finish_tile(const TileArgs &a, const FmtParams &
         if (MODE == kStepAdam) pieces_to_lanes(st.vq, rv, lds, lane);
     }
 
-    if (PREFETCH) issue_loads<B, MODE, KEEP>(a, e0 + kTileElems, lane, st);
+    if (PREFETCH) issue_loads<B, MODE, KEEP>(a, e0 + to_next, lane, st);
 
     uint32_t o[B];
     if constexpr (VARIANT == 2 && B == 8 && MODE != kDecompress) {
@@ -858,27 +869,66 @@ __device__ __forceinline__ void finish_tile(const TileArgs &a, const FmtParams &
 // as full tiles go, reduced into one Partial.  The caller guarantees at least one full tile.  `tiles` is
 // tiles_per_chunk(B) for the work items of a plan; the single-variable calls pass a larger number for huge
 // variables, so that the finalize has at most a few thousand partial sums to add.
-template <int B, int MODE, int VARIANT, bool KEEP = true>
+// NW waves share the item, wave w taking its tiles w, w + NW, ...; `lds`: kLdsDwords dwords a wave.
+template <int B, int MODE, int VARIANT, bool KEEP = true, int NW = 1>
 __device__ __forceinline__ void do_chunk(const TileArgs &a, const FmtParams &fp, const OptConst &oc,
                                          uint32_t chunk, uint32_t *lds, Partial *partial_out,
                                          uint32_t tiles = tiles_per_chunk(B)) {
-    const uint32_t lane = threadIdx.x;
+    const uint32_t lane = NW == 1 ? threadIdx.x : threadIdx.x & 63u;
+    const uint32_t wave = NW == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     FitAcc acc;
     acc.clear();
     const uint64_t first_tile = static_cast<uint64_t>(chunk) * tiles;
     const uint64_t full_tiles = a.n / kTileElems;
     const uint32_t ntiles = static_cast<uint32_t>((full_tiles - first_tile < tiles) ? full_tiles - first_tile : tiles);
     const uint64_t begin = first_tile * kTileElems;
-    Stage<B, MODE> st;
-    issue_loads<B, MODE, KEEP>(a, begin, lane, st);
-    for (uint32_t t = 0; t + 1 < ntiles; ++t) {
-        const uint64_t e0 = begin + static_cast<uint64_t>(t) * kTileElems;
-        finish_tile<B, MODE, VARIANT, Tuning<MODE, B>::prefetch, KEEP>(a, fp, oc, e0, lane, lds, st, acc);
-        if (!Tuning<MODE, B>::prefetch) issue_loads<B, MODE, KEEP>(a, e0 + kTileElems, lane, st);
+    uint32_t *mine = lds + wave * kLdsDwords;
+    uint32_t t = wave;
+    if (NW == 1 || t < ntiles) {
+        Stage<B, MODE> st;
+        issue_loads<B, MODE, KEEP>(a, begin + static_cast<uint64_t>(t) * kTileElems, lane, st);
+        for (; t + NW < ntiles; t += NW) {
+            const uint64_t e0 = begin + static_cast<uint64_t>(t) * kTileElems;
+            finish_tile<B, MODE, VARIANT, Tuning<MODE, B>::prefetch, KEEP>(a, fp, oc, e0, lane, mine, st, acc, NW * kTileElems);
+            if (!Tuning<MODE, B>::prefetch) issue_loads<B, MODE, KEEP>(a, e0 + NW * kTileElems, lane, st);
+        }
+        finish_tile<B, MODE, VARIANT, false, KEEP>(a, fp, oc, begin + static_cast<uint64_t>(t) * kTileElems, lane, mine, st, acc);
     }
-    finish_tile<B, MODE, VARIANT, false, KEEP>(a, fp, oc, begin + static_cast<uint64_t>(ntiles - 1) * kTileElems,
-                                               lane, lds, st, acc);
-    if (MODE != kDecompress) acc.template reduce_and_store<variant_exact(VARIANT)>(partial_out);
+    if (MODE == kDecompress) return;
+    constexpr bool kExact = variant_exact(VARIANT);
+    if constexpr (NW == 1) {
+        acc.template reduce_and_store<kExact>(partial_out);
+    } else {
+        Partial *sums = reinterpret_cast<Partial *>(lds);      // over the first wave's region
+        static_assert(NW * sizeof(Partial) <= 4 * kLdsDwords, "fits a wave's region");
+        __syncthreads();                                      // both waves are done with their regions
+        acc.template reduce_and_store<kExact>(sums + wave);
+        __syncthreads();
+        if (threadIdx.x != 0) return;
+        Partial p = sums[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
+            const Partial q = sums[w];
+            if (kExact) {                                     // (the error words are zero otherwise)
+                sum_with_error(p.sV, p.lV, q.sV);
+                sum_with_error(p.sT, p.lT, q.sT);
+                sum_with_error(p.sVT, p.lVT, q.sVT);
+                sum_with_error(p.sTT, p.lTT, q.sTT);
+                p.lV += q.lV;
+                p.lT += q.lT;
+                p.lVT += q.lVT;
+                p.lTT += q.lTT;
+            } else {
+                p.sV += q.sV;
+                p.sT += q.sT;
+                p.sVT += q.sVT;
+                p.sTT += q.sTT;
+            }
+            p.tmin = fminf(p.tmin, q.tmin);
+            p.tmax = fmaxf(p.tmax, q.tmax);
+        }
+        *partial_out = p;
+    }
 }
 
 // ---- the ragged tail of a variable ----------------------------------------------------------------------
@@ -898,7 +948,7 @@ constexpr uint32_t kTailBatch = 8;
 template <int MODE>
 __device__ __forceinline__ void do_tail(const TileArgs &a, const FmtParams &fp, const OptConst &oc, uint32_t *lds,
                                         Partial *partial_out) {
-    const uint32_t lane = threadIdx.x;
+    const uint32_t lane = threadIdx.x & 63u;                 // (the first wave of the workgroup)
     const uint32_t B = fp.bits;
     const uint64_t e0 = (a.n / kTileElems) * kTileElems;
     const uint32_t count = static_cast<uint32_t>(a.n - e0);

@@ -122,3 +122,26 @@ def test_reselection_between_rounds():
     ob, osb_b = oracle_arena(specs, mask_b, fmts, lay_b, mid_ref)
     assert np.array_equal(arena_b.cpu().numpy(), ob)
     assert bits_equal(sb_b.cpu().numpy()[mask_b], osb_b[mask_b])
+
+
+@pytest.mark.parametrize("many", [False, True])
+def test_parts_of_the_copies(many):
+    """Copies of fp32 variables that end around the 1024 elements of a part, the 256 of a piece and the four of a lane's, in few work items
+    (parts of all items in turn) and in many (an item's parts one after the other)."""
+    plain = [1, 3, 4, 5, 255, 257, 1021, 1023, 1024, 1025, 1283, 4095, 4096, 4097, 2 * 4096 + 1024 + 2] + ([1100 * 4096 + 6] if many else [])
+    specs = [synth.VarSpec("w", (2 * 2048 + 5,), 2 * 2048 + 5, True)] + [synth.VarSpec(f"b{n}", (n,), n, False) for n in plain]
+    mask = np.array([s.is_matrix for s in specs])
+    lay, plan = build(specs, mask, [(3, 7)] * len(specs))
+    vals = synth.init_values(lay, 12)
+    want, want_sb = oracle_arena(specs, mask, [(3, 7)] * len(specs), lay, vals)
+    arena, sb = gpu_compress_set(lay, plan, vals, len(specs))
+    assert np.array_equal(arena.cpu().numpy(), want)
+    out = torch.full((lay.aux_elems,), float("nan"), device="cuda")
+    omc.omc_decompress_set(arena, plan, sb, out)
+    torch.cuda.synchronize()
+    o = out.cpu().numpy()
+    for i, s in enumerate(specs):
+        a, end = int(lay.aux_offset[i]), int(lay.aux_offset[i + 1]) if i + 1 < len(specs) else lay.aux_elems
+        if not mask[i]:
+            assert bits_equal(o[a:a + s.n], vals[a:a + s.n]), s.name
+        assert np.all(np.isnan(o[a + s.n:end]))

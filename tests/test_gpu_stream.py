@@ -345,3 +345,20 @@ def test_tails_of_every_kind_in_one_launch(kind, lr, full_tile):
         vs.step_oracle(g, kind, lr, t)
         vs.step_gpu(to_dev(g), kind, lr, t)
         assert vs.compare(kind, f"t={t}") == 0
+
+
+@pytest.mark.parametrize("many", [False, True])
+@pytest.mark.parametrize("kind,lr", [(0, 0.05), (1, 0.05), (2, 1e-3)])
+def test_parts_of_fp32_items_and_waves_that_share_an_item(kind, lr, many):
+    """Variables in fp32 that end around the 512 elements of a part, the 256 of a batch's piece and the four of a lane's, in few work items
+    (parts of all items in turn) and in many (an item's parts one after the other); quantized ones of one to five full tiles, which
+    one wave or two take, in formats of two and of four tiles to an item."""
+    quantized = [(n, f) for f in ((4, 3), (2, 3), (3, 9), (4, 14)) for n in (2048, 2 * 2048, 3 * 2048 + 1, 5 * 2048 + 2047)]
+    plain = [1, 3, 4, 5, 255, 256, 257, 511, 512, 513, 515, 1021, 4095, 4096, 4097, 2 * 4096 + 3 * 512 + 2] + ([1100 * 4096 + 6] if many else [])
+    specs = [synth.VarSpec(f"w{i}", (n,), n, True) for i, (n, _) in enumerate(quantized)] + [synth.VarSpec(f"b{n}", (n,), n, False) for n in plain]
+    vs = VarSet(specs, [True] * len(quantized) + [False] * len(plain), [f for _, f in quantized] + [None] * len(plain), seed=11)
+    for t in range(1, 3):
+        g = synth.gradients(vs.lay, 0.05, 60 + t)
+        vs.step_oracle(g, kind, lr, t)
+        vs.step_gpu(to_dev(g), kind, lr, t)
+        assert vs.compare(kind, f"t={t}") == 0
