@@ -963,15 +963,11 @@ omc_status omc_reselect(const void *rs_host, const void *rs_dev, const void *are
     if (sb_old == sb_new) return OMC_ERR_SIZE;
     const uint8_t *hb = static_cast<const uint8_t *>(rs_host);
     const uint8_t *db = static_cast<const uint8_t *>(rs_dev);
-    int rc = 0;
-    if (rh->plan_c_bytes)
-        rc = launch_compress_set(static_cast<const float *>(arena_old), reinterpret_cast<const PlanHeader *>(hb + rh->plan_c_off),
-                                 db + rh->plan_c_off, arena_new, sb_new, static_cast<Partial *>(ws), stream);
-    if (rc == 0 && rh->plan_d_bytes)
-        rc = launch_decompress_set(arena_old, reinterpret_cast<const PlanHeader *>(hb + rh->plan_d_off), db + rh->plan_d_off,
-                                   sb_old, static_cast<float *>(arena_new), stream);
-    if (rc == 0)
-        rc = launch_reselect_sb(reinterpret_cast<const uint32_t *>(db + rh->action_off), rh->nvars, sb_old, sb_new, stream);
+    auto derived = [&](uint64_t off, uint64_t bytes) {
+        return bytes ? PlanPair{reinterpret_cast<const PlanHeader *>(hb + off), db + off} : PlanPair{nullptr, nullptr};
+    };
+    const int rc = launch_reselect(arena_old, sb_old, arena_new, sb_new, derived(rh->plan_c_off, rh->plan_c_bytes), derived(rh->plan_d_off, rh->plan_d_bytes),
+                                   reinterpret_cast<const uint32_t *>(db + rh->action_off), rh->nvars, static_cast<Partial *>(ws), stream);
     return rc == 0 ? OMC_OK : OMC_ERR_DEVICE;
 }
 

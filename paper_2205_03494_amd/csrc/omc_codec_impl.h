@@ -137,16 +137,14 @@ __device__ __forceinline__ void codec_tail(const CodecArgs &ca, uint32_t index, 
 
 // Grid: ragged tails, then full-tile work items, then copies of fp32 variables.
 template <int B, int MODE, int VARIANT>
-__global__ __launch_bounds__((64 * Tuning<MODE, B>::item_waves), (Tuning<MODE, B>::waves)) void codec_kernel(CodecArgs ca) {
-    constexpr int NW = Tuning<MODE, B>::item_waves;
-    __shared__ __attribute__((aligned(16))) uint32_t lds[NW * kLdsDwords];
-    if (blockIdx.x < ca.tail_nitems) {
-        if (NW == 1 || threadIdx.x < 64) codec_tail<MODE>(ca, blockIdx.x, lds);
+__device__ __forceinline__ void codec_block(const CodecArgs &ca, uint32_t index, uint32_t *lds) {
+    if (index < ca.tail_nitems) {
+        codec_tail<MODE>(ca, index, lds);
         return;
     }
-    const uint32_t block = blockIdx.x - ca.tail_nitems;
+    const uint32_t block = index - ca.tail_nitems;
     if (block >= ca.nitems) {
-        const uint32_t part = (block - ca.nitems) * NW + (NW == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+        const uint32_t part = block - ca.nitems;
         const bool many = ca.fp32_nitems > kFewCopyItems;    // (of few items, mostly vectors, the parts that are often empty come last)
         copy_fp32_item<MODE>(ca, ca.fp32_first + (many ? part / kCopyParts : part % ca.fp32_nitems), many ? part % kCopyParts : part / ca.fp32_nitems);
         return;
@@ -167,15 +165,21 @@ __global__ __launch_bounds__((64 * Tuning<MODE, B>::item_waves), (Tuning<MODE, B
     TileArgs a{};
     codec_tile_args<MODE>(ca, pv, var, a);
     OptConst oc{};
-    do_chunk<B, MODE, VARIANT, true, NW>(a, pv.fp, oc, chunk, lds, ca.ws + item, tiles);
+    do_chunk<B, MODE, VARIANT>(a, pv.fp, oc, chunk, lds, ca.ws + item, tiles);
+}
+
+template <int B, int MODE, int VARIANT>
+__global__ __launch_bounds__(64, (Tuning<MODE, B>::waves)) void codec_kernel(CodecArgs ca) {
+    __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsDwords];
+    codec_block<B, MODE, VARIANT>(ca, blockIdx.x, lds);
 }
 
 // Tails, the quantized variables' items and the parts of the copies.
+inline uint32_t codec_blocks(const CodecArgs &ca) { return ca.tail_nitems + ca.nitems + ca.fp32_nitems * kCopyParts; }
 template <int B, int MODE, int VARIANT>
 inline void launch_codec(const CodecArgs &ca, hipStream_t st) {
-    constexpr uint32_t NW = Tuning<MODE, B>::item_waves;
-    static_assert(kCopyParts % NW == 0, "an fp32 item is whole workgroups");
-    codec_kernel<B, MODE, VARIANT><<<dim3(ca.tail_nitems + ca.nitems + ca.fp32_nitems * (kCopyParts / NW)), dim3(64 * NW), 0, st>>>(ca);
+    static_assert(Tuning<MODE, B>::item_waves == 1, "one wave per workgroup");
+    codec_kernel<B, MODE, VARIANT><<<dim3(codec_blocks(ca)), dim3(64), 0, st>>>(ca);
 }
 
 // Tails of a set that has no full tile at all.

@@ -237,7 +237,13 @@ int launch_decompress_set(const void *arena, const PlanHeader *ph, const void *p
 int launch_step(void *arena, const PlanHeader *ph, const void *plan_dev, float *sb_table,
                 const float *grads, float *state0, float *state1, const omc_opt &opt, Partial *ws,
                 void *stream, void *const *events);
-int launch_reselect_sb(const uint32_t *actions_dev, uint32_t nvars, const float *sb_old, float *sb_new, void *stream);
+// A derived plan, host and device copy; host == nullptr: there is none.
+struct PlanPair {
+    const PlanHeader *host;
+    const uint8_t *dev;
+};
+int launch_reselect(const void *arena_old, const float *sb_old, void *arena_new, float *sb_new, const PlanPair &to_codes,
+                    const PlanPair &to_fp32, const uint32_t *actions_dev, uint32_t nvars, Partial *ws, void *stream);
 int launch_transport_pack(const PlanHeader *ph, const void *plan_dev, const void *arena, const float *sb_table,
                           void *msg_dev, const TransportHeader &th, void *stream);
 int gemm_fp8_tile(uint32_t M, uint32_t N, uint32_t K);

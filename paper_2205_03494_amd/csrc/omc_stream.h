@@ -1164,6 +1164,14 @@ __device__ __forceinline__ void finalize_variable(const Partial *__restrict__ pa
     sb_out[1] = static_cast<float>(b);
 }
 
+// New (s, b) of a quantized variable of a plan, by a workgroup of NW waves.
+template <int NW>
+__device__ __forceinline__ void finalize_plan_variable(const PlanVar &pv, const Partial *__restrict__ ws, float *__restrict__ sb_table, double *red) {
+    finalize_variable<NW>(pv.nitems ? ws + pv.first_item : ws, pv.nitems,
+                          pv.tail_item != kNoItem ? ws + pv.tail_item : nullptr, pv.n,
+                          !(pv.flags & OMC_VAR_NO_PVT), variant_exact(pv.fp.variant), sb_table + 2 * static_cast<uint64_t>(pv.sb_index), red);
+}
+
 // One workgroup of NW waves per variable: new (s, b) of every quantized variable of a plan.
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void finalize_plan_kernel(const uint8_t *__restrict__ plan, uint64_t var_off,
@@ -1172,10 +1180,7 @@ __global__ __launch_bounds__(64 * NW) void finalize_plan_kernel(const uint8_t *_
     __shared__ double red[NW * 10];
     const PlanVar *vars = reinterpret_cast<const PlanVar *>(plan + var_off);
     const PlanVar pv = to_scalar_regs(vars[blockIdx.x]);
-    if (!(pv.flags & OMC_VAR_QUANTIZED)) return;
-    finalize_variable<NW>(pv.nitems ? ws + pv.first_item : ws, pv.nitems,
-                          pv.tail_item != kNoItem ? ws + pv.tail_item : nullptr, pv.n,
-                          !(pv.flags & OMC_VAR_NO_PVT), variant_exact(pv.fp.variant), sb_table + 2 * static_cast<uint64_t>(pv.sb_index), red);
+    if (pv.flags & OMC_VAR_QUANTIZED) finalize_plan_variable<NW>(pv, ws, sb_table, red);
 }
 constexpr int kFinalizeWaves = 4;
 

@@ -1,6 +1,5 @@
 // Device side of omc_transport_pack (paper Sec. 1: parameters are kept and transported in compressed
-// form) and the (s, b) bookkeeping of omc_reselect (Sec. 2.5).  Pure data movement: no arithmetic of the
-// method happens here.
+// form).  Pure data movement: no arithmetic of the method happens here.
 #include "omc_stream.h"
 
 namespace omc {
@@ -167,27 +166,6 @@ int launch_transport_pack(const PlanHeader *ph, const void *plan_dev, const void
     transport_pack_kernel<<<dim3(static_cast<uint32_t>(runs)), dim3(kPackThreads), 0, st>>>(
         static_cast<const uint8_t *>(plan_dev), ph->var_off, static_cast<const uint8_t *>(arena),
         static_cast<uint8_t *>(msg_dev), th.payload_off, th.payload_bytes, ph->nvars, run);
-    return static_cast<int>(hipGetLastError());
-}
-
-// (s, b) of the variables that omc_reselect only moves: copied for those that stay quantized, (1, 0) for
-// those that are fp32 afterwards; the entries of newly quantized variables are written by their fit.
-__global__ __launch_bounds__(256) void reselect_sb_kernel(const uint32_t *__restrict__ actions, uint32_t nvars,
-                                                          const float *__restrict__ sb_old, float *__restrict__ sb_new) {
-    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= nvars) return;
-    const uint32_t a = actions[i];
-    if (a == kRsCopyQuantized) {
-        sb_new[2 * static_cast<uint64_t>(i)] = sb_old[2 * static_cast<uint64_t>(i)];
-        sb_new[2 * static_cast<uint64_t>(i) + 1] = sb_old[2 * static_cast<uint64_t>(i) + 1];
-    } else if (a != kRsToQuantized) {
-        sb_new[2 * static_cast<uint64_t>(i)] = 1.0f;
-        sb_new[2 * static_cast<uint64_t>(i) + 1] = 0.0f;
-    }
-}
-
-int launch_reselect_sb(const uint32_t *actions_dev, uint32_t nvars, const float *sb_old, float *sb_new, void *stream) {
-    reselect_sb_kernel<<<dim3((nvars + 255) / 256), dim3(256), 0, static_cast<hipStream_t>(stream)>>>(actions_dev, nvars, sb_old, sb_new);
     return static_cast<int>(hipGetLastError());
 }
 

@@ -289,3 +289,19 @@ def test_transport_payload_of_many_sizes(count):
         assert not host[at + b:at + (b + 15) // 16 * 16].any(), i
     table_sb = host[sb_off:sb_off + 8 * count].view(np.float32).reshape(count, 2)
     assert np.array_equal(table_sb, np.where(mask[:, None], sb, np.array([1.0, 0.0], np.float32)))
+
+
+@pytest.mark.parametrize("case", ["shared width", "one side each", "tails to codes", "tails to fp32", "tails against tiles"])
+def test_compressions_and_decompressions_in_one_launch(case):
+    """Widths that only one direction has, that both have, sets without a full tile in one direction or the other: each variable is
+    (size, format, quantized before, quantized after)."""
+    tile, tail = 2 * 2048 + 77, 700
+    variables = {
+        "shared width": [(tile, (3, 7), 0, 1), (tile, (3, 7), 1, 0), (tile, (4, 3), 1, 0), (tile, (4, 3), 0, 1), (tile, (8, 7), 0, 1), (tile, (5, 10), 1, 0), (tile, (2, 3), 0, 1)],
+        "one side each": [(tile, (3, 7), 0, 1), (tile, (4, 3), 1, 0), (tail, (4, 3), 1, 0), (5000, (4, 3), 0, 0)],
+        "tails to codes": [(tail, (3, 7), 0, 1), (tail, (4, 14), 0, 1), (9, (4, 3), 1, 1)],
+        "tails to fp32": [(tail, (3, 7), 1, 0), (tail, (4, 14), 1, 0), (9, (4, 3), 0, 0)],
+        "tails against tiles": [(tail, (3, 7), 0, 1), (tile, (4, 3), 1, 0), (tile, (5, 10), 1, 0)],
+    }[case]
+    specs = [synth.VarSpec(f"v{i}", (n,), n, True) for i, (n, _, _, _) in enumerate(variables)]
+    run_reselect(specs, [f for _, f, _, _ in variables], [bool(a) for _, _, a, _ in variables], [bool(b) for _, _, _, b in variables], steps=1, kind=0)
