@@ -278,11 +278,16 @@ void gemm_bits_kernel(BitsArgs ga) {
     store_tile<TEAMS * WN, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 32 * TN * wn, N, acc, rowsum, 32 * TM * wm, lane, s, b);
 }
 
-// (11-bit codes; the other widths differ in the decode alone.)  8192 x 4096 x 1024: 82 us with 256 x 256, 107 with 128 x 128;
-// 2048 x 512 x 2048: 50 us with 256 x 256, 27 with 128 x 128, 19 / 14 / 13 with 64 x 64 and 1 / 2 / 4 teams.
+// Fitted to 8-, 11- and 13-bit codes, 48 sizes in both directions, every tile timed: the chosen one takes 0.6 % longer than the best of these on
+// average, at worst 5 %.  256 x 128 by four waves, one to a SIMD, each of 128 x 64, decodes a code for 256 rows and reads its
+// fragments from LDS half as often as 128 x 256 by eight (9216 x 896 x 1120, input gradient, 13 bits, 30 us; 36 with 128 x 128; 8192 x 1024 x 2048 46;
+// 51 with 128 x 256).  128 x 64 by four waves, three workgroups on a unit, fills the chip with half the decoding of 64 x 64 (2304 x 3712 x 192
+// 13.2 us, 15.2 with 64 x 64, 14.5 with 128 x 128; 1536 x 2944 x 704 16.4, 19.8, 18.4).  Against 128 x 256 and 64 x 64 in their places, as it was: 4 % over
+// the 48 sizes.  8192 x 4096 x 1024: 82 us with 256 x 256, 107 with 128 x 128; 2048 x 512 x 2048: 50 with 256 x 256, 27 with 128 x 128, 14 / 13 with
+// 64 x 64 and 2 / 4 teams.
 static constexpr GemmTile kBitsTiles[] = {
-    {256, 256, 1, 1, 7.0, 1.30, 1.855, 8.0}, {128, 256, 1, 1, 4.7, 1.00, 1.18, 5.0}, {128, 128, 1, 2, 3.0, 0.76, 0.66, 2.6},
-    {64, 64, 1, 4, 2.2, 0.54, 0.263, 0.65},  {64, 64, 2, 2, 1.0, 0.70, 0.50, 1.6}, {64, 64, 4, 1, 1.0, 1.15, 1.15, 3.2},
+    {256, 256, 1, 1, 5.27, 1.438, 2.178, 8.19}, {256, 128, 1, 1, 4.55, 1.024, 1.127, 5.49}, {128, 128, 1, 2, 3.26, 0.586, 0.769, 2.55},
+    {128, 64, 1, 3, 2.90, 0.651, 0.403, 1.17},  {64, 64, 2, 2, 2.57, 0.888, 0.527, 1.08},  {64, 64, 4, 1, 3.27, 1.230, 1.227, 1.94},
 };
 
 template <int B, bool TRANS>
@@ -290,9 +295,9 @@ inline int launch_bits_tile(int which, const BitsArgs &ga, hipStream_t st) {
     const dim3 grid(ga.tiles_m * ga.tiles_n);
     switch (which) {
         case 0: gemm_bits_kernel<B, 32, 2, 4, 4, 2, 1, 2, TRANS><<<grid, dim3(512), 0, st>>>(ga); break;
-        case 1: gemm_bits_kernel<B, 32, 2, 4, 2, 2, 1, 2, TRANS><<<grid, dim3(512), 0, st>>>(ga); break;
+        case 1: gemm_bits_kernel<B, 32, 2, 2, 4, 2, 1, 1, TRANS><<<grid, dim3(256), 0, st>>>(ga); break;
         case 2: gemm_bits_kernel<B, 16, 2, 4, 2, 1, 1, 4, TRANS><<<grid, dim3(512), 0, st>>>(ga); break;
-        case 3: gemm_bits_kernel<B, 16, 2, 2, 1, 1, 1, 4, TRANS><<<grid, dim3(256), 0, st>>>(ga); break;
+        case 3: gemm_bits_kernel<B, 16, 2, 2, 2, 1, 1, 3, TRANS><<<grid, dim3(256), 0, st>>>(ga); break;
         case 4: gemm_bits_kernel<B, 16, 2, 2, 1, 1, 2, 4, TRANS><<<grid, dim3(512), 0, st>>>(ga); break;
         case 5: gemm_bits_kernel<B, 16, 2, 2, 1, 1, 4, 4, TRANS><<<grid, dim3(1024), 0, st>>>(ga); break;
         default: return static_cast<int>(hipErrorInvalidValue);
