@@ -60,13 +60,13 @@ __device__ __forceinline__ void wait_stage(uint32_t j, uint32_t total) {
     else wait_loads_and_sync<0>();
 }
 
-// Host: which of a kernel's tile sizes to launch for an M x N result over K.  All figures are measured, in us: `base` is a launch
+// Host: which of a kernel's tile sizes to launch for an M x N result over K.  All figures are in us and come from measurements: `base` stands for a launch
 // with one tile per compute unit and nothing to multiply, `step` a step of 64 k (of TEAMS times as many with several teams) when
 // every compute unit has at most `resident` workgroups, `loaded` what a step costs per workgroup and unit when all 256 units
 // are busy (matrix cores, LDS and memory together), `stores` the C stores of 256 tiles (with several teams, also
-// what a round of workgroups loses before its first and after its last step).  Over 54 random sizes (M 256 - 16384, N 128 - 4096, K 256 - 4096,
-// both directions) of S1E4M3 codes the chosen tile takes 4.5 % longer than the best one on average and more than 7 % longer in 15 of them, at
-// worst 25 % (9728 x 128 x 3680, input gradient: 27.3 us with 64 x 64 by two teams, 21.8 with 64 x 128); over 48 of other formats 0.6 %, at worst 5 %.
+// what a round of workgroups loses before its first and after its last step).  They are fitted
+// to random sizes (M 256 - 16384, N 128 - 4096, K 128 - 4096, both directions) with every tile timed: over 78 of S1E4M3 codes the chosen tile takes
+// 0.7 % longer than the best one on average, at worst 15 %; over 48 of other formats 0.6 %, at worst 5 %.
 struct GemmTile {
     uint32_t bm, bn, teams, resident;
     double base, step, loaded, stores;
