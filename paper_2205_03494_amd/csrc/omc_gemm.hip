@@ -11,7 +11,9 @@ namespace omc {
 
 // Host only, not part of the interface: index of the tile that a product of these sizes takes (columns N of the result, contraction K), in
 // the table of the FP8 kernel or of the other formats' kernel.
-extern "C" int omc_internal_gemm_tile(int fp8, uint32_t M, uint32_t N, uint32_t K) { return fp8 ? gemm_fp8_tile(M, N, K) : pick_tile(kBitsTiles, M, N, K); }
+extern "C" int omc_internal_gemm_tile(int fp8, uint32_t M, uint32_t N, uint32_t K) { return fp8 ? gemm_fp8_tile(M, N, K) : gemm_bits_tile(M, N, K); }
+// Host only, not part of the interface: into how many chains of fp32 sums, of teams and in a team, that product's contraction is dealt.
+extern "C" uint32_t omc_internal_gemm_sums(int fp8, uint32_t M, uint32_t N, uint32_t K) { return fp8 ? gemm_fp8_sums(M, N, K) : gemm_bits_sums(M, N, K); }
 
 // C[M x N] = A[M x K] * W (trans == 0, W packed as [K x N]) or A * W^T (trans != 0, W packed as [N x K])
 int launch_dequant_gemm(const uint16_t *A, const void *codes, const FmtParams &fp, const float *sb, float *C,

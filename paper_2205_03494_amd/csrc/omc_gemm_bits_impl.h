@@ -15,6 +15,8 @@
 // A staged through registers, a patch of 4 x 4 codes per thread with run-time shifts; 256 x 128 by 16 waves for long contractions):
 // forward 8192 x 4096 x 1024 104 -> 82 us, 2048 x 2048 x 512 18.6 -> 11.4, input gradient 2048 x 512 x 2048 53.6 -> 13.
 #pragma once
+#include <algorithm>
+
 #include "omc_mma.h"
 
 #pragma clang fp contract(off)
@@ -86,8 +88,9 @@ __device__ __forceinline__ u32x4 decode_piece(const Unit<B, U> &u, int i, const 
 }
 
 // WM x WN waves of TM x TN matrix tiles (32 x 32) each, TEAMS times: team t multiplies the steps t, t + TEAMS, ... of the
-// contraction in LDS stages of its own, and team 0 adds up the teams' tiles in order.  OCC waves per SIMD.
-template <int B, int U, int WM, int WN, int TM, int TN, int TEAMS, int OCC, bool TRANS>
+// contraction in LDS stages of its own, and team 0 adds up the teams' tiles in order.  A team's sums are CHAINS chains (which of
+// them, the quarter of the step decides).  OCC waves per SIMD.
+template <int B, int U, int WM, int WN, int TM, int TN, int TEAMS, int CHAINS, int OCC, bool TRANS>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN * TEAMS, 64 * WM * WN * TEAMS))) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 void gemm_bits_kernel(BitsArgs ga) {
     constexpr int NW = WM * WN, NT = 64 * NW, BM = 32 * TM * WM, BN = 32 * TN * WN;
@@ -192,25 +195,16 @@ void gemm_bits_kernel(BitsArgs ga) {
         }
     };
 
-    f32x16 acc[TM][TN];
-    float rsum[TM];
-#pragma unroll
-    for (int mi = 0; mi < TM; ++mi) {
-        rsum[mi] = 0.0f;
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
-    }
-    auto multiply = [&](const Frags &f, bool sum) {
+    f32x16 acc[CHAINS][TM][TN];
+    RowSums<WN, TM, CHAINS> rsum;
+    auto multiply = [&](const Frags &f, auto quarter, bool sum) {
+        constexpr int Q = decltype(quarter)::value, chain = Q % CHAINS;
 #pragma unroll
         for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
-            for (int mi = 0; mi < TM; ++mi) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mi], f.w[ni], acc[mi][ni], 0, 0, 0);
-        if (sum) {
-#pragma unroll
-            for (int mi = 0; mi < TM; ++mi) rsum[mi] = add_fragment(f.a[mi], rsum[mi]);
-        }
+            for (int mi = 0; mi < TM; ++mi)
+                acc[chain][mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mi], f.w[ni], acc[chain][mi][ni], 0, 0, 0);
+        if (sum) rsum.template add<Q>(f.a);
     };
 
     // step i: A and W of the step are in stage `cur`; the dwords of step i + 1 are in `next` (asked for during step i - 1)
@@ -219,9 +213,17 @@ void gemm_bits_kernel(BitsArgs ga) {
     Unit<B, U> now, next;
 #pragma unroll
     for (int i = 0; i < Unit<B, U>::kDwords; ++i) next.w[i] = 0;
+    auto clear = [&]() {
+        clear_chains(acc);
+        rsum.clear();
+    };
+    if (CHAINS == 1) clear();
     if (steps > 0) {
         load_a(0, 0);
         load_w(0, next);
+    }
+    if (CHAINS > 1) clear();                                  // (while they are on their way)
+    if (steps > 0) {
         now = next;
         if (steps > 1) load_w(1, next);
         align_unit<B, U>(now, u_shift);
@@ -238,16 +240,16 @@ void gemm_bits_kernel(BitsArgs ga) {
         if (more1) load_a(other, i + 1);
         if (more2) load_w(i + 2, next);
         if (more1) align_unit<B, U>(now, u_shift);
-        if (!first) multiply(f1, false);
+        if (!first) multiply(f1, UintTag<3>{}, false);
         read_frags(cur, a_at[1], w_at[1], f1);
         if (more1) store_piece(other, now, 0);
-        multiply(f0, true);
+        multiply(f0, UintTag<0>{}, true);
         read_frags(cur, a_at[2], w_at[2], f0);
         if (more1) store_piece(other, now, 1);
-        multiply(f1, false);
+        multiply(f1, UintTag<1>{}, false);
         read_frags(cur, a_at[3], w_at[3], f1);
         if (more1 && kPieces > 2) store_piece(other, now, 2);
-        multiply(f0, WN == 2);
+        multiply(f0, UintTag<2>{}, WN == 2);
         if (more1 && kPieces > 2) store_piece(other, now, 3);
         cur = other;
     };
@@ -256,26 +258,26 @@ void gemm_bits_kernel(BitsArgs ga) {
         uint32_t i = 1;
         for (; i + 2 < steps; ++i) step(i, false, true, true);
         for (; i < full; ++i) step(i, false, i + 1 < steps, i + 2 < steps);
-        multiply(f1, false);
+        multiply(f1, UintTag<3>{}, false);
     }
     if (full < steps) {                                       // 32 k more: two quarters
         wait_loads_and_sync<0>();
-        for (uint32_t ks = 0; ks < 2; ++ks) {
-            read_frags(cur, a_place(ks), w_place(ks), f0);
-            multiply(f0, false);
-            if (ks % WN == wn) {
-#pragma unroll
-                for (int mi = 0; mi < TM; ++mi) rsum[mi] = add_fragment(f0.a[mi], rsum[mi]);
-            }
-        }
+        auto quarter = [&](auto ks) {
+            read_frags(cur, a_place(ks.value), w_place(ks.value), f0);
+            multiply(f0, ks, false);
+            if (ks.value % WN == wn) rsum.template add<0>(f0.a);
+        };
+        quarter(UintTag<0>{});
+        quarter(UintTag<1>{});
     }
     for (uint32_t i = steps; i < (steps_k + TEAMS - 1) / TEAMS; ++i) wait_loads_and_sync<0>();   // teams wait for each other
     wait_loads_and_sync<0>();                                 // nobody reads a stage any more
     const float s = ga.sb ? ga.sb[0] : 1.0f, b = ga.sb ? ga.sb[1] : 0.0f;
     float *rowsum = reinterpret_cast<float *>(lds_all);       // [TEAMS * WN][BM]
-    publish_row_sums<WN, BM, TM>(rowsum, rsum, ga.sb != nullptr, team, 32 * TM * wm, wn, lane);
-    if (!add_teams<TEAMS, NW, TM, TN>(rowsum + TEAMS * WN * BM, acc, team, wave, lane)) return;
-    store_tile<TEAMS * WN, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 32 * TN * wn, N, acc, rowsum, 32 * TM * wm, lane, s, b);
+    join_chains(acc);
+    publish_row_sums<WN, BM, TM>(rowsum, rsum.total(), ga.sb != nullptr, team, 32 * TM * wm, wn, lane);
+    if (!add_teams<TEAMS, NW, TM, TN>(rowsum + TEAMS * WN * BM, acc[0], team, wave, lane)) return;
+    store_tile<TEAMS * WN, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 32 * TN * wn, N, acc[0], rowsum, 32 * TM * wm, lane, s, b);
 }
 
 // Fitted to 8-, 11- and 13-bit codes, 48 sizes in both directions, every tile timed: the chosen one takes 0.6 % longer than the best of these on
@@ -286,32 +288,60 @@ void gemm_bits_kernel(BitsArgs ga) {
 // the 48 sizes.  8192 x 4096 x 1024: 82 us with 256 x 256, 107 with 128 x 128; 2048 x 512 x 2048: 50 with 256 x 256, 27 with 128 x 128, 14 / 13 with
 // 64 x 64 and 2 / 4 teams.
 static constexpr GemmTile kBitsTiles[] = {
-    {256, 256, 1, 1, 5.27, 1.438, 2.178, 8.19}, {256, 128, 1, 1, 4.55, 1.024, 1.127, 5.49}, {128, 128, 1, 2, 3.26, 0.586, 0.769, 2.55},
-    {128, 64, 1, 3, 2.90, 0.651, 0.403, 1.17},  {64, 64, 2, 2, 2.57, 0.888, 0.527, 1.08},  {64, 64, 4, 1, 3.27, 1.230, 1.227, 1.94},
+    {256, 256, 1, 1, 1, 5.27, 1.438, 2.178, 8.19}, {256, 128, 1, 1, 1, 4.55, 1.024, 1.127, 5.49}, {128, 128, 1, 2, 2, 3.26, 0.586, 0.769, 2.55},
+    {128, 64, 1, 2, 3, 2.90, 0.651, 0.403, 1.17},  {64, 64, 2, 2, 2, 2.57, 0.888, 0.527, 1.08},  {64, 64, 4, 1, 1, 3.27, 1.230, 1.227, 1.94},
 };
 
+// Chains of fp32 sums that a contraction is dealt into, by the result's 64 x 64 tiles and the steps: at least as many as it was dealt into when the
+// choice fell on two or four teams for more of the small products (11 bits, 5888 x 256 x 192: 2.7e-8 off 64 bits in two chains, 3.1e-8 in one).  The
+// second chain of 128 x 128 does not fit 128 registers: that kernel has a compute unit to itself, which costs nothing, as results that
+// want two chains have at most 192 of these tiles.
+inline uint32_t bits_chains(uint32_t M, uint32_t N, uint32_t K) {
+    const uint64_t small_tiles = static_cast<uint64_t>(M / 64) * (N / 64), steps = (static_cast<uint64_t>(K) + 63) / 64;
+    if (steps >= 3 && small_tiles <= std::min<uint64_t>(256, 16 + 9 * steps)) return 4;
+    return small_tiles <= (steps > 40 ? 768 : steps <= 3 ? 400 : std::min<uint64_t>(512, 428 + 6 * steps)) ? 2 : 1;
+}
+inline int gemm_bits_tile(uint32_t M, uint32_t N, uint32_t K) { return pick_tile(kBitsTiles, M, N, K, bits_chains(M, N, K)); }
+inline uint32_t gemm_bits_sums(uint32_t M, uint32_t N, uint32_t K) {
+    const int which = gemm_bits_tile(M, N, K);
+    return which < 0 ? 0 : kBitsTiles[which].teams * chains_per_team(kBitsTiles[which], bits_chains(M, N, K));
+}
+
+template <int B, int WN, int U, int TM, int TN, int TEAMS, int CHAINS, int OCC, bool TRANS>
+inline void launch_bits_one(const BitsArgs &ga, hipStream_t st) {
+    gemm_bits_kernel<B, U, 2, WN, TM, TN, TEAMS, CHAINS, OCC, TRANS><<<dim3(ga.tiles_m * ga.tiles_n), dim3(128 * WN * TEAMS), 0, st>>>(ga);
+}
 template <int B, bool TRANS>
-inline int launch_bits_tile(int which, const BitsArgs &ga, hipStream_t st) {
-    const dim3 grid(ga.tiles_m * ga.tiles_n);
+inline int launch_bits_tile(int which, uint32_t chains, const BitsArgs &ga, hipStream_t st) {
     switch (which) {
-        case 0: gemm_bits_kernel<B, 32, 2, 4, 4, 2, 1, 2, TRANS><<<grid, dim3(512), 0, st>>>(ga); break;
-        case 1: gemm_bits_kernel<B, 32, 2, 2, 4, 2, 1, 1, TRANS><<<grid, dim3(256), 0, st>>>(ga); break;
-        case 2: gemm_bits_kernel<B, 16, 2, 4, 2, 1, 1, 4, TRANS><<<grid, dim3(512), 0, st>>>(ga); break;
-        case 3: gemm_bits_kernel<B, 16, 2, 2, 2, 1, 1, 3, TRANS><<<grid, dim3(256), 0, st>>>(ga); break;
-        case 4: gemm_bits_kernel<B, 16, 2, 2, 1, 1, 2, 4, TRANS><<<grid, dim3(512), 0, st>>>(ga); break;
-        case 5: gemm_bits_kernel<B, 16, 2, 2, 1, 1, 4, 4, TRANS><<<grid, dim3(1024), 0, st>>>(ga); break;
+        case 0: launch_bits_one<B, 4, 32, 4, 2, 1, 1, 2, TRANS>(ga, st); break;
+        case 1: launch_bits_one<B, 2, 32, 4, 2, 1, 1, 1, TRANS>(ga, st); break;
+        case 2:
+            if (chains == 2) launch_bits_one<B, 4, 16, 2, 1, 1, 2, 2, TRANS>(ga, st);
+            else launch_bits_one<B, 4, 16, 2, 1, 1, 1, 4, TRANS>(ga, st);
+            break;
+        case 3:
+            if (chains == 2) launch_bits_one<B, 2, 16, 2, 1, 1, 2, 3, TRANS>(ga, st);
+            else launch_bits_one<B, 2, 16, 2, 1, 1, 1, 3, TRANS>(ga, st);
+            break;
+        case 4:
+            if (chains == 2) launch_bits_one<B, 2, 16, 1, 1, 2, 2, 4, TRANS>(ga, st);
+            else launch_bits_one<B, 2, 16, 1, 1, 2, 1, 4, TRANS>(ga, st);
+            break;
+        case 5: launch_bits_one<B, 2, 16, 1, 1, 4, 1, 4, TRANS>(ga, st); break;
         default: return static_cast<int>(hipErrorInvalidValue);
     }
     return static_cast<int>(hipGetLastError());
 }
 template <int B>
 inline int launch_bits(const BitsArgs &args, uint32_t M, int trans, hipStream_t st) {
-    const int which = pick_tile(kBitsTiles, M, args.N, args.K);
+    const int which = gemm_bits_tile(M, args.N, args.K);
     if (which < 0) return static_cast<int>(hipErrorInvalidValue);
     BitsArgs ga = args;
     ga.tiles_m = M / kBitsTiles[which].bm;
     ga.tiles_n = args.N / kBitsTiles[which].bn;
-    return trans ? launch_bits_tile<B, true>(which, ga, st) : launch_bits_tile<B, false>(which, ga, st);
+    const uint32_t chains = chains_per_team(kBitsTiles[which], bits_chains(M, args.N, args.K));
+    return trans ? launch_bits_tile<B, true>(which, chains, ga, st) : launch_bits_tile<B, false>(which, chains, ga, st);
 }
 
 // one translation unit per range of widths

@@ -32,6 +32,8 @@
 // of theirs, for fragments that are read one quarter of a step ahead, for the step's barrier, and at a contraction of 1024 for the C
 // stores where nothing covers them; 1300 TFLOP/s at 8192 x 4096 x 4096.  Not for LDS bandwidth (67.6 -> 67.1 us at the first shape without
 // the bank conflicts there were).
+#include <algorithm>
+
 #include "omc_mma.h"
 
 #pragma clang fp contract(off)
@@ -71,8 +73,9 @@ struct Fp8Args {
 };
 
 // WM x WN waves of TM x TN matrix tiles (32 x 32) each, TEAMS times: team t multiplies the steps t, t + TEAMS, ... of the
-// contraction in LDS stages of its own, and team 0 adds up the teams' tiles in order.  S stages, OCC waves per SIMD.
-template <int WM, int WN, int TM, int TN, int TEAMS, int S, int OCC, bool TRANS>
+// contraction in LDS stages of its own, and team 0 adds up the teams' tiles in order.  A team's sums are CHAINS chains (which
+// of them, the quarter of the step decides).  S stages, OCC waves per SIMD.
+template <int WM, int WN, int TM, int TN, int TEAMS, int CHAINS, int S, int OCC, bool TRANS>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN * TEAMS, 64 * WM * WN * TEAMS))) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 void gemm_fp8_kernel(Fp8Args ga) {
     constexpr int NW = WM * WN, BM = 32 * TM * WM, BN = 32 * TN * WN;
@@ -167,37 +170,33 @@ void gemm_fp8_kernel(Fp8Args ga) {
         }
     };
 
-    f32x16 acc[TM][TN];
-    float rsum[TM];
+    f32x16 acc[CHAINS][TM][TN];
+    RowSums<WN, TM, CHAINS> rsum;
     auto holds_nan = [&]() {                                  // one row of every column tells
         bool bad = false;
 #pragma unroll
-        for (int ni = 0; ni < TN; ++ni) bad = bad || acc[0][ni][0] != acc[0][ni][0];
+        for (int ni = 0; ni < TN; ++ni) bad = bad || acc[0][0][ni][0] != acc[0][0][ni][0];
         return __any(bad);
     };
     // Without EXACT it may stop on the way, in all waves of the workgroup alike, with a NaN in some wave's sums.
     auto compute = [&](auto exact_tag) {
         constexpr bool EXACT = decltype(exact_tag)::value;
-#pragma unroll
-        for (int mi = 0; mi < TM; ++mi) {
-            rsum[mi] = 0.0f;
-#pragma unroll
-            for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
-        }
-        auto multiply = [&](const Frags &f, bool sum) {
+        auto multiply = [&](const Frags &f, auto quarter, bool sum) {
+            constexpr int Q = decltype(quarter)::value, chain = Q % CHAINS;
 #pragma unroll
             for (int ni = 0; ni < TN; ++ni) {
                 const bf16x8 w = fp8x8_to_bf16<EXACT>(f.w[ni]);
 #pragma unroll
-                for (int mi = 0; mi < TM; ++mi) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mi], w, acc[mi][ni], 0, 0, 0);
+                for (int mi = 0; mi < TM; ++mi)
+                    acc[chain][mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mi], w, acc[chain][mi][ni], 0, 0, 0);
             }
-            if (sum) {
-#pragma unroll
-                for (int mi = 0; mi < TM; ++mi) rsum[mi] = add_fragment(f.a[mi], rsum[mi]);
-            }
+            if (sum) rsum.template add<Q>(f.a);
         };
+        auto clear = [&]() {
+            clear_chains(acc);
+            rsum.clear();
+        };
+        if (CHAINS == 1) clear();
         const uint32_t shortest = stages_k / TEAMS;
         uint32_t steady_end = stages > S - 1 ? stages - (S - 1) : 0, full_end = full, slots = (stages_k + TEAMS - 1) / TEAMS;
         bool half = full < stages;
@@ -205,11 +204,11 @@ void gemm_fp8_kernel(Fp8Args ga) {
         uint32_t cur = 0, far = (S - 1) * kStage;
         auto rest_of_step = [&]() {                           // everything but the first quarter's reads and the last one's products
             read_frags(cur, a_at[1], w_at[1], f1);
-            multiply(f0, true);
+            multiply(f0, UintTag<0>{}, true);
             read_frags(cur, a_at[2], w_at[2], f0);
-            multiply(f1, false);
+            multiply(f1, UintTag<1>{}, false);
             read_frags(cur, a_at[3], w_at[3], f1);
-            multiply(f0, WN == 2);
+            multiply(f0, UintTag<2>{}, WN == 2);
             cur = cur == (S - 1) * kStage ? 0 : cur + kStage;
             far = far == (S - 1) * kStage ? 0 : far + kStage;
         };
@@ -217,6 +216,7 @@ void gemm_fp8_kernel(Fp8Args ga) {
 #pragma unroll
         for (uint32_t i = 0; i < S - 1; ++i)
             if (i < stages) load_stage(i * kStage, i);
+        if (CHAINS > 1) clear();                              // (while the first stages are on their way)
         if (full > 0) {
             wait_stage<S, kLoads>(0, stages);
             read_frags(cur, a_at[0], w_at[0], f0);
@@ -227,7 +227,7 @@ void gemm_fp8_kernel(Fp8Args ga) {
                 wait_loads_and_sync<(S - 2) * kLoads>();
                 read_frags(cur, a_at[0], w_at[0], f0);
                 load_stage(far, j + S - 1);
-                multiply(f1, false);
+                multiply(f1, UintTag<3>{}, false);
                 rest_of_step();
             };
             if (!EXACT && kLookEarly && shortest >= 16) {     // (every team gets this far)
@@ -243,24 +243,24 @@ void gemm_fp8_kernel(Fp8Args ga) {
             for (; j < full_end; ++j) {
                 wait_stage<S, kLoads>(j, stages);
                 read_frags(cur, a_at[0], w_at[0], f0);
-                multiply(f1, false);
+                multiply(f1, UintTag<3>{}, false);
                 rest_of_step();
             }
-            multiply(f1, false);
+            multiply(f1, UintTag<3>{}, false);
         }
         if (half) {                                           // 32 k more: two quarters
             wait_loads_and_sync<0>();
-            for (uint32_t ks = 0; ks < 2; ++ks) {
-                read_frags(cur, a_place(ks), w_place(ks), f0);
-                multiply(f0, false);
-                if (ks % WN == wn) {
-#pragma unroll
-                    for (int mi = 0; mi < TM; ++mi) rsum[mi] = add_fragment(f0.a[mi], rsum[mi]);
-                }
-            }
+            auto quarter = [&](auto ks) {
+                read_frags(cur, a_place(ks.value), w_place(ks.value), f0);
+                multiply(f0, ks, false);
+                if (ks.value % WN == wn) rsum.template add<0>(f0.a);
+            };
+            quarter(UintTag<0>{});
+            quarter(UintTag<1>{});
         }
         for (uint32_t i = stages; i < slots; ++i) wait_loads_and_sync<0>();   // teams wait for each other
         wait_loads_and_sync<0>();                             // nobody reads a stage any more
+        join_chains(acc);
     };
 
     float *rowsum = reinterpret_cast<float *>(lds_all);       // [TEAMS * WN][BM], then a flag per wave, then the other teams' tiles
@@ -277,9 +277,9 @@ void gemm_fp8_kernel(Fp8Args ga) {
     __syncthreads();                                          // the flags are read before anything overwrites them
     if (__builtin_amdgcn_readfirstlane(any_top) != 0) compute(BoolTag<true>{});
     const float s = ga.sb ? ga.sb[0] : 1.0f, b = ga.sb ? ga.sb[1] : 0.0f;
-    publish_row_sums<WN, BM, TM>(rowsum, rsum, ga.sb != nullptr, team, 32 * TM * wm, wn, lane);
-    if (!add_teams<TEAMS, NW, TM, TN>(parts, acc, team, wave, lane)) return;
-    store_tile<TEAMS * WN, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 32 * TN * wn, N, acc, rowsum, 32 * TM * wm, lane, s, b);
+    publish_row_sums<WN, BM, TM>(rowsum, rsum.total(), ga.sb != nullptr, team, 32 * TM * wm, wn, lane);
+    if (!add_teams<TEAMS, NW, TM, TN>(parts, acc[0], team, wave, lane)) return;
+    store_tile<TEAMS * WN, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 32 * TN * wn, N, acc[0], rowsum, 32 * TM * wm, lane, s, b);
 }
 
 // 128 x 256 by four waves has two workgroups on a compute unit, so that one's C stores pass under the other's products: it
@@ -294,35 +294,66 @@ void gemm_fp8_kernel(Fp8Args ga) {
 // 10.1 with 64 x 64), where the figures before, which preferred four teams on small products, were 6.6 % and 36 % off: 512 x 512 x 512 6.0 us, 5.0
 // with one team; 2048 x 512 x 2048, input gradient, 10.5, 9.2 with two; 1280 x 1408 x 1984 14.1 with 64 x 64, 11.7 with 64 x 128.
 static constexpr GemmTile kFp8Tiles[] = {
-    {256, 256, 1, 1, 6.5, 1.13, 1.48, 8.3},     {128, 256, 1, 2, 4.5, 0.88, 0.81, 2.2},     {128, 256, 1, 1, 4.953, 0.43, 0.847, 3.39},
-    {128, 128, 1, 2, 3.265, 0.468, 0.494, 1.617}, {64, 128, 1, 2, 3.104, 0.266, 0.36, 0.52},  {64, 64, 1, 4, 2.961, 0.277, 0.201, 0.225},
-    {64, 64, 2, 2, 3.898, 0.333, 0.388, 0.256}, {64, 64, 4, 1, 3.097, 0.713, 3.142, 5.835},
+    {256, 256, 1, 1, 1, 6.5, 1.13, 1.48, 8.3},     {128, 256, 1, 1, 2, 4.5, 0.88, 0.81, 2.2},     {128, 256, 1, 1, 1, 4.953, 0.43, 0.847, 3.39},
+    {128, 128, 1, 1, 2, 3.265, 0.468, 0.494, 1.617}, {64, 128, 1, 2, 2, 3.104, 0.266, 0.36, 0.52},  {64, 64, 1, 4, 4, 2.961, 0.277, 0.201, 0.225},
+    {64, 64, 2, 2, 2, 3.898, 0.333, 0.388, 0.256}, {64, 64, 4, 1, 1, 3.097, 0.713, 3.142, 5.835},
 };
 
+// Chains of fp32 sums that a contraction is dealt into, by the result's 64 x 64 tiles and the steps: at least as many as when the choice fell
+// on four or two teams of waves for nearly every small product.  Those are slower than one team or two on most of them, but an error against 64 bits grows
+// with a chain's length: 512 x 512 x 512 3.4e-8 in four chains, 4.0e-8 in one, 512 x 512 x 4096 6.0e-8 in four, 7.2e-8 in two, 5120 x 256 x 1472 5.2e-8 in
+// two, 6.5e-8 in one.  So one team keeps the chains of four: 64 more registers and 48 additions at the end, 4.33 -> 4.45 us for 256 x 384 x 416
+// (5.29 with four teams), 9.27 -> 9.7 for 2048 x 512 x 2048 with two teams of two chains (9.8 - 10.0 with four).
+static uint32_t fp8_chains(uint32_t M, uint32_t N, uint32_t K) {
+    const uint64_t small_tiles = static_cast<uint64_t>(M / 64) * (N / 64), steps = (static_cast<uint64_t>(K) + 63) / 64;
+    if (small_tiles <= (steps <= 2 ? 120 : std::min<uint64_t>(256, 156 + 4 * steps))) return 4;
+    return steps >= 4 && small_tiles <= std::min<uint64_t>(432, 248 + 8 * steps) ? 2 : 1;
+}
+
+template <int WM, int WN, int TM, int TN, int TEAMS, int CHAINS, int S, int OCC, bool TRANS>
+static void launch_one(const Fp8Args &ga, hipStream_t st) {
+    gemm_fp8_kernel<WM, WN, TM, TN, TEAMS, CHAINS, S, OCC, TRANS><<<dim3(ga.tiles_m * ga.tiles_n), dim3(64 * WM * WN * TEAMS), 0, st>>>(ga);
+}
+// `chains`: of each team
 template <bool TRANS>
-static int launch_tile(int which, const Fp8Args &ga, uint32_t tiles, hipStream_t st) {
+static int launch_tile(int which, uint32_t chains, const Fp8Args &ga, hipStream_t st) {
     switch (which) {
-        case 0: gemm_fp8_kernel<2, 4, 4, 2, 1, 3, 2, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
-        case 1: gemm_fp8_kernel<2, 2, 2, 4, 1, 2, 2, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
-        case 2: gemm_fp8_kernel<2, 4, 2, 2, 1, 3, 2, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
-        case 3: gemm_fp8_kernel<2, 2, 2, 2, 1, 3, 2, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
-        case 4: gemm_fp8_kernel<2, 4, 1, 1, 1, 3, 4, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
-        case 5: gemm_fp8_kernel<2, 2, 1, 1, 1, 3, 4, TRANS><<<dim3(tiles), dim3(256), 0, st>>>(ga); break;
-        case 6: gemm_fp8_kernel<2, 2, 1, 1, 2, 3, 4, TRANS><<<dim3(tiles), dim3(512), 0, st>>>(ga); break;
-        case 7: gemm_fp8_kernel<2, 2, 1, 1, 4, 3, 4, TRANS><<<dim3(tiles), dim3(1024), 0, st>>>(ga); break;
+        case 0: launch_one<2, 4, 4, 2, 1, 1, 3, 2, TRANS>(ga, st); break;
+        case 1: launch_one<2, 2, 2, 4, 1, 1, 2, 2, TRANS>(ga, st); break;
+        case 2: launch_one<2, 4, 2, 2, 1, 1, 3, 2, TRANS>(ga, st); break;
+        case 3: launch_one<2, 2, 2, 2, 1, 1, 3, 2, TRANS>(ga, st); break;
+        case 4:
+            if (chains == 2) launch_one<2, 4, 1, 1, 1, 2, 3, 4, TRANS>(ga, st);
+            else launch_one<2, 4, 1, 1, 1, 1, 3, 4, TRANS>(ga, st);
+            break;
+        case 5:
+            if (chains == 4) launch_one<2, 2, 1, 1, 1, 4, 3, 4, TRANS>(ga, st);
+            else if (chains == 2) launch_one<2, 2, 1, 1, 1, 2, 3, 4, TRANS>(ga, st);
+            else launch_one<2, 2, 1, 1, 1, 1, 3, 4, TRANS>(ga, st);
+            break;
+        case 6:
+            if (chains == 2) launch_one<2, 2, 1, 1, 2, 2, 3, 4, TRANS>(ga, st);
+            else launch_one<2, 2, 1, 1, 2, 1, 3, 4, TRANS>(ga, st);
+            break;
+        case 7: launch_one<2, 2, 1, 1, 4, 1, 3, 4, TRANS>(ga, st); break;
         default: return static_cast<int>(hipErrorInvalidValue);
     }
     return static_cast<int>(hipGetLastError());
 }
 
-int gemm_fp8_tile(uint32_t M, uint32_t N, uint32_t K) { return pick_tile(kFp8Tiles, M, N, K); }
+int gemm_fp8_tile(uint32_t M, uint32_t N, uint32_t K) { return pick_tile(kFp8Tiles, M, N, K, fp8_chains(M, N, K)); }
+uint32_t gemm_fp8_sums(uint32_t M, uint32_t N, uint32_t K) {
+    const int which = gemm_fp8_tile(M, N, K);
+    return which < 0 ? 0 : kFp8Tiles[which].teams * chains_per_team(kFp8Tiles[which], fp8_chains(M, N, K));
+}
 
 int launch_gemm_fp8(const uint16_t *A, const void *codes, const float *sb, float *C, uint32_t M, uint32_t N, uint32_t K, int trans, hipStream_t st) {
     const int which = gemm_fp8_tile(M, N, K);
     if (which < 0) return static_cast<int>(hipErrorInvalidValue);
     const GemmTile &t = kFp8Tiles[which];
     const Fp8Args ga{A, static_cast<const uint8_t *>(codes), sb, C, N, K, M / t.bm, N / t.bn};
-    return trans ? launch_tile<true>(which, ga, ga.tiles_m * ga.tiles_n, st) : launch_tile<false>(which, ga, ga.tiles_m * ga.tiles_n, st);
+    const uint32_t chains = chains_per_team(t, fp8_chains(M, N, K));
+    return trans ? launch_tile<true>(which, chains, ga, st) : launch_tile<false>(which, chains, ga, st);
 }
 
 }  // namespace omc

@@ -247,6 +247,7 @@ int launch_reselect(const void *arena_old, const float *sb_old, void *arena_new,
 int launch_transport_pack(const PlanHeader *ph, const void *plan_dev, const void *arena, const float *sb_table,
                           void *msg_dev, const TransportHeader &th, void *stream);
 int gemm_fp8_tile(uint32_t M, uint32_t N, uint32_t K);
+uint32_t gemm_fp8_sums(uint32_t M, uint32_t N, uint32_t K);
 int launch_gemm_fp8(const uint16_t *A, const void *codes, const float *sb, float *C, uint32_t M, uint32_t N, uint32_t K,
                     int trans, struct ihipStream_t *stream);   // S1E4M3 codes, bias 7
 size_t dw_workspace_bytes(uint32_t bits, uint32_t M, uint32_t N, uint32_t K);

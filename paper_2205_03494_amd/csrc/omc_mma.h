@@ -68,16 +68,18 @@ __device__ __forceinline__ void wait_stage(uint32_t j, uint32_t total) {
 // to random sizes (M 256 - 16384, N 128 - 4096, K 128 - 4096, both directions) with every tile timed: over 78 of S1E4M3 codes the chosen tile takes
 // 0.7 % longer than the best one on average, at worst 15 %; over 48 of other formats 0.6 %, at worst 5 %.
 struct GemmTile {
-    uint32_t bm, bn, teams, resident;
+    uint32_t bm, bn, teams, chains, resident;                 // chains: the most that one team can keep
     double base, step, loaded, stores;
 };
+inline uint32_t chains_per_team(const GemmTile &t, uint32_t chains) { return (chains + t.teams - 1) / t.teams; }
+// `chains`: into how many chains of fp32 sums the contraction is to be dealt at least
 template <int COUNT>
-inline int pick_tile(const GemmTile (&tiles)[COUNT], uint32_t M, uint32_t N, uint32_t K) {
+inline int pick_tile(const GemmTile (&tiles)[COUNT], uint32_t M, uint32_t N, uint32_t K, uint32_t chains) {
     int best = -1;
     double best_cost = 0.0;
     for (int i = 0; i < COUNT; ++i) {
         const GemmTile &t = tiles[i];
-        if (M % t.bm != 0 || N % t.bn != 0) continue;
+        if (M % t.bm != 0 || N % t.bn != 0 || chains_per_team(t, chains) > t.chains) continue;
         const uint64_t count = static_cast<uint64_t>(M / t.bm) * (N / t.bn);
         if (count > 0x7fffffffull) continue;
         const double per_unit = static_cast<double>(count) / 256.0;
@@ -92,7 +94,6 @@ inline int pick_tile(const GemmTile (&tiles)[COUNT], uint32_t M, uint32_t N, uin
     }
     return best;
 }
-
 // Tile of this workgroup in a grid of tiles_m x tiles_n (one-dimensional launch).  Workgroups go to the 8 dies in turn and
 // each die has an L2 of its own, so every die gets a contiguous run of the tile order, in which groups of `group_rows` tile rows
 // share their columns.  The tiles of a die at one time should need as many bytes of the one operand as of the other: eight rows for
@@ -109,26 +110,82 @@ __device__ __forceinline__ void tile_of_block(uint32_t group_rows, uint32_t tile
     tn = in / height;
 }
 
-// acc += sum of the 8 bfloat16 values of a fragment
-__device__ __forceinline__ float add_fragment(bf16x8 f, float acc) {
+// acc[0] .. acc[PARTS - 1] += the 8 bfloat16 values of a fragment, two at a time, dealt out in turn
+template <int PARTS>
+__device__ __forceinline__ void add_fragment(bf16x8 f, float *acc) {
     const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
     const u32x4 x = __builtin_bit_cast(u32x4, f);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const uint32_t w = x[i];
-        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, acc, false);
+        acc[i % PARTS] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, acc[i % PARTS], false);
     }
-    return acc;
+}
+
+// A wave's share of the row sums of A.  With two column waves it sums two quarters of each step (the first and third that it
+// multiplies), with four one, and where the products are summed in several chains so are these.
+template <int WN, int TM, int CHAINS>
+struct RowSums {
+    static constexpr int kChains = WN == 2 ? CHAINS : 1, kPerFragment = kChains == 4 ? 2 : 1;
+    float sum[TM][kChains];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+            for (int c = 0; c < kChains; ++c) sum[mi][c] = 0.0f;
+    }
+    template <int QUARTER>
+    __device__ __forceinline__ void add(const bf16x8 (&a)[TM]) {
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi) add_fragment<kPerFragment>(a[mi], sum[mi] + (QUARTER == 2 ? kChains / 2 : 0));
+    }
+    struct Total {
+        float row[TM];
+    };
+    __device__ __forceinline__ Total total() const {
+        Total t;
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi) {
+            t.row[mi] = sum[mi][0];
+#pragma unroll
+            for (int c = 1; c < kChains; ++c) t.row[mi] += sum[mi][c];
+        }
+        return t;
+    }
+};
+
+template <int CHAINS, int TM, int TN>
+__device__ __forceinline__ void clear_chains(f32x16 (&acc)[CHAINS][TM][TN]) {
+#pragma unroll
+    for (int c = 0; c < CHAINS; ++c)
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[c][mi][ni][v] = 0.0f;
+}
+// The chains' sums, added in order, in the first one.
+template <int CHAINS, int TM, int TN>
+__device__ __forceinline__ void join_chains(f32x16 (&acc)[CHAINS][TM][TN]) {
+#pragma unroll
+    for (int c = 1; c < CHAINS; ++c)
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[0][mi][ni][v] += acc[c][mi][ni][v];
 }
 
 // A wave's share of the row sums of A to LDS, [team * WN + column wave][BM]; without an offset they must not enter the result,
 // whatever they are.
-template <int WN, int BM, int TM>
-__device__ __forceinline__ void publish_row_sums(float *rowsum, const float (&rsum)[TM], bool wanted, uint32_t team, uint32_t row0,
+template <int WN, int BM, int TM, typename Total>
+__device__ __forceinline__ void publish_row_sums(float *rowsum, const Total &rsum, bool wanted, uint32_t team, uint32_t row0,
                                                  uint32_t wn, uint32_t lane) {
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi) {
-        const float t = rsum[mi] + __shfl_xor(rsum[mi], 32);
+        const float t = rsum.row[mi] + __shfl_xor(rsum.row[mi], 32);
         if (lane < 32) rowsum[(team * WN + wn) * BM + row0 + 32 * mi + lane] = wanted ? t : 0.0f;
     }
 }

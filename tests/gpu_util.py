@@ -26,6 +26,13 @@ def gemm_tile(EM, M, N, K):
     return fn(int(tuple(EM) == (4, 3)), M, N, K)
 
 
+def gemm_sums(EM, M, N, K):
+    """Into how many chains of fp32 sums the contraction of that product is dealt, by teams of waves and within a team."""
+    fn = omc._lib.omc_internal_gemm_sums
+    fn.restype, fn.argtypes = C.c_uint32, [C.c_int] + [C.c_uint32] * 3
+    return fn(int(tuple(EM) == (4, 3)), M, N, K)
+
+
 def dw_route(bits, M, N, K):
     """(one kernel?, tile, splits) of a weight-gradient call; tiles 256 x 128 by two teams, 128 x 128 by one and two, 64 x 64 by one, two, four."""
     fn = omc._lib.omc_internal_dw_route

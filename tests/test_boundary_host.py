@@ -1,6 +1,7 @@
 """Host-side checks of the C-ABI boundary: the library loads, exports every symbol the header
 declares, and rejects bad arguments before touching a device.  No compute calls are made."""
 import ctypes as C
+import math
 import os
 import re
 
@@ -9,7 +10,7 @@ import pytest
 
 from oracle import omc_oracle as orc
 from paper_2205_03494_amd import omc, synth
-from gpu_util import dw_route, gemm_tile
+from gpu_util import dw_route, gemm_sums, gemm_tile
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -445,3 +446,37 @@ def test_gpu_tests_reach_every_tile():
     assert {tile for one, tile, _ in routes if not one} == set(range(6))
     assert {splits for one, _, splits in routes if not one} == set(range(1, 9))
     assert any(tile == 0 and splits > 1 for one, tile, splits in routes if not one)
+    for EM, variants in (((4, 3), test_gpu_gemm.FP8_KERNELS), ((3, 7), test_gpu_gemm.BITS_KERNELS)):
+        for (tile, sums), shape in variants.items():
+            assert (gemm_tile(EM, *shape), gemm_sums(EM, *shape)) == (tile, sums), (EM, shape)
+        sizes = [(256 * m, 128 * n, K) for m in (1, 2, 3, 5, 7, 10, 14, 21, 30, 37, 43, 57, 64) for n in (1, 2, 3, 5, 7, 9, 13, 17, 22, 27, 32)
+                 for K in (32, 96, 160, 224, 352, 480, 608, 992, 1440, 2080, 2592, 3104, 4096, 8224)]
+        assert {(gemm_tile(EM, *shape), gemm_sums(EM, *shape)) for shape in sizes} <= set(variants), EM
+
+
+# (rows, columns, teams, workgroups on a unit, launch, step, step on a busy unit, stores): the estimates by which the teams of waves were chosen
+# before a team could keep several chains of sums
+FORMER_ESTIMATES = {
+    (4, 3): [(256, 256, 1, 1, 6.5, 1.13, 1.48, 8.3), (128, 256, 1, 2, 4.5, 0.88, 0.81, 2.2), (128, 256, 1, 1, 4.3, 0.66, 0.84, 4.0),
+             (128, 128, 1, 2, 3.8, 0.46, 0.46, 1.5), (64, 128, 1, 2, 3.5, 0.285, 0.24, 1.2), (64, 64, 1, 4, 3.0, 0.27, 0.178, 0.3),
+             (64, 64, 2, 2, 2.9, 0.40, 0.34, 0.8), (64, 64, 4, 1, 1.5, 0.70, 0.70, 3.0)],
+    (3, 7): [(256, 256, 1, 1, 7.0, 1.30, 1.855, 8.0), (128, 256, 1, 1, 4.7, 1.00, 1.18, 5.0), (128, 128, 1, 2, 3.0, 0.76, 0.66, 2.6),
+             (64, 64, 1, 4, 2.2, 0.54, 0.263, 0.65), (64, 64, 2, 2, 1.0, 0.70, 0.50, 1.6), (64, 64, 4, 1, 1.0, 1.15, 1.15, 3.2)],
+}
+
+
+@pytest.mark.parametrize("EM", list(FORMER_ESTIMATES))
+def test_no_product_is_summed_in_fewer_chains_than_it_was(EM):
+    """The error of a product grows with the length of its fp32 sums.  Whatever tile is the fastest, its contraction is dealt into at least as many
+    chains as it was by the teams of waves that the choice used to fall on."""
+    def teams(M, N, K):
+        def estimate(t):
+            bm, bn, teams, resident, launch, step, loaded, stores = t
+            tiles = (M // bm) * (N // bn)
+            return launch + stores * tiles / 256 + math.ceil(K / (64 * teams)) * max(step * math.ceil(tiles / (256 * resident)), loaded * tiles / 256)
+        return min((t for t in FORMER_ESTIMATES[EM] if M % t[0] == 0 and N % t[1] == 0), key=estimate)[2]
+
+    fewer = [(M, N, K) for M in range(256, 16385, 512) for N in range(128, 4097, 256)
+             for K in (32, 64, 96, 128, 160, 192, 224, 256, 320, 384, 448, 512, 640, 768, 1024, 1536, 2048, 2592, 3072, 3584, 4096, 8192)
+             if gemm_sums(EM, M, N, K) < teams(M, N, K)]
+    assert not fewer, fewer[:5]

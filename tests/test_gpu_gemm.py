@@ -225,6 +225,35 @@ def test_every_tile_size_ends_on_half_a_step(EM, shape):
     assert both_directions(EM, M, N, K, tile_sample_rows(M, seed=K, per_quarter=4)) < 1e-5
 
 
+# One size for every kernel of the products, by tile and chains of sums (a test without a GPU holds that); all contractions end on half a step.
+FP8_KERNELS = {(0, 1): (3584, 3584, 2976), (1, 1): (2816, 3840, 96), (2, 1): (1280, 3584, 1440), (3, 1): (1536, 2432, 224), (4, 1): (768, 2176, 352),
+               (4, 2): (1280, 896, 1056), (5, 1): (256, 2048, 32), (5, 2): (256, 2816, 224), (5, 4): (256, 128, 32), (6, 2): (256, 3200, 608),
+               (6, 4): (256, 256, 608), (7, 4): (256, 128, 224)}
+BITS_KERNELS = {(0, 1): (8704, 2304, 32), (1, 1): (3072, 2432, 352), (2, 1): (1280, 1664, 480), (2, 2): (1280, 1664, 2592), (3, 1): (768, 2176, 32),
+                (3, 2): (256, 896, 32), (4, 2): (256, 128, 32), (4, 4): (256, 128, 160), (5, 4): (256, 128, 416)}
+
+
+@pytest.mark.parametrize("EM,kernel", [((4, 3), k) for k in FP8_KERNELS] + [(EM, k) for EM in ((2, 3), (5, 2), (3, 7), (4, 7), (5, 7)) for k in BITS_KERNELS])
+def test_every_kernel_with_a_visible_offset(EM, kernel):
+    """Both directions of every kernel in 6, 8, 11, 12 and 13 bits (odd widths start a thread's codes in the middle of a dword), with an offset whose row
+    sums count for more than the products do.  1e-5: fp32 sums of at most 2976 products."""
+    M, N, K = (FP8_KERNELS if EM == (4, 3) else BITS_KERNELS)[kernel]
+    assert both_directions(EM, M, N, K, tile_sample_rows(M, seed=K + N), sb=np.array([0.75, 0.125], np.float32)) < 1e-5
+
+
+@pytest.mark.parametrize("shape,bound", [((512, 512, 512), 3.7e-8), ((5120, 256, 1472), 5.8e-8), ((512, 512, 4096), 6.6e-8)])
+def test_small_products_against_64_bits(shape, bound):
+    """S1E4M3 codes without a transformation: every product is exact, what is off are the fp32 sums.  Dealt into two or four chains they
+    are 3.4e-8, 5.2e-8 and 6.0e-8 off; in half or a quarter as many 4.0e-8, 6.5e-8 and 7.2e-8.  The bounds lie between the two."""
+    of, gf = pair(4, 3)
+    M, N, K = shape
+    A = synth.to_bf16_bits(synth.normal_f32(M * K, 1.0, 3))
+    packed, _ = orc.compress(synth.normal_f32(K * N, 1 / np.sqrt(K), 4), of)
+    for got, want in ((run_gemm(A, packed, gf, None, M, N, K), orc.dequant_gemm(A, packed, of, None, M, N, K, threads=8)),
+                      (run_gemm_dx(A, packed, gf, None, M, K, N), orc.dequant_gemm_dx(A, packed, of, None, M, K, N, threads=8))):
+        assert np.linalg.norm(got.astype(np.float64) - want) <= bound * np.linalg.norm(want)
+
+
 @pytest.mark.parametrize("shape", [(4096, 2048, 160), (256, 256, 544)])
 def test_top_codes_in_some_tiles_only(shape):
     """A tile that meets the code that the FP8 conversion reads as NaN is computed again; its neighbours are not."""
