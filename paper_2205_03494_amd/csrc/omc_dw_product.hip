@@ -257,10 +257,11 @@ void dw_product_kernel(ProductArgs pa, DwArgs a) {
     }
 }
 
-// Tiles: their figures are for steps of 32 rows (of TEAMS times as many with several teams), see GemmTile.
+// Tiles: their figures are for steps of 32 rows (of TEAMS times as many with several teams), see GemmTile
+// (`fresh` is not counted here).
 static constexpr GemmTile kProductTiles[] = {
-    {256, 128, 2, 1, 1, 6.2, 0.64, 0.88, 0.0}, {128, 128, 1, 1, 2, 3.5, 0.30, 0.28, 0.0}, {128, 128, 2, 1, 1, 4.7, 0.355, 0.57, 0.0},
-    {64, 64, 1, 1, 4, 3.2, 0.13, 0.126, 0.0},  {64, 64, 2, 1, 2, 1.0, 0.20, 0.215, 3.0},  {64, 64, 4, 1, 1, 1.0, 0.40, 0.46, 3.0},
+    {256, 128, 2, 1, 1, 6.2, 0.64, 0.88, 0.0, 0.0}, {128, 128, 1, 1, 2, 3.5, 0.30, 0.28, 0.0, 0.0}, {128, 128, 2, 1, 1, 4.7, 0.355, 0.57, 0.0, 0.0},
+    {64, 64, 1, 1, 4, 3.2, 0.13, 0.126, 0.0, 0.0},  {64, 64, 2, 1, 2, 1.0, 0.20, 0.215, 3.0, 0.0},  {64, 64, 4, 1, 1, 1.0, 0.40, 0.46, 3.0, 0.0},
 };
 
 // What the one-kernel route's epilogue takes, in us per workgroup of a compute unit, under momentum (under SGD 0.6 of it, under

@@ -280,17 +280,22 @@ void gemm_bits_kernel(BitsArgs ga) {
     store_tile<TEAMS * WN, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 32 * TN * wn, N, acc[0], rowsum, 32 * TM * wm, lane, s, b);
 }
 
-// Fitted to 8-, 11- and 13-bit codes, 48 sizes in both directions, every tile timed: the chosen one takes 0.6 % longer than the best of these on
-// average, at worst 5 %.  256 x 128 by four waves, one to a SIMD, each of 128 x 64, decodes a code for 256 rows and reads its
-// fragments from LDS half as often as 128 x 256 by eight (9216 x 896 x 1120, input gradient, 13 bits, 30 us; 36 with 128 x 128; 8192 x 1024 x 2048 46;
-// 51 with 128 x 256).  128 x 64 by four waves, three workgroups on a unit, fills the chip with half the decoding of 64 x 64 (2304 x 3712 x 192
-// 13.2 us, 15.2 with 64 x 64, 14.5 with 128 x 128; 1536 x 2944 x 704 16.4, 19.8, 18.4).  Against 128 x 256 and 64 x 64 in their places, as it was: 4 % over
-// the 48 sizes.  8192 x 4096 x 1024: 82 us with 256 x 256, 107 with 128 x 128; 2048 x 512 x 2048: 50 with 256 x 256, 27 with 128 x 128, 14 / 13 with
-// 64 x 64 and 2 / 4 teams.
+// 256 x 128 by four waves, one to a SIMD, each of 128 x 64, decodes a code for 256 rows and reads its fragments from LDS half as often as 128 x 256 by eight
+// (9216 x 896 x 1120, input gradient, 13 bits, 28 us; 36 with 128 x 128; 8192 x 1024 x 2048 45, 50 with 128 x 256); the latter is faster forward where
+// every unit has one tile and a result has few columns (15360 x 512 x 1120, 11 bits: 27 us, 32 with 256 x 128).  128 x 64 by four waves, three
+// workgroups on a unit, fills the chip with half the decoding of 64 x 64 (2304 x 3712 x 192 12.6 us, 14.5 with 128 x 128; 1536 x 2944 x 704 16.4, 18.4), which
+// wins on short contractions (8192 x 128 x 320, 11 bits: 5.5 us, 5.8 with 128 x 64).  8192 x 4096 x 1024: 82 us with 256 x 256, 107 with 128 x 128; 2048 x
+// 512 x 2048: 50 with 256 x 256, 27 with 128 x 128, 14 / 13 with 64 x 64 and 2 / 4 teams.
+// Fitted to 1532 sizes in 6, 8, 11 and 13 bits.  On 1180 others the chosen tile takes 0.6 % longer than the best one on average, more than 7 % longer on 33 of
+// them, at worst 29 % (13056 x 256 x 3744, 11 bits, input gradient: 72 us with 128 x 128, 56 with 128 x 64); in 4 and 16 bits, which are not in the fit, 0.8 and 0.9 %, at
+// worst 15 and 27 % (120 sizes each); on 90 with K = 32 - 96, smaller than any in the fit, 1.4 %, at worst 9 %.
 static constexpr GemmTile kBitsTiles[] = {
-    {256, 256, 1, 1, 1, 5.27, 1.438, 2.178, 8.19}, {256, 128, 1, 1, 1, 4.55, 1.024, 1.127, 5.49}, {128, 128, 1, 2, 2, 3.26, 0.586, 0.769, 2.55},
-    {128, 64, 1, 2, 3, 2.90, 0.651, 0.403, 1.17},  {64, 64, 2, 2, 2, 2.57, 0.888, 0.527, 1.08},  {64, 64, 4, 1, 1, 3.27, 1.230, 1.227, 1.94},
+    {256, 256, 1, 1, 1, 2.271, 1.395, 1.354, 11.2, 0.065}, {256, 128, 1, 1, 1, 2.589, 0.728, 1.008, 5.458, 0.082},
+    {128, 256, 1, 1, 1, 2.2, 0.561, 1.087, 4.948, 0.057}, {128, 128, 1, 2, 2, 3.136, 0.679, 0.572, 1.55, 0.051},
+    {128, 64, 1, 1, 3, 3.229, 0.578, 0.346, 0.638, 0.075}, {64, 64, 1, 2, 4, 2.533, 0.549, 0.281, 0.235, 0.099},
+    {64, 64, 2, 2, 2, 2.397, 0.715, 0.462, 0.732, 0.088}, {64, 64, 4, 1, 1, 3.275, 0.993, 0.881, 0.934, 0.088},
 };
+static constexpr double kBitsUneven = 1.0;
 
 // Chains of fp32 sums that a contraction is dealt into, by the result's 64 x 64 tiles and the steps: at least as many as it was dealt into when the
 // choice fell on two or four teams for more of the small products (11 bits, 5888 x 256 x 192: 2.7e-8 off 64 bits in two chains, 3.1e-8 in one).  The
@@ -301,7 +306,7 @@ inline uint32_t bits_chains(uint32_t M, uint32_t N, uint32_t K) {
     if (steps >= 3 && small_tiles <= std::min<uint64_t>(256, 16 + 9 * steps)) return 4;
     return small_tiles <= (steps > 40 ? 768 : steps <= 3 ? 400 : std::min<uint64_t>(512, 428 + 6 * steps)) ? 2 : 1;
 }
-inline int gemm_bits_tile(uint32_t M, uint32_t N, uint32_t K) { return pick_tile(kBitsTiles, M, N, K, bits_chains(M, N, K)); }
+inline int gemm_bits_tile(uint32_t M, uint32_t N, uint32_t K) { return pick_tile(kBitsTiles, kBitsUneven, M, N, K, bits_chains(M, N, K)); }
 inline uint32_t gemm_bits_sums(uint32_t M, uint32_t N, uint32_t K) {
     const int which = gemm_bits_tile(M, N, K);
     return which < 0 ? 0 : kBitsTiles[which].teams * chains_per_team(kBitsTiles[which], bits_chains(M, N, K));
@@ -316,19 +321,21 @@ inline int launch_bits_tile(int which, uint32_t chains, const BitsArgs &ga, hipS
     switch (which) {
         case 0: launch_bits_one<B, 4, 32, 4, 2, 1, 1, 2, TRANS>(ga, st); break;
         case 1: launch_bits_one<B, 2, 32, 4, 2, 1, 1, 1, TRANS>(ga, st); break;
-        case 2:
+        case 2: launch_bits_one<B, 4, 32, 2, 2, 1, 1, 2, TRANS>(ga, st); break;
+        case 3:
             if (chains == 2) launch_bits_one<B, 4, 16, 2, 1, 1, 2, 2, TRANS>(ga, st);
             else launch_bits_one<B, 4, 16, 2, 1, 1, 1, 4, TRANS>(ga, st);
             break;
-        case 3:
-            if (chains == 2) launch_bits_one<B, 2, 16, 2, 1, 1, 2, 3, TRANS>(ga, st);
-            else launch_bits_one<B, 2, 16, 2, 1, 1, 1, 3, TRANS>(ga, st);
+        case 4: launch_bits_one<B, 2, 16, 2, 1, 1, 1, 3, TRANS>(ga, st); break;
+        case 5:
+            if (chains == 2) launch_bits_one<B, 2, 16, 1, 1, 1, 2, 4, TRANS>(ga, st);
+            else launch_bits_one<B, 2, 16, 1, 1, 1, 1, 4, TRANS>(ga, st);
             break;
-        case 4:
+        case 6:
             if (chains == 2) launch_bits_one<B, 2, 16, 1, 1, 2, 2, 4, TRANS>(ga, st);
             else launch_bits_one<B, 2, 16, 1, 1, 2, 1, 4, TRANS>(ga, st);
             break;
-        case 5: launch_bits_one<B, 2, 16, 1, 1, 4, 1, 4, TRANS>(ga, st); break;
+        case 7: launch_bits_one<B, 2, 16, 1, 1, 4, 1, 4, TRANS>(ga, st); break;
         default: return static_cast<int>(hipErrorInvalidValue);
     }
     return static_cast<int>(hipGetLastError());

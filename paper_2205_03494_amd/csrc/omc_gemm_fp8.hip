@@ -289,15 +289,15 @@ void gemm_fp8_kernel(Fp8Args ga) {
 // (8192 x 1024 x 4096: 60 to 62 us).  The small tiles win where they spread a short product over more units, and several teams where
 // even those leave most of them idle (2048 x 512 x 2048: 25 us with 128 x 256, 19 with 128 x 128, 12 with 64 x 128, 11.6 / 9.2 / 10.5
 // with 64 x 64 and 1 / 2 / 4 teams).
-// The figures of the last six are fitted to 78 sizes in both directions, every tile timed, those of the first two are as they were: among the large
-// tiles nothing changes.  The chosen one takes 0.7 % longer than the best one on average, at worst 15 % (4352 x 2048 x 160: 11.7 us with 128 x 256,
-// 10.1 with 64 x 64), where the figures before, which preferred four teams on small products, were 6.6 % and 36 % off: 512 x 512 x 512 6.0 us, 5.0
-// with one team; 2048 x 512 x 2048, input gradient, 10.5, 9.2 with two; 1280 x 1408 x 1984 14.1 with 64 x 64, 11.7 with 64 x 128.
+// Fitted to 1308 sizes.  On 918 others the chosen tile takes 0.5 % longer than the best one on average, more than 7 % longer on 15 of them, at worst
+// 17 % (5888 x 384 x 992, input gradient: 13.2 us with 64 x 128, 11.3 with 128 x 128); on 90 with K = 32 - 96, smaller than any in the fit, 0.3 % and 9 %.
 static constexpr GemmTile kFp8Tiles[] = {
-    {256, 256, 1, 1, 1, 6.5, 1.13, 1.48, 8.3},     {128, 256, 1, 1, 2, 4.5, 0.88, 0.81, 2.2},     {128, 256, 1, 1, 1, 4.953, 0.43, 0.847, 3.39},
-    {128, 128, 1, 1, 2, 3.265, 0.468, 0.494, 1.617}, {64, 128, 1, 2, 2, 3.104, 0.266, 0.36, 0.52},  {64, 64, 1, 4, 4, 2.961, 0.277, 0.201, 0.225},
-    {64, 64, 2, 2, 2, 3.898, 0.333, 0.388, 0.256}, {64, 64, 4, 1, 1, 3.097, 0.713, 3.142, 5.835},
+    {256, 256, 1, 1, 1, 2.628, 1.024, 1.283, 11.45, 0.078}, {128, 256, 1, 1, 2, 2.2, 0.948, 0.658, 4.66, 0.112},
+    {128, 256, 1, 1, 1, 2.2, 0.595, 0.788, 6.411, 0.037}, {128, 128, 1, 1, 2, 2.915, 0.462, 0.456, 1.795, 0.057},
+    {64, 128, 1, 2, 2, 2.682, 0.238, 0.287, 1.055, 0.067}, {64, 64, 1, 4, 4, 2.646, 0.238, 0.192, 0.249, 0.08},
+    {64, 64, 2, 2, 2, 3.007, 0.375, 0.363, 0.551, 0.055}, {64, 64, 4, 1, 1, 3.396, 0.722, 0.895, 0.293, 0.072},
 };
+static constexpr double kFp8Uneven = 0.5;
 
 // Chains of fp32 sums that a contraction is dealt into, by the result's 64 x 64 tiles and the steps: at least as many as when the choice fell
 // on four or two teams of waves for nearly every small product.  Those are slower than one team or two on most of them, but an error against 64 bits grows
@@ -341,7 +341,7 @@ static int launch_tile(int which, uint32_t chains, const Fp8Args &ga, hipStream_
     return static_cast<int>(hipGetLastError());
 }
 
-int gemm_fp8_tile(uint32_t M, uint32_t N, uint32_t K) { return pick_tile(kFp8Tiles, M, N, K, fp8_chains(M, N, K)); }
+int gemm_fp8_tile(uint32_t M, uint32_t N, uint32_t K) { return pick_tile(kFp8Tiles, kFp8Uneven, M, N, K, fp8_chains(M, N, K)); }
 uint32_t gemm_fp8_sums(uint32_t M, uint32_t N, uint32_t K) {
     const int which = gemm_fp8_tile(M, N, K);
     return which < 0 ? 0 : kFp8Tiles[which].teams * chains_per_team(kFp8Tiles[which], fp8_chains(M, N, K));

@@ -60,21 +60,23 @@ __device__ __forceinline__ void wait_stage(uint32_t j, uint32_t total) {
     else wait_loads_and_sync<0>();
 }
 
-// Host: which of a kernel's tile sizes to launch for an M x N result over K.  All figures are in us and come from measurements: `base` stands for a launch
-// with one tile per compute unit and nothing to multiply, `step` a step of 64 k (of TEAMS times as many with several teams) when
-// every compute unit has at most `resident` workgroups, `loaded` what a step costs per workgroup and unit when all 256 units
-// are busy (matrix cores, LDS and memory together), `stores` the C stores of 256 tiles (with several teams, also
-// what a round of workgroups loses before its first and after its last step).  They are fitted
-// to random sizes (M 256 - 16384, N 128 - 4096, K 128 - 4096, both directions) with every tile timed: over 78 of S1E4M3 codes the chosen tile takes
-// 0.7 % longer than the best one on average, at worst 15 %; over 48 of other formats 0.6 %, at worst 5 %.
+// Host: which of a kernel's tile sizes to launch for an M x N result over K, by an estimate of its time.  In us: `base` is a launch; `step` a step of
+// 64 k (of TEAMS times as many with several teams) of workgroups that nothing else slows down, `resident` of them on a compute unit; `loaded` what a step
+// costs per workgroup of a unit where all units are busy (matrix cores, LDS and memory together); `stores` the C stores of 256 tiles; `fresh` a megabyte
+// of A and W on its way from memory, W at a byte a code.  A launch ends with the unit that has the most workgroups, and while others have run out of
+// theirs it is faster: `uneven` is the share of its surplus over the average that counts (9728 x 128 x 3680, input gradient: 304 tiles
+// of 64 x 64, two on some units, 37 us by two teams; 152 of 64 x 128, one on a unit, 34).
+// Each row is fitted to its tile's own times, and all rows were then moved by at most 12 % towards the choices that cost least.  A row gives the times of its tile
+// within 6 - 9 % (standard deviation, sizes where it is within 1.5 of the best).  How good the choice is was measured on other sizes, see the tables.
 struct GemmTile {
     uint32_t bm, bn, teams, chains, resident;                 // chains: the most that one team can keep
-    double base, step, loaded, stores;
+    double base, step, loaded, stores, fresh;
 };
 inline uint32_t chains_per_team(const GemmTile &t, uint32_t chains) { return (chains + t.teams - 1) / t.teams; }
 // `chains`: into how many chains of fp32 sums the contraction is to be dealt at least
 template <int COUNT>
-inline int pick_tile(const GemmTile (&tiles)[COUNT], uint32_t M, uint32_t N, uint32_t K, uint32_t chains) {
+inline int pick_tile(const GemmTile (&tiles)[COUNT], double uneven, uint32_t M, uint32_t N, uint32_t K, uint32_t chains) {
+    const double megabytes = (2.0 * M + N) * K / 1e6;
     int best = -1;
     double best_cost = 0.0;
     for (int i = 0; i < COUNT; ++i) {
@@ -84,9 +86,9 @@ inline int pick_tile(const GemmTile (&tiles)[COUNT], uint32_t M, uint32_t N, uin
         if (count > 0x7fffffffull) continue;
         const double per_unit = static_cast<double>(count) / 256.0;
         const double alone = t.step * static_cast<double>((count + 256ull * t.resident - 1) / (256ull * t.resident));
-        const double busy = t.loaded * per_unit;
+        const double busy = t.loaded * (per_unit + uneven * (static_cast<double>((count + 255) / 256) - per_unit));
         const uint64_t steps = (static_cast<uint64_t>(K) + 64ull * t.teams - 1) / (64ull * t.teams);
-        const double cost = t.base + t.stores * per_unit + static_cast<double>(steps) * (alone > busy ? alone : busy);
+        const double cost = t.base + t.stores * per_unit + t.fresh * megabytes + static_cast<double>(steps) * (alone > busy ? alone : busy);
         if (best < 0 || cost < best_cost) {
             best = i;
             best_cost = cost;

@@ -19,8 +19,8 @@ def pair(E, M, bias=None):
 
 def gemm_tile(EM, M, N, K):
     """Index of the tile that A [M x K] times K x N (or transposed N x K) weights takes: 256 x 256, 128 x 256 by four waves and by eight,
-    128 x 128, 64 x 128, 64 x 64 by one, two and four teams of waves for S1E4M3; 256 x 256, 256 x 128, 128 x 128, 128 x 64, 64 x 64 by two and
-    four for the other formats."""
+    128 x 128, 64 x 128, 64 x 64 by one, two and four teams of waves for S1E4M3; 256 x 256, 256 x 128, 128 x 256, 128 x 128, 128 x 64, 64 x 64 by
+    one, two and four for the other formats."""
     fn = omc._lib.omc_internal_gemm_tile
     fn.restype, fn.argtypes = C.c_int, [C.c_int] + [C.c_uint32] * 3
     return fn(int(tuple(EM) == (4, 3)), M, N, K)

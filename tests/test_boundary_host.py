@@ -436,7 +436,7 @@ def test_gpu_tests_reach_every_tile():
     import test_gpu_dw
     import test_gpu_gemm
 
-    for EM, tiles in (((4, 3), 8), ((3, 7), 6)):
+    for EM, tiles in (((4, 3), 8), ((3, 7), 8)):
         reached = {gemm_tile(EM, *shape) for shape in test_gpu_gemm.HALF_STEP_SHAPES[EM]}
         assert reached == set(range(tiles)), (EM, reached)
         assert all(K % 64 == 32 for _, _, K in test_gpu_gemm.HALF_STEP_SHAPES[EM])
@@ -480,3 +480,13 @@ def test_no_product_is_summed_in_fewer_chains_than_it_was(EM):
              for K in (32, 64, 96, 128, 160, 192, 224, 256, 320, 384, 448, 512, 640, 768, 1024, 1536, 2048, 2592, 3072, 3584, 4096, 8192)
              if gemm_sums(EM, M, N, K) < teams(M, N, K)]
     assert not fewer, fewer[:5]
+
+
+@pytest.mark.parametrize("EM,shape,tile", [((4, 3), (9728, 128, 3680), 4), ((4, 3), (14336, 128, 1568), 4), ((4, 3), (9728, 128, 2432), 4), ((4, 3), (2048, 1152, 640), 5),
+                                           ((4, 3), (8192, 4096, 1024), 1), ((4, 3), (8192, 1024, 4096), 2), ((5, 2), (5376, 3584, 256), 3),
+                                           ((5, 2), (14336, 1280, 288), 3), ((3, 7), (9216, 2944, 320), 3), ((3, 7), (15360, 512, 1120), 2),
+                                           ((3, 7), (512, 3200, 160), 5), ((3, 7), (2048, 1024, 256), 5), ((3, 7), (9472, 256, 224), 5)])
+def test_tiles_that_estimates_by_the_average_unit_missed(EM, shape, tile):
+    """Sizes where a choice by the average number of workgroups on a compute unit, or without the tiles of short contractions, took 2 - 40 % longer
+    than the tile here, which is within 3 % of the best."""
+    assert gemm_tile(EM, *shape) == tile

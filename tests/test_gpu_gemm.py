@@ -6,7 +6,7 @@ import torch
 
 from oracle import omc_oracle as orc
 from paper_2205_03494_amd import omc, synth
-from gpu_util import pair, to_dev
+from gpu_util import gemm_sums, gemm_tile, pair, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -90,13 +90,17 @@ def test_config5_shapes_sampled_rows(shape):
         assert check(C, ref, (r0, r0 + 24)) < 1e-5
 
 
-@pytest.mark.parametrize("K", [256, 2048])                  # (both by four teams of waves)
+SMALL_KERNELS = {256: (5, 4), 2048: (6, 4), 4000: (7, 4)}    # of 256 x 128 results over so many products: 64 x 64 by one, two and four teams
+
+
+@pytest.mark.parametrize("K", list(SMALL_KERNELS))
 @pytest.mark.parametrize("top_at", [None, 0, -1, 12345])
 def test_every_byte_code_exact_with_and_without_the_top_code(top_at, K):
     """S1E4M3 / bias 7 takes the hardware FP8 conversion, which reads a top code (value 480) as NaN; a tile whose sums show one anywhere in
     the stream is computed again, and both conversions must give the exact code values."""
     of, gf = pair(4, 3)
     M, N = 256, 128
+    assert (gemm_tile((4, 3), M, N, K), gemm_sums((4, 3), M, N, K)) == SMALL_KERNELS[K]
     A = np.zeros((M, K), np.float32)
     pick = (np.arange(M) * 7 + 3) % K
     A[np.arange(M), pick] = 1.0
@@ -133,12 +137,13 @@ def test_dx_small_shapes_all_rows(EM, shape):
     check(dX, orc.dequant_gemm_dx(dY, packed, of, None, M, N, K, threads=8), (0, M))
 
 
-@pytest.mark.parametrize("N", [64, 2048])                   # (both by four teams of waves)
+@pytest.mark.parametrize("N", [64] + list(SMALL_KERNELS))   # (64: one step, by one team)
 @pytest.mark.parametrize("top_at", [None, 777])
 def test_dx_identity_pattern_pins_the_transposed_layout(top_at, N):
     # dY = one-hot rows: dX must reproduce columns of W exactly, with and without a top code (both conversions)
     of, gf = pair(4, 3)
     M, K = 256, 128
+    assert gemm_tile((4, 3), M, K, N) == SMALL_KERNELS.get(N, (5, 4))[0]
     dY = np.zeros((M, N), np.float32)
     pick = (np.arange(M) * 5 + 1) % N
     dY[np.arange(M), pick] = 1.0
@@ -212,31 +217,32 @@ def test_every_code_width_half_steps_and_teams(EM, shape):
 
 HALF_STEP = [(256, 256, 2080), (2304, 896, 544), (4096, 1024, 288), (4096, 2048, 96), (4096, 4096, 288), (8192, 1024, 2080)]
 HALF_STEP_SHAPES = {                                        # every tile of the two dispatch tables
-    (4, 3): HALF_STEP + [(3584, 3584, 2976), (1536, 4352, 1312), (512, 4864, 544), (256, 2816, 224), (256, 128, 1056)],
-    (3, 7): HALF_STEP + [(2560, 3328, 1056), (1536, 4608, 1056), (512, 3968, 1056), (256, 1408, 1056)],
+    (4, 3): HALF_STEP + [(3584, 3584, 2976), (1536, 4352, 1312), (512, 4864, 544), (256, 2816, 224), (256, 128, 1056), (256, 128, 4000)],
+    (3, 7): HALF_STEP + [(2560, 3328, 1056), (1536, 4608, 1056), (1792, 3584, 544), (512, 3968, 1056), (256, 1408, 1056)],
 }
 
 
 @pytest.mark.parametrize("EM,shape", [(EM, shape) for EM, shapes in HALF_STEP_SHAPES.items() for shape in shapes])
 def test_every_tile_size_ends_on_half_a_step(EM, shape):
-    """At least one shape per tile of the two dispatch tables (a test without a GPU holds that), 64 x 64 by four teams up to 256 x 256, rows of
-    every tile."""
+    """At least one shape per tile of the two dispatch tables (a test without a GPU holds that), 64 x 64 up to 256 x 256, rows of every
+    tile."""
     M, N, K = shape
     assert both_directions(EM, M, N, K, tile_sample_rows(M, seed=K, per_quarter=4)) < 1e-5
 
 
-# One size for every kernel of the products, by tile and chains of sums (a test without a GPU holds that); all contractions end on half a step.
-FP8_KERNELS = {(0, 1): (3584, 3584, 2976), (1, 1): (2816, 3840, 96), (2, 1): (1280, 3584, 1440), (3, 1): (1536, 2432, 224), (4, 1): (768, 2176, 352),
-               (4, 2): (1280, 896, 1056), (5, 1): (256, 2048, 32), (5, 2): (256, 2816, 224), (5, 4): (256, 128, 32), (6, 2): (256, 3200, 608),
-               (6, 4): (256, 256, 608), (7, 4): (256, 128, 224)}
-BITS_KERNELS = {(0, 1): (8704, 2304, 32), (1, 1): (3072, 2432, 352), (2, 1): (1280, 1664, 480), (2, 2): (1280, 1664, 2592), (3, 1): (768, 2176, 32),
-                (3, 2): (256, 896, 32), (4, 2): (256, 128, 32), (4, 4): (256, 128, 160), (5, 4): (256, 128, 416)}
+# One size for every kernel of the products, by tile and chains of sums (a test without a GPU holds that); nearly all contractions end on half a step.
+FP8_KERNELS = {(0, 1): (3584, 3584, 2976), (1, 1): (2560, 3328, 224), (2, 1): (5632, 768, 416), (3, 1): (1792, 1792, 224), (4, 1): (9472, 128, 288),
+               (4, 2): (8448, 128, 288), (5, 1): (256, 2048, 32), (5, 2): (256, 2816, 224), (5, 4): (256, 128, 32), (6, 2): (6400, 128, 608),
+               (6, 4): (256, 128, 480), (7, 4): (256, 128, 4000)}
+BITS_KERNELS = {(0, 1): (3328, 3840, 224), (1, 1): (3328, 1920, 672), (2, 1): (1792, 3584, 544), (3, 1): (12544, 256, 160), (3, 2): (1280, 1664, 2592),
+                (4, 1): (1792, 2944, 96), (5, 1): (768, 2176, 32), (5, 2): (256, 128, 32), (6, 2): (256, 128, 96), (6, 4): (256, 128, 160),
+                (7, 4): (256, 128, 672)}
 
 
 @pytest.mark.parametrize("EM,kernel", [((4, 3), k) for k in FP8_KERNELS] + [(EM, k) for EM in ((2, 3), (5, 2), (3, 7), (4, 7), (5, 7)) for k in BITS_KERNELS])
 def test_every_kernel_with_a_visible_offset(EM, kernel):
     """Both directions of every kernel in 6, 8, 11, 12 and 13 bits (odd widths start a thread's codes in the middle of a dword), with an offset whose row
-    sums count for more than the products do.  1e-5: fp32 sums of at most 2976 products."""
+    sums count for more than the products do.  1e-5: fp32 sums of at most 4000 products."""
     M, N, K = (FP8_KERNELS if EM == (4, 3) else BITS_KERNELS)[kernel]
     assert both_directions(EM, M, N, K, tile_sample_rows(M, seed=K + N), sb=np.array([0.75, 0.125], np.float32)) < 1e-5
 
@@ -273,14 +279,14 @@ def test_top_codes_in_some_tiles_only(shape):
     assert np.array_equal(got, W.reshape(N, K)[:, pick].T)
 
 
-TOP_CODE_SHAPES = [(3584, 3584, 2976), (7936, 1024, 1056), (1536, 4352, 1312), (1280, 2944, 1056), (768, 2688, 1056), (512, 2816, 1056),
-                   (256, 2816, 1056), (256, 128, 1056)]     # every tile in turn
+TOP_CODE_SHAPES = [(3584, 3584, 2976), (2560, 3328, 1056), (7936, 1024, 1056), (1536, 4352, 1312), (1280, 2944, 1056), (768, 2688, 1056),
+                   (512, 2816, 1056), (512, 4864, 544), (256, 2816, 1056), (256, 128, 1056), (256, 128, 4000)]     # every tile in turn
 
 
 @pytest.mark.parametrize("where", ["early", "late", "everywhere"])
 @pytest.mark.parametrize("shape", TOP_CODE_SHAPES)
 def test_top_codes_along_a_long_contraction(shape, where):
-    """The large tiles (256 x 256 and both of 128 x 256, the first three shapes) look for top codes after an eighth of the steps too and stop
+    """The large tiles (256 x 256 and both of 128 x 256, the first four shapes) look for top codes after an eighth of the steps too and stop
     there; whether they do, find one at the end, or find none, every weight has its exact value."""
     of, gf = pair(4, 3)
     M, N, K = shape
