@@ -3,6 +3,8 @@
 // variables).  out[i] = (v_0[i] + v_1[i] + ... + v_{R-1}[i]) / R over the clients' decompressed
 // values, summed in client order in fp32, every operation rounded once.  One pass: each client's
 // copy is read once in the form it arrived in (packed codes or fp32), the mean is written once.
+#include <algorithm>
+
 #include "omc_stream.h"
 
 #ifndef OMC_TUNE_AGG_NT
@@ -357,23 +359,24 @@ int launch_aggregate_mean(const AggHeader *ah, const void *agg_dev, const AggPoi
         if (groups[gi].kind == kGroupFp32 && groups[gi].nitems > 0) flat = &groups[gi];
         if (groups[gi].kind == kGroupTail && groups[gi].nitems > 0) tail = &groups[gi];
     }
-    uint64_t rest_blocks = 0;
-    if (tail) {
-        aa.tail_first = tail->first_item;
-        rest_blocks += static_cast<uint64_t>(tail->nitems) * kTailParts;
-    }
-    if (flat) {
-        aa.flat_first = flat->first_item;
-        rest_blocks += static_cast<uint64_t>(flat->nitems) * kFlatParts;
-    }
-    if (rest_blocks > 0x7fffffffull) return static_cast<int>(hipErrorInvalidValue);
-    aa.tail_blocks = tail ? tail->nitems * kTailParts : 0;
+    uint32_t tails = 0, tails_left = tail ? tail->nitems : 0, flats = 0, flats_left = flat ? flat->nitems : 0;
+    auto take_rest = [&]() -> uint64_t {                     // at most one launch's share of what is left: its workgroups
+        aa.tail_first = tail ? tail->first_item + tails : 0;
+        aa.flat_first = flat ? flat->first_item + flats : 0;
+        const uint32_t nt = std::min(tails_left, kMostSharingBlocks / kTailParts), nf = std::min(flats_left, kMostSharingBlocks / kFlatParts);
+        tails += nt;
+        tails_left -= nt;
+        flats += nf;
+        flats_left -= nf;
+        aa.tail_blocks = nt * kTailParts;
+        return static_cast<uint64_t>(aa.tail_blocks) + nf * kFlatParts;
+    };
     for (uint32_t gi = 0; gi < ah->ngroups; ++gi) {
         const PlanGroup &g = groups[gi];
         if (g.nitems == 0 || g.kind != kGroupFull) continue;
         aa.first_item = g.first_item;
         aa.parts = parts_of(g.bits, g.nitems);
-        const uint64_t blocks = static_cast<uint64_t>(g.nitems) * aa.parts + rest_blocks;
+        const uint64_t blocks = static_cast<uint64_t>(g.nitems) * aa.parts + take_rest();
         if (blocks > 0x7fffffffull) return static_cast<int>(hipErrorInvalidValue);
         aa.full_blocks = g.nitems * aa.parts;
         const dim3 grid(static_cast<uint32_t>(blocks));
@@ -389,12 +392,11 @@ int launch_aggregate_mean(const AggHeader *ah, const void *agg_dev, const AggPoi
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return static_cast<int>(e);
-        rest_blocks = 0;
-        aa.tail_blocks = 0;
     }
-    if (rest_blocks > 0) {
+    while (tails_left > 0 || flats_left > 0) {               // what no full tile's launch took
+        const uint64_t blocks = take_rest();
         aa.full_blocks = 0;
-        aggregate_rest_kernel<<<dim3(static_cast<uint32_t>(rest_blocks)), dim3(64), 0, st>>>(aa);
+        aggregate_rest_kernel<<<dim3(static_cast<uint32_t>(blocks)), dim3(64), 0, st>>>(aa);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return static_cast<int>(e);
     }

@@ -182,6 +182,19 @@ inline void launch_codec(const CodecArgs &ca, hipStream_t st) {
     codec_kernel<B, MODE, VARIANT><<<dim3(codec_blocks(ca)), dim3(64), 0, st>>>(ca);
 }
 
+// Moves what is left of a set's copies, at most one launch's share, to this launch.
+inline void take_copies(SetGroups &rest, CodecArgs &ca) {
+    ca.fp32_first = rest.fp32_first;
+    ca.fp32_nitems = rest.fp32_nitems < kMostSharingBlocks / kCopyParts ? rest.fp32_nitems : kMostSharingBlocks / kCopyParts;
+    rest.fp32_first += ca.fp32_nitems;
+    rest.fp32_nitems -= ca.fp32_nitems;
+}
+inline void take_tails(SetGroups &rest, CodecArgs &ca) {
+    ca.tail_first = rest.tail_first;
+    ca.tail_nitems = rest.tail_nitems;
+    rest.tail_nitems = 0;
+}
+
 // Tails of a set that has no full tile at all.
 template <int MODE>
 __global__ __launch_bounds__(64) void codec_tail_kernel(CodecArgs ca) {

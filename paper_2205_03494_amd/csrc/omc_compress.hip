@@ -135,37 +135,30 @@ int launch_compress_set(const float *values, const PlanHeader *ph, const void *p
     ca.vin = values;
     ca.ws = ws;
     // the copies of fp32 variables and the ragged tails ride along with the first full-tile launch
-    const SetGroups sg = set_groups(groups, ph->ngroups);
-    bool rode = false;
+    SetGroups rest = set_groups(groups, ph->ngroups);
     for (uint32_t gi = 0; gi < ph->ngroups; ++gi) {
         const PlanGroup &g = groups[gi];
         if (g.nitems == 0 || g.kind != kGroupFull) continue;
         ca.first_item = g.first_item;
         ca.nitems = g.nitems;
-        ca.fp32_first = sg.fp32_first;
-        ca.fp32_nitems = rode ? 0u : sg.fp32_nitems;
-        ca.tail_first = sg.tail_first;
-        ca.tail_nitems = rode ? 0u : sg.tail_nitems;
-        rode = true;
+        take_copies(rest, ca);
+        take_tails(rest, ca);
         const int rc = launch_full(g.bits, g.wide, ca, st);
         if (rc != 0) return rc;
     }
-    if (!rode) {                                       // no full tile in the whole set
-        ca.first_item = ca.nitems = 0;
-        ca.fp32_first = sg.fp32_first;
-        ca.fp32_nitems = sg.fp32_nitems;
+    ca.first_item = ca.nitems = 0;                     // what no full tile's launch took
+    while (rest.fp32_nitems > 0) {
+        take_copies(rest, ca);
         ca.tail_nitems = 0;
-        if (sg.fp32_nitems > 0) {
-            launch_codec<8, kCompress, 0>(ca, st);
-            const int rc = static_cast<int>(hipGetLastError());
-            if (rc != 0) return rc;
-        }
-        ca.tail_first = sg.tail_first;
-        if (sg.tail_nitems > 0) {
-            codec_tail_kernel<kCompress><<<dim3(sg.tail_nitems), dim3(64), 0, st>>>(ca);
-            const int rc = static_cast<int>(hipGetLastError());
-            if (rc != 0) return rc;
-        }
+        launch_codec<8, kCompress, 0>(ca, st);
+        const int rc = static_cast<int>(hipGetLastError());
+        if (rc != 0) return rc;
+    }
+    if (rest.tail_nitems > 0) {
+        take_tails(rest, ca);
+        codec_tail_kernel<kCompress><<<dim3(ca.tail_nitems), dim3(64), 0, st>>>(ca);
+        const int rc = static_cast<int>(hipGetLastError());
+        if (rc != 0) return rc;
     }
     if (ph->nquant > 0) {
         finalize_plan_kernel<kFinalizeWaves><<<dim3(ph->nvars), dim3(64 * kFinalizeWaves), 0, st>>>(

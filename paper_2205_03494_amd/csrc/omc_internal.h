@@ -214,6 +214,10 @@ constexpr uint64_t kTransportAlign = 256;
 bool make_fmt_params(omc_format f, FmtParams *out);
 const PlanHeader *plan_check(const void *plan_host);
 
+// HIP counts the work-items of a launch in 32 bits: a grid of 2^32 or more runs modulo 2^32, without an error unless nothing is left.  Work items that
+// several workgroups share are therefore launched in runs of at most so many workgroups (a set of millions of small variables has several).
+constexpr uint32_t kMostSharingBlocks = 1u << 22;
+
 // ---- launchers, one translation unit each (device code) -----------------------------------
 // Arguments already validated.  Return hipError_t as int.
 struct VarArgs {

@@ -76,14 +76,13 @@ __global__ __launch_bounds__(64 * kFinalizeWaves) void reselect_sb_kernel(const 
     }
 }
 
-// A plan's full-tile groups; tails and copies ride on whichever launch is first.
+// A plan's full-tile groups; tails and copies ride on whichever launch is first (of more copies than one launch takes, the others on the next ones).
 struct Side {
     CodecArgs args;
     const PlanGroup *groups;
     uint32_t ngroups;
     SetGroups rest;
-    bool rode;
-    Side(const PlanPair &plan) : args{}, groups(nullptr), ngroups(0), rest{}, rode(false) {
+    Side(const PlanPair &plan) : args{}, groups(nullptr), ngroups(0), rest{} {
         if (!plan.host) return;
         args.plan = plan.dev;
         args.var_off = plan.host->var_off;
@@ -92,24 +91,19 @@ struct Side {
         ngroups = plan.host->ngroups;
         rest = set_groups(groups, ngroups);
     }
-    // arguments for this group (nullptr: none of its width), with the tails and copies if they have not been launched yet
+    // arguments for this group (nullptr: none of its width), with what is left of the tails and copies
     CodecArgs take(const PlanGroup *g) {
         CodecArgs ca = args;
         if (g) {
             ca.first_item = g->first_item;
             ca.nitems = g->nitems;
         }
-        if (!rode) {
-            ca.tail_first = rest.tail_first;
-            ca.tail_nitems = rest.tail_nitems;
-            ca.fp32_first = rest.fp32_first;
-            ca.fp32_nitems = rest.fp32_nitems;
-        }
-        rode = true;
+        take_copies(rest, ca);
+        take_tails(rest, ca);
         return ca;
     }
     const PlanGroup *full(uint32_t i) const { return groups[i].kind == kGroupFull && groups[i].nitems > 0 ? &groups[i] : nullptr; }
-    bool left() const { return !rode && (rest.tail_nitems > 0 || rest.fp32_nitems > 0); }
+    bool left() const { return rest.tail_nitems > 0 || rest.fp32_nitems > 0; }
 };
 
 int launch_reselect(const void *arena_old, const float *sb_old, void *arena_new, float *sb_new, const PlanPair &to_codes,
@@ -140,7 +134,7 @@ int launch_reselect(const void *arena_old, const float *sb_old, void *arena_new,
         const int rc = launch_width(g->bits, 0, c.left() ? c.take(nullptr) : CodecArgs{}, d.take(g), st);
         if (rc != 0) return rc;
     }
-    if (c.left() || d.left()) {                              // no full tile anywhere: any width serves
+    while (c.left() || d.left()) {                           // what no full tile's launch took: any width serves
         const int rc = launch_width(8, 0, c.left() ? c.take(nullptr) : CodecArgs{}, d.left() ? d.take(nullptr) : CodecArgs{}, st);
         if (rc != 0) return rc;
     }

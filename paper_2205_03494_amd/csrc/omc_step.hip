@@ -86,6 +86,21 @@ int launch_step(void *arena, const PlanHeader *ph, const void *plan_dev, float *
         const uint64_t left = cache > all_codes ? cache - all_codes : 0;
         if (fp32_group && ((OMC_TUNE_KEEP_FP32 >> opt.kind) & 1)) fp32_keep_items = static_cast<uint32_t>(std::min<uint64_t>(fp32_group->nitems, left / (4ull * kChunkElems)));
     }
+    // fp32 items from this one of the group on, in launches of their own (see kMostSharingBlocks)
+    constexpr uint32_t kFp32Run = kMostSharingBlocks / kFp32Parts;
+    auto launch_fp32 = [&](uint32_t from) -> int {
+        for (; from < fp32_group->nitems; from += kFp32Run) {
+            sa.first_item = sa.fp32_first = fp32_group->first_item + from;
+            sa.fp32_keep_items = fp32_keep_items > from ? fp32_keep_items - from : 0;
+            const dim3 grid(std::min(fp32_group->nitems - from, kFp32Run) * kFp32Parts);
+            if (opt.kind == OMC_SGD) step_fp32_kernel<kStepSgd><<<grid, dim3(64), 0, st>>>(sa);
+            else if (opt.kind == OMC_MOMENTUM) step_fp32_kernel<kStepMomentum><<<grid, dim3(64), 0, st>>>(sa);
+            else step_fp32_kernel<kStepAdam><<<grid, dim3(64), 0, st>>>(sa);
+            const int rc = static_cast<int>(hipGetLastError());
+            if (rc != 0) return rc;
+        }
+        return 0;
+    };
     auto take = [&](uint32_t nitems, uint64_t item_bytes) -> uint32_t {   // how many of nitems the budget still covers
         const uint64_t k = std::min<uint64_t>(nitems, keep_budget / item_bytes);
         keep_budget -= k * item_bytes;
@@ -108,7 +123,7 @@ int launch_step(void *arena, const PlanHeader *ph, const void *plan_dev, float *
             sa.tail_nitems = tail_nitems;
             if (fp32_group) {
                 sa.fp32_first = fp32_group->first_item;
-                sa.fp32_nitems = fp32_group->nitems;
+                sa.fp32_nitems = std::min(fp32_group->nitems, kFp32Run);
                 sa.fp32_keep_items = fp32_keep_items;
             }
             fused_done = true;
@@ -122,22 +137,19 @@ int launch_step(void *arena, const PlanHeader *ph, const void *plan_dev, float *
             else step_tail_kernel<kStepAdam><<<dim3(tail_nitems), dim3(64), 0, st>>>(sa);
             rc = static_cast<int>(hipGetLastError());
         } else if (g.kind == kGroupFp32) {
-            sa.fp32_first = g.first_item;
-            sa.fp32_keep_items = fp32_keep_items;
-            if (opt.kind == OMC_SGD) step_fp32_kernel<kStepSgd><<<dim3(g.nitems * kFp32Parts), dim3(64), 0, st>>>(sa);
-            else if (opt.kind == OMC_MOMENTUM) step_fp32_kernel<kStepMomentum><<<dim3(g.nitems * kFp32Parts), dim3(64), 0, st>>>(sa);
-            else step_fp32_kernel<kStepAdam><<<dim3(g.nitems * kFp32Parts), dim3(64), 0, st>>>(sa);
-            rc = static_cast<int>(hipGetLastError());
+            rc = launch_fp32(0);
         } else {
             const uint32_t kept = take(g.nitems, static_cast<uint64_t>(tiles_per_chunk(g.bits)) * kTileElems * g.bits / 8);
             for (int part = 0; part < 2 && rc == 0; ++part) {              // the cached items, then the streaming ones
                 sa.first_item = g.first_item + (part == 0 ? 0 : kept);
                 sa.nitems = part == 0 ? kept : g.nitems - kept;
                 if (sa.nitems == 0) continue;
+                const bool first = !fused_done;
                 ride_along();
                 if (opt.kind == OMC_SGD) rc = launch_step_group_sgd(g.bits, g.wide, sa, part == 0, st);
                 else if (opt.kind == OMC_MOMENTUM) rc = launch_step_group_momentum(g.bits, g.wide, sa, part == 0, st);
                 else rc = launch_step_group_adam(g.bits, g.wide, sa, part == 0, st);
+                if (rc == 0 && first && fp32_group) rc = launch_fp32(kFp32Run);
             }
         }
         if (rc != 0) return rc;

@@ -145,3 +145,68 @@ def test_parts_of_the_copies(many):
         if not mask[i]:
             assert bits_equal(o[a:a + s.n], vals[a:a + s.n]), s.name
         assert np.all(np.isnan(o[a + s.n:end]))
+
+
+def many_small_variables(count, quantized):
+    """A table of `count` variables of one to seven elements, 32 bytes apart in the arena and eight elements in the aux order; no layout helper, which
+    would take minutes."""
+    rows = np.zeros(count, np.dtype([("data", "<u8"), ("aux", "<u8"), ("n", "<u8"), ("E", "u1"), ("M", "u1"), ("bias", "<i2"), ("flags", "<u4")]))
+    rows["data"] = 32 * np.arange(count, dtype=np.uint64)
+    rows["aux"] = 8 * np.arange(count, dtype=np.uint64)
+    rows["n"] = 1 + np.arange(count) % 7
+    rows["E"], rows["M"], rows["bias"] = 4, 3, 7
+    rows["flags"] = np.where(quantized, omc.OMC_VAR_QUANTIZED, 0)
+    live = (np.arange(8)[None, :] < rows["n"][:, None].astype(np.int64)).ravel()
+    return (omc.omc_var * count).from_buffer(rows), torch.from_numpy(live).cuda()
+
+
+@pytest.mark.parametrize("count,full_tile", [((1 << 19) + 11, True), ((1 << 23) + 11, False)])
+def test_millions_of_small_fp32_variables(count, full_tile):
+    """Every fp32 item is eight workgroups' work.  More than 2^19 of them take several launches, with a launch of full tiles before them and without; a grid of 2^32
+    work-items or more (more than 2^23 items in one launch) would run only what is left of it modulo 2^32."""
+    table, live = many_small_variables(count, np.zeros(count, bool))
+    if full_tile:                                           # the last variable: quantized, one tile, in room of its own behind the others
+        table[count - 1].n, table[count - 1].flags = 2048, omc.OMC_VAR_QUANTIZED
+    plan = omc.omc_plan_build(table)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    aux = max(8 * count, plan.aux_elems)
+    w = torch.zeros(aux, device="cuda").normal_(0, 1, generator=g)
+    grad = torch.zeros(aux, device="cuda").normal_(0, 1, generator=g)
+    arena = torch.zeros(max(32 * count, plan.arena_bytes), dtype=torch.uint8, device="cuda")
+    sb = torch.tensor([1.0, 0.0], device="cuda").repeat(count, 1).contiguous()
+    ws = torch.empty(max(plan.workspace_bytes, 16), dtype=torch.uint8, device="cuda")
+    omc.omc_compress_set(w, plan, arena, sb, ws)
+    omc.omc_step_update_recompress(arena, plan, sb, grad, None, None, omc.opt(omc.OMC_SGD, 0.5), ws)
+    out = torch.full((aux,), float("nan"), device="cuda")
+    omc.omc_decompress_set(arena, plan, sb, out)
+    last = 8 * (count - 1) if full_tile else 8 * count
+    want = w - 0.5 * grad
+    got, mask = out[:last], live[:last]
+    assert torch.equal(got[mask], want[:last][mask])        # (0.5 times a float is exact)
+    assert torch.isnan(got[~mask]).all()
+
+
+@pytest.mark.parametrize("quantized", ["nowhere", "at one client"])
+def test_mean_of_millions_of_small_variables(quantized):
+    """2^20 and more all-fp32 items, four workgroups each, and as many ragged tails, eight each: more than one launch's share."""
+    count = (1 << 20) + 11
+    masks = [np.full(count, quantized == "at one client"), np.zeros(count, bool)]
+    plans, arenas, sbs, values = [], [], [], []
+    for r, mask in enumerate(masks):
+        table, live = many_small_variables(count, mask)
+        plan = omc.omc_plan_build(table)
+        w = torch.zeros(8 * count, device="cuda").normal_(0, 1, generator=torch.Generator(device="cuda").manual_seed(r))
+        arena = torch.zeros(32 * count, dtype=torch.uint8, device="cuda")
+        sb = torch.tensor([1.0, 0.0], device="cuda").repeat(count, 1).contiguous()
+        ws = torch.empty(max(plan.workspace_bytes, 16), dtype=torch.uint8, device="cuda")
+        omc.omc_compress_set(w, plan, arena, sb, ws)
+        back = torch.zeros(8 * count, device="cuda")
+        omc.omc_decompress_set(arena, plan, sb, back)
+        if not mask.any():
+            assert torch.equal(back[live], w[live])
+        plans.append(plan), arenas.append(arena), sbs.append(sb), values.append(back)
+    agg = omc.omc_aggregate_plan_build(plans)
+    out = torch.full((8 * count,), float("nan"), device="cuda")
+    omc.omc_aggregate_mean(agg, arenas, sbs, out)
+    assert torch.equal(out[live], ((values[0] + values[1]) / 2)[live])
+    assert torch.isnan(out[~live]).all()
