@@ -47,7 +47,6 @@ inline SetGroups set_groups(const PlanGroup *groups, uint32_t ngroups) {
 // Four waves to an item, each with all its loads in flight at once and no load behind its own stores: conversions of 115 M elements 199 -> 195
 // us, a change of a tenth of the 11-bit variables and the message 150 -> 143; eight waves 195 and 147.
 constexpr uint32_t kCopyParts = OMC_TUNE_COPY_PARTS;
-constexpr uint32_t kFewCopyItems = 1024;
 constexpr int kCopyPartElems = kChunkElems / static_cast<int>(kCopyParts);
 // fp32 variable of a set: plain copy between the aux-indexed array and the arena (16-byte pieces)
 template <int MODE>
@@ -145,8 +144,7 @@ __device__ __forceinline__ void codec_block(const CodecArgs &ca, uint32_t index,
     const uint32_t block = index - ca.tail_nitems;
     if (block >= ca.nitems) {
         const uint32_t part = block - ca.nitems;
-        const bool many = ca.fp32_nitems > kFewCopyItems;    // (of few items, mostly vectors, the parts that are often empty come last)
-        copy_fp32_item<MODE>(ca, ca.fp32_first + (many ? part / kCopyParts : part % ca.fp32_nitems), many ? part % kCopyParts : part / ca.fp32_nitems);
+        copy_fp32_item<MODE>(ca, ca.fp32_first + part / kCopyParts, part % kCopyParts);
         return;
     }
     uint32_t item = block, var = 0, chunk = block;
