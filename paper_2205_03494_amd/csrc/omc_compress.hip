@@ -38,7 +38,7 @@ static int launch_full(uint32_t bits, uint32_t variant, const CodecArgs &ca, hip
     switch (bits) {
 #define X(BITS)                                                                                  \
     case BITS:                                                                                   \
-        launch_generic_variant<BITS>(variant, ca, st);                                     \
+        launch_generic_variant<BITS>(variant, ca, st);                                           \
         break;
         OMC_FOR_EACH_BITS(X)
 #undef X

@@ -7,7 +7,7 @@ static int launch_full(uint32_t bits, const CodecArgs &ca, hipStream_t st) {
     switch (bits) {
 #define X(BITS)                                                                       \
     case BITS:                                                                        \
-        launch_codec<BITS, kDecompress, 0>(ca, st);      \
+        launch_codec<BITS, kDecompress, 0>(ca, st);                                   \
         break;
         OMC_FOR_EACH_BITS(X)
 #undef X

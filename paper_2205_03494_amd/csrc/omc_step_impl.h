@@ -33,14 +33,10 @@ struct StepArgs {
 };
 
 // Variables kept in fp32 (paper Sec. 2.4, 2.5): the update alone, 16-byte pieces, coalesced.
-// Every stream is touched once per step, so all loads and stores are non-temporal; a batch of
-// kFp32Batch pieces per lane is loaded before any of them is updated (memory-level parallelism is
-// all this loop needs).
+// Every stream is touched once per step, so all loads and stores are non-temporal; all pieces of a lane
+// are loaded before any of them is updated (memory-level parallelism is all that is needed).
 #ifndef OMC_TUNE_FP32_NT
 #define OMC_TUNE_FP32_NT 1
-#endif
-#ifndef OMC_TUNE_FP32_BATCH
-#define OMC_TUNE_FP32_BATCH 2
 #endif
 #ifndef OMC_TUNE_FP32_PARTS
 #define OMC_TUNE_FP32_PARTS 8
@@ -55,7 +51,6 @@ template <int MODE, bool KEEPW>
 __device__ __forceinline__ void fp32_item_body(const StepArgs &sa, uint32_t item, uint32_t part) {
     constexpr bool NT = OMC_TUNE_FP32_NT != 0;
     constexpr bool NTW = NT && !KEEPW;                   // the values themselves: read and rewritten by every step
-    constexpr int kFp32Batch = OMC_TUNE_FP32_BATCH;
     const PlanItem *items = reinterpret_cast<const PlanItem *>(sa.plan + sa.item_off);
     const PlanVar *vars = reinterpret_cast<const PlanVar *>(sa.plan + sa.var_off);
     const PlanItem it = to_scalar_regs(items[item]);
@@ -67,8 +62,7 @@ __device__ __forceinline__ void fp32_item_body(const StepArgs &sa, uint32_t item
     float *__restrict__ v = sa.st1 ? sa.st1 + pv.aux_offset : nullptr;
     const uint64_t n = pv.n;
     const uint64_t begin = static_cast<uint64_t>(it.chunk) * kChunkElems + part * kFp32PartElems;
-    constexpr int kIters = kFp32PartElems / 256;
-    static_assert(kIters % kFp32Batch == 0, "batches tile the chunk");
+    constexpr int kPieces = kFp32PartElems / 256;            // per lane
     auto ld = [&](const float *p, bool nt = NT) {
         const f32x4 *q = reinterpret_cast<const f32x4 *>(p);
         return nt ? __builtin_nontemporal_load(q) : *q;
@@ -77,75 +71,69 @@ __device__ __forceinline__ void fp32_item_body(const StepArgs &sa, uint32_t item
         f32x4 *q = reinterpret_cast<f32x4 *>(p);
         if (nt) __builtin_nontemporal_store(x, q); else *q = x;
     };
-    for (int j0 = 0; j0 < kIters; j0 += kFp32Batch) {
-        const uint64_t e0 = begin + (static_cast<uint64_t>(j0) * 64 + lane) * 4;
-        if (begin + static_cast<uint64_t>(j0 + kFp32Batch) * 256 <= n) {          // the whole batch is inside: wave-uniform
-            f32x4 xw[kFp32Batch], xg[kFp32Batch], xm[kFp32Batch], xv[kFp32Batch];
+    const uint64_t e0 = begin + static_cast<uint64_t>(lane) * 4;
+    f32x4 xw[kPieces], xg[kPieces], xm[kPieces], xv[kPieces];
+    auto update = [&](int u) {
 #pragma unroll
-            for (int u = 0; u < kFp32Batch; ++u) {
-                const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
-                xw[u] = ld(w + e, NTW);
-                xg[u] = ld(g + e);
-                xm[u] = (MODE >= kStepMomentum) ? ld(m + e) : f32x4{0, 0, 0, 0};
-                xv[u] = (MODE == kStepAdam) ? ld(v + e) : f32x4{0, 0, 0, 0};
-            }
-#pragma unroll
-            for (int u = 0; u < kFp32Batch; ++u) {
-                const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    float tm = xm[u][c], tv = xv[u][c];
-                    xw[u][c] = apply_update<MODE>(xw[u][c], xg[u][c], tm, tv, sa.oc);
-                    xm[u][c] = tm;
-                    xv[u][c] = tv;
-                }
-                st(w + e, xw[u], NTW);
-                if (MODE >= kStepMomentum) st(m + e, xm[u]);
-                if (MODE == kStepAdam) st(v + e, xv[u]);
-            }
-            continue;
+        for (int c = 0; c < 4; ++c) {
+            float tm = xm[u][c], tv = xv[u][c];
+            xw[u][c] = apply_update<MODE>(xw[u][c], xg[u][c], tm, tv, sa.oc);
+            xm[u][c] = tm;
+            xv[u][c] = tv;
         }
-        if (begin + static_cast<uint64_t>(j0) * 256 >= n) return;
-        // the variable ends in this batch: whole pieces where there are any, all loads in flight together
-        f32x4 xw[kFp32Batch], xg[kFp32Batch], xm[kFp32Batch], xv[kFp32Batch];
-        uint32_t live[kFp32Batch];                                                 // this lane's elements of a piece
-        auto ld_live = [&](const float *p, uint32_t count) {
-            f32x4 x = {0, 0, 0, 0};
-            if (count == 4) x = ld(p);
-            else
-                for (uint32_t c = 0; c < 3; ++c)
-                    if (c < count) x[c] = p[c];
-            return x;
-        };
-        auto st_live = [&](float *p, const f32x4 &x, uint32_t count) {
-            if (count == 4) st(p, x);
-            else
-                for (uint32_t c = 0; c < 3; ++c)
-                    if (c < count) p[c] = x[c];
-        };
+    };
+    if (begin + kFp32PartElems <= n) {                       // the whole part is inside: wave-uniform
 #pragma unroll
-        for (int u = 0; u < kFp32Batch; ++u) {
+        for (int u = 0; u < kPieces; ++u) {
             const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
-            live[u] = e >= n ? 0u : n - e < 4 ? static_cast<uint32_t>(n - e) : 4u;
-            xw[u] = ld_live(w + e, live[u]);
-            xg[u] = ld_live(g + e, live[u]);
-            xm[u] = (MODE >= kStepMomentum) ? ld_live(m + e, live[u]) : f32x4{0, 0, 0, 0};
-            xv[u] = (MODE == kStepAdam) ? ld_live(v + e, live[u]) : f32x4{0, 0, 0, 0};
+            xw[u] = ld(w + e, NTW);
+            xg[u] = ld(g + e);
+            xm[u] = (MODE >= kStepMomentum) ? ld(m + e) : f32x4{0, 0, 0, 0};
+            xv[u] = (MODE == kStepAdam) ? ld(v + e) : f32x4{0, 0, 0, 0};
         }
 #pragma unroll
-        for (int u = 0; u < kFp32Batch; ++u) {
+        for (int u = 0; u < kPieces; ++u) {
             const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                float tm = xm[u][c], tv = xv[u][c];
-                xw[u][c] = apply_update<MODE>(xw[u][c], xg[u][c], tm, tv, sa.oc);
-                xm[u][c] = tm;
-                xv[u][c] = tv;
-            }
-            st_live(w + e, xw[u], live[u]);
-            if (MODE >= kStepMomentum) st_live(m + e, xm[u], live[u]);
-            if (MODE == kStepAdam) st_live(v + e, xv[u], live[u]);
+            update(u);
+            st(w + e, xw[u], NTW);
+            if (MODE >= kStepMomentum) st(m + e, xm[u]);
+            if (MODE == kStepAdam) st(v + e, xv[u]);
         }
+        return;
+    }
+    if (begin >= n) return;
+    // the variable ends in this part: whole pieces where there are any, all loads in flight together
+    uint32_t live[kPieces];                                  // this lane's elements of a piece
+    auto ld_live = [&](const float *p, uint32_t count) {
+        f32x4 x = {0, 0, 0, 0};
+        if (count == 4) x = ld(p);
+        else
+            for (uint32_t c = 0; c < 3; ++c)
+                if (c < count) x[c] = p[c];
+        return x;
+    };
+    auto st_live = [&](float *p, const f32x4 &x, uint32_t count) {
+        if (count == 4) st(p, x);
+        else
+            for (uint32_t c = 0; c < 3; ++c)
+                if (c < count) p[c] = x[c];
+    };
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
+        const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
+        live[u] = e >= n ? 0u : n - e < 4 ? static_cast<uint32_t>(n - e) : 4u;
+        xw[u] = ld_live(w + e, live[u]);
+        xg[u] = ld_live(g + e, live[u]);
+        xm[u] = (MODE >= kStepMomentum) ? ld_live(m + e, live[u]) : f32x4{0, 0, 0, 0};
+        xv[u] = (MODE == kStepAdam) ? ld_live(v + e, live[u]) : f32x4{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
+        const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
+        update(u);
+        st_live(w + e, xw[u], live[u]);
+        if (MODE >= kStepMomentum) st_live(m + e, xm[u], live[u]);
+        if (MODE == kStepAdam) st_live(v + e, xv[u], live[u]);
     }
 }
 
@@ -261,7 +249,7 @@ inline int launch_step_group_keep(uint32_t bits, uint32_t variant, const StepArg
     switch (bits) {
 #define X(BITS)                                                              \
     case BITS:                                                               \
-        launch_step_generic_variant<BITS, MODE, KEEP>(variant, sa, st); \
+        launch_step_generic_variant<BITS, MODE, KEEP>(variant, sa, st);      \
         break;
         OMC_FOR_EACH_BITS(X)
 #undef X
