@@ -25,8 +25,10 @@ beside it.  `cpu_baseline` is the CPU oracle timed on a bounded sample of the he
 machine's host cores, one thread and all cores.
 """
 import argparse
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -159,6 +161,34 @@ def kernel_times(torch, omc, wl, steps, flags=0, flush=None):
             for j in range(nl)]
 
 
+
+STEP_KERNEL_SOURCES = ("omc_internal.h", "omc_step_impl.h", "omc_stream.h")
+
+
+def step_kernel_digest():
+    """Of the step kernels' sources without comments and white space: what a counter profile belongs to."""
+    h = hashlib.sha256()
+    for name in STEP_KERNEL_SOURCES:
+        with open(os.path.join(ROOT, "paper_2205_03494_amd", "csrc", name)) as fh:
+            text = re.sub(r"/\*.*?\*/", "", fh.read(), flags=re.S)
+        h.update(re.sub(r"//[^\n]*|\s+", "", text).encode())
+    return h.hexdigest()[:16]
+
+
+def profiled_traffic(workload, elements, folder=None):
+    """HBM bytes of a step launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, if a committed profile of exactly these kernel sources, this workload and
+    this many elements exists: not a reading of this run, so it is labelled with its source and `traffic` stays null."""
+    path = os.path.join(folder or os.path.join(ROOT, "profiles"), f"step_kernel_{workload}_traffic.json")
+    if not os.path.exists(path):
+        return None
+    with open(path) as fh:
+        t = json.load(fh)
+    if t.get("elements_per_launch") != elements or t.get("kernel_sources") != step_kernel_digest():
+        return None
+    return {"bytes": t["fetch_bytes_per_launch"] + t["write_bytes_per_launch"], "fetch_bytes": t["fetch_bytes_per_launch"],
+            "write_bytes": t["write_bytes_per_launch"], "source": t.get("source")}
+
+
 def roofline_block(wl, regimes):
     """regimes: {"evicted": ms list, "back_to_back": ms list, "keep_codes": ms list}.  The dominant kernel is the
     launch that takes longest in the evicted regime."""
@@ -181,16 +211,9 @@ def roofline_block(wl, regimes):
                "frac": rate(regimes["keep_codes"][dom]) / HBM_PEAK_GBS,
                "note": "opt-in: packed codes come back from the 256 MB memory-side cache; not an HBM figure"},
            "all_launches_ms_evicted": ev, "all_launches_ms_back_to_back": regimes["back_to_back"]}
-    # HBM bytes of the same launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, if a committed profile of exactly this
-    # kernel and workload exists: not a reading of this run, so it is labelled with its source and `traffic` stays null
-    tpath = os.path.join(ROOT, "profiles", f"step_kernel_{wl['name']}_traffic.json")
-    if os.path.exists(tpath):
-        with open(tpath) as fh:
-            tj = json.load(fh)
-        if tj.get("elements_per_launch") == L["elements"]:
-            blk["traffic_from_profile"] = {"bytes": tj["fetch_bytes_per_launch"] + tj["write_bytes_per_launch"],
-                                           "fetch_bytes": tj["fetch_bytes_per_launch"],
-                                           "write_bytes": tj["write_bytes_per_launch"], "source": tj.get("source")}
+    traffic = profiled_traffic(wl["name"], L["elements"])
+    if traffic:
+        blk["traffic_from_profile"] = traffic
     return blk
 
 
@@ -562,6 +585,7 @@ def main():
                     help="seconds of untimed steps before any measurement, so that the GPU clocks have ramped up")
     ap.add_argument("--gemm-only", action="store_true", help="only the matrix-core leg (for profiler runs)")
     ap.add_argument("--aggregate-only", action="store_true", help="only the server aggregation leg")
+    ap.add_argument("--round-only", action="store_true", help="only the leg of the change of the subset and the message")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="only run a plain device-to-device copy of known size (1 GiB read + 1 GiB written "
                          "per launch) to calibrate profiler byte counters and show the copy ceiling")
@@ -592,6 +616,9 @@ def main():
         return
     if args.aggregate_only:
         print(json.dumps({"server_aggregation": aggregate_leg(torch, omc, synth, 17)}))
+        return
+    if args.round_only:
+        print(json.dumps({"round_boundary": round_boundary_leg(torch, omc, synth, 17)}))
         return
 
     flush = (torch.empty(1 << 27, device="cuda"), torch.empty(1 << 27, device="cuda"))    # 512 MiB each

@@ -431,6 +431,26 @@ def test_binding_works_without_torchs_private_stream_lookup(monkeypatch):
     assert module._stream(types.SimpleNamespace(cuda_stream=7)) == 7
 
 
+def test_counters_of_other_kernels_are_not_quoted(tmp_path):
+    """bench.py quotes the HBM bytes of a committed counter profile only for the kernel sources, workload and size that were counted."""
+    import importlib.util
+    import json
+
+    spec = importlib.util.spec_from_file_location("bench_under_test", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    profile = {"elements_per_launch": 5, "fetch_bytes_per_launch": 2.0, "write_bytes_per_launch": 1.0, "source": "here"}
+
+    def quoted(elements=5, **changes):
+        (tmp_path / "step_kernel_w_traffic.json").write_text(json.dumps(dict(profile, **changes)))
+        return bench.profiled_traffic("w", elements, str(tmp_path))
+
+    assert quoted(kernel_sources=bench.step_kernel_digest()) == {"bytes": 3.0, "fetch_bytes": 2.0, "write_bytes": 1.0, "source": "here"}
+    assert quoted() is None and quoted(kernel_sources="0123456789abcdef") is None
+    assert quoted(elements=6, kernel_sources=bench.step_kernel_digest()) is None
+    assert bench.profiled_traffic("other", 5, str(tmp_path)) is None
+
+
 def test_gpu_tests_reach_every_tile():
     """The tiles are chosen by measured constants; the sizes in the GPU tests have to reach each of them, whatever the constants."""
     import test_gpu_dw
