@@ -14,8 +14,9 @@
 namespace omc {
 
 // Loads of a batch of clients are in flight together.  Byte codes: eight clients at three waves per SIMD 291 us, four at four 301, two at
-// six 304 (115 M elements, 8 clients; one at eight 311).  The other widths hold a client in 32 registers, and more waves are worth more than
-// more clients: 10 layers of 397 x 1191 in 11 bits, 4 clients, one client at four waves 66 us, two at three 71, four at two 80.
+// six 304 (115 M elements, 8 clients; one at eight 311).  A batch takes 16 registers a client, as a client may be in fp32, and at three waves 12 registers
+// are spilled: 16 bytes a lane out and back per slab of 1024 elements, of which hardly any leaves the caches (1 % of the bytes written to memory).  The other
+// widths hold a client in 32 registers, and more waves are worth more than more clients: 10 layers of 397 x 1191 in 11 bits, 4 clients, one client at four waves 66 us, two at three 71, four at two 80.
 constexpr uint32_t kByteBatch = 8, kByteWaves = 3, kTileWaves = 4, kFlatBatch = 8, kTailBatchClients = 4;
 constexpr uint32_t kTailPart = 256;       // elements of a ragged tail that one workgroup takes: four per lane
 constexpr uint32_t kTailParts = kTileElems / kTailPart;

@@ -63,18 +63,20 @@ struct OptConst {
 template <int MODE, int B>
 struct Tuning {
     static constexpr int light = (B <= 12) ? OMC_TUNE_WAVES_LIGHT : (OMC_TUNE_WAVES_LIGHT > 3 ? 3 : OMC_TUNE_WAVES_LIGHT);
-    // Adam on codes of OMC_TUNE_ADAM_WIDE_BITS bits or more does not fit 256 registers without spilling (and
-    // scratch is memory traffic): one wave per SIMD with the next tile's loads in flight instead
-    // byte-multiple code widths: lanes own 4-element groups, fp32 streams skip the LDS transposition
-    // (not for 8-bit momentum: the registers it saves raise that kernel's occupancy from two to three waves
-    // per SIMD, which measures 2 % slower there)
+    // Byte-multiple code widths: lanes own 4-element groups, fp32 streams skip the LDS transposition (not for 8-bit momentum, which measures 1 %
+    // slower so: 115 M elements 300 us against 297).
     static constexpr bool direct = (B % 8 == 0) && (OMC_TUNE_DIRECT != 0) && !(MODE == kStepMomentum && B == 8);
+    // Adam on codes of OMC_TUNE_ADAM_WIDE_BITS bits or more: one wave per SIMD (256 registers and more), items of one wave with the next tile's
+    // loads in flight.  Items of two waves take 136 - 168 registers, three waves per SIMD.  115 M elements, this way / with two waves, us: 13 bits 491 / 496, 17 bits
+    // 510 / 519, 19 bits 519 / 528; but 16 bits 531 / 526, 24 bits 646 / 556, 32 bits 663 / 607, and on small sets two waves are faster at any width
+    // (13 bits, 6 blocks of 256 x 1024, 66 / 57; one 512 x 512 matrix 19.0 / 13.4): the line pays only for the odd widths on large sets.
     static constexpr bool adam_wide = MODE == kStepAdam && B >= OMC_TUNE_ADAM_WIDE_BITS;
     // Two waves take a work item together, a tile each, where there is state to write back.  A wave's stores and loads share a counter, so one
-    // that goes on to a second tile waits for its own stores before it can use what it loads.  115 M elements, one wave -> two, us:
+    // that goes on to a second tile waits for its own stores before it can use what it loads.  And with no second tile to keep in flight a wave needs
+    // fewer registers, so that twice as many are resident: momentum on 8 / 11 / 13 bits 189 / 201 / 208 -> 103 / 115 / 116, two -> four waves per SIMD; Adam
+    // on 8 / 11 bits 223 / 256 -> 133 / 165, two -> three.  115 M elements, one wave -> two, us:
     // Adam 8 bits 481 -> 463, 11 bits 494 -> 475, 6 bits 486 -> 464; momentum 8 bits 292 -> 287, 13 bits 326 -> 318, 6 bits 291 -> 276; 604 M
-    // elements in 11 bits, momentum 1596 -> 1574.  Plain SGD prefers one (11 bits 139 -> 150, 8 bits under its cap 118 -> 138), and wide Adam,
-    // whose next tile's loads are in flight early, does not care.
+    // elements in 11 bits, momentum 1596 -> 1574.  Plain SGD prefers one (11 bits 139 -> 150, 8 bits under its cap 118 -> 138).
     static constexpr int item_waves = (MODE == kStepMomentum || (MODE == kStepAdam && !adam_wide)) ? 2 : 1;
     static constexpr int waves = adam_wide ? 1 : (MODE == kStepAdam) ? OMC_TUNE_WAVES_ADAM
                                  : (MODE == kStepMomentum) ? OMC_TUNE_WAVES_MOMENTUM : light;
