@@ -133,3 +133,30 @@ def test_parts_of_tails_and_batches_of_clients(R, EM):
     rng = np.random.default_rng(R)
     masks = [np.array([s.is_matrix and (r == R - 1 or rng.random() < 0.6) for s in specs]) for r in range(R)]
     run_case(specs, [EM] * len(specs), masks)
+
+
+@pytest.mark.parametrize("EM", [(3, 7), (2, 3), (5, 10)])
+def test_more_work_items_than_the_chip_holds(EM):
+    """More than 8192 items of full tiles, each one workgroup's, which goes on from tile to tile in the same LDS.  (Smaller sets share an item's tiles out.)
+    Against the mean of what omc_decompress_set gives, which other tests hold to the oracle."""
+    item = 4096 if EM != (2, 3) else 8192
+    sizes = [5000 * item + 2048 + 5, 3300 * item + 77, 4097]
+    gf = omc.fmt(*EM)
+    plans, arenas, sbs, total = [], [], [], None
+    for r, mask in enumerate(((True, True, False), (False, True, True))):
+        at, table = 0, []
+        aux = [sum((n + 3) // 4 * 4 for n in sizes[:i]) for i in range(4)]
+        for i, n in enumerate(sizes):
+            table.append(dict(data_offset=at, aux_offset=aux[i], n=n, fmt=gf, quantized=mask[i]))
+            at += (omc.omc_packed_bytes(gf, n) if mask[i] else 4 * n) + 15 & ~15
+        plan = omc.omc_plan_build(omc.make_var_table(table))
+        w = torch.zeros(aux[3], device="cuda").normal_(0, 0.05, generator=torch.Generator(device="cuda").manual_seed(r))
+        arena, sb = torch.zeros(at, dtype=torch.uint8, device="cuda"), torch.zeros((3, 2), device="cuda")
+        omc.omc_compress_set(w, plan, arena, sb, torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda"))
+        omc.omc_decompress_set(arena, plan, sb, w)
+        total = w if total is None else total + w
+        plans.append(plan), arenas.append(arena), sbs.append(sb)
+    out = torch.full((aux[3],), float("nan"), device="cuda")
+    omc.omc_aggregate_mean(omc.omc_aggregate_plan_build(plans), arenas, sbs, out)
+    for i, n in enumerate(sizes):
+        assert torch.equal(out[aux[i]:aux[i] + n], (total / 2)[aux[i]:aux[i] + n]), i
