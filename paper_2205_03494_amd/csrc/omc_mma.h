@@ -96,6 +96,7 @@ inline int pick_tile(const GemmTile (&tiles)[COUNT], double uneven, uint32_t M, 
     }
     return best;
 }
+
 // Tile of this workgroup in a grid of tiles_m x tiles_n (one-dimensional launch).  Workgroups go to the 8 dies in turn and
 // each die has an L2 of its own, so every die gets a contiguous run of the tile order, in which groups of `group_rows` tile rows
 // share their columns.  The tiles of a die at one time should need as many bytes of the one operand as of the other: eight rows for

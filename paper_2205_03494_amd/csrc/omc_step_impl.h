@@ -30,6 +30,7 @@ struct StepArgs {
     Partial *ws;
     OptConst oc;
     uint32_t fp32_keep_items;           // the first so many fp32 work items keep their values cached from step to step
+    uint32_t fp32_item_by_item;         // parts of the fp32 items on this launch's grid: an item's one after the other, or the first ones of all items first
 };
 
 // Variables kept in fp32 (paper Sec. 2.4, 2.5): the update alone, 16-byte pieces, coalesced.
@@ -45,7 +46,6 @@ struct StepArgs {
 // of the first, as stores and loads share a counter.  Half of 115 M elements in fp32, 2 waves of two batches of four pieces / 4 of
 // one / 8 of one batch of two, us: Adam 569 / 556 / 538, momentum 366 / 356 / 352, SGD 195 / 190 / 184 (one wave, four batches: 591, 374, 201).
 constexpr uint32_t kFp32Parts = OMC_TUNE_FP32_PARTS;
-constexpr uint32_t kFewFp32Items = 512;
 constexpr int kFp32PartElems = kChunkElems / static_cast<int>(kFp32Parts);
 template <int MODE, bool KEEPW>
 __device__ __forceinline__ void fp32_item_body(const StepArgs &sa, uint32_t item, uint32_t part) {
@@ -197,11 +197,8 @@ void step_kernel(StepArgs sa) {
     const uint32_t block = blockIdx.x - sa.tail_nitems;
     if (block >= sa.nitems) {                            // the workgroups past the end serve fp32 variables, a wave a part of an item
         const uint32_t part = (block - sa.nitems) * NW + (NW == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
-        // Neighbouring parts at the same time, but of so few items that all parts are under way at once first the first part of each: momentum, half
-        // of a small encoder in fp32, 332 items 13.6 us (14.1 the other way), 374 18.3 (18.6); 1019 items 26.8 (25.1), 1698 42 (38), half of 115 M
-        // elements 22 % more.  Where the items are vectors alone, whose later parts are empty, it makes no difference.
-        const bool many = sa.fp32_nitems > kFewFp32Items;
-        do_fp32_item<MODE>(sa, sa.fp32_first + (many ? part / kFp32Parts : part % sa.fp32_nitems), many ? part % kFp32Parts : part / sa.fp32_nitems);
+        const bool whole = sa.fp32_item_by_item != 0;
+        do_fp32_item<MODE>(sa, sa.fp32_first + (whole ? part / kFp32Parts : part % sa.fp32_nitems), whole ? part % kFp32Parts : part / sa.fp32_nitems);
         return;
     }
     const PlanItem *items = reinterpret_cast<const PlanItem *>(sa.plan + sa.item_off);
