@@ -131,8 +131,9 @@ __device__ __forceinline__ void codec_tail(const CodecArgs &ca, uint32_t index, 
     do_tail<MODE>(a, pv.fp, oc, lds, ca.ws + item);
 }
 
-// Grid: ragged tails, then full-tile work items, then copies of fp32 variables.
-template <int B, int MODE, int VARIANT>
+// Grid: ragged tails, then full-tile work items, then copies of fp32 variables: more than FEW_COPIES copy by copy, neighbouring addresses at the same time, fewer by
+// the first parts of all of them first, the parts that are empty last.
+template <int B, int MODE, int VARIANT, uint32_t FEW_COPIES = 0>
 __device__ __forceinline__ void codec_block(const CodecArgs &ca, uint32_t index, uint32_t *lds) {
     if (index < ca.tail_nitems) {
         codec_tail<MODE>(ca, index, lds);
@@ -141,7 +142,8 @@ __device__ __forceinline__ void codec_block(const CodecArgs &ca, uint32_t index,
     const uint32_t block = index - ca.tail_nitems;
     if (block >= ca.nitems) {
         const uint32_t part = block - ca.nitems;
-        copy_fp32_item<MODE>(ca, ca.fp32_first + part / kCopyParts, part % kCopyParts);
+        const bool whole = ca.fp32_nitems > FEW_COPIES;
+        copy_fp32_item<MODE>(ca, ca.fp32_first + (whole ? part / kCopyParts : part % ca.fp32_nitems), whole ? part % kCopyParts : part / ca.fp32_nitems);
         return;
     }
     uint32_t item = block, var = 0, chunk = block;

@@ -8,11 +8,15 @@ namespace omc {
 // the old arena and write different variables of the new one.  A launch that only drains and fills again costs 3 - 5 us: change of the
 // subset and message of 599 variables in 11 bits 141.5 -> 135 us, of 4 blocks of 170 x 511 in three formats 39 -> 30 (with the two launches for
 // (s, b) in one, and in the latter figure the shorter copies).
+// A few copies beside the conversions, codes and vectors of all sizes: their first parts first (encoder of 9 blocks, 229 wide, 19 bits, with the message
+// 30.7 us, 31.3 copy by copy; 16 blocks, 495 wide, three formats 158.2, 160.9).  The conversions of a whole set prefer copy by copy however few they are (1019 copies
+// 24.0 us, 25.2 the other way; 393 54.0, 54.5).
+constexpr uint32_t kFewCopies = 1024;
 template <int B, int VARIANT>
 __global__ __launch_bounds__(64, (Tuning<kCompress, B>::waves)) void reselect_kernel(CodecArgs to_codes, uint32_t first, CodecArgs to_fp32) {
     __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsDwords];
-    if (blockIdx.x < first) codec_block<B, kCompress, VARIANT>(to_codes, blockIdx.x, lds);
-    else codec_block<B, kDecompress, 0>(to_fp32, blockIdx.x - first, lds);
+    if (blockIdx.x < first) codec_block<B, kCompress, VARIANT, kFewCopies>(to_codes, blockIdx.x, lds);
+    else codec_block<B, kDecompress, 0, kFewCopies>(to_fp32, blockIdx.x - first, lds);
 }
 
 template <int B, int VARIANT>
