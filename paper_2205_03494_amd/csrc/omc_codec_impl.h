@@ -60,37 +60,42 @@ __device__ __forceinline__ void copy_fp32_item(const CodecArgs &ca, uint32_t ite
     const float *src = (MODE == kCompress) ? ca.vin + pv.aux_offset : in_arena;
     float *dst = (MODE == kCompress) ? in_arena : ca.vout + pv.aux_offset;
     const uint64_t begin = static_cast<uint64_t>(it.chunk) * kChunkElems + part * kCopyPartElems;
-    constexpr int kPieces = kCopyPartElems / 256;          // per lane, all in flight together; both streams are touched once
-    const uint64_t e0 = begin + static_cast<uint64_t>(lane) * 4;
-    f32x4 x[kPieces];
-    if (begin + kCopyPartElems <= pv.n) {                    // the whole part is inside: wave-uniform
+    // Pieces per lane in flight; both streams are touched once.  (A part is one batch; written without the loop, small
+    // re-selections take 1 % longer, 24.3 -> 24.5 us.)
+    constexpr int kBatch = kCopyPartElems / 256 < 8 ? kCopyPartElems / 256 : 8;
+    for (int j0 = 0; j0 < kCopyPartElems / 256; j0 += kBatch) {
+        const uint64_t e0 = begin + (static_cast<uint64_t>(j0) * 64 + lane) * 4;
+        if (begin + static_cast<uint64_t>(j0 + kBatch) * 256 <= pv.n) {   // the whole batch is inside: wave-uniform
+            f32x4 x[kBatch];
 #pragma unroll
-        for (int u = 0; u < kPieces; ++u)
-            x[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(src + e0 + static_cast<uint64_t>(u) * 256));
+            for (int u = 0; u < kBatch; ++u)
+                x[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(src + e0 + static_cast<uint64_t>(u) * 256));
 #pragma unroll
-        for (int u = 0; u < kPieces; ++u)
-            __builtin_nontemporal_store(x[u], reinterpret_cast<f32x4 *>(dst + e0 + static_cast<uint64_t>(u) * 256));
-        return;
-    }
-    if (begin >= pv.n) return;
-    uint32_t live[kPieces];                                  // the variable ends in this part: whole pieces where there are any
+            for (int u = 0; u < kBatch; ++u)
+                __builtin_nontemporal_store(x[u], reinterpret_cast<f32x4 *>(dst + e0 + static_cast<uint64_t>(u) * 256));
+            continue;
+        }
+        if (begin + static_cast<uint64_t>(j0) * 256 >= pv.n) return;
+        f32x4 x[kBatch];                                     // the variable ends in this batch: whole pieces where there are any
+        uint32_t live[kBatch];                               // this lane's elements of a piece
 #pragma unroll
-    for (int u = 0; u < kPieces; ++u) {
-        const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
-        live[u] = e >= pv.n ? 0u : pv.n - e < 4 ? static_cast<uint32_t>(pv.n - e) : 4u;   // this lane's elements of a piece
-        x[u] = f32x4{0, 0, 0, 0};
-        if (live[u] == 4) x[u] = *reinterpret_cast<const f32x4 *>(src + e);
-        else
-            for (uint32_t c = 0; c < 3; ++c)
-                if (c < live[u]) x[u][c] = src[e + c];
-    }
+        for (int u = 0; u < kBatch; ++u) {
+            const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
+            live[u] = e >= pv.n ? 0u : pv.n - e < 4 ? static_cast<uint32_t>(pv.n - e) : 4u;
+            x[u] = f32x4{0, 0, 0, 0};
+            if (live[u] == 4) x[u] = *reinterpret_cast<const f32x4 *>(src + e);
+            else
+                for (uint32_t c = 0; c < 3; ++c)
+                    if (c < live[u]) x[u][c] = src[e + c];
+        }
 #pragma unroll
-    for (int u = 0; u < kPieces; ++u) {
-        const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
-        if (live[u] == 4) *reinterpret_cast<f32x4 *>(dst + e) = x[u];
-        else
-            for (uint32_t c = 0; c < 3; ++c)
-                if (c < live[u]) dst[e + c] = x[u][c];
+        for (int u = 0; u < kBatch; ++u) {
+            const uint64_t e = e0 + static_cast<uint64_t>(u) * 256;
+            if (live[u] == 4) *reinterpret_cast<f32x4 *>(dst + e) = x[u];
+            else
+                for (uint32_t c = 0; c < 3; ++c)
+                    if (c < live[u]) dst[e + c] = x[u][c];
+        }
     }
 }
 
