@@ -7,16 +7,16 @@
 //
 // Both operands lie along the contraction, X as [M x K] and dY as [M x N], and go from global memory straight into a ring of S LDS
 // stages of 32 rows, as they are.  The transposing 16-bit read (ds_read_b64_tr_b16) makes matrix fragments of them: of 16 lanes
-// that point at four rows x 16 columns, lane c receives column c's four rows.  Staging costs no vector instruction.  The
-// 64-byte groups of a row are XOR-swizzled by f(row) = (row & 3) + 4 * (bit 3 of the row), as far as the row has groups, on the way in
-// (the lane picks the piece, its LDS place is fixed): the eight rows of one read then lie on different banks.
+// that point at four rows x 16 columns, lane c receives column c's four rows.  Staging costs no vector instruction.  On the way in
+// (the lane picks the piece, its LDS place is fixed) the 64-byte groups of a row are exchanged by the lowest bits of the row and the 16-byte pieces in them by its bit 3: the eight rows of
+// one read then lie on different banks.
 //
 // A weight matrix gives few tiles (4 M weights = 128 of 256 x 128) and the contraction is long, so it is shared out twice: between
 // TEAMS of waves of a workgroup, which add up their tiles through LDS, and between workgroups (nsplit).
 //
-// What bounds it: the loads (48 bytes per clock and compute unit at the matrix cores' rate; with all of them hitting the L2 the 8192-row product
-// of 4096 x 1024 weights takes 64 instead of 71 us), not the LDS reads: plain or 16-byte reads in their place change nothing.  The
-// matrix cores are busy in 41 - 47 % of the cycles, the waves wait in 35 - 47 % of theirs.
+// Matrix instructions of 16 x 16 x 32 and the order of reads and products written down, a column of tiles at a time: 8192 rows, 4096 x 1024 weights, 8 bits, momentum, with the update: 3 of 77 us less than 32 x 32 x 16 and the compiler's order.
+//
+// What bounds it: power and the loads (48 bytes per clock and compute unit at the matrix cores' rate), not the LDS reads: plain or 16-byte reads in their place change nothing.
 #include "omc_dw_args.h"
 #include "omc_mma.h"
 
@@ -80,13 +80,13 @@ __device__ __forceinline__ void update_tile(const DwArgs &a, const float *grad, 
     }
 }
 
-// WM x WN waves of TM x TN matrix tiles (32 x 32) each, TEAMS times; S stages, OCC waves per SIMD.  MODE: kPark for partial sums, else
+// WM x WN waves of TM x TN matrix tiles (16 x 16) each, TEAMS times; S stages, OCC waves per SIMD.  MODE: kPark for partial sums, else
 // the optimizer of the one-kernel route.
 constexpr int kPark = -1;
 template <int WM, int WN, int TM, int TN, int TEAMS, int S, int OCC, int MODE>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN * TEAMS, 64 * WM * WN * TEAMS))) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 void dw_product_kernel(ProductArgs pa, DwArgs a) {
-    constexpr int NW = WM * WN, BK = 32 * TM * WM, BN = 32 * TN * WN;
+    constexpr int NW = WM * WN, BK = 16 * TM * WM, BN = 16 * TN * WN;
     constexpr int kXLoads = BK / 16 / NW, kYLoads = BN / 16 / NW, kLoads = kXLoads + kYLoads;   // 1 KB loads per wave and stage
     constexpr uint32_t kXBytes = BK * 64, kStage = kXBytes + BN * 64;
     static_assert(BK % (16 * NW) == 0 && BN % (16 * NW) == 0, "whole loads");
@@ -109,31 +109,39 @@ void dw_product_kernel(ProductArgs pa, DwArgs a) {
     const uint32_t end = static_cast<uint32_t>(static_cast<uint64_t>(pa.steps) * (split + 1) / pa.nsplit);
     const uint32_t mine = (end - begin + TEAMS - 1 - team) / TEAMS, most = (end - begin + TEAMS - 1) / TEAMS;
 
-    // ---- global -> LDS
-    auto f = [](uint32_t row) { return (row & 3u) | ((row >> 1) & 4u); };
-    auto load_operand = [&](auto width, const uint16_t *base, uint32_t ld, uint32_t col0, uint32_t at, uint32_t j) {
+    // ---- global -> LDS: stage i holds the rows of this team's step i
+    auto swizzle_group = [](uint32_t row, uint32_t groups) { return groups >= 4 ? row & 3u : (row >> 1) & 1u; };
+    auto swizzle_piece = [](uint32_t row) { return (row >> 2) & 2u; };
+    const uint64_t first_row = 32ull * (begin + team);
+    const uint8_t *x_from = reinterpret_cast<const uint8_t *>(pa.X + first_row * K + k0), *y_from = reinterpret_cast<const uint8_t *>(pa.dY + first_row * N + n0);
+    auto load_operand = [&](auto width, const uint8_t *from, uint32_t ld, uint32_t at) {
         constexpr uint32_t W = decltype(width)::value, kRows = 512 / W, kSlots = W / 8;
-        const uint8_t *from = reinterpret_cast<const uint8_t *>(base) + (static_cast<uint64_t>(j) * 32 * ld + col0) * 2;
 #pragma unroll
         for (uint32_t i = 0; i < W / 16 / NW; ++i) {
             const uint32_t c = wave + NW * i, in = lane / kSlots, row = c * kRows + in, slot = lane % kSlots;
-            const uint32_t piece = (((slot >> 2) ^ (f(row) & (W / 32 - 1))) << 2) | (slot & 3u);
+            const uint32_t piece = (((slot >> 2) ^ swizzle_group(row, W / 32)) << 2) | ((slot & 3u) ^ swizzle_piece(row));
             load_to_lds(from + static_cast<uint64_t>(c) * kRows * ld * 2, in * ld * 2 + piece * 16, lds0 + at + c * 1024);
         }
     };
-    auto load_stage = [&](uint32_t at, uint32_t i) {
-        const uint32_t j = begin + team + TEAMS * i;
-        load_operand(UintTag<BK>{}, pa.X, K, k0, at, j);
-        load_operand(UintTag<BN>{}, pa.dY, N, n0, at + kXBytes, j);
+    auto load_stage = [&](uint32_t at) {
+        load_operand(UintTag<BK>{}, x_from, K, at);
+        load_operand(UintTag<BN>{}, y_from, N, at + kXBytes);
+        x_from += 64ull * TEAMS * K;
+        y_from += 64ull * TEAMS * N;
     };
 
-    // ---- LDS -> fragments of 16 rows: 32 columns x 8 rows of either half
-    const uint32_t row = 8 * (lane >> 5) + ((lane & 15u) >> 2), piece = 2 * ((lane >> 4) & 1u) + ((lane >> 1) & 1u), byte = 8 * (lane & 1u);
+    // ---- LDS -> fragments of 32 rows: 16 lanes take 8 of them
+    const uint32_t row = 8 * (lane >> 4) + ((lane & 15u) >> 2), byte = 8 * (lane & 1u);
+    auto place = [&](uint32_t tile, uint32_t width) {
+        const uint32_t piece = 2 * (tile & 1u) + ((lane >> 1) & 1u);
+        return row * (2 * width) + (((tile >> 1) ^ swizzle_group(row, width / 32)) * 4 + (piece ^ swizzle_piece(row))) * 16 + byte;
+    };
     uint32_t x_at[TM], y_at[TN];
 #pragma unroll
-    for (uint32_t mi = 0; mi < TM; ++mi) x_at[mi] = row * (2 * BK) + (((TM * wm + mi) ^ (f(row) & (BK / 32 - 1))) * 4 + piece) * 16 + byte;
+    for (uint32_t mi = 0; mi < TM; ++mi) x_at[mi] = place(TM * wm + mi, BK);
 #pragma unroll
-    for (uint32_t ni = 0; ni < TN; ++ni) y_at[ni] = kXBytes + row * (2 * BN) + (((TN * wn + ni) ^ (f(row) & (BN / 32 - 1))) * 4 + piece) * 16 + byte;
+    for (uint32_t ni = 0; ni < TN; ++ni) y_at[ni] = kXBytes + place(TN * wn + ni, BN);
+    uint32_t cur = 0, far = (S - 1) * kStage;
     auto read_one = [&](uint32_t at, uint32_t four_rows) {
         typedef short s16x8 __attribute__((ext_vector_type(8)));
         uint8_t *q = lds + at;
@@ -142,60 +150,61 @@ void dw_product_kernel(ProductArgs pa, DwArgs a) {
         const s16x8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
         return __builtin_bit_cast(bf16x8, both);
     };
-    struct Frags {
-        bf16x8 x[TM], y[TN];
-    };
-    auto read_frags = [&](uint32_t at, uint32_t half, Frags &t) {
-#pragma unroll
-        for (int mi = 0; mi < TM; ++mi) t.x[mi] = read_one(at + x_at[mi] + half * 16 * (2 * BK), 4 * 2 * BK);
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni) t.y[ni] = read_one(at + y_at[ni] + half * 16 * (2 * BN), 4 * 2 * BN);
-    };
-    f32x16 acc[TM][TN];
+    // A step's products in two parts, the first and the last TM / 2 tiles of X by all of dY, column by column of the tiles.  X's fragments of a part are read beside the products of the part
+    // before, those of the first part behind the step's barrier, and dY's of a step each as soon as its predecessor has been multiplied for the last time.
+    constexpr int kRows = TM / 2;
+    bf16x8 x[2][kRows], y[TN];
+    f32x4 acc[TM][TN];
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
-    auto multiply = [&](const Frags &t) {
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-            for (int mi = 0; mi < TM; ++mi) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(t.x[mi], t.y[ni], acc[mi][ni], 0, 0, 0);
+        for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto read_x = [&](auto part, auto index) {
+        constexpr int P = decltype(part)::value, I = decltype(index)::value;
+        x[P][I] = read_one(cur + x_at[P * kRows + I], 4 * 2 * BK);
     };
-
-    Frags f0, f1;
-    uint32_t cur = 0, far = (S - 1) * kStage;
-    auto rest_of_step = [&]() {
-        read_frags(cur, 1, f1);
-        multiply(f0);
+    auto read_y = [&](auto index) { y[decltype(index)::value] = read_one(cur + y_at[decltype(index)::value], 4 * 2 * BN); };
+    // `more`: with the reads for the part behind it
+    auto multiply = [&](auto part, auto more) {
+        constexpr int P = decltype(part)::value;
+        for_constants<TN>([&](auto group) {
+            constexpr int G = decltype(group)::value, R0 = G * kRows / TN, R1 = (G + 1) * kRows / TN;
+            if constexpr (decltype(more)::value) for_constants<R1 - R0>([&](auto i) { read_x(UintTag<1 - P>{}, UintTag<R0 + decltype(i)::value>{}); });
+#pragma unroll
+            for (int mi = 0; mi < kRows; ++mi)
+                acc[P * kRows + mi][G] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[P][mi], y[G], acc[P * kRows + mi][G], 0, 0, 0);
+            if constexpr (P == 1 && decltype(more)::value) read_y(group);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    const BoolTag<true> yes;
+    auto first_part = [&]() {
+        multiply(UintTag<0>{}, yes);
         cur = cur == (S - 1) * kStage ? 0 : cur + kStage;
         far = far == (S - 1) * kStage ? 0 : far + kStage;
     };
 #pragma unroll
     for (uint32_t i = 0; i < S - 1; ++i)
-        if (i < mine) load_stage(i * kStage, i);
+        if (i < mine) load_stage(i * kStage);
     if (mine > 0) {
         wait_stage<S, kLoads>(0, mine);
-        read_frags(cur, 0, f0);
-        if (mine > S - 1) load_stage(far, S - 1);
-        rest_of_step();
+        for_constants<TN>([&](auto i) { read_y(i); });
+        for_constants<kRows>([&](auto i) { read_x(UintTag<0>{}, i); });
+        if (mine > S - 1) load_stage(far);
+        first_part();
         uint32_t i = 1;
         for (; i + (S - 1) < mine; ++i) {
             wait_loads_and_sync<(S - 2) * kLoads>();
-            read_frags(cur, 0, f0);
-            load_stage(far, i + S - 1);
-            multiply(f1);
-            rest_of_step();
+            load_stage(far);
+            multiply(UintTag<1>{}, yes);
+            first_part();
         }
         for (; i < mine; ++i) {
             wait_stage<S, kLoads>(i, mine);
-            read_frags(cur, 0, f0);
-            multiply(f1);
-            rest_of_step();
+            multiply(UintTag<1>{}, yes);
+            first_part();
         }
-        multiply(f1);
+        multiply(UintTag<1>{}, BoolTag<false>{});
     }
     for (uint32_t i = mine; i < most; ++i) wait_loads_and_sync<0>();   // teams wait for each other
     wait_loads_and_sync<0>();                                 // nobody reads a stage any more
@@ -203,27 +212,37 @@ void dw_product_kernel(ProductArgs pa, DwArgs a) {
     const bool lead = add_teams<TEAMS, NW, TM, TN>(reinterpret_cast<float *>(lds_all), acc, team, wave, lane);
     if constexpr (MODE == kPark) {
         if (!lead) return;
-        float *to = pa.partials + static_cast<uint64_t>(split) * K * N + static_cast<uint64_t>(k0 + 32 * TM * wm + 4 * (lane >> 5)) * N +
-                    n0 + 32 * TN * wn + (lane & 31u);
+        float *to = pa.partials + static_cast<uint64_t>(split) * K * N + static_cast<uint64_t>(k0 + 16 * TM * wm + 8 * (lane >> 5)) * N +
+                    n0 + 16 * TN * wn + (lane & 31u);
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
+            for (int v = 0; v < 4; ++v)
 #pragma unroll
-                for (int ni = 0; ni < TN; ++ni) to[static_cast<uint64_t>(32 * mi + 8 * (v >> 2) + (v & 3)) * N + 32 * ni] = acc[mi][ni][v];
+                for (int ni = 0; ni < TN; ni += 2) {
+                    float p = acc[mi][ni][v], q = acc[mi][ni + 1][v];
+                    side_by_side(p, q);
+                    to[static_cast<uint64_t>(16 * mi + v) * N + 16 * ni] = p;
+                    to[static_cast<uint64_t>(16 * mi + v + 4) * N + 16 * ni] = q;
+                }
     } else {
         static_assert(BK * BN * 4 + 16 * static_cast<int>(sizeof(Partial)) <= TEAMS * S * static_cast<int>(kStage) + kExtra, "the tile fits the stages");
         float *tile = reinterpret_cast<float *>(lds_all);
         Partial *sums = reinterpret_cast<Partial *>(lds_all + BK * BN * 4);
         if (TEAMS > 1) __syncthreads();                       // the other teams' tiles are read
         if (lead) {
-            float *to = tile + (32 * TM * wm + 4 * (lane >> 5)) * BN + 32 * TN * wn + (lane & 31u);
+            float *to = tile + (16 * TM * wm + 8 * (lane >> 5)) * BN + 16 * TN * wn + (lane & 31u);
 #pragma unroll
             for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
+                for (int v = 0; v < 4; ++v)
 #pragma unroll
-                    for (int ni = 0; ni < TN; ++ni) to[(32 * mi + 8 * (v >> 2) + (v & 3)) * BN + 32 * ni] = acc[mi][ni][v];
+                    for (int ni = 0; ni < TN; ni += 2) {
+                        float p = acc[mi][ni][v], q = acc[mi][ni + 1][v];
+                        side_by_side(p, q);
+                        to[(16 * mi + v) * BN + 16 * ni] = p;
+                        to[(16 * mi + v + 4) * BN + 16 * ni] = q;
+                    }
         }
         __syncthreads();
         FitAcc fit;
@@ -339,12 +358,12 @@ static int launch_product(int tile, ProductArgs pa, const DwArgs &a, hipStream_t
     pa.group_rows = tile_group(kProductTiles[tile], pa.tiles_n, 32 * pa.steps, pa.N, pa.K, MODE >= kStepMomentum);
     const dim3 grid(pa.tiles_k * pa.tiles_n, pa.nsplit);
     switch (tile) {
-        case 0: dw_product_kernel<2, 2, 4, 2, 2, 3, 2, MODE><<<grid, dim3(512), 0, st>>>(pa, a); break;
-        case 1: dw_product_kernel<2, 2, 2, 2, 1, 4, 2, MODE><<<grid, dim3(256), 0, st>>>(pa, a); break;
-        case 2: dw_product_kernel<2, 2, 2, 2, 2, 4, 2, MODE><<<grid, dim3(512), 0, st>>>(pa, a); break;
-        case 3: dw_product_kernel<2, 2, 1, 1, 1, 4, 4, MODE><<<grid, dim3(256), 0, st>>>(pa, a); break;
-        case 4: dw_product_kernel<2, 2, 1, 1, 2, 4, 4, MODE><<<grid, dim3(512), 0, st>>>(pa, a); break;
-        default: dw_product_kernel<2, 2, 1, 1, 4, 4, 4, MODE><<<grid, dim3(1024), 0, st>>>(pa, a); break;
+        case 0: dw_product_kernel<2, 2, 8, 4, 2, 3, 2, MODE><<<grid, dim3(512), 0, st>>>(pa, a); break;
+        case 1: dw_product_kernel<2, 2, 4, 4, 1, 4, 2, MODE><<<grid, dim3(256), 0, st>>>(pa, a); break;
+        case 2: dw_product_kernel<2, 2, 4, 4, 2, 4, 2, MODE><<<grid, dim3(512), 0, st>>>(pa, a); break;
+        case 3: dw_product_kernel<2, 2, 2, 2, 1, 4, 4, MODE><<<grid, dim3(256), 0, st>>>(pa, a); break;
+        case 4: dw_product_kernel<2, 2, 2, 2, 2, 4, 4, MODE><<<grid, dim3(512), 0, st>>>(pa, a); break;
+        default: dw_product_kernel<2, 2, 2, 2, 4, 4, 4, MODE><<<grid, dim3(1024), 0, st>>>(pa, a); break;
     }
     return static_cast<int>(hipGetLastError());
 }

@@ -7,96 +7,37 @@
 // 16-bit read turns into fragments, TRANS as half of a column's 64 k, laid out like A.  Each code is decoded once per
 // workgroup, during the products of the step before; its dwords were asked for two steps before.
 //
-// Forward W rows: the 64 bytes of a unit go to group g ^ f(k) of the row, f = (k & 3) + 4 * (bit 3 of k) as far as the row has
-// groups, and its four pieces are rotated by g / 2: the eight k rows of a transposing read and the eight lanes of a store then
-// lie on different banks.  (No conflict is counted forward; TRANS 2.1 - 4.2 million cycles over all compute units in a launch of 84 - 91 us.)
+// Forward W rows: a row's 64-byte groups are exchanged by the lowest bits of k, so that four rows of one group lie on different banks, and the 16-byte pieces in a group by bit 3 of k, so that
+// the eight rows that a transposing read takes at a time do, and by the group, so that the eight lanes of a store do.
 //
-// What bounds it: the decode, about five vector instructions per code, beside 64 KB through LDS per 16 k of a 256 x 256 tile.  Measured on 11-bit codes against the kernels before (256 x 128 or 128 x 128 tile,
+// The order of the instructions is written down, a column of matrix tiles at a time, as in the FP8 kernel; vector and scalar arithmetic may move, and the decoding of a step's codes is spread evenly over its
+// columns.  11 bits, us, 32 x 32 x 16 instructions and the compiler's order -> this: 2048 x 2048 x 512 10.9 -> 10.2, 2304 x 3712 x 192 12.5 -> 11.3, 4096 x 1024 x 1056 17.2 -> 16.6, 512 x 512 x 512 5.73 -> 5.49.  The 256 x 256
+// tile alone is faster the old way and has a kernel of its own (omc_gemm_bits_large.h).
+//
+// What bounds it: the decode, about five vector instructions per code, which hold up the matrix cores by some 3 clocks each (64 x 128 x 32 by 32 matrix instructions, 64 vector instructions beside
+// them: 512 -> 703 clocks).  Measured on 11-bit codes against the first kernels (256 x 128 or 128 x 128 tile,
 // A staged through registers, a patch of 4 x 4 codes per thread with run-time shifts; 256 x 128 by 16 waves for long contractions):
-// forward 8192 x 4096 x 1024 104 -> 82 us, 2048 x 2048 x 512 18.6 -> 11.4, input gradient 2048 x 512 x 2048 53.6 -> 13.
+// forward 8192 x 4096 x 1024 104 -> 80 us, 2048 x 2048 x 512 18.6 -> 10.2, input gradient 2048 x 512 x 2048 53.6 -> 13.
 #pragma once
 #include <algorithm>
 
-#include "omc_mma.h"
+#include "omc_gemm_bits_codes.h"
+#include "omc_gemm_bits_large.h"
 
 #pragma clang fp contract(off)
 
 namespace omc {
 
-struct BitsArgs {
-    const uint16_t *A;
-    const uint32_t *codes;
-    const float *sb;
-    float *C;
-    uint32_t N, K, tiles_m, tiles_n;
-    FmtParams fp;
-};
-
-// U consecutive codes (U = 32 or 16) as dwords.  Sixteen codes of an odd width start in the middle of a dword every other time;
-// their dwords never reach past those of the 32 codes they belong to.
-template <int B, int U>
-struct Unit {
-    static constexpr int kDwords = (U * B + 31) / 32;
-    static constexpr bool kShifted = (U * B) % 32 != 0;
-    uint32_t w[kDwords];
-};
-template <int B, int U>
-__device__ __forceinline__ void load_unit(const uint32_t *__restrict__ from, Unit<B, U> &u) {
-    typedef uint32_t x4 __attribute__((ext_vector_type(4), aligned(4)));
-    typedef uint32_t x2 __attribute__((ext_vector_type(2), aligned(4)));
-    constexpr int n = Unit<B, U>::kDwords;
-    int i = 0;
-#pragma unroll
-    for (; i + 4 <= n; i += 4) {
-        const x4 t = *reinterpret_cast<const x4 *>(from + i);
-        u.w[i] = t[0]; u.w[i + 1] = t[1]; u.w[i + 2] = t[2]; u.w[i + 3] = t[3];
-    }
-    if constexpr ((n & 2) != 0) {
-        const x2 t = *reinterpret_cast<const x2 *>(from + (n & ~3));
-        u.w[n & ~3] = t[0];
-        u.w[(n & ~3) + 1] = t[1];
-    }
-    if constexpr ((n & 1) != 0) u.w[n - 1] = from[n - 1];
-}
-// moves the codes of a unit that starts `shift` bits into its first dword to bit 0
-template <int B, int U>
-__device__ __forceinline__ void align_unit(Unit<B, U> &u, uint32_t shift) {
-    if constexpr (Unit<B, U>::kShifted) {
-#pragma unroll
-        for (int i = 0; i < Unit<B, U>::kDwords; ++i)
-            u.w[i] = __builtin_amdgcn_alignbit(i + 1 < Unit<B, U>::kDwords ? u.w[i + 1] : 0u, u.w[i], shift);
-    }
-}
-// code i with its sign bit at bit 31 (what lies below is masked by the decoder)
-template <int B, int U>
-__device__ __forceinline__ uint32_t unit_code(const Unit<B, U> &u, int i) {
-    const int p = i * B, idx = p >> 5, off = p & 31;
-    if (off + B <= 32) return u.w[idx] << (32 - B - off);
-    return __builtin_amdgcn_alignbit(u.w[idx + 1], u.w[idx], off + B - 32);
-}
-// codes 8 i .. 8 i + 7 of a unit as bfloat16 (their fp32 images have nothing in the low 16 bits)
-template <int B, int U>
-__device__ __forceinline__ u32x4 decode_piece(const Unit<B, U> &u, int i, const FmtParams &fp) {
-    u32x4 o;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const uint32_t lo = __float_as_uint(decode_top(unit_code<B, U>(u, 8 * i + 2 * p), fp));
-        const uint32_t hi = __float_as_uint(decode_top(unit_code<B, U>(u, 8 * i + 2 * p + 1), fp));
-        o[p] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
-    }
-    return o;
-}
-
-// WM x WN waves of TM x TN matrix tiles (32 x 32) each, TEAMS times: team t multiplies the steps t, t + TEAMS, ... of the
+// WM x WN waves of TM x TN matrix tiles (16 x 16) each, TEAMS times: team t multiplies the steps t, t + TEAMS, ... of the
 // contraction in LDS stages of its own, and team 0 adds up the teams' tiles in order.  A team's sums are CHAINS chains (which of
-// them, the quarter of the step decides).  OCC waves per SIMD.
+// them, the half of the step decides).  OCC waves per SIMD.
 template <int B, int U, int WM, int WN, int TM, int TN, int TEAMS, int CHAINS, int OCC, bool TRANS>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN * TEAMS, 64 * WM * WN * TEAMS))) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 void gemm_bits_kernel(BitsArgs ga) {
-    constexpr int NW = WM * WN, NT = 64 * NW, BM = 32 * TM * WM, BN = 32 * TN * WN;
+    constexpr int NW = WM * WN, NT = 64 * NW, BM = 16 * TM * WM, BN = 16 * TN * WN;
     constexpr int kALoads = BM / 8 / NW, kUnits = 64 * BN / U, kGroups = BN / 32, kRowUnits = BN / U;
     constexpr uint32_t kABytes = BM * 128, kStage = kABytes + BN * 128;
-    static_assert(WM == 2 && (WN == 2 || WN == 4), "how the quarters are dealt below");
+    static_assert(WM == 2 && (WN == 2 || WN == 4), "how the row sums are dealt below");
     static_assert(BM % (8 * NW) == 0 && kUnits == NT, "whole loads, one unit per thread");
     __shared__ __attribute__((aligned(1024))) uint8_t lds_all[TEAMS * 2 * kStage];
     const uint32_t team = TEAMS == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
@@ -117,106 +58,118 @@ void gemm_bits_kernel(BitsArgs ga) {
     const uint32_t full = (full_k + TEAMS - 1 - team) / TEAMS, steps = (steps_k + TEAMS - 1 - team) / TEAMS;   // this team's
     const uint8_t *a_base = reinterpret_cast<const uint8_t *>(ga.A) + static_cast<uint64_t>(m0) * K * 2;
     const uint32_t a_row = lane >> 3, a_piece = (lane & 7u) ^ ((a_row >> 1) + 4 * (wave & 1u));
+    const uint8_t *a_from = a_base + static_cast<uint64_t>(8 * wave) * 2 * K + 128 * team;   // of the step that is asked for next
+    const uint64_t a_stride = 16ull * NW * K;                 // between a wave's kilobytes
     auto load_a = [&](uint32_t at, uint32_t i) {
-        const uint32_t j = team + TEAMS * i;
-        const uint32_t a_off = a_row * K * 2 + (j == full_k ? a_piece & 3u : a_piece) * 16;
+        const uint32_t a_off = a_row * K * 2 + (team + TEAMS * i == full_k ? a_piece & 3u : a_piece) * 16;
 #pragma unroll
-        for (int q = 0; q < kALoads; ++q) {
-            const uint32_t c = wave + NW * q;                 // rows 8 c ..
-            load_to_lds(a_base + static_cast<uint64_t>(j) * 128 + static_cast<uint64_t>(c) * 16 * K, a_off, lds0 + at + c * 1024);
-        }
+        for (int q = 0; q < kALoads; ++q) load_to_lds(a_from + q * a_stride, a_off, lds0 + at + (wave + NW * q) * 1024);
+        a_from += 128 * TEAMS;
     };
     // this thread's unit: TRANS column u_row, part u_part of its 64 k; forward k row u_row, part u_part of its BN columns
-    constexpr uint32_t kParts = TRANS ? 64 / U : kRowUnits, kPieces = U / 8;
-    const uint32_t u_row = tid / kParts, u_part = tid % kParts;
+    constexpr uint32_t kUnitParts = TRANS ? 64 / U : kRowUnits, kPieces = U / 8;
+    const uint32_t u_row = tid / kUnitParts, u_part = tid % kUnitParts;
     const uint32_t u_shift = Unit<B, U>::kShifted ? 16u * (u_part & 1u) : 0u;
+    const uint64_t first_code = TRANS ? static_cast<uint64_t>(n0 + u_row) * K + 64 * team + U * u_part : (64ull * team + u_row) * N + n0 + U * u_part;
+    const uint32_t *w_from = ga.codes + (first_code * B >> 5);   // of the step that is asked for next
+    const uint64_t w_step = TRANS ? 2ull * B * TEAMS : 2ull * B * TEAMS * N;   // (64 codes or rows of them are whole dwords)
     auto load_w = [&](uint32_t i, Unit<B, U> &u) {
-        const uint32_t j = team + TEAMS * i;
-        const bool half = j == full_k;
-        const uint64_t e = TRANS ? (static_cast<uint64_t>(n0 + u_row) * K + static_cast<uint64_t>(j) * 64 + U * (half ? u_part % (32 / U) : u_part))
-                                 : ((static_cast<uint64_t>(j) * 64 + (half ? u_row & 31u : u_row)) * N + n0 + U * u_part);
-        load_unit<B, U>(ga.codes + (e * B >> 5), u);
+        const bool back = team + TEAMS * i == full_k && (TRANS ? u_part >= 32 / U : u_row >= 32);
+        load_unit<B, U>(back ? w_from - (TRANS ? B : static_cast<uint64_t>(B) * N) : w_from, u);
+        w_from += w_step;
     };
-    auto swizzle_f = [](uint32_t k) { return ((k & 3u) | ((k >> 1) & 4u)) & (kGroups - 1); };
-    uint32_t u_at[kPieces];
-#pragma unroll
-    for (uint32_t i = 0; i < kPieces; ++i) {
-        const uint32_t piece = u_part * kPieces + i, group = piece / 4;
-        u_at[i] = kABytes + (TRANS ? u_row * 128 + ((piece ^ ((u_row >> 1) & 7u)) << 4)
-                                   : u_row * (2 * BN) + ((group ^ swizzle_f(u_row)) * 4 + ((piece & 3u) ^ ((group >> 1) & 3u))) * 16);
-    }
-    auto store_piece = [&](uint32_t at, const Unit<B, U> &u, int i) {
-        *reinterpret_cast<u32x4 *>(lds + at + u_at[i]) = decode_piece<B, U>(u, i, fp);
+    // forward: where piece `piece` (16 bytes, of the whole row) of k row `k` lies
+    auto w_row_place = [](uint32_t k, uint32_t piece) {
+        const uint32_t group = piece / 4, other_group = kGroups >= 4 ? k & 3u : (k >> 1) & 1u;
+        return kABytes + k * (2 * BN) + ((group ^ other_group) * 4 + ((piece & 3u) ^ ((k >> 2) & 2u) ^ (group & 1u) ^ ((group >> 1) & 2u))) * 16;
     };
+    // where its first piece goes; the others lie beside it, before the swizzle
+    const uint32_t u_at = TRANS ? kABytes + u_row * 128 + (((u_part * kPieces) ^ ((u_row >> 1) & 7u)) << 4) : w_row_place(u_row, u_part * kPieces);
+    auto store_piece = [&](uint32_t at, uint32_t i, u32x4 piece) { *reinterpret_cast<u32x4 *>(lds + at + (u_at ^ (16u * i))) = piece; };
 
-    // ---- LDS -> fragments
-    const uint32_t f_row = lane & 31u, f_half = lane >> 5;
-    auto a_place = [&](uint32_t ks) {
-        const uint32_t row = 32 * TM * wm + f_row;
-        return row * 128 + (((2 * ks + f_half) ^ ((row >> 1) & 7u)) << 4);
+    // ---- LDS -> fragments of 32 k
+    const uint32_t f_row = lane & 15u, f_k = lane >> 4;
+    typedef RowOrder<WN, TM> Order;
+    const Order order(wn);
+    auto a_place = [&](uint32_t half) {
+        const uint32_t row = 16 * TM * wm + f_row;            // (of the wave's first row tile, which need not be the one it multiplies first)
+        return row * 128 + (((4 * half + f_k) ^ ((row >> 1) & 7u)) << 4);
     };
-    const uint32_t block = lane >> 4, in = lane & 15u;          // forward: 16 lanes point at 4 k rows x 16 columns
-    uint32_t w_base[TN];                                        // forward: quarter 0's place per column block
+    // A step's products in parts, kParts to a half: two row tiles (or one of two), column by column of the tiles.  A's fragments of a part are read
+    // beside the products of the part before, those of the first part behind the step's barrier, and W's of a half each as soon as its predecessor has been multiplied
+    // for the last time.
+    constexpr int kRows = TM >= 4 ? 2 : 1, kParts = TM / kRows;
+    static_assert(Order::kSlots % kRows == 0, "the rows of a part follow each other");
+    uint32_t a_part[kParts];                                    // where the parts' rows begin
 #pragma unroll
-    for (uint32_t ni = 0; ni < TN; ++ni) {
-        const uint32_t g = TN * wn + ni, k = 8 * (block >> 1) + (in >> 2), piece = 2 * (block & 1u) + ((in >> 1) & 1u);
-        w_base[ni] = kABytes + k * (2 * BN) + ((g ^ swizzle_f(k)) * 4 + (piece ^ ((g >> 1) & 3u))) * 16 + 8 * (in & 1u);
+    for (uint32_t q = 0; q < kParts; ++q) a_part[q] = 128 * order.row(q * kRows);
+    uint32_t w_first[TN / 2];                                   // forward: the first half's place per two column tiles; 16 lanes point at 4 k rows x 16 columns
+#pragma unroll
+    for (uint32_t n2 = 0; n2 < TN / 2; ++n2) w_first[n2] = w_row_place(8 * f_k + (f_row >> 2), 2 * (TN * wn + 2 * n2) + ((f_row >> 1) & 1u)) + 8 * (f_row & 1u);
+    auto w_place = [&](uint32_t half) {                         // TRANS: place of column tile 0; forward: step to the half
+        if (!TRANS) return half * 32 * (2 * BN);
+        const uint32_t col = 16 * TN * wn + f_row;
+        return kABytes + col * 128 + (((4 * half + f_k) ^ ((col >> 1) & 7u)) << 4);
+    };
+    uint32_t a_at[2], w_at[2];                                  // of the half that is multiplied first, and the other one
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        a_at[p] = a_place((p + wn) & 1u);
+        w_at[p] = w_place((p + wn) & 1u);
     }
-    auto w_place = [&](uint32_t ks) {                           // TRANS: place of column block 0; forward: step to quarter ks
-        if (!TRANS) return ks * 16 * (2 * BN);
-        const uint32_t col = 32 * TN * wn + f_row;
-        return kABytes + col * 128 + (((2 * ks + f_half) ^ ((col >> 1) & 7u)) << 4);
+    bf16x8 fa[2][kRows], fw[TN];
+    uint32_t cur = 0;
+    auto read_a = [&](uint32_t a_off, auto part, auto index) {
+        constexpr int P = decltype(part)::value, I = decltype(index)::value;
+        fa[P % 2][I] = *reinterpret_cast<const bf16x8 *>(lds + cur + a_off + a_part[P % kParts] + 16 * 128 * I);
     };
-    uint32_t a_at[4], w_at[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const uint32_t ks = (p + wn + 2 * wm) & 3u;
-        a_at[p] = a_place(ks);
-        w_at[p] = w_place(ks);
-    }
-    struct Frags {
-        bf16x8 a[TM], w[TN];
-    };
-    auto read_frags = [&](uint32_t at, uint32_t a_off, uint32_t w_off, Frags &f) {
-#pragma unroll
-        for (int mi = 0; mi < TM; ++mi) f.a[mi] = *reinterpret_cast<const bf16x8 *>(lds + at + a_off + 32 * 128 * mi);
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni) {
-            if (TRANS) {
-                f.w[ni] = *reinterpret_cast<const bf16x8 *>(lds + at + w_off + 32 * 128 * ni);
-            } else {
-                typedef short s16x8 __attribute__((ext_vector_type(8)));
-                uint8_t *q = lds + (at + w_off + w_base[ni]);
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((OMC_LDS s16x4 *)(q));
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((OMC_LDS s16x4 *)(q + 4 * 2 * BN));
-                const s16x8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                f.w[ni] = __builtin_bit_cast(bf16x8, both);
-            }
+    auto read_w = [&](uint32_t w_off, auto index) {
+        constexpr int ni = decltype(index)::value;
+        if (TRANS) {
+            fw[ni] = *reinterpret_cast<const bf16x8 *>(lds + cur + w_off + 16 * 128 * ni);
+        } else {
+            typedef short s16x8 __attribute__((ext_vector_type(8)));
+            uint8_t *q = lds + (cur + w_off + (w_first[ni / 2] ^ (32u * (ni & 1))));   // (the second of two: two pieces on, before the swizzle)
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((OMC_LDS s16x4 *)(q));
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((OMC_LDS s16x4 *)(q + 4 * 2 * BN));
+            const s16x8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            fw[ni] = __builtin_bit_cast(bf16x8, both);
         }
     };
 
-    f32x16 acc[CHAINS][TM][TN];
-    RowSums<WN, TM, CHAINS> rsum;
-    auto multiply = [&](const Frags &f, auto quarter, bool sum) {
-        constexpr int Q = decltype(quarter)::value, chain = Q % CHAINS;
+    Sums<CHAINS, TM, TN> acc;
+    RowSums<WN, TM> rsum;
+    Unit<B, U> now, next;
+    // NEXT: the part whose fragments are read meanwhile, or kAll; PAIRS: of the unit's pairs of codes those from FIRST on are decoded meanwhile, and whole pieces stored in the other stage
+    constexpr int kAll = 2 * kParts, kPairs = U / 2;
+    u32x4 piece = {0, 0, 0, 0};
+    auto multiply = [&](auto part, auto next_part, auto first_pair, auto pairs) {
+        constexpr int P = decltype(part)::value, NEXT = decltype(next_part)::value, HALF = P / kParts, chain = HALF % CHAINS;
+        constexpr int FIRST = decltype(first_pair)::value, PAIRS = decltype(pairs)::value, R = (P % kParts) * kRows;
+        for_constants<TN>([&](auto group) {
+            constexpr int G = decltype(group)::value, R0 = G * kRows / TN, R1 = (G + 1) * kRows / TN, D0 = FIRST + G * PAIRS / TN, D1 = FIRST + (G + 1) * PAIRS / TN;
+            if constexpr (NEXT < kAll) for_constants<R1 - R0>([&](auto i) { read_a(a_at[NEXT / kParts], next_part, UintTag<R0 + decltype(i)::value>{}); });
 #pragma unroll
-        for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-            for (int mi = 0; mi < TM; ++mi)
-                acc[chain][mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mi], f.w[ni], acc[chain][mi][ni], 0, 0, 0);
-        if (sum) rsum.template add<Q>(f.a);
+            for (int mi = 0; mi < kRows; ++mi)
+                acc[chain][R + mi][G] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[P % 2][mi], fw[G], acc[chain][R + mi][G], 0, 0, 0);
+            for_constants<R1 - R0>([&](auto i) { rsum.template add<R + R0 + decltype(i)::value, HALF>(fa[P % 2][R0 + decltype(i)::value]); });
+            if constexpr (NEXT < kAll && NEXT % kParts == 0) read_w(w_at[NEXT / kParts], group);
+            for_constants<D1 - D0>([&](auto i) {
+                constexpr int pair = D0 + decltype(i)::value;
+                piece[pair % 4] = decode_pair<B, U>(now, pair, fp);
+                if constexpr (pair % 4 == 3) store_piece(kStage - cur, pair / 4, piece);
+            });
+            __builtin_amdgcn_sched_barrier(0x6);              // the columns keep their order, but for vector and scalar arithmetic
+        });
     };
 
-    // step i: A and W of the step are in stage `cur`; the dwords of step i + 1 are in `next` (asked for during step i - 1)
-    Frags f0, f1;
-    uint32_t cur = 0;
-    Unit<B, U> now, next;
-#pragma unroll
-    for (int i = 0; i < Unit<B, U>::kDwords; ++i) next.w[i] = 0;
+    // step i: A and W of the step are in stage `cur`, the dwords of step i + 1 in `next` (asked for during step i - 1)
     auto clear = [&]() {
-        clear_chains(acc);
+        clear_chains<CHAINS, TM, TN>(acc);
         rsum.clear();
     };
+#pragma unroll
+    for (int i = 0; i < Unit<B, U>::kDwords; ++i) next.w[i] = 0;
     if (CHAINS == 1) clear();
     if (steps > 0) {
         load_a(0, 0);
@@ -228,56 +181,72 @@ void gemm_bits_kernel(BitsArgs ga) {
         if (steps > 1) load_w(1, next);
         align_unit<B, U>(now, u_shift);
 #pragma unroll
-        for (int i = 0; i < static_cast<int>(kPieces); ++i) store_piece(0, now, i);
+        for (int i = 0; i < static_cast<int>(kPieces); ++i) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) piece[p] = decode_pair<B, U>(now, 4 * i + p, fp);
+            store_piece(0, i, piece);
+        }
     }
-    auto step = [&](uint32_t i, bool first, bool more1, bool more2) {
+    const UintTag<0> p0;
+    const UintTag<kAll - 1> last;
+    const UintTag<kAll> nothing;
+    // the step's decoding is spread evenly over its parts, of which the one before its own first comes first
+    auto pairs_before = [](int place) { return place * kPairs / kAll; };
+    auto step = [&](uint32_t i, auto first, auto more1, bool more2) {
+        constexpr bool FIRST = decltype(first)::value, MORE = decltype(more1)::value;
         wait_loads_and_sync<0>();
 #pragma unroll
         for (int q = 0; q < Unit<B, U>::kDwords; ++q) pin(next.w[q]);   // they have arrived: their uses need no wait of their own
-        now = next;
-        const uint32_t other = kStage - cur;
-        read_frags(cur, a_at[0], w_at[0], f0);
-        if (more1) load_a(other, i + 1);
+        if constexpr (MORE) now = next;
+        if constexpr (MORE) load_a(kStage - cur, i + 1);
         if (more2) load_w(i + 2, next);
-        if (more1) align_unit<B, U>(now, u_shift);
-        if (!first) multiply(f1, UintTag<3>{}, false);
-        read_frags(cur, a_at[1], w_at[1], f1);
-        if (more1) store_piece(other, now, 0);
-        multiply(f0, UintTag<0>{}, true);
-        read_frags(cur, a_at[2], w_at[2], f0);
-        if (more1) store_piece(other, now, 1);
-        multiply(f1, UintTag<1>{}, false);
-        read_frags(cur, a_at[3], w_at[3], f1);
-        if (more1 && kPieces > 2) store_piece(other, now, 2);
-        multiply(f0, UintTag<2>{}, WN == 2);
-        if (more1 && kPieces > 2) store_piece(other, now, 3);
-        cur = other;
+        if constexpr (MORE) align_unit<B, U>(now, u_shift);
+        constexpr int kBegin = FIRST ? 0 : pairs_before(1);   // (the first step has no part before its own)
+        if constexpr (FIRST) {
+            for_constants<TN>([&](auto n) { read_w(w_at[0], n); });
+            for_constants<kRows>([&](auto n) { read_a(a_at[0], p0, n); });
+        } else {
+            multiply(last, p0, p0, UintTag<MORE ? kBegin : 0>{});
+        }
+        for_constants<kAll - 1>([&](auto part) {
+            constexpr int P = decltype(part)::value, D0 = P == 0 ? kBegin : pairs_before(P + 1), D1 = pairs_before(P + 2);
+            multiply(part, UintTag<P + 1>{}, UintTag<D0>{}, UintTag<MORE ? D1 - D0 : 0>{});
+        });
+        cur = kStage - cur;
     };
+    const BoolTag<true> yes;
+    const BoolTag<false> no;
     if (full > 0) {
-        step(0, true, steps > 1, steps > 2);
+        if (steps > 1) step(0, yes, yes, steps > 2);
+        else step(0, yes, no, false);
         uint32_t i = 1;
-        for (; i + 2 < steps; ++i) step(i, false, true, true);
-        for (; i < full; ++i) step(i, false, i + 1 < steps, i + 2 < steps);
-        multiply(f1, UintTag<3>{}, false);
+        for (; i + 2 < steps; ++i) step(i, no, yes, true);
+        if (i + 1 < steps && i < full) step(i++, no, yes, false);   // (of whole steps only the last has none behind it)
+        if (i < full) step(i, no, no, false);
+        multiply(last, nothing, p0, p0);
     }
-    if (full < steps) {                                       // 32 k more: two quarters
+    if (full < steps) {                                       // 32 k more, the same ones first in all waves
         wait_loads_and_sync<0>();
-        auto quarter = [&](auto ks) {
-            read_frags(cur, a_place(ks.value), w_place(ks.value), f0);
-            multiply(f0, ks, false);
-            if (ks.value % WN == wn) rsum.template add<0>(f0.a);
-        };
-        quarter(UintTag<0>{});
-        quarter(UintTag<1>{});
+        a_at[0] = a_place(0);
+        const uint32_t w_off = w_place(0);
+        const auto before = rsum;                             // (where two waves share the rows, one's are enough)
+        for_constants<TN>([&](auto n) { read_w(w_off, n); });
+        for_constants<kRows>([&](auto n) { read_a(a_at[0], p0, n); });
+        for_constants<kParts - 1>([&](auto part) {
+            constexpr int P = decltype(part)::value;
+            multiply(part, UintTag<P + 1>{}, p0, p0);
+        });
+        multiply(UintTag<kParts - 1>{}, nothing, p0, p0);
+        if (Order::kByHalf && (wn & 1u)) rsum = before;
     }
     for (uint32_t i = steps; i < (steps_k + TEAMS - 1) / TEAMS; ++i) wait_loads_and_sync<0>();   // teams wait for each other
     wait_loads_and_sync<0>();                                 // nobody reads a stage any more
     const float s = ga.sb ? ga.sb[0] : 1.0f, b = ga.sb ? ga.sb[1] : 0.0f;
-    float *rowsum = reinterpret_cast<float *>(lds_all);       // [TEAMS * WN][BM]
-    join_chains(acc);
-    publish_row_sums<WN, BM, TM>(rowsum, rsum.total(), ga.sb != nullptr, team, 32 * TM * wm, wn, lane);
-    if (!add_teams<TEAMS, NW, TM, TN>(rowsum + TEAMS * WN * BM, acc[0], team, wave, lane)) return;
-    store_tile<TEAMS * WN, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 32 * TN * wn, N, acc[0], rowsum, 32 * TM * wm, lane, s, b);
+    float *rowsum = reinterpret_cast<float *>(lds_all);       // [TEAMS * kParts][BM]
+    join_chains<CHAINS, TM, TN>(acc);
+    publish_row_sums<WN, BM, TM>(rowsum, rsum, ga.sb != nullptr, team, 16 * TM * wm, wn, lane);
+    if (!add_teams<TEAMS, NW, TM, TN>(rowsum + TEAMS * Order::kParts * BM, acc[0], team, wave, lane)) return;
+    store_tile<TEAMS * Order::kParts, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 16 * TN * wn, N, acc[0], rowsum, 16 * TM * wm, order, lane, s, b);
 }
 
 // 256 x 128 by four waves, one to a SIMD, each of 128 x 64, decodes a code for 256 rows and reads its fragments from LDS half as often as 128 x 256 by eight
@@ -319,23 +288,23 @@ inline void launch_bits_one(const BitsArgs &ga, hipStream_t st) {
 template <int B, bool TRANS>
 inline int launch_bits_tile(int which, uint32_t chains, const BitsArgs &ga, hipStream_t st) {
     switch (which) {
-        case 0: launch_bits_one<B, 4, 32, 4, 2, 1, 1, 2, TRANS>(ga, st); break;
-        case 1: launch_bits_one<B, 2, 32, 4, 2, 1, 1, 1, TRANS>(ga, st); break;
-        case 2: launch_bits_one<B, 4, 32, 2, 2, 1, 1, 2, TRANS>(ga, st); break;
+        case 0: gemm_bits_large_kernel<B, TRANS><<<dim3(ga.tiles_m * ga.tiles_n), dim3(512), 0, st>>>(ga); break;
+        case 1: launch_bits_one<B, 2, 32, 8, 4, 1, 1, 1, TRANS>(ga, st); break;
+        case 2: launch_bits_one<B, 4, 32, 4, 4, 1, 1, 2, TRANS>(ga, st); break;
         case 3:
-            if (chains == 2) launch_bits_one<B, 4, 16, 2, 1, 1, 2, 2, TRANS>(ga, st);
-            else launch_bits_one<B, 4, 16, 2, 1, 1, 1, 4, TRANS>(ga, st);
+            if (chains == 2) launch_bits_one<B, 4, 16, 4, 2, 1, 2, 2, TRANS>(ga, st);
+            else launch_bits_one<B, 4, 16, 4, 2, 1, 1, 4, TRANS>(ga, st);
             break;
-        case 4: launch_bits_one<B, 2, 16, 2, 1, 1, 1, 3, TRANS>(ga, st); break;
+        case 4: launch_bits_one<B, 2, 16, 4, 2, 1, 1, 3, TRANS>(ga, st); break;
         case 5:
-            if (chains == 2) launch_bits_one<B, 2, 16, 1, 1, 1, 2, 4, TRANS>(ga, st);
-            else launch_bits_one<B, 2, 16, 1, 1, 1, 1, 4, TRANS>(ga, st);
+            if (chains == 2) launch_bits_one<B, 2, 16, 2, 2, 1, 2, 4, TRANS>(ga, st);
+            else launch_bits_one<B, 2, 16, 2, 2, 1, 1, 4, TRANS>(ga, st);
             break;
         case 6:
-            if (chains == 2) launch_bits_one<B, 2, 16, 1, 1, 2, 2, 4, TRANS>(ga, st);
-            else launch_bits_one<B, 2, 16, 1, 1, 2, 1, 4, TRANS>(ga, st);
+            if (chains == 2) launch_bits_one<B, 2, 16, 2, 2, 2, 2, 4, TRANS>(ga, st);
+            else launch_bits_one<B, 2, 16, 2, 2, 2, 1, 4, TRANS>(ga, st);
             break;
-        case 7: launch_bits_one<B, 2, 16, 1, 1, 4, 1, 4, TRANS>(ga, st); break;
+        case 7: launch_bits_one<B, 2, 16, 2, 2, 4, 1, 4, TRANS>(ga, st); break;
         default: return static_cast<int>(hipErrorInvalidValue);
     }
     return static_cast<int>(hipGetLastError());

@@ -8,14 +8,14 @@
 // codes.  Staging costs no vector instruction and W passes through LDS at one byte per weight.
 //
 // 16-byte pieces are XOR-swizzled on their way in (the lane picks the piece, its LDS place is fixed): A pieces by half the row,
-// forward W pieces by twice the k row, TRANS W pieces by a quarter of the column, so that the 16 pieces that one read takes at
-// a time lie on different ones of the 64 banks (A by the whole row: 8.1 clocks a read instead of 4.4, W 4.2 instead of 3.2 and
-// 8.0 instead of 4.2).  Forward no bank conflict is counted; TRANS reads half of a 16-byte piece at a time, and these reads still conflict,
-// 4.2 million cycles over all compute units in a launch of 62 - 68 us at the shapes below.
+// forward W pieces by the k row as far as a row has pieces, TRANS W pieces by a quarter of the column, so that the 16 pieces of A that one read takes at
+// a time, or the 16 k rows of one piece of W, lie on different ones of the 64 banks.  Forward no bank conflict is counted; TRANS reads half of a 16-byte piece at a time, and these reads conflict,
+// 4.2 million cycles over all compute units in a launch of 60 us at the shapes below.
 //
-// Fragments of a quarter step are read while the quarter before is multiplied; the last quarter is multiplied after the
-// barrier of the next step, under that step's first reads.  Waves start their quarters at different places
-// (WN + WM rotation), which also deals the row sums of A evenly and without branches: each column wave sums its own quarters.
+// The order of the instructions is written down, a column of matrix tiles at a time: its products, and beside them a share of the reads of the next part's fragments, the conversion of
+// the next column, and a share of the loads of a later stage.  Left to itself the compiler puts the reads right before their use, and the address arithmetic of the loads in one run of 100
+// scalar instructions; addresses now advance from stage to stage.  The last part of a step is multiplied after the
+// barrier of the next step, under that step's first reads.  The column waves start with different halves of a step.
 //
 // The top code reads as NaN in the hardware conversion, without its sign.  No pass over the codes looks for it beforehand, and no
 // instruction in the loop: it makes every row of its column NaN, so a wave looks at one row of its sums, and a workgroup that finds
@@ -26,12 +26,10 @@
 // kernel of other formats behind it); a top code in one column of 64, in the last row of k, 134 / 135 (156 / 154; 95 / 108); none 65 / 58
 // either way.  Looking more often costs up to 9 % where there is none, and so does looking in small tiles (up to 4 %).
 //
-// Measured (us, 8192 x 4096 x 1024 / 8192 x 1024 x 4096, fp32 output, new operands each time), against the kernel before (256 x 128 tile,
-// A fragments from global memory, W decoded on the way into LDS, a 5 us pass over the codes for top codes first): 83 / 81 ->
-// 65 / 58.  What bounds it now: waits.  The matrix cores are busy in 45 - 48 % of the cycles, at 2.1 - 2.2 GHz, and the waves wait in 34 - 47 %
-// of theirs, for fragments that are read one quarter of a step ahead, for the step's barrier, and at a contraction of 1024 for the C
-// stores where nothing covers them; 1300 TFLOP/s at 8192 x 4096 x 4096.  Not for LDS bandwidth (67.6 -> 67.1 us at the first shape without
-// the bank conflicts there were).
+// Measured (us, 8192 x 4096 x 1024 / 8192 x 1024 x 4096, fp32 output, new operands each time): 65 / 59 with matrix instructions of 32 x 32 x 16, row sums by dot products and the
+// compiler's order, 62 / 57 now.  What bounds it: power.  With two waves a SIMD and K = 4096 it ran at 1.77 GHz, the matrix cores busy in 80 % of the cycles (of two tiles a compute unit); now it is 1.88 GHz.  Instructions
+// taken out of the loop make the clock fall again, by and large: without the reads of fragments it is 2.38 GHz, without the loads 2.23.  At a contraction of 1024 also the C stores: a workgroup's take 5 us, in which
+// the other one of the unit has the matrix cores to itself and uses them half as well as two.
 #include <algorithm>
 
 #include "omc_mma.h"
@@ -72,19 +70,19 @@ struct Fp8Args {
     uint32_t N, K, tiles_m, tiles_n;
 };
 
-// WM x WN waves of TM x TN matrix tiles (32 x 32) each, TEAMS times: team t multiplies the steps t, t + TEAMS, ... of the
+// WM x WN waves of TM x TN matrix tiles (16 x 16) each, TEAMS times: team t multiplies the steps t, t + TEAMS, ... of the
 // contraction in LDS stages of its own, and team 0 adds up the teams' tiles in order.  A team's sums are CHAINS chains (which
-// of them, the quarter of the step decides).  S stages, OCC waves per SIMD.
+// of them, the half of the step decides, of four also whether the step is odd).  S stages, OCC waves per SIMD.
 template <int WM, int WN, int TM, int TN, int TEAMS, int CHAINS, int S, int OCC, bool TRANS>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN * TEAMS, 64 * WM * WN * TEAMS))) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 void gemm_fp8_kernel(Fp8Args ga) {
-    constexpr int NW = WM * WN, BM = 32 * TM * WM, BN = 32 * TN * WN;
+    constexpr int NW = WM * WN, BM = 16 * TM * WM, BN = 16 * TN * WN;
     constexpr int kALoads = BM / 8 / NW, kWLoads = BN / 16 / NW, kLoads = kALoads + kWLoads;   // 1 KB loads per wave and stage
     constexpr int kPieces = BN / 16;                        // 16-byte pieces in a k row of the forward W tile
     constexpr uint32_t kABytes = BM * 128, kStage = kABytes + BN * 64;
     constexpr bool kLookEarly = BM * BN >= 128 * 256;
-    static_assert(WM == 2 && (WN == 2 || WN == 4), "how the quarters are dealt below; with an even number of waves a wave's loads bring one half of 16 rows");
-    static_assert(BM % (8 * NW) == 0 && BN % (16 * NW) == 0 && (64 / kPieces) * NW % kPieces == 0, "whole loads, one swizzle per wave");
+    static_assert(WM == 2 && (WN == 2 || WN == 4), "how the row sums are dealt below; with an even number of waves a wave's loads bring one half of 16 rows");
+    static_assert(BM % (8 * NW) == 0 && BN % (16 * NW) == 0 && (64 / kPieces) * NW % 16 == 0, "whole loads, one swizzle per wave");
     __shared__ __attribute__((aligned(1024))) uint8_t lds_all[TEAMS * S * kStage];
     __shared__ uint32_t top_met;
     const uint32_t team = TEAMS == 1 ? 0u : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
@@ -102,76 +100,98 @@ void gemm_fp8_kernel(Fp8Args ga) {
     // bring the lower half twice instead of reading past the row, and nobody multiplies the upper half
     const uint32_t full_k = K / 64, stages_k = (K + 63) / 64;
     const uint32_t full = (full_k + TEAMS - 1 - team) / TEAMS, stages = (stages_k + TEAMS - 1 - team) / TEAMS;   // this team's
-    const uint8_t *a_base = reinterpret_cast<const uint8_t *>(ga.A) + static_cast<uint64_t>(m0) * K * 2;
     const uint32_t a_row = lane >> 3, a_piece = (lane & 7u) ^ ((a_row >> 1) + 4 * (wave & 1u));
-    const uint8_t *w_base = TRANS ? ga.codes + static_cast<uint64_t>(n0) * K : ga.codes + n0;
     const uint32_t w_row = TRANS ? lane >> 2 : lane / kPieces;
-    auto w_swizzle = [](uint32_t k_row) { return k_row * kPieces / 8 & (kPieces - 2u); };
+    auto w_swizzle = [](uint32_t k_row) { return k_row * kPieces / 16 & (kPieces - 1u); };
     const uint32_t w_piece = TRANS ? (lane & 3u) ^ (lane >> 4) : (lane % kPieces) ^ w_swizzle(wave * (64 / kPieces) + w_row);
-    auto load_stage = [&](uint32_t at, uint32_t step) {
-        const uint32_t j = team + TEAMS * step;
-        const bool half = j == full_k;
-        const uint32_t a_off = a_row * K * 2 + (half ? a_piece & 3u : a_piece) * 16;
-#pragma unroll
-        for (int i = 0; i < kALoads; ++i) {
-            const uint32_t c = wave + NW * i;                 // rows 8 c ..
-            load_to_lds(a_base + static_cast<uint64_t>(j) * 128 + static_cast<uint64_t>(c) * 16 * K, a_off, lds0 + at + c * 1024);
-        }
-        const uint32_t w_off = TRANS ? w_row * K + (half ? w_piece & 1u : w_piece) * 16 : w_row * N + w_piece * 16;
-#pragma unroll
-        for (int i = 0; i < kWLoads; ++i) {
-            const uint32_t c = wave + NW * i;
-            const uint32_t first = TRANS ? 16 * c : (half ? (c * (64 / kPieces)) & 31u : c * (64 / kPieces));   // column / k row
-            const uint8_t *from = TRANS ? w_base + static_cast<uint64_t>(j) * 64 + static_cast<uint64_t>(first) * K
-                                        : w_base + (static_cast<uint64_t>(j) * 64 + first) * N;
-            load_to_lds(from, w_off, lds0 + at + kABytes + c * 1024);
-        }
+    const uint8_t *a_from, *w_from;                           // of the stage that is asked for next: this wave's first kilobyte
+    uint32_t a_off, w_off;                                    // this lane's piece of a kilobyte
+    auto first_stage = [&]() {
+        a_from = reinterpret_cast<const uint8_t *>(ga.A) + static_cast<uint64_t>(m0 + 8 * wave) * K * 2 + 128 * team;
+        w_from = TRANS ? ga.codes + static_cast<uint64_t>(n0 + 16 * wave) * K + 64 * team
+                       : ga.codes + static_cast<uint64_t>(64 * team + 64 / kPieces * wave) * N + n0;
+        a_off = a_row * K * 2 + a_piece * 16;
+        w_off = TRANS ? w_row * K + w_piece * 16 : w_row * N + w_piece * 16;
     };
-
-    // ---- LDS -> fragments.  The k of a quarter's two halves may be any, as long as both operands agree: TRANS takes 16 codes of
-    // a column as the same half of two quarters, so that A's pieces follow that order.
-    const uint32_t f_row = lane & 31u, f_half = lane >> 5;
-    auto a_place = [&](uint32_t ks) {
-        const uint32_t row = 32 * TM * wm + f_row;
-        const uint32_t piece = TRANS ? 4 * (ks >> 1) + 2 * f_half + (ks & 1u) : 2 * ks + f_half;
-        return row * 128 + ((piece ^ ((row >> 1) & 7u)) << 4);
+    auto next_stage = [&]() {
+        a_from += 128 * TEAMS;
+        w_from += TRANS ? 64 * TEAMS : 64ull * TEAMS * N;
     };
-    auto w_place = [&](uint32_t ks) {
-        if (TRANS) {
-            const uint32_t col = 32 * TN * wn + f_row, piece = 2 * (ks >> 1) + f_half;
-            return kABytes + col * 64 + ((piece ^ ((col >> 2) & 3u)) << 4) + 8 * (ks & 1u);
-        }
-        const uint32_t block = lane >> 4, in = lane & 15u;      // 16 lanes: 16 columns x 8 k
-        const uint32_t row = 16 * ks + 8 * (block >> 1) + (in >> 1), piece = 2 * TN * wn + (block & 1u);
-        return kABytes + row * BN + ((piece ^ w_swizzle(row)) << 4) + 8 * (in & 1u);
-    };
-    uint32_t a_at[4], w_at[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const uint32_t ks = (p + wn + 2 * wm) & 3u;
-        a_at[p] = a_place(ks);
-        w_at[p] = w_place(ks);
-    }
-    struct Frags {
-        bf16x8 a[TM];
-        u32x2 w[TN];
-    };
-    auto read_frags = [&](uint32_t at, uint32_t a_off, uint32_t w_off, Frags &f) {
-#pragma unroll
-        for (int mi = 0; mi < TM; ++mi) f.a[mi] = *reinterpret_cast<const bf16x8 *>(lds + at + a_off + 32 * 128 * mi);
-#pragma unroll
-        for (int ni = 0; ni < TN; ++ni) {
+    const uint64_t a_stride = 16ull * NW * K, w_stride = TRANS ? 16ull * NW * K : 64ull / kPieces * NW * N;   // between a wave's kilobytes
+    auto load_one = [&](uint32_t at, auto index, bool half) {
+        constexpr uint32_t I = decltype(index)::value;
+        if constexpr (I < kALoads) {
+            load_to_lds(a_from + I * a_stride, half ? a_off - (a_piece & 4u) * 16 : a_off, lds0 + at + (wave + NW * I) * 1024);
+        } else {
+            constexpr uint32_t i = I - kALoads;
             if (TRANS) {
-                f.w[ni] = *reinterpret_cast<const u32x2 *>(lds + at + w_off + 32 * 64 * ni);
-            } else {                                        // 32 columns on: two pieces on, before the swizzle
-                const i32x2 t = __builtin_amdgcn_ds_read_tr8_b64_v2i32((OMC_LDS i32x2 *)(lds + at + (w_off ^ (32u * ni))));
-                f.w[ni] = u32x2{static_cast<uint32_t>(t[0]), static_cast<uint32_t>(t[1])};
+                load_to_lds(w_from + i * w_stride, half ? w_off - (w_piece & 2u) * 16 : w_off, lds0 + at + kABytes + (wave + NW * i) * 1024);
+            } else {                                          // k rows from 32 on: 32 rows back (these are whole kilobytes)
+                const bool back = half && (wave + NW * i) * (64 / kPieces) >= 32;
+                load_to_lds(back ? w_from + i * w_stride - 32ull * N : w_from + i * w_stride, w_off, lds0 + at + kABytes + (wave + NW * i) * 1024);
             }
         }
     };
+    auto is_half = [&](uint32_t step) { return team + TEAMS * step == full_k; };
+    auto load_stage = [&](uint32_t at, uint32_t step) {
+        const bool half = is_half(step);
+        for_constants<kLoads>([&](auto i) { load_one(at, i, half); });
+        next_stage();
+    };
 
-    f32x16 acc[CHAINS][TM][TN];
-    RowSums<WN, TM, CHAINS> rsum;
+    // ---- LDS -> fragments of 32 k
+    const uint32_t f_row = lane & 15u, f_k = lane >> 4;
+    auto a_place = [&](uint32_t half) {
+        const uint32_t row = 16 * TM * wm + f_row;            // (of the wave's first row tile, which need not be the one it multiplies first)
+        return row * 128 + (((4 * half + f_k) ^ ((row >> 1) & 7u)) << 4);
+    };
+    auto w_place = [&](uint32_t half) {
+        if (TRANS) {
+            const uint32_t col = 16 * TN * wn + f_row;
+            return kABytes + col * 64 + (((2 * half + (f_k >> 1)) ^ ((col >> 2) & 3u)) << 4) + 8 * (f_k & 1u);
+        }
+        const uint32_t row = 32 * half + 8 * f_k + (f_row >> 1);   // 16 lanes: 16 columns x 8 k
+        return kABytes + row * BN + (((TN * wn) ^ w_swizzle(row)) << 4) + 8 * (f_row & 1u);
+    };
+    uint32_t a_at[2], w_at[2];                                // of the half that is multiplied first, and the other one
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        a_at[p] = a_place((p + wn) & 1u);
+        w_at[p] = w_place((p + wn) & 1u);
+    }
+    typedef RowOrder<WN, TM> Order;
+    const Order order(wn);
+    constexpr int kRun = Order::kSlots < TM / 2 ? Order::kSlots : TM / 2;   // so many of its row tiles follow each other
+    uint32_t a_run[TM / kRun];                                // where the runs begin
+#pragma unroll
+    for (uint32_t r = 0; r < TM / kRun; ++r) a_run[r] = 128 * order.row(r * kRun);
+    typedef StepFrags<TM, TN, bf16x8, u32x2> Frags;
+    Frags f;
+    // read `index` of phase P's, in the order they are needed
+    auto read_one = [&](uint32_t at, uint32_t a_off, uint32_t w_off, auto phase, auto index) {
+        constexpr int P = decltype(phase)::value, I = decltype(index)::value;
+        constexpr bool kReadsB = Frags::reads_b(P);
+        constexpr int mi = Frags::reads_a(P) ? I - (kReadsB ? 1 : 0) : -1;
+        if constexpr (mi >= 0 && mi < Frags::kRows) {
+            constexpr int tile = Frags::first_row(P) + mi;
+            f.a[Frags::a_slot(P)][mi] = *reinterpret_cast<const bf16x8 *>(lds + at + a_off + a_run[tile / kRun] + 16 * 128 * (tile % kRun));
+        } else {
+            constexpr int i = I == 0 ? 0 : I - (Frags::reads_a(P) ? Frags::kRows : 0), ni = Frags::first_col(P) + i;
+            if (TRANS) {
+                f.b[Frags::b_slot(P)][i] = *reinterpret_cast<const u32x2 *>(lds + at + w_off + 16 * 64 * ni);
+            } else {                                          // 16 columns on: a piece on, before the swizzle
+                const i32x2 t = __builtin_amdgcn_ds_read_tr8_b64_v2i32((OMC_LDS i32x2 *)(lds + at + (w_off ^ (16u * ni))));
+                f.b[Frags::b_slot(P)][i] = u32x2{static_cast<uint32_t>(t[0]), static_cast<uint32_t>(t[1])};
+            }
+        }
+    };
+    auto read_frags = [&](uint32_t at, uint32_t a_off, uint32_t w_off, auto phase) {
+        for_constants<Frags::reads(decltype(phase)::value)>([&](auto i) { read_one(at, a_off, w_off, phase, i); });
+    };
+
+    Sums<CHAINS, TM, TN> acc;
+    uint32_t cur = 0, far = 0;
+    RowSums<WN, TM> rsum;
     auto holds_nan = [&]() {                                  // one row of every column tells
         bool bad = false;
 #pragma unroll
@@ -181,54 +201,84 @@ void gemm_fp8_kernel(Fp8Args ga) {
     // Without EXACT it may stop on the way, in all waves of the workgroup alike, with a NaN in some wave's sums.
     auto compute = [&](auto exact_tag) {
         constexpr bool EXACT = decltype(exact_tag)::value;
-        auto multiply = [&](const Frags &f, auto quarter, bool sum) {
-            constexpr int Q = decltype(quarter)::value, chain = Q % CHAINS;
+        constexpr int kLast = Frags::kPhases - 1, kGroups = Frags::kCols;
+        // Over so many columns of a step its loads are spread: over all of them, or where the next step waits for them over half (8192 x 4096 x 1024 by two stages 62.0 us, 65.7 over
+        // all; 2048 x 2048 x 512 by three 8.40 over all, 8.56 over half).
+        constexpr int kLoadColumns = kGroups * Frags::kPhases / (S == 2 ? 2 : 1);
+        bf16x8 w;                                             // the column of fragments that is multiplied next
+        auto convert = [&](auto phase, auto col) { w = fp8x8_to_bf16<EXACT>(f.b[Frags::b_slot(decltype(phase)::value)][decltype(col)::value]); };
+        // The products of a phase, column by column of its tiles.  Beside each column: a share of the reads of phase NEXT from the stage at `at`, the conversion of the column after
+        // it, and a share of the stage's loads (the step begins with its last phase's share).
+        auto multiply = [&](auto phase, auto odd, auto next, uint32_t at, auto load, bool half) {
+            constexpr int P = decltype(phase)::value, NEXT = decltype(next)::value, chain = (Frags::half(P) + 2 * static_cast<int>(decltype(odd)::value)) % CHAINS;
+            constexpr int A = Frags::a_slot(P), R = Frags::first_row(P), C = Frags::first_col(P);
+            for_constants<kGroups>([&](auto group) {
+                constexpr int G = decltype(group)::value;
+                const bf16x8 now = w;
+                if constexpr (NEXT <= kLast) {
+                    constexpr int N0 = G * Frags::reads(NEXT) / kGroups, N1 = (G + 1) * Frags::reads(NEXT) / kGroups;
+                    for_constants<N1 - N0>([&](auto i) { read_one(at, a_at[Frags::half(NEXT)], w_at[Frags::half(NEXT)], next, UintTag<N0 + decltype(i)::value>{}); });
+                }
+                if constexpr (decltype(load)::value) {
+                    constexpr int place = ((P + 1) % Frags::kPhases) * kGroups + G, here = place < kLoadColumns ? place : kLoadColumns;
+                    constexpr int L0 = here * kLoads / kLoadColumns, L1 = here < kLoadColumns ? (here + 1) * kLoads / kLoadColumns : L0;
+                    for_constants<L1 - L0>([&](auto i) { load_one(far, UintTag<L0 + decltype(i)::value>{}, half); });
+                }
 #pragma unroll
-            for (int ni = 0; ni < TN; ++ni) {
-                const bf16x8 w = fp8x8_to_bf16<EXACT>(f.w[ni]);
-#pragma unroll
-                for (int mi = 0; mi < TM; ++mi)
-                    acc[chain][mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mi], w, acc[chain][mi][ni], 0, 0, 0);
-            }
-            if (sum) rsum.template add<Q>(f.a);
+                for (int mi = 0; mi < Frags::kRows; ++mi)
+                    acc[chain][R + mi][C + G] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[A][mi], now, acc[chain][R + mi][C + G], 0, 0, 0);
+                if constexpr (G + 1 < kGroups) convert(phase, UintTag<G + 1>{});
+                else if constexpr (NEXT <= kLast) convert(next, UintTag<0>{});
+                if constexpr (Frags::reads_a(P)) {
+                    constexpr int S0 = G * Frags::kRows / kGroups, S1 = (G + 1) * Frags::kRows / kGroups;
+                    for_constants<S1 - S0>([&](auto i) { rsum.template add<R + S0 + decltype(i)::value, Frags::half(P)>(f.a[A][S0 + decltype(i)::value]); });
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
         };
         auto clear = [&]() {
-            clear_chains(acc);
+            clear_chains<CHAINS, TM, TN>(acc);
             rsum.clear();
         };
         if (CHAINS == 1) clear();
         const uint32_t shortest = stages_k / TEAMS;
         uint32_t steady_end = stages > S - 1 ? stages - (S - 1) : 0, full_end = full, slots = (stages_k + TEAMS - 1) / TEAMS;
         bool half = full < stages;
-        Frags f0, f1;
-        uint32_t cur = 0, far = (S - 1) * kStage;
-        auto rest_of_step = [&]() {                           // everything but the first quarter's reads and the last one's products
-            read_frags(cur, a_at[1], w_at[1], f1);
-            multiply(f0, UintTag<0>{}, true);
-            read_frags(cur, a_at[2], w_at[2], f0);
-            multiply(f1, UintTag<1>{}, false);
-            read_frags(cur, a_at[3], w_at[3], f1);
-            multiply(f0, UintTag<2>{}, WN == 2);
+        cur = 0;
+        far = (S - 1) * kStage;
+        const BoolTag<false> no;
+        const UintTag<kLast + 1> nothing;
+        auto rest_of_step = [&](auto odd, auto load, bool half_stage) {   // everything but the first part's reads and the last one's products
+            for_constants<kLast>([&](auto phase) { multiply(phase, odd, UintTag<decltype(phase)::value + 1>{}, cur, load, half_stage); });
             cur = cur == (S - 1) * kStage ? 0 : cur + kStage;
             far = far == (S - 1) * kStage ? 0 : far + kStage;
         };
+        // `what` for an even or an odd step, where its chains depend on that
+        auto by_parity = [&](uint32_t j, auto what) {
+            if (CHAINS == 4 && (j & 1u) != 0) what(BoolTag<true>{}, BoolTag<false>{});
+            else what(BoolTag<false>{}, BoolTag<true>{});
+        };
         if (!EXACT && kLookEarly && threadIdx.x == 0) top_met = 0;
+        first_stage();
 #pragma unroll
         for (uint32_t i = 0; i < S - 1; ++i)
             if (i < stages) load_stage(i * kStage, i);
         if (CHAINS > 1) clear();                              // (while the first stages are on their way)
         if (full > 0) {
             wait_stage<S, kLoads>(0, stages);
-            read_frags(cur, a_at[0], w_at[0], f0);
+            read_frags(cur, a_at[0], w_at[0], UintTag<0>{});
             if (stages > S - 1) load_stage(far, S - 1);
-            rest_of_step();
+            convert(UintTag<0>{}, UintTag<0>{});
+            rest_of_step(no, no, false);
             uint32_t j = 1;
             auto steady_step = [&]() {
                 wait_loads_and_sync<(S - 2) * kLoads>();
-                read_frags(cur, a_at[0], w_at[0], f0);
-                load_stage(far, j + S - 1);
-                multiply(f1, UintTag<3>{}, false);
-                rest_of_step();
+                const bool half_stage = is_half(j + S - 1);
+                by_parity(j, [&](auto odd, auto even) {
+                    multiply(UintTag<kLast>{}, even, UintTag<0>{}, cur, BoolTag<true>{}, half_stage);
+                    rest_of_step(odd, BoolTag<true>{}, half_stage);
+                });
+                next_stage();
             };
             if (!EXACT && kLookEarly && shortest >= 16) {     // (every team gets this far)
                 for (const uint32_t look = shortest / 8; j < look; ++j) steady_step();
@@ -242,31 +292,43 @@ void gemm_fp8_kernel(Fp8Args ga) {
             for (; j < steady_end; ++j) steady_step();
             for (; j < full_end; ++j) {
                 wait_stage<S, kLoads>(j, stages);
-                read_frags(cur, a_at[0], w_at[0], f0);
-                multiply(f1, UintTag<3>{}, false);
-                rest_of_step();
+                by_parity(j, [&](auto odd, auto even) {
+                    multiply(UintTag<kLast>{}, even, UintTag<0>{}, cur, no, false);
+                    rest_of_step(odd, no, false);
+                });
             }
-            multiply(f1, UintTag<3>{}, false);
+            by_parity(j, [&](auto, auto even) { multiply(UintTag<kLast>{}, even, nothing, 0, no, false); });
         }
-        if (half) {                                           // 32 k more: two quarters
+        if (half) {                                           // 32 k more, the same ones first in all waves
             wait_loads_and_sync<0>();
-            auto quarter = [&](auto ks) {
-                read_frags(cur, a_place(ks.value), w_place(ks.value), f0);
-                multiply(f0, ks, false);
-                if (ks.value % WN == wn) rsum.template add<0>(f0.a);
-            };
-            quarter(UintTag<0>{});
-            quarter(UintTag<1>{});
+            if (wn & 1u) {
+                a_at[0] = a_place(0);
+                w_at[0] = w_place(0);
+            }
+            const auto before = rsum;                         // (where two waves share the rows, one's are enough)
+            read_frags(cur, a_at[0], w_at[0], UintTag<0>{});
+            convert(UintTag<0>{}, UintTag<0>{});
+            if constexpr (kLast == 3) {
+                multiply(UintTag<0>{}, no, UintTag<1>{}, cur, no, false);
+                multiply(UintTag<1>{}, no, nothing, cur, no, false);
+            } else {
+                multiply(UintTag<0>{}, no, nothing, cur, no, false);
+            }
+            if (Order::kByHalf && (wn & 1u)) rsum = before;
+            if (wn & 1u) {
+                a_at[0] = a_place(1);
+                w_at[0] = w_place(1);
+            }
         }
         for (uint32_t i = stages; i < slots; ++i) wait_loads_and_sync<0>();   // teams wait for each other
         wait_loads_and_sync<0>();                             // nobody reads a stage any more
-        join_chains(acc);
+        join_chains<CHAINS, TM, TN>(acc);
     };
 
-    float *rowsum = reinterpret_cast<float *>(lds_all);       // [TEAMS * WN][BM], then a flag per wave, then the other teams' tiles
-    uint32_t *tops = reinterpret_cast<uint32_t *>(rowsum + TEAMS * WN * BM);
+    float *rowsum = reinterpret_cast<float *>(lds_all);       // [TEAMS * kParts][BM], then a flag per wave, then the other teams' tiles
+    uint32_t *tops = reinterpret_cast<uint32_t *>(rowsum + TEAMS * Order::kParts * BM);
     float *parts = reinterpret_cast<float *>(tops + 64);
-    static_assert(4 * (TEAMS * WN * BM + 64 + (TEAMS - 1) * BM * BN) <= TEAMS * S * static_cast<int>(kStage), "fits the stages");
+    static_assert(4 * (TEAMS * Order::kParts * BM + 64 + (TEAMS - 1) * BM * BN) <= TEAMS * S * static_cast<int>(kStage), "fits the stages");
     compute(BoolTag<false>{});
     const bool mine = holds_nan();
     if (lane == 0) tops[team * NW + wave] = mine ? 1u : 0u;
@@ -277,9 +339,9 @@ void gemm_fp8_kernel(Fp8Args ga) {
     __syncthreads();                                          // the flags are read before anything overwrites them
     if (__builtin_amdgcn_readfirstlane(any_top) != 0) compute(BoolTag<true>{});
     const float s = ga.sb ? ga.sb[0] : 1.0f, b = ga.sb ? ga.sb[1] : 0.0f;
-    publish_row_sums<WN, BM, TM>(rowsum, rsum.total(), ga.sb != nullptr, team, 32 * TM * wm, wn, lane);
+    publish_row_sums<WN, BM, TM>(rowsum, rsum, ga.sb != nullptr, team, 16 * TM * wm, wn, lane);
     if (!add_teams<TEAMS, NW, TM, TN>(parts, acc[0], team, wave, lane)) return;
-    store_tile<TEAMS * WN, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 32 * TN * wn, N, acc[0], rowsum, 32 * TM * wm, lane, s, b);
+    store_tile<TEAMS * Order::kParts, BM, TM, TN>(ga.C + static_cast<uint64_t>(m0) * N + n0 + 16 * TN * wn, N, acc[0], rowsum, 16 * TM * wm, order, lane, s, b);
 }
 
 // 128 x 256 by four waves has two workgroups on a compute unit, so that one's C stores pass under the other's products: it
@@ -318,24 +380,24 @@ static void launch_one(const Fp8Args &ga, hipStream_t st) {
 template <bool TRANS>
 static int launch_tile(int which, uint32_t chains, const Fp8Args &ga, hipStream_t st) {
     switch (which) {
-        case 0: launch_one<2, 4, 4, 2, 1, 1, 3, 2, TRANS>(ga, st); break;
-        case 1: launch_one<2, 2, 2, 4, 1, 1, 2, 2, TRANS>(ga, st); break;
-        case 2: launch_one<2, 4, 2, 2, 1, 1, 3, 2, TRANS>(ga, st); break;
-        case 3: launch_one<2, 2, 2, 2, 1, 1, 3, 2, TRANS>(ga, st); break;
+        case 0: launch_one<2, 4, 8, 4, 1, 1, 3, 2, TRANS>(ga, st); break;
+        case 1: launch_one<2, 2, 4, 8, 1, 1, 2, 2, TRANS>(ga, st); break;
+        case 2: launch_one<2, 4, 4, 4, 1, 1, 3, 2, TRANS>(ga, st); break;
+        case 3: launch_one<2, 2, 4, 4, 1, 1, 3, 2, TRANS>(ga, st); break;
         case 4:
-            if (chains == 2) launch_one<2, 4, 1, 1, 1, 2, 3, 4, TRANS>(ga, st);
-            else launch_one<2, 4, 1, 1, 1, 1, 3, 4, TRANS>(ga, st);
+            if (chains == 2) launch_one<2, 4, 2, 2, 1, 2, 3, 4, TRANS>(ga, st);
+            else launch_one<2, 4, 2, 2, 1, 1, 3, 4, TRANS>(ga, st);
             break;
         case 5:
-            if (chains == 4) launch_one<2, 2, 1, 1, 1, 4, 3, 4, TRANS>(ga, st);
-            else if (chains == 2) launch_one<2, 2, 1, 1, 1, 2, 3, 4, TRANS>(ga, st);
-            else launch_one<2, 2, 1, 1, 1, 1, 3, 4, TRANS>(ga, st);
+            if (chains == 4) launch_one<2, 2, 2, 2, 1, 4, 3, 2, TRANS>(ga, st);
+            else if (chains == 2) launch_one<2, 2, 2, 2, 1, 2, 3, 4, TRANS>(ga, st);
+            else launch_one<2, 2, 2, 2, 1, 1, 3, 4, TRANS>(ga, st);
             break;
         case 6:
-            if (chains == 2) launch_one<2, 2, 1, 1, 2, 2, 3, 4, TRANS>(ga, st);
-            else launch_one<2, 2, 1, 1, 2, 1, 3, 4, TRANS>(ga, st);
+            if (chains == 2) launch_one<2, 2, 2, 2, 2, 2, 3, 4, TRANS>(ga, st);
+            else launch_one<2, 2, 2, 2, 2, 1, 3, 4, TRANS>(ga, st);
             break;
-        case 7: launch_one<2, 2, 1, 1, 4, 1, 3, 4, TRANS>(ga, st); break;
+        case 7: launch_one<2, 2, 2, 2, 4, 1, 3, 4, TRANS>(ga, st); break;
         default: return static_cast<int>(hipErrorInvalidValue);
     }
     return static_cast<int>(hipGetLastError());

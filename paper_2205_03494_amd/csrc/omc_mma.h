@@ -6,7 +6,6 @@ namespace omc {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -21,6 +20,15 @@ template <uint32_t V>
 struct UintTag {
     static constexpr uint32_t value = V;
 };
+
+// f(UintTag<0>) .. f(UintTag<COUNT - 1>)
+template <int COUNT, int FROM = 0, typename F>
+__device__ __forceinline__ void for_constants(F &&f) {
+    if constexpr (FROM < COUNT) {
+        f(UintTag<FROM>{});
+        for_constants<COUNT, FROM + 1>(f);
+    }
+}
 
 // LDS byte offset of a __shared__ object, as the direct-to-LDS loads take it.
 __device__ __forceinline__ uint32_t lds_offset(const void *p) {
@@ -113,64 +121,56 @@ __device__ __forceinline__ void tile_of_block(uint32_t group_rows, uint32_t tile
     tn = in / height;
 }
 
-// acc[0] .. acc[PARTS - 1] += the 8 bfloat16 values of a fragment, two at a time, dealt out in turn
-template <int PARTS>
-__device__ __forceinline__ void add_fragment(bf16x8 f, float *acc) {
-    const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
-    const u32x4 x = __builtin_bit_cast(u32x4, f);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t w = x[i];
-        acc[i % PARTS] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, acc[i % PARTS], false);
-    }
-}
+// The products are matrix instructions of 16 x 16 results over 32 k, not of 32 x 32 over 16.  Both multiply 1024 pairs per clock, but large
+// products run at the card's power limit, and the smaller ones take less power: registers full of normal values, nothing but matrix instructions, 1750 TFLOP/s
+// at 1.71 GHz with 32 x 32 x 16, 1935 at 1.95 GHz with 16 x 16 x 32.  Either adds up its k in the same order (results bit for bit the same over K = 64 - 8192).
+// A: lane l holds row l % 16, k 8 (l / 16) ..; B likewise its column; the result's value v of lane l is row 4 (l / 16) + v, column l % 16.
+template <int CHAINS, int TM, int TN>
+using Sums = f32x4[CHAINS][TM][TN];
 
-// A wave's share of the row sums of A.  With two column waves it sums two quarters of each step (the first and third that it
-// multiplies), with four one, and where the products are summed in several chains so are these.
-template <int WN, int TM, int CHAINS>
+// How the row sums of A are dealt out over the WN column waves that multiply the same rows, and where the rows of a wave's tiles lie.  Each wave sums the rows of its first
+// tiles, over either half of the steps in a chain of its own; where it has few tiles (kByHalf), of four waves two share the rows and each takes the half that it multiplies first.  So that
+// those are other rows in each wave, their order differs: tile mi lies at row 16 * (mi ^ flip).
+template <int WN, int TM>
+struct RowOrder {
+    static constexpr bool kByHalf = WN == 4 && TM < 8;
+    static constexpr int kSlots = kByHalf ? TM / 2 : TM / WN, kParts = kByHalf ? 2 : 1;   // kParts: waves that share a row
+    uint32_t flip;
+    __device__ __forceinline__ explicit RowOrder(uint32_t wn) : flip((kByHalf ? wn >> 1 : wn) * kSlots) {}
+    __device__ __forceinline__ uint32_t row(uint32_t mi) const { return 16 * (mi ^ flip); }
+};
+// A wave's share of them: products with ones.  One costs a 16 x 32 fragment 16 clocks of the matrix cores; the four two-element dot products of a lane that
+// do the same hold them up for 40, as they cannot run beside them (64 matrix instructions and 16 of the former a step of 256 x 256: 205000 clocks for 8192 x 4096 x 4096, 160000 without any).
+template <int WN, int TM>
 struct RowSums {
-    static constexpr int kChains = WN == 2 ? CHAINS : 1, kPerFragment = kChains == 4 ? 2 : 1;
-    float sum[TM][kChains];
+    typedef RowOrder<WN, TM> Order;
+    static constexpr int kChains = Order::kByHalf ? 1 : 2;
+    f32x4 sum[Order::kSlots][kChains];
     __device__ __forceinline__ void clear() {
 #pragma unroll
-        for (int mi = 0; mi < TM; ++mi)
+        for (int mi = 0; mi < Order::kSlots; ++mi)
 #pragma unroll
-            for (int c = 0; c < kChains; ++c) sum[mi][c] = 0.0f;
+            for (int c = 0; c < kChains; ++c) sum[mi][c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    template <int QUARTER>
-    __device__ __forceinline__ void add(const bf16x8 (&a)[TM]) {
-#pragma unroll
-        for (int mi = 0; mi < TM; ++mi) add_fragment<kPerFragment>(a[mi], sum[mi] + (QUARTER == 2 ? kChains / 2 : 0));
-    }
-    struct Total {
-        float row[TM];
-    };
-    __device__ __forceinline__ Total total() const {
-        Total t;
-#pragma unroll
-        for (int mi = 0; mi < TM; ++mi) {
-            t.row[mi] = sum[mi][0];
-#pragma unroll
-            for (int c = 1; c < kChains; ++c) t.row[mi] += sum[mi][c];
-        }
-        return t;
+    template <int MI, int HALF>
+    __device__ __forceinline__ void add(bf16x8 a) {
+        const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+        if constexpr (MI < Order::kSlots && HALF < kChains) sum[MI][HALF] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, ones), sum[MI][HALF], 0, 0, 0);
     }
 };
 
 template <int CHAINS, int TM, int TN>
-__device__ __forceinline__ void clear_chains(f32x16 (&acc)[CHAINS][TM][TN]) {
+__device__ __forceinline__ void clear_chains(Sums<CHAINS, TM, TN> &acc) {
 #pragma unroll
     for (int c = 0; c < CHAINS; ++c)
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[c][mi][ni][v] = 0.0f;
+            for (int ni = 0; ni < TN; ++ni) acc[c][mi][ni] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 }
 // The chains' sums, added in order, in the first one.
 template <int CHAINS, int TM, int TN>
-__device__ __forceinline__ void join_chains(f32x16 (&acc)[CHAINS][TM][TN]) {
+__device__ __forceinline__ void join_chains(Sums<CHAINS, TM, TN> &acc) {
 #pragma unroll
     for (int c = 1; c < CHAINS; ++c)
 #pragma unroll
@@ -178,71 +178,123 @@ __device__ __forceinline__ void join_chains(f32x16 (&acc)[CHAINS][TM][TN]) {
 #pragma unroll
             for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[0][mi][ni][v] += acc[c][mi][ni][v];
+                for (int v = 0; v < 4; ++v) acc[0][mi][ni][v] += acc[c][mi][ni][v];
 }
 
-// A wave's share of the row sums of A to LDS, [team * WN + column wave][BM]; without an offset they must not enter the result,
+// The fragments of a step of 64 k in the order they are multiplied: two halves of 32 k, of which each is dealt into parts of rows or columns, whichever the wave has
+// more of, while the other operand's fragments stay.  Those of a part are read while the part before is multiplied; the last part is
+// multiplied after the barrier of the next step, under that step's first reads.  A wave of 64 x 128 has 48 registers of them (operands of the FP8 kernel), with whole halves
+// it would be 64.
+template <int TM, int TN, typename FragA, typename FragB>
+struct StepFrags {
+    static constexpr bool kSplitN = TN >= 4 && TN > TM, kSplitM = !kSplitN && TM >= 4;
+    static constexpr int kParts = kSplitN || kSplitM ? 2 : 1, kPhases = 2 * kParts;     // of a step
+    static constexpr int kRows = kSplitM ? TM / 2 : TM, kCols = kSplitN ? TN / 2 : TN;  // tiles in a part
+    FragA a[2][kRows];
+    FragB b[2][kCols];
+    static constexpr int half(int phase) { return phase / kParts; }
+    static constexpr int part(int phase) { return phase % kParts; }
+    static constexpr int a_slot(int phase) { return kSplitM ? part(phase) : half(phase); }
+    static constexpr int b_slot(int phase) { return kSplitN ? part(phase) : half(phase); }
+    static constexpr int first_row(int phase) { return kSplitM ? part(phase) * kRows : 0; }
+    static constexpr int first_col(int phase) { return kSplitN ? part(phase) * kCols : 0; }
+    static constexpr bool reads_a(int phase) { return kSplitM || part(phase) == 0; }
+    static constexpr bool reads_b(int phase) { return kSplitN || part(phase) == 0; }
+    static constexpr int reads(int phase) { return (reads_a(phase) ? kRows : 0) + (reads_b(phase) ? kCols : 0); }
+};
+
+// A wave's share of the row sums of A to LDS, [team * kParts + part][BM]; without an offset they must not enter the result,
 // whatever they are.
-template <int WN, int BM, int TM, typename Total>
-__device__ __forceinline__ void publish_row_sums(float *rowsum, const Total &rsum, bool wanted, uint32_t team, uint32_t row0,
+template <int WN, int BM, int TM>
+__device__ __forceinline__ void publish_row_sums(float *rowsum, const RowSums<WN, TM> &rsum, bool wanted, uint32_t team, uint32_t row0,
                                                  uint32_t wn, uint32_t lane) {
+    typedef RowOrder<WN, TM> Order;
+    const Order order(wn);
 #pragma unroll
-    for (int mi = 0; mi < TM; ++mi) {
-        const float t = rsum.row[mi] + __shfl_xor(rsum.row[mi], 32);
-        if (lane < 32) rowsum[(team * WN + wn) * BM + row0 + 32 * mi + lane] = wanted ? t : 0.0f;
+    for (int mi = 0; mi < Order::kSlots; ++mi) {
+        f32x4 t = rsum.sum[mi][0];                            // every column of the products with ones holds the sums
+#pragma unroll
+        for (int c = 1; c < RowSums<WN, TM>::kChains; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t[v] += rsum.sum[mi][c][v];
+        if (!wanted) t = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if ((lane & 15u) == 0) *reinterpret_cast<f32x4 *>(rowsum + (team * Order::kParts + (Order::kByHalf ? wn & 1u : 0u)) * BM + row0 + order.row(mi) + 4 * (lane >> 4)) = t;
     }
 }
 
 // Team 0's waves add the other teams' tiles to theirs, in order; true for team 0.  `parts`: LDS for (TEAMS - 1) tiles.
 // The barrier also makes the row sums visible.
 template <int TEAMS, int NW, int TM, int TN>
-__device__ __forceinline__ bool add_teams(float *parts, f32x16 (&acc)[TM][TN], uint32_t team, uint32_t wave, uint32_t lane) {
-    constexpr uint32_t kWaveFloats = TM * TN * 16 * 64;
+__device__ __forceinline__ bool add_teams(float *parts, f32x4 (&acc)[TM][TN], uint32_t team, uint32_t wave, uint32_t lane) {
+    constexpr uint32_t kWaveQuads = TM * TN * 64;
+    f32x4 *quads = reinterpret_cast<f32x4 *>(parts);
     if (TEAMS > 1 && team > 0) {
-        float *to = parts + ((team - 1) * NW + wave) * kWaveFloats + lane;
+        f32x4 *to = quads + ((team - 1) * NW + wave) * kWaveQuads + lane;
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) to[((mi * TN + ni) * 16 + v) * 64] = acc[mi][ni][v];
+            for (int ni = 0; ni < TN; ++ni) to[(mi * TN + ni) * 64] = acc[mi][ni];
     }
     __syncthreads();
     if (TEAMS > 1 && team > 0) return false;
 #pragma unroll
     for (int t = 1; t < TEAMS; ++t) {
-        const float *from = parts + ((t - 1) * NW + wave) * kWaveFloats + lane;
+        const f32x4 *from = quads + ((t - 1) * NW + wave) * kWaveQuads + lane;
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-            for (int ni = 0; ni < TN; ++ni)
+            for (int ni = 0; ni < TN; ++ni) {
+                const f32x4 q = from[(mi * TN + ni) * 64];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[mi][ni][v] += from[((mi * TN + ni) * 16 + v) * 64];
+                for (int v = 0; v < 4; ++v) acc[mi][ni][v] += q[v];
+            }
     }
     return true;
 }
 
-// C tile = s * acc + b * row sums.  Several waves (PARTS) have each summed a part of the
-// contraction: `rowsum` in LDS, [PARTS][BM].  A lane's accumulators are one column of each 32-column block, so a store instruction of a wave writes two rows
-// of 128 contiguous bytes.  The result is
+// Value v of two tiles that lie side by side, exchanged between lanes so that an access takes two rows of 32 neighbouring values: `x` becomes row 8 (lane / 32) + v of
+// them, `y` the row four below, both column lane % 32.
+__device__ __forceinline__ void side_by_side(float &x, float &y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r[0]);
+    y = __uint_as_float(r[1]);
+}
+
+// C tile = s * acc + b * row sums.  PARTS waves have each summed a part of the
+// contraction: `rowsum` in LDS, [PARTS][BM].  A store instruction of a wave writes two rows of 128 contiguous bytes.  The result is
 // read by another kernel at the earliest: with ordinary stores it displaces the operands, 71.2 instead of 66.4 us and 84 instead
 // of 80 (8192 x 1024 x 4096 and 8192 x 4096 x 1024, new operands each time).
-template <int PARTS, int BM, int TM, int TN>
-__device__ __forceinline__ void store_tile(float *__restrict__ C, uint32_t ldc, const f32x16 (&acc)[TM][TN], const float *rowsum,
-                                           uint32_t row0, uint32_t lane, float s, float b) {
-    const uint32_t f_row = lane & 31u, f_half = lane >> 5;
+template <int PARTS, int BM, int TM, int TN, typename Order>
+__device__ __forceinline__ void store_tile(float *__restrict__ C, uint32_t ldc, const f32x4 (&acc)[TM][TN], const float *rowsum,
+                                           uint32_t row0, const Order &order, uint32_t lane, float s, float b) {
+    static_assert(TN % 2 == 0, "pairs of tiles");
+    const uint32_t col = lane & 31u, row8 = 8 * (lane >> 5);
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi) {
+        const uint32_t row = row0 + order.row(mi) + row8;
+        f32x4 add[2];                                         // rows row .. row + 3, row + 4 ..
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const uint32_t row = row0 + 32 * mi + 8 * (v >> 2) + 4 * f_half + (v & 3);
-            float sum = rowsum[row];
+        for (int r = 0; r < 2; ++r) {
+            add[r] = *reinterpret_cast<const f32x4 *>(rowsum + row + 4 * r);
 #pragma unroll
-            for (int q = 1; q < PARTS; ++q) sum += rowsum[q * BM + row];
-            const float add = b * sum;
-            float *to = C + static_cast<uint64_t>(row) * ldc + f_row;
+            for (int q = 1; q < PARTS; ++q) {
+                const f32x4 t = *reinterpret_cast<const f32x4 *>(rowsum + q * BM + row + 4 * r);
 #pragma unroll
-            for (int ni = 0; ni < TN; ++ni) __builtin_nontemporal_store(s * acc[mi][ni][v] + add, to + 32 * ni);
+                for (int v = 0; v < 4; ++v) add[r][v] += t[v];
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) add[r][v] = b * add[r][v];
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            float *to = C + static_cast<uint64_t>(row + v) * ldc + col;
+#pragma unroll
+            for (int ni = 0; ni < TN; ni += 2) {
+                float x = acc[mi][ni][v], y = acc[mi][ni + 1][v];
+                side_by_side(x, y);
+                __builtin_nontemporal_store(s * x + add[0][v], to + 16 * ni);
+                __builtin_nontemporal_store(s * y + add[1][v], to + 4 * static_cast<uint64_t>(ldc) + 16 * ni);
+            }
         }
     }
 }
