@@ -257,9 +257,12 @@ void dw_product_kernel(ProductArgs pa, DwArgs a) {
             const Partial *from = sums + (lane & (kWaves - 1));
             DD one{(&from->sV)[lane >> 4], 0.0};              // 16 lanes a sum: V, Vt, V Vt, Vt^2
             float tmin = from->tmin, tmax = from->tmax;
+            if constexpr (kWaves > 8) one = dd_add(one, dd_xor_in_row<8>(one));
+            if constexpr (kWaves > 4) one = dd_add(one, dd_xor_in_row<4>(one));
+            if constexpr (kWaves > 2) one = dd_add(one, dd_xor_in_row<2>(one));
+            if constexpr (kWaves > 1) one = dd_add(one, dd_xor_in_row<1>(one));
 #pragma unroll
             for (int off = kWaves / 2; off >= 1; off >>= 1) {
-                one = dd_add(one, dd_shfl_xor(one, off));
                 tmin = fminf(tmin, __shfl_xor(tmin, off));
                 tmax = fmaxf(tmax, __shfl_xor(tmax, off));
             }

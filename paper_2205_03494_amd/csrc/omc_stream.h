@@ -408,6 +408,44 @@ __device__ __forceinline__ float apply_update(float w, float g, float &m, float 
     }
 }
 
+// ---- sums over a wave -----------------------------------------------------------------------------
+// The exchanges of a butterfly over the 64 lanes as moves between registers (the general shuffle passes through LDS).
+// dealt_out<32>(a, b): lanes 0 - 31 get a(lane) + a(lane ^ 32), lanes 32 - 63 the same of b: two sums for one addition.  <16>: likewise over rows of 16 lanes, the even rows a's.
+__device__ __forceinline__ double double_of(uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32 | lo); }
+template <int OFF>
+__device__ __forceinline__ void swap_halves(double &a, double &b) {
+    static_assert(OFF == 32 || OFF == 16, "halves of a wave, or of its two halves");
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const uint32_t x0 = static_cast<uint32_t>(x), x1 = static_cast<uint32_t>(x >> 32), y0 = static_cast<uint32_t>(y), y1 = static_cast<uint32_t>(y >> 32);
+    if constexpr (OFF == 32) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(x0, y0, false, false), hi = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
+        a = double_of(lo[0], hi[0]);
+        b = double_of(lo[1], hi[1]);
+    } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap(x0, y0, false, false), hi = __builtin_amdgcn_permlane16_swap(x1, y1, false, false);
+        a = double_of(lo[0], hi[0]);
+        b = double_of(lo[1], hi[1]);
+    }
+}
+template <int OFF>
+__device__ __forceinline__ uint32_t xor_in_row(uint32_t v) {
+    static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8, "within 16 lanes");
+    const int x = static_cast<int>(v);
+    if constexpr (OFF == 1) return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xf, 0xf, true);        // quad_perm 1 0 3 2
+    else if constexpr (OFF == 2) return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xf, 0xf, true);   // quad_perm 2 3 0 1
+    else if constexpr (OFF == 4) return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x141, 0xf, 0xf, true), 0x1B, 0xf, 0xf, true);   // row_half_mirror, quad_perm 3 2 1 0
+    else return __builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, true);                           // row_ror 8
+}
+template <int OFF>
+__device__ __forceinline__ double xor_in_row(double v) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    return double_of(xor_in_row<OFF>(static_cast<uint32_t>(x)), xor_in_row<OFF>(static_cast<uint32_t>(x >> 32)));
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {   // of the same lane in all lanes
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    return double_of(__builtin_amdgcn_readlane(static_cast<int>(x), lane), __builtin_amdgcn_readlane(static_cast<int>(x >> 32), lane));
+}
+
 // ---- fit accumulators -----------------------------------------------------------------------------
 // Unevaluated sum hi + lo of two doubles, and the additions that keep one (Knuth's two-sum for the
 // error of an addition; used by the wide-mantissa kernels and by the finalize).
@@ -425,12 +463,19 @@ __device__ __forceinline__ DD dd_add(DD a, double x) {
     return r;
 }
 __device__ __forceinline__ DD dd_add(DD a, DD b) { return dd_add(dd_add(a, b.hi), b.lo); }
-__device__ __forceinline__ DD dd_shfl_xor(DD a, int off) {
-    DD r;
-    r.hi = __shfl_xor(a.hi, off);
-    r.lo = __shfl_xor(a.lo, off);
-    return r;
+template <int OFF>
+__device__ __forceinline__ DD dealt_out(DD a, DD b) {
+    swap_halves<OFF>(a.hi, b.hi);
+    swap_halves<OFF>(a.lo, b.lo);
+    return dd_add(a, b);
 }
+template <int OFF>
+__device__ __forceinline__ double dealt_out(double a, double b) {
+    swap_halves<OFF>(a, b);
+    return a + b;
+}
+template <int OFF>
+__device__ __forceinline__ DD dd_xor_in_row(DD a) { return DD{xor_in_row<OFF>(a.hi), xor_in_row<OFF>(a.lo)}; }
 // s += x with the rounding error of the addition added to l
 __device__ __forceinline__ void sum_with_error(double &s, double &l, double x) {
     const double t = s + x;
@@ -495,41 +540,41 @@ struct FitAcc {
         tmin = equal ? __uint_as_float(t0) : -inf;
         tmax = equal ? __uint_as_float(t0) : inf;
     }
-    // butterfly over the 64 lanes; every lane ends with the same totals, in an order that does
-    // not depend on scheduling; lane 0 stores them
+    // Butterfly over the 64 lanes in an order that does not depend on scheduling, the four sums dealt out on the way: the lanes of row r (16 of them) end with sum r.
     template <bool EXACT = false>
     __device__ __forceinline__ void reduce_and_store(Partial *out) {
         float tmin, tmax;
         lane_range(tmin, tmax);
+        double sum, error = 0.0;
         if constexpr (EXACT) {
-            DD dV{sV, lV}, dT{sT, lT}, dVT{sVT, lVT}, dTT{sTT, lTT};
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                dV = dd_add(dV, dd_shfl_xor(dV, off));
-                dT = dd_add(dT, dd_shfl_xor(dT, off));
-                dVT = dd_add(dVT, dd_shfl_xor(dVT, off));
-                dTT = dd_add(dTT, dd_shfl_xor(dTT, off));
-                tmin = fminf(tmin, __shfl_xor(tmin, off));
-                tmax = fmaxf(tmax, __shfl_xor(tmax, off));
-            }
-            sV = dV.hi; lV = dV.lo; sT = dT.hi; lT = dT.lo; sVT = dVT.hi; lVT = dVT.lo; sTT = dTT.hi; lTT = dTT.lo;
+            DD x = dealt_out<32>(DD{sV, lV}, DD{sVT, lVT}), y = dealt_out<32>(DD{sT, lT}, DD{sTT, lTT});
+            x = dealt_out<16>(x, y);
+            x = dd_add(x, dd_xor_in_row<8>(x));
+            x = dd_add(x, dd_xor_in_row<4>(x));
+            x = dd_add(x, dd_xor_in_row<2>(x));
+            x = dd_add(x, dd_xor_in_row<1>(x));
+            sum = x.hi;
+            error = x.lo;
         } else {
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                sV += __shfl_xor(sV, off);
-                sT += __shfl_xor(sT, off);
-                sVT += __shfl_xor(sVT, off);
-                sTT += __shfl_xor(sTT, off);
-                tmin = fminf(tmin, __shfl_xor(tmin, off));
-                tmax = fmaxf(tmax, __shfl_xor(tmax, off));
-            }
+            sum = dealt_out<16>(dealt_out<32>(sV, sVT), dealt_out<32>(sT, sTT));
+            sum += xor_in_row<8>(sum);
+            sum += xor_in_row<4>(sum);
+            sum += xor_in_row<2>(sum);
+            sum += xor_in_row<1>(sum);
         }
-        if ((threadIdx.x & 63u) == 0) {
-            Partial p;
-            p.sV = sV; p.sT = sT; p.sVT = sVT; p.sTT = sTT;
-            p.lV = EXACT ? lV : 0.0; p.lT = EXACT ? lT : 0.0; p.lVT = EXACT ? lVT : 0.0; p.lTT = EXACT ? lTT : 0.0;
-            p.tmin = tmin; p.tmax = tmax; p.pad[0] = p.pad[1] = 0;
-            *out = p;
+        // all of the wave's values are equal: every lane that has any has the same one throughout
+        const uint64_t with = __ballot(have);
+        const float first = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__float_as_int(tmin), with ? __builtin_ctzll(with) : 0));
+        const bool equal = __all(!have || (tmin == first && tmax == first));
+        const float inf = __builtin_huge_valf();
+        const uint32_t lane = threadIdx.x & 63u;
+        if ((lane & 15u) == 0) {
+            (&out->sV)[lane >> 4] = sum;
+            (&out->lV)[lane >> 4] = error;
+        }
+        if (lane == 0) {
+            out->tmin = with == 0 ? inf : equal ? first : -inf;
+            out->tmax = with == 0 ? -inf : equal ? first : inf;
         }
     }
 };
@@ -1048,13 +1093,10 @@ __device__ __forceinline__ void do_tail(const TileArgs &a, const FmtParams &fp, 
 // partials t, t + 64 NW, ...; lanes combine by a butterfly; waves combine by a butterfly.  Then the
 // closed form in fp64, stored as fp32.  `red` is LDS scratch of NW * 10 doubles.  `exact`: the partials
 // carry error words (formats of 16 or more mantissa bits), which are added as well.
-// What bounds it is the chain of dependent fp64 additions of one or a few waves.  The four sums are therefore dealt out
-// on the way: the first exchange of the butterfly leaves a lane with two of them, the second with one, so that six
-// exchanges cost 7 additions of pairs instead of 24.
-__device__ __forceinline__ DD keep_half(bool upper, DD lower_sum, DD upper_sum, int off) {
-    const DD mine = upper ? upper_sum : lower_sum, other = upper ? lower_sum : upper_sum;
-    return dd_add(mine, dd_shfl_xor(other, off));
-}
+// What bounds it is a chain of round trips and dependent fp64 additions.  So up to kOneWave partials are one wave's (the others leave at once): up to four in each lane cost
+// less than a pass of sums through LDS (sets of 13 bits, 8 blocks of 284 x 573, 47.8 us; 48.1 with 1024 for 256, 48.0 with 64; all as it was before 48.8; one variable of 9.4 M 30.4 -> 29.4).  The four sums are dealt out on the way through the butterfly: the first exchange leaves a
+// lane with two of them, the second with one, so that six exchanges cost 7 additions of pairs instead of 24, and they are moves between registers.
+constexpr uint32_t kOneWave = 256;
 template <int NW>
 __device__ __forceinline__ void finalize_variable(const Partial *__restrict__ parts, uint32_t nparts,
                                                   const Partial *__restrict__ tail, uint64_t n, bool use_pvt,
@@ -1069,15 +1111,17 @@ __device__ __forceinline__ void finalize_variable(const Partial *__restrict__ pa
     float tmin = __builtin_huge_valf(), tmax = -__builtin_huge_valf();
     bool finite = true;
     const uint32_t total = nparts + (tail ? 1u : 0u);
+    const uint32_t waves = NW > 1 && total > kOneWave ? NW : 1u, stride = 64u * waves;
+    if (NW > 1 && wave >= waves) return;
     // a lane's partials are fetched a few at a time before they are added (same order of additions; the
     // loads of a batch are in flight together instead of one memory round trip per partial)
-    constexpr uint32_t kBatch = NW > 8 ? 2 : 8, kStride = 64 * NW;   // (16 waves share the registers: eight would spill)
-    for (uint32_t i0 = tid; i0 < total; i0 += kBatch * kStride) {
+    constexpr uint32_t kBatch = NW > 8 ? 2 : 8;                // (16 waves share the registers: eight would spill)
+    for (uint32_t i0 = tid; i0 < total; i0 += kBatch * stride) {
         double p[kBatch][4], l[kBatch][4];
         float lo[kBatch], hi[kBatch];
 #pragma unroll
         for (uint32_t u = 0; u < kBatch; ++u) {
-            const uint32_t i = i0 + u * kStride;
+            const uint32_t i = i0 + u * stride;
             if (i >= total) break;
             const Partial *q = (i < nparts) ? parts + i : tail;
             p[u][0] = q->sV; p[u][1] = q->sT; p[u][2] = q->sVT; p[u][3] = q->sTT;
@@ -1086,7 +1130,7 @@ __device__ __forceinline__ void finalize_variable(const Partial *__restrict__ pa
         }
 #pragma unroll
         for (uint32_t u = 0; u < kBatch; ++u) {
-            if (i0 + u * kStride >= total) break;
+            if (i0 + u * stride >= total) break;
             finite = finite && isfinite(p[u][0]);
             if (finite) {
                 sV = dd_add(sV, p[u][0]);
@@ -1105,17 +1149,20 @@ __device__ __forceinline__ void finalize_variable(const Partial *__restrict__ pa
         }
     }
     // lanes 0-15 end with the wave's sum of V, 16-31 of Vt, 32-47 of V Vt, 48-63 of Vt^2
-    const DD two0 = keep_half((lane & 32u) != 0, sV, sVT, 32), two1 = keep_half((lane & 32u) != 0, sT, sTT, 32);
-    DD one = keep_half((lane & 16u) != 0, two0, two1, 16);
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) one = dd_add(one, dd_shfl_xor(one, off));
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        tmin = fminf(tmin, __shfl_xor(tmin, off));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, off));
-    }
+    DD one = dealt_out<16>(dealt_out<32>(sV, sVT), dealt_out<32>(sT, sTT));
+    one = dd_add(one, dd_xor_in_row<8>(one));
+    one = dd_add(one, dd_xor_in_row<4>(one));
+    one = dd_add(one, dd_xor_in_row<2>(one));
+    one = dd_add(one, dd_xor_in_row<1>(one));
+    // all values equal: the same one in all lanes that have any
+    const float inf = __builtin_huge_valf();
+    const uint64_t with = __ballot(tid < total);
+    const float first = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__float_as_int(tmin), 0));
+    const bool same = __all(tid >= total || (tmin == first && tmax == first));
+    tmin = with == 0 ? inf : same ? first : -inf;
+    tmax = with == 0 ? -inf : same ? first : inf;
     finite = __all(finite);
-    if (NW > 1) {
+    if (NW > 1 && waves > 1) {
         double *r = red + wave * 10;
         if ((lane & 15u) == 0) {
             r[lane >> 3] = one.hi;
@@ -1133,14 +1180,17 @@ __device__ __forceinline__ void finalize_variable(const Partial *__restrict__ pa
         tmin = static_cast<float>(from[8]);
         tmax = static_cast<float>(from[9]);
         finite = __all(from[9] == from[9]);
+        if constexpr (NW > 8) one = dd_add(one, dd_xor_in_row<8>(one));
+        if constexpr (NW > 4) one = dd_add(one, dd_xor_in_row<4>(one));
+        if constexpr (NW > 2) one = dd_add(one, dd_xor_in_row<2>(one));
+        if constexpr (NW > 1) one = dd_add(one, dd_xor_in_row<1>(one));
 #pragma unroll
         for (int off = NW / 2; off >= 1; off >>= 1) {
-            one = dd_add(one, dd_shfl_xor(one, off));
             tmin = fminf(tmin, __shfl_xor(tmin, off));
             tmax = fmaxf(tmax, __shfl_xor(tmax, off));
         }
     }
-    const double SV = __shfl(one.hi, 0), ST = __shfl(one.hi, 16), SVT = __shfl(one.hi, 32), STT = __shfl(one.hi, 48);
+    const double SV = lane_value(one.hi, 0), ST = lane_value(one.hi, 16), SVT = lane_value(one.hi, 32), STT = lane_value(one.hi, 48);
     if (tid != 0) return;
     if (!finite) {                                   // a non-finite input value poisons the fit
         sb_out[0] = __builtin_nanf("");
