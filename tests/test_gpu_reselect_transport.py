@@ -291,6 +291,39 @@ def test_transport_payload_of_many_sizes(count):
     assert np.array_equal(table_sb, np.where(mask[:, None], sb, np.array([1.0, 0.0], np.float32)))
 
 
+@pytest.mark.parametrize("count", [1, 3, 256, 257, 700])
+def test_transport_is_the_same_with_and_without_gaps(count):
+    """An arena without gaps is packed by one launch that takes the places from the plan, one with a gap by two: the same message, whatever
+    the arena's first offset, the bytes between the variables, and the sizes (fp32 ones that are no multiple of four among them)."""
+    rng = np.random.default_rng(count)
+    ns = [int(n) for n in rng.integers(1, 3000, count)]
+    ns[0] = 50003
+    mask = [bool(q) for q in rng.random(count) < 0.5]
+    sizes = [omc.omc_packed_bytes(omc.fmt(3, 7), n) if q else 4 * n for n, q in zip(ns, mask)]
+    payload = [rng.integers(0, 256, b, dtype=np.uint8) for b in sizes]
+    sb = rng.standard_normal((count, 2)).astype(np.float32)
+    messages = []
+    for first, gap_before in ((0, count), (32, count), (16, count // 2), (0, count - 1)):   # `count`: no gap
+        off, aux, table = first, 0, []
+        for i, (n, q, b) in enumerate(zip(ns, mask, sizes)):
+            off += 16 if i == gap_before and i > 0 else 0
+            table.append(dict(data_offset=off, aux_offset=aux, n=n, fmt=omc.fmt(3, 7), quantized=q))
+            off += (b + 15) // 16 * 16
+            aux += (n + 3) // 4 * 4
+        plan = omc.omc_plan_build(omc.make_var_table(table))
+        arena = rng.integers(0, 256, off, dtype=np.uint8)
+        for t, p in zip(table, payload):
+            arena[t["data_offset"]:t["data_offset"] + p.size] = p
+        msg = torch.full((omc.omc_transport_bytes(plan) + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        msg[: omc.omc_transport_meta_bytes(count)] = 0        # (the padding behind the table is nobody's)
+        omc.omc_transport_pack(plan, to_dev(arena), to_dev(sb), msg)
+        torch.cuda.synchronize()
+        messages.append(msg.cpu().numpy())
+    open_message(messages[0][:-64])
+    for m in messages[1:]:
+        assert np.array_equal(m, messages[0])
+
+
 @pytest.mark.parametrize("case", ["shared width", "one side each", "tails to codes", "tails to fp32", "tails against tiles"])
 def test_compressions_and_decompressions_in_one_launch(case):
     """Widths that only one direction has, that both have, sets without a full tile in one direction or the other: each variable is
