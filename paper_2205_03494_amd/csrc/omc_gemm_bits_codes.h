@@ -65,4 +65,53 @@ __device__ __forceinline__ uint32_t decode_pair(const Unit<B, U> &u, int i, cons
     return __builtin_amdgcn_perm(hi, lo, 0x07060302u);
 }
 
+// A unit on its way to LDS, as pairs of bfloat16.  HW: the hardware converts the format: S1E2M3 with bias 1 is the microscaling formats' 6-bit E2M3, of which one instruction converts 32 codes;
+// S1E5M2 with bias 15 is OCP FP8 E5M2 but for the top exponent (Inf and NaN there), whose codes are converted with the exponent below it and get the missing one afterwards, 11
+// instructions for four codes.  The bit-domain decode takes 18.
+template <int B, bool HW>
+constexpr bool converts_units() { return HW && B == 6; }
+inline bool hardware_converts(const FmtParams &fp) {
+    return (fp.exp_bits == 2 && fp.man_bits == 3 && fp.bias == 1) || (fp.exp_bits == 5 && fp.man_bits == 2 && fp.bias == 15);
+}
+template <int B, int U, bool HW>
+struct Pairs {
+    static constexpr int kWords = converts_units<B, HW>() ? U / 2 : Unit<B, U>::kDwords;
+    uint32_t w[kWords];                                       // pairs already, or the codes
+    __device__ __forceinline__ void take(const Unit<B, U> &from, uint32_t shift) {
+        if constexpr (converts_units<B, HW>()) {
+            typedef uint32_t x6 __attribute__((ext_vector_type(6)));
+            typedef __bf16 bf16x32 __attribute__((ext_vector_type(32)));
+            typedef uint32_t x16 __attribute__((ext_vector_type(16)));
+            x6 c = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int i = 0; i < Unit<B, U>::kDwords; ++i) c[i] = from.w[i];
+            const bf16x32 v = __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(c, 1.0f);
+            const x16 d = __builtin_bit_cast(x16, v);
+#pragma unroll
+            for (int i = 0; i < kWords; ++i) w[i] = d[i];
+        } else {
+            Unit<B, U> u = from;
+            align_unit<B, U>(u, shift);
+#pragma unroll
+            for (int i = 0; i < kWords; ++i) w[i] = u.w[i];
+        }
+    }
+    __device__ __forceinline__ uint32_t pair(int i, const FmtParams &fp) const {
+        if constexpr (converts_units<B, HW>()) {
+            return w[i];
+        } else if constexpr (HW && B == 8) {
+            const uint32_t codes = w[i / 2], top = ((codes & 0x7c7c7c7cu) + 0x04040404u) & 0x80808080u;   // bit 7 of the bytes with the top exponent
+            const uint32_t lower = codes - (top >> 5);
+            const uint32_t two = i % 2 ? __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8(lower, 1.0f, true))
+                                       : __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8(lower, 1.0f, false));
+            return two + __builtin_amdgcn_perm(0u, top, i % 2 ? 0x0c030c02u : 0x0c010c00u);               // one more in the exponent
+        } else {
+            Unit<B, U> u;
+#pragma unroll
+            for (int d = 0; d < kWords; ++d) u.w[d] = w[d];
+            return decode_pair<B, U>(u, i, fp);
+        }
+    }
+};
+
 }  // namespace omc

@@ -31,7 +31,7 @@ namespace omc {
 // WM x WN waves of TM x TN matrix tiles (16 x 16) each, TEAMS times: team t multiplies the steps t, t + TEAMS, ... of the
 // contraction in LDS stages of its own, and team 0 adds up the teams' tiles in order.  A team's sums are CHAINS chains (which of
 // them, the half of the step decides).  OCC waves per SIMD.
-template <int B, int U, int WM, int WN, int TM, int TN, int TEAMS, int CHAINS, int OCC, bool TRANS>
+template <int B, int U, int WM, int WN, int TM, int TN, int TEAMS, int CHAINS, int OCC, bool TRANS, bool HW>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * WM * WN * TEAMS, 64 * WM * WN * TEAMS))) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 void gemm_bits_kernel(BitsArgs ga) {
     constexpr int NW = WM * WN, NT = 64 * NW, BM = 16 * TM * WM, BN = 16 * TN * WN;
@@ -139,7 +139,8 @@ void gemm_bits_kernel(BitsArgs ga) {
 
     Sums<CHAINS, TM, TN> acc;
     RowSums<WN, TM> rsum;
-    Unit<B, U> now, next;
+    Unit<B, U> next;
+    Pairs<B, U, HW> now;
     // NEXT: the part whose fragments are read meanwhile, or kAll; PAIRS: of the unit's pairs of codes those from FIRST on are decoded meanwhile, and whole pieces stored in the other stage
     constexpr int kAll = 2 * kParts, kPairs = U / 2;
     u32x4 piece = {0, 0, 0, 0};
@@ -156,7 +157,7 @@ void gemm_bits_kernel(BitsArgs ga) {
             if constexpr (NEXT < kAll && NEXT % kParts == 0) read_w(w_at[NEXT / kParts], group);
             for_constants<D1 - D0>([&](auto i) {
                 constexpr int pair = D0 + decltype(i)::value;
-                piece[pair % 4] = decode_pair<B, U>(now, pair, fp);
+                piece[pair % 4] = now.pair(pair, fp);
                 if constexpr (pair % 4 == 3) store_piece(kStage - cur, pair / 4, piece);
             });
             __builtin_amdgcn_sched_barrier(0x6);              // the columns keep their order, but for vector and scalar arithmetic
@@ -177,13 +178,12 @@ void gemm_bits_kernel(BitsArgs ga) {
     }
     if (CHAINS > 1) clear();                                  // (while they are on their way)
     if (steps > 0) {
-        now = next;
+        now.take(next, u_shift);
         if (steps > 1) load_w(1, next);
-        align_unit<B, U>(now, u_shift);
 #pragma unroll
         for (int i = 0; i < static_cast<int>(kPieces); ++i) {
 #pragma unroll
-            for (int p = 0; p < 4; ++p) piece[p] = decode_pair<B, U>(now, 4 * i + p, fp);
+            for (int p = 0; p < 4; ++p) piece[p] = now.pair(4 * i + p, fp);
             store_piece(0, i, piece);
         }
     }
@@ -197,10 +197,9 @@ void gemm_bits_kernel(BitsArgs ga) {
         wait_loads_and_sync<0>();
 #pragma unroll
         for (int q = 0; q < Unit<B, U>::kDwords; ++q) pin(next.w[q]);   // they have arrived: their uses need no wait of their own
-        if constexpr (MORE) now = next;
+        if constexpr (MORE) now.take(next, u_shift);
         if constexpr (MORE) load_a(kStage - cur, i + 1);
         if (more2) load_w(i + 2, next);
-        if constexpr (MORE) align_unit<B, U>(now, u_shift);
         constexpr int kBegin = FIRST ? 0 : pairs_before(1);   // (the first step has no part before its own)
         if constexpr (FIRST) {
             for_constants<TN>([&](auto n) { read_w(w_at[0], n); });
@@ -281,30 +280,30 @@ inline uint32_t gemm_bits_sums(uint32_t M, uint32_t N, uint32_t K) {
     return which < 0 ? 0 : kBitsTiles[which].teams * chains_per_team(kBitsTiles[which], bits_chains(M, N, K));
 }
 
-template <int B, int WN, int U, int TM, int TN, int TEAMS, int CHAINS, int OCC, bool TRANS>
+template <int B, int WN, int U, int TM, int TN, int TEAMS, int CHAINS, int OCC, bool TRANS, bool HW>
 inline void launch_bits_one(const BitsArgs &ga, hipStream_t st) {
-    gemm_bits_kernel<B, U, 2, WN, TM, TN, TEAMS, CHAINS, OCC, TRANS><<<dim3(ga.tiles_m * ga.tiles_n), dim3(128 * WN * TEAMS), 0, st>>>(ga);
+    gemm_bits_kernel<B, U, 2, WN, TM, TN, TEAMS, CHAINS, OCC, TRANS, HW><<<dim3(ga.tiles_m * ga.tiles_n), dim3(128 * WN * TEAMS), 0, st>>>(ga);
 }
-template <int B, bool TRANS>
+template <int B, bool TRANS, bool HW>
 inline int launch_bits_tile(int which, uint32_t chains, const BitsArgs &ga, hipStream_t st) {
     switch (which) {
-        case 0: gemm_bits_large_kernel<B, TRANS><<<dim3(ga.tiles_m * ga.tiles_n), dim3(512), 0, st>>>(ga); break;
-        case 1: launch_bits_one<B, 2, 32, 8, 4, 1, 1, 1, TRANS>(ga, st); break;
-        case 2: launch_bits_one<B, 4, 32, 4, 4, 1, 1, 2, TRANS>(ga, st); break;
+        case 0: gemm_bits_large_kernel<B, TRANS, HW><<<dim3(ga.tiles_m * ga.tiles_n), dim3(512), 0, st>>>(ga); break;
+        case 1: launch_bits_one<B, 2, 32, 8, 4, 1, 1, 1, TRANS, HW>(ga, st); break;
+        case 2: launch_bits_one<B, 4, 32, 4, 4, 1, 1, 2, TRANS, HW>(ga, st); break;
         case 3:
-            if (chains == 2) launch_bits_one<B, 4, 16, 4, 2, 1, 2, 2, TRANS>(ga, st);
-            else launch_bits_one<B, 4, 16, 4, 2, 1, 1, 4, TRANS>(ga, st);
+            if (chains == 2) launch_bits_one<B, 4, 16, 4, 2, 1, 2, 2, TRANS, HW>(ga, st);
+            else launch_bits_one<B, 4, 16, 4, 2, 1, 1, 4, TRANS, HW>(ga, st);
             break;
-        case 4: launch_bits_one<B, 2, 16, 4, 2, 1, 1, 3, TRANS>(ga, st); break;
+        case 4: launch_bits_one<B, 2, 16, 4, 2, 1, 1, 3, TRANS, HW>(ga, st); break;
         case 5:
-            if (chains == 2) launch_bits_one<B, 2, 16, 2, 2, 1, 2, 4, TRANS>(ga, st);
-            else launch_bits_one<B, 2, 16, 2, 2, 1, 1, 4, TRANS>(ga, st);
+            if (chains == 2) launch_bits_one<B, 2, 16, 2, 2, 1, 2, 4, TRANS, HW>(ga, st);
+            else launch_bits_one<B, 2, 16, 2, 2, 1, 1, 4, TRANS, HW>(ga, st);
             break;
         case 6:
-            if (chains == 2) launch_bits_one<B, 2, 16, 2, 2, 2, 2, 4, TRANS>(ga, st);
-            else launch_bits_one<B, 2, 16, 2, 2, 2, 1, 4, TRANS>(ga, st);
+            if (chains == 2) launch_bits_one<B, 2, 16, 2, 2, 2, 2, 4, TRANS, HW>(ga, st);
+            else launch_bits_one<B, 2, 16, 2, 2, 2, 1, 4, TRANS, HW>(ga, st);
             break;
-        case 7: launch_bits_one<B, 2, 16, 2, 2, 4, 1, 4, TRANS>(ga, st); break;
+        case 7: launch_bits_one<B, 2, 16, 2, 2, 4, 1, 4, TRANS, HW>(ga, st); break;
         default: return static_cast<int>(hipErrorInvalidValue);
     }
     return static_cast<int>(hipGetLastError());
@@ -317,7 +316,10 @@ inline int launch_bits(const BitsArgs &args, uint32_t M, int trans, hipStream_t 
     ga.tiles_m = M / kBitsTiles[which].bm;
     ga.tiles_n = args.N / kBitsTiles[which].bn;
     const uint32_t chains = chains_per_team(kBitsTiles[which], bits_chains(M, args.N, args.K));
-    return trans ? launch_bits_tile<B, true>(which, chains, ga, st) : launch_bits_tile<B, false>(which, chains, ga, st);
+    if constexpr (B == 6 || B == 8) {
+        if (hardware_converts(ga.fp)) return trans ? launch_bits_tile<B, true, true>(which, chains, ga, st) : launch_bits_tile<B, false, true>(which, chains, ga, st);
+    }
+    return trans ? launch_bits_tile<B, true, false>(which, chains, ga, st) : launch_bits_tile<B, false, false>(which, chains, ga, st);
 }
 
 // one translation unit per range of widths

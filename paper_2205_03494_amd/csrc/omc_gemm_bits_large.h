@@ -13,7 +13,7 @@ namespace omc {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-template <int B, bool TRANS>
+template <int B, bool TRANS, bool HW>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512))) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_bits_large_kernel(BitsArgs ga) {
     constexpr int U = 32, WM = 2, WN = 4, TM = 4, TN = 2, NW = WM * WN, BM = 32 * TM * WM, BN = 32 * TN * WN;
@@ -60,10 +60,10 @@ void gemm_bits_large_kernel(BitsArgs ga) {
         u_at[i] = kABytes + (TRANS ? u_row * 128 + ((piece ^ ((u_row >> 1) & 7u)) << 4)
                                    : u_row * (2 * BN) + ((group ^ swizzle_f(u_row)) * 4 + ((piece & 3u) ^ ((group >> 1) & 3u))) * 16);
     }
-    auto store_piece = [&](uint32_t at, const Unit<B, U> &u, int i) {
+    auto store_piece = [&](uint32_t at, const Pairs<B, U, HW> &u, int i) {
         u32x4 piece;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) piece[p] = decode_pair<B, U>(u, 4 * i + p, fp);
+        for (int p = 0; p < 4; ++p) piece[p] = u.pair(4 * i + p, fp);
         *reinterpret_cast<u32x4 *>(lds + at + u_at[i]) = piece;
     };
 
@@ -138,7 +138,8 @@ void gemm_bits_large_kernel(BitsArgs ga) {
     // step i: A and W of the step are in stage `cur`; the dwords of step i + 1 are in `next` (asked for during step i - 1)
     Frags f0, f1;
     uint32_t cur = 0;
-    Unit<B, U> now, next;
+    Unit<B, U> next;
+    Pairs<B, U, HW> now;
 #pragma unroll
     for (int i = 0; i < Unit<B, U>::kDwords; ++i) next.w[i] = 0;
 #pragma unroll
@@ -151,7 +152,7 @@ void gemm_bits_large_kernel(BitsArgs ga) {
     }
     load_a(0, 0);
     load_w(0, next);
-    now = next;
+    now.take(next, 0);
     if (steps > 1) load_w(1, next);
 #pragma unroll
     for (int i = 0; i < static_cast<int>(kPieces); ++i) store_piece(0, now, i);
@@ -159,7 +160,7 @@ void gemm_bits_large_kernel(BitsArgs ga) {
         wait_loads_and_sync<0>();
 #pragma unroll
         for (int q = 0; q < Unit<B, U>::kDwords; ++q) pin(next.w[q]);   // they have arrived: their uses need no wait of their own
-        now = next;
+        now.take(next, 0);
         const uint32_t other = kStage - cur;
         read_frags(cur, a_at[0], w_at[0], f0);
         if (more1) load_a(other, i + 1);
