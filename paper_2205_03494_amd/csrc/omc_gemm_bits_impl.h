@@ -11,8 +11,8 @@
 // the eight rows that a transposing read takes at a time do, and by the group, so that the eight lanes of a store do.
 //
 // The order of the instructions is written down, a column of matrix tiles at a time, as in the FP8 kernel; vector and scalar arithmetic may move, and the decoding of a step's codes is spread evenly over its
-// columns.  11 bits, us, 32 x 32 x 16 instructions and the compiler's order -> this: 2048 x 2048 x 512 10.9 -> 10.2, 2304 x 3712 x 192 12.5 -> 11.3, 4096 x 1024 x 1056 17.2 -> 16.6, 512 x 512 x 512 5.73 -> 5.49.  The 256 x 256
-// tile alone is faster the old way and has a kernel of its own (omc_gemm_bits_large.h).
+// columns.  11 bits, us, 32 x 32 x 16 instructions and the compiler's order -> this: 2048 x 2048 x 512 10.9 -> 10.2, 2304 x 3712 x 192 12.5 -> 11.3, 4096 x 1024 x 1056 17.2 -> 16.6, 512 x 512 x 512 5.73 -> 5.49.  The tiles of 256
+// rows are faster the old way and have a kernel of their own (omc_gemm_bits_large.h).
 //
 // What bounds it: the decode, about five vector instructions per code, which hold up the matrix cores by some 3 clocks each (64 x 128 x 32 by 32 matrix instructions, 64 vector instructions beside
 // them: 512 -> 703 clocks).  Measured on 11-bit codes against the first kernels (256 x 128 or 128 x 128 tile,
@@ -48,7 +48,7 @@ void gemm_bits_kernel(BitsArgs ga) {
     const uint32_t N = ga.N, K = ga.K;
     const FmtParams fp = ga.fp;
     uint32_t m0, n0;
-    tile_of_block(BM == 256 ? 4 : 8, ga.tiles_m, ga.tiles_n, m0, n0);
+    tile_of_block(8, ga.tiles_m, ga.tiles_n, m0, n0);
     m0 *= BM;
     n0 *= BN;
 
@@ -95,10 +95,10 @@ void gemm_bits_kernel(BitsArgs ga) {
         const uint32_t row = 16 * TM * wm + f_row;            // (of the wave's first row tile, which need not be the one it multiplies first)
         return row * 128 + (((4 * half + f_k) ^ ((row >> 1) & 7u)) << 4);
     };
-    // A step's products in parts, kParts to a half: two row tiles (or one of two), column by column of the tiles.  A's fragments of a part are read
+    // A step's products in parts, two to a half: its first and its last TM / 2 row tiles, column by column of the tiles.  A's fragments of a part are read
     // beside the products of the part before, those of the first part behind the step's barrier, and W's of a half each as soon as its predecessor has been multiplied
     // for the last time.
-    constexpr int kRows = TM >= 4 ? 2 : 1, kParts = TM / kRows;
+    constexpr int kRows = TM / 2, kParts = 2;
     static_assert(Order::kSlots % kRows == 0, "the rows of a part follow each other");
     uint32_t a_part[kParts];                                    // where the parts' rows begin
 #pragma unroll
@@ -287,8 +287,8 @@ inline void launch_bits_one(const BitsArgs &ga, hipStream_t st) {
 template <int B, bool TRANS, bool HW>
 inline int launch_bits_tile(int which, uint32_t chains, const BitsArgs &ga, hipStream_t st) {
     switch (which) {
-        case 0: gemm_bits_large_kernel<B, TRANS, HW><<<dim3(ga.tiles_m * ga.tiles_n), dim3(512), 0, st>>>(ga); break;
-        case 1: launch_bits_one<B, 2, 32, 8, 4, 1, 1, 1, TRANS, HW>(ga, st); break;
+        case 0: gemm_bits_large_kernel<B, 4, TRANS, HW><<<dim3(ga.tiles_m * ga.tiles_n), dim3(512), 0, st>>>(ga); break;
+        case 1: gemm_bits_large_kernel<B, 2, TRANS, HW><<<dim3(ga.tiles_m * ga.tiles_n), dim3(256), 0, st>>>(ga); break;
         case 2: launch_bits_one<B, 4, 32, 4, 4, 1, 1, 2, TRANS, HW>(ga, st); break;
         case 3:
             if (chains == 2) launch_bits_one<B, 4, 16, 4, 2, 1, 2, 2, TRANS, HW>(ga, st);

@@ -1,9 +1,9 @@
-// The 256 x 256 tile of the products on codes of any width, by eight waves of 4 x 2 matrix tiles of 32 x 32.
+// The tiles of 256 rows of the products on codes of any width: WN column waves, two row waves, each of 4 x 2 matrix tiles of 32 x 32: 256 x 256 by eight waves, 256 x 128 by four.
 //
 // Built like gemm_bits_kernel, but on matrix instructions of 32 x 32 x 16.  A wave decodes 32 codes a step beside its products, 3 vector instructions in every 16 clocks, and with the
-// smaller matrix instructions there is then an instruction to issue in every slot: 11 bits, 8192 x 4096 x 1024 / 8192 x 4096 x 4096 80 / 243 us this way, 86 / 258 with 16 x 16 x 32 (other orders of
-// the fragments, two or four row tiles at a time, decoding in place or a step ahead: 85 - 88 / 256 - 270), though those take less power.  No part of a step stands out there either: without the decoding
-// 80 / 231, without the loads of A 81 / 229, without reading its fragments 81 / 238.
+// smaller matrix instructions there is then an instruction to issue in every slot.  256 x 256, 11 bits, 8192 x 4096 x 1024 / 8192 x 4096 x 4096: 80 / 243 us this way, 86 / 258 with 16 x 16 x 32 (other orders of
+// the fragments, two or four row tiles at a time, decoding in place or a step ahead: 85 - 88 / 256 - 270), though those take less power; no part of a step stands out there either: without the decoding
+// 80 / 231, without the loads of A 81 / 229, without reading its fragments 81 / 238.  256 x 128, 13 bits, 5632 x 1280 x 2560 50.3 / 53.2 us, 2816 x 2432 x 3136 58.8 / 60.7, 7936 x 1024 x 1472 34.0 / 33.0.
 #pragma once
 #include "omc_gemm_bits_codes.h"
 
@@ -13,10 +13,10 @@ namespace omc {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-template <int B, bool TRANS, bool HW>
-__global__ __attribute__((amdgpu_flat_work_group_size(512, 512))) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int B, int WN, bool TRANS, bool HW>
+__global__ __attribute__((amdgpu_flat_work_group_size(128 * WN, 128 * WN))) __attribute__((amdgpu_waves_per_eu(WN / 2, WN / 2)))
 void gemm_bits_large_kernel(BitsArgs ga) {
-    constexpr int U = 32, WM = 2, WN = 4, TM = 4, TN = 2, NW = WM * WN, BM = 32 * TM * WM, BN = 32 * TN * WN;
+    constexpr int U = 32, WM = 2, TM = 4, TN = 2, NW = WM * WN, BM = 32 * TM * WM, BN = 32 * TN * WN;
     constexpr int kALoads = BM / 8 / NW, kGroups = BN / 32, kRowUnits = BN / U;
     constexpr uint32_t kABytes = BM * 128, kStage = kABytes + BN * 128;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * kStage];
@@ -114,7 +114,7 @@ void gemm_bits_large_kernel(BitsArgs ga) {
     };
 
     f32x16 acc[TM][TN];
-    float rsum[TM];                                             // its share of the row sums of A: of the quarter of a step that it multiplies first
+    float rsum[TM];                                             // its share of the row sums of A: of the quarter of a step that it multiplies first, with two column waves also the third
     auto add_row_sums = [&](const Frags &f) {
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi) {
@@ -176,6 +176,7 @@ void gemm_bits_large_kernel(BitsArgs ga) {
         read_frags(cur, a_at[3], w_at[3], f1);
         if (more1) store_piece(other, now, 2);
         multiply(f0);
+        if (WN == 2) add_row_sums(f0);
         if (more1) store_piece(other, now, 3);
         cur = other;
     };
@@ -191,7 +192,7 @@ void gemm_bits_large_kernel(BitsArgs ga) {
         auto quarter = [&](auto ks) {
             read_frags(cur, a_place(ks.value), w_place(ks.value), f0);
             multiply(f0);
-            if (ks.value == wn) add_row_sums(f0);
+            if (ks.value % WN == wn) add_row_sums(f0);
         };
         quarter(UintTag<0>{});
         quarter(UintTag<1>{});

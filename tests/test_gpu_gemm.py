@@ -57,6 +57,30 @@ def test_small_shapes_all_rows(EM, shape):
     check(C, orc.dequant_gemm(A, packed, of, None, M, N, K, threads=8), (0, M))
 
 
+@pytest.mark.parametrize("EM", [(2, 3), (5, 2), (2, 3, 2), (5, 2, 14), (3, 4)])
+@pytest.mark.parametrize("shape", [(256, 128, 64), (512, 256, 96), (2048, 2048, 512), (7936, 1024, 1536), (8192, 4096, 1024)])
+def test_every_code_is_converted_exactly(EM, shape):
+    """Formats that the hardware converts (S1E2M3 with bias 1, S1E5M2 with bias 15, whose top exponent the hardware reads as Inf and NaN) beside others of the same width:
+    with one-hot rows of A the product is the weights' values, every code among them, in both directions and in tiles of 64, 128 and 256 rows."""
+    of, gf = pair(*EM)
+    M, N, K = shape
+    bits = 1 + EM[0] + EM[1]
+    rng = np.random.default_rng(bits)
+    codes = np.concatenate([np.arange(1 << bits), rng.integers(0, 1 << bits, K * N - (1 << bits))]).astype(np.uint32)
+    packed = to_dev(orc.pack(codes, bits))
+    W = to_dev(orc.decode(codes, of)).reshape(K, N)
+    ws = torch.empty(omc.omc_dequant_gemm_workspace_bytes(M), dtype=torch.uint8, device="cuda")
+    rows = torch.arange(M, device="cuda")
+    for width, product in ((K, omc.omc_dequant_gemm), (N, omc.omc_dequant_gemm_dx)):
+        if width == N and K % 128 != 0:
+            continue                                          # refused in this direction
+        A = torch.zeros(M, width, dtype=torch.bfloat16, device="cuda")
+        A[rows, rows % width] = 1.0
+        C = torch.full((M, N + K - width), float("nan"), device="cuda")
+        product(A, packed, gf, None, C, M, N, K, ws)
+        assert torch.equal(C, (W if width == K else W.t())[rows % width])
+
+
 def test_identity_pattern_pins_the_tile_layout():
     # A = one-hot rows, W = distinct representable values: C must reproduce W's rows exactly
     of, gf = pair(4, 3)
