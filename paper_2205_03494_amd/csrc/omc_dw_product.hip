@@ -279,7 +279,7 @@ void dw_product_kernel(ProductArgs pa, DwArgs a) {
     }
 }
 
-// Tiles: their figures are for steps of 32 rows (of TEAMS times as many with several teams), see GemmTile
+// Tiles (fitted with matrix instructions of 32 x 32 x 16): their figures are for steps of 32 rows (of TEAMS times as many with several teams), see GemmTile
 // (`fresh` is not counted here).
 static constexpr GemmTile kProductTiles[] = {
     {256, 128, 2, 1, 1, 6.2, 0.64, 0.88, 0.0, 0.0}, {128, 128, 1, 1, 2, 3.5, 0.30, 0.28, 0.0, 0.0}, {128, 128, 2, 1, 1, 4.7, 0.355, 0.57, 0.0, 0.0},

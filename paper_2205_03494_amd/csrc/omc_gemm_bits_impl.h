@@ -254,6 +254,7 @@ void gemm_bits_kernel(BitsArgs ga) {
 // workgroups on a unit, fills the chip with half the decoding of 64 x 64 (2304 x 3712 x 192 12.6 us, 14.5 with 128 x 128; 1536 x 2944 x 704 16.4, 18.4), which
 // wins on short contractions (8192 x 128 x 320, 11 bits: 5.5 us, 5.8 with 128 x 64).  8192 x 4096 x 1024: 82 us with 256 x 256, 107 with 128 x 128; 2048 x
 // 512 x 2048: 50 with 256 x 256, 27 with 128 x 128, 14 / 13 with 64 x 64 and 2 / 4 teams.
+// (These times and the fit were taken with matrix instructions of 32 x 32 x 16 and the bit-domain decode throughout; with the present ones the tiles of 64 and 128 rows are 2 - 10 % faster.)
 // Fitted to 1532 sizes in 6, 8, 11 and 13 bits.  On 1180 others the chosen tile takes 0.6 % longer than the best one on average, more than 7 % longer on 33 of
 // them, at worst 29 % (13056 x 256 x 3744, 11 bits, input gradient: 72 us with 128 x 128, 56 with 128 x 64); in 4 and 16 bits, which are not in the fit, 0.8 and 0.9 %, at
 // worst 15 and 27 % (120 sizes each); on 90 with K = 32 - 96, smaller than any in the fit, 1.4 %, at worst 9 %.

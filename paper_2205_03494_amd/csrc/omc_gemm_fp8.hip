@@ -10,7 +10,7 @@
 // 16-byte pieces are XOR-swizzled on their way in (the lane picks the piece, its LDS place is fixed): A pieces by half the row,
 // forward W pieces by the k row as far as a row has pieces, TRANS W pieces by a quarter of the column, so that the 16 pieces of A that one read takes at
 // a time, or the 16 k rows of one piece of W, lie on different ones of the 64 banks.  Forward no bank conflict is counted; TRANS reads half of a 16-byte piece at a time, and these reads conflict,
-// 4.2 million cycles over all compute units in a launch of 60 us at the shapes below.
+// 1.1 - 2.1 million cycles over all compute units in a launch of 60 us at the shapes below.
 //
 // The order of the instructions is written down, a column of matrix tiles at a time: its products, and beside them a share of the reads of the next part's fragments, the conversion of
 // the next column, and a share of the loads of a later stage.  Left to itself the compiler puts the reads right before their use, and the address arithmetic of the loads in one run of 100
@@ -356,6 +356,7 @@ void gemm_fp8_kernel(Fp8Args ga) {
 // (8192 x 1024 x 4096: 60 to 62 us).  The small tiles win where they spread a short product over more units, and several teams where
 // even those leave most of them idle (2048 x 512 x 2048: 25 us with 128 x 256, 19 with 128 x 128, 12 with 64 x 128, 11.6 / 9.2 / 10.5
 // with 64 x 64 and 1 / 2 / 4 teams).
+// (These times, the fit below and those of top codes above were taken with matrix instructions of 32 x 32 x 16; with the present ones every tile is 2 - 9 % faster.)
 // Fitted to 1308 sizes.  On 918 others the chosen tile takes 0.5 % longer than the best one on average, more than 7 % longer on 15 of them, at worst
 // 17 % (5888 x 384 x 992, input gradient: 13.2 us with 64 x 128, 11.3 with 128 x 128); on 90 with K = 32 - 96, smaller than any in the fit, 0.3 % and 9 %.
 static constexpr GemmTile kFp8Tiles[] = {
