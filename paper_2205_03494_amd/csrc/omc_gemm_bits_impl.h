@@ -138,13 +138,13 @@ void gemm_bits_kernel(BitsArgs ga) {
     };
 
     Sums<CHAINS, TM, TN> acc;
-    RowSums<WN, TM> rsum;
+    RowSums<WN, TM, true> rsum;
     Unit<B, U> next;
     Pairs<B, U, HW> now;
     // NEXT: the part whose fragments are read meanwhile, or kAll; PAIRS: of the unit's pairs of codes those from FIRST on are decoded meanwhile, and whole pieces stored in the other stage
     constexpr int kAll = 2 * kParts, kPairs = U / 2;
     u32x4 piece = {0, 0, 0, 0};
-    auto multiply = [&](auto part, auto next_part, auto first_pair, auto pairs) {
+    auto multiply = [&](auto part, auto odd, auto next_part, auto first_pair, auto pairs) {
         constexpr int P = decltype(part)::value, NEXT = decltype(next_part)::value, HALF = P / kParts, chain = HALF % CHAINS;
         constexpr int FIRST = decltype(first_pair)::value, PAIRS = decltype(pairs)::value, R = (P % kParts) * kRows;
         for_constants<TN>([&](auto group) {
@@ -153,7 +153,7 @@ void gemm_bits_kernel(BitsArgs ga) {
 #pragma unroll
             for (int mi = 0; mi < kRows; ++mi)
                 acc[chain][R + mi][G] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[P % 2][mi], fw[G], acc[chain][R + mi][G], 0, 0, 0);
-            for_constants<R1 - R0>([&](auto i) { rsum.template add<R + R0 + decltype(i)::value, HALF>(fa[P % 2][R0 + decltype(i)::value]); });
+            for_constants<R1 - R0>([&](auto i) { rsum.template add<R + R0 + decltype(i)::value, HALF, decltype(odd)::value>(fa[P % 2][R0 + decltype(i)::value]); });
             if constexpr (NEXT < kAll && NEXT % kParts == 0) read_w(w_at[NEXT / kParts], group);
             for_constants<D1 - D0>([&](auto i) {
                 constexpr int pair = D0 + decltype(i)::value;
@@ -192,7 +192,8 @@ void gemm_bits_kernel(BitsArgs ga) {
     const UintTag<kAll> nothing;
     // the step's decoding is spread evenly over its parts, of which the one before its own first comes first
     auto pairs_before = [](int place) { return place * kPairs / kAll; };
-    auto step = [&](uint32_t i, auto first, auto more1, bool more2) {
+    // `odd`: the step's number, or what passes for it at the ends
+    auto step = [&](uint32_t i, auto first, auto more1, bool more2, auto odd) {
         constexpr bool FIRST = decltype(first)::value, MORE = decltype(more1)::value;
         wait_loads_and_sync<0>();
 #pragma unroll
@@ -205,24 +206,28 @@ void gemm_bits_kernel(BitsArgs ga) {
             for_constants<TN>([&](auto n) { read_w(w_at[0], n); });
             for_constants<kRows>([&](auto n) { read_a(a_at[0], p0, n); });
         } else {
-            multiply(last, p0, p0, UintTag<MORE ? kBegin : 0>{});
+            multiply(last, BoolTag<!decltype(odd)::value>{}, p0, p0, UintTag<MORE ? kBegin : 0>{});
         }
         for_constants<kAll - 1>([&](auto part) {
             constexpr int P = decltype(part)::value, D0 = P == 0 ? kBegin : pairs_before(P + 1), D1 = pairs_before(P + 2);
-            multiply(part, UintTag<P + 1>{}, UintTag<D0>{}, UintTag<MORE ? D1 - D0 : 0>{});
+            multiply(part, odd, UintTag<P + 1>{}, UintTag<D0>{}, UintTag<MORE ? D1 - D0 : 0>{});
         });
         cur = kStage - cur;
     };
     const BoolTag<true> yes;
     const BoolTag<false> no;
     if (full > 0) {
-        if (steps > 1) step(0, yes, yes, steps > 2);
-        else step(0, yes, no, false);
+        if (steps > 1) step(0, yes, yes, steps > 2, no);
+        else step(0, yes, no, false, no);
         uint32_t i = 1;
-        for (; i + 2 < steps; ++i) step(i, no, yes, true);
-        if (i + 1 < steps && i < full) step(i++, no, yes, false);   // (of whole steps only the last has none behind it)
-        if (i < full) step(i, no, no, false);
-        multiply(last, nothing, p0, p0);
+        for (; i + 3 < steps; i += 2) {
+            step(i, no, yes, true, yes);
+            step(i + 1, no, yes, true, no);
+        }
+        if (i + 2 < steps) step(i++, no, yes, true, yes);
+        if (i + 1 < steps && i < full) step(i++, no, yes, false, no);   // (of whole steps only the last has none behind it)
+        if (i < full) step(i, no, no, false, yes);
+        multiply(last, no, nothing, p0, p0);
     }
     if (full < steps) {                                       // 32 k more, the same ones first in all waves
         wait_loads_and_sync<0>();
@@ -233,9 +238,9 @@ void gemm_bits_kernel(BitsArgs ga) {
         for_constants<kRows>([&](auto n) { read_a(a_at[0], p0, n); });
         for_constants<kParts - 1>([&](auto part) {
             constexpr int P = decltype(part)::value;
-            multiply(part, UintTag<P + 1>{}, p0, p0);
+            multiply(part, no, UintTag<P + 1>{}, p0, p0);
         });
-        multiply(UintTag<kParts - 1>{}, nothing, p0, p0);
+        multiply(UintTag<kParts - 1>{}, no, nothing, p0, p0);
         if (Order::kByHalf && (wn & 1u)) rsum = before;
     }
     for (uint32_t i = steps; i < (steps_k + TEAMS - 1) / TEAMS; ++i) wait_loads_and_sync<0>();   // teams wait for each other

@@ -129,7 +129,7 @@ template <int CHAINS, int TM, int TN>
 using Sums = f32x4[CHAINS][TM][TN];
 
 // How the row sums of A are dealt out over the WN column waves that multiply the same rows, and where the rows of a wave's tiles lie.  Each wave sums the rows of its first
-// tiles, over either half of the steps in a chain of its own; where it has few tiles (kByHalf), of four waves two share the rows and each takes the half that it multiplies first.  So that
+// tiles, over either half of the steps; where it has few tiles (kByHalf), of four waves two share the rows and each takes the half that it multiplies first.  So that
 // those are other rows in each wave, their order differs: tile mi lies at row 16 * (mi ^ flip).
 template <int WN, int TM>
 struct RowOrder {
@@ -141,21 +141,52 @@ struct RowOrder {
 };
 // A wave's share of them: products with ones.  One costs a 16 x 32 fragment 16 clocks of the matrix cores; the four two-element dot products of a lane that
 // do the same hold them up for 40, as they cannot run beside them (64 matrix instructions and 16 of the former a step of 256 x 256: 205000 clocks for 8192 x 4096 x 4096, 160000 without any).
-template <int WN, int TM>
+// Each half of a step has a chain of its own (of waves that share rows, each its half), and with that alone they are too long: 8192 x 8192 x 8192, A of one sign 11.4e-8 off 64 bits, mean zero 6.1e-8, where
+// dot products dealt out over lanes and waves were 4.3e-8 and 5.1e-8.  BY_PARITY: odd steps have chains of their own, which costs no instruction in a loop of two steps (4.4e-8 - 5.1e-8 and 5.1e-8 - 5.3e-8 over 8192).
+// Otherwise the chains end every kChainSteps steps, and a sum of 64 bits takes what they hold (2.2e-8 - 3.1e-8 and 2.8e-8 - 4.0e-8).  Which one is measured, by kernel: waves of 128 x 64 and 64 x 128 have no registers for the
+// former (they spill 20 - 50), and ending chains makes the compiler move the loads of the other codes' kernels (11 bits, 1536 x 1536 x 4096, input gradient: 48.1 us, 51.9 so, 47.4 by parity).
+constexpr uint32_t kChainSteps = 8;
+template <int WN, int TM, bool BY_PARITY>
 struct RowSums {
     typedef RowOrder<WN, TM> Order;
-    static constexpr int kChains = Order::kByHalf ? 1 : 2;
+    static constexpr int kHalves = Order::kByHalf ? 1 : 2, kChains = BY_PARITY ? 2 * kHalves : kHalves;
+    u32x4 ones;
     f32x4 sum[Order::kSlots][kChains];
+    double ended[Order::kSlots];                              // of row 4 (lane / 16) + lane % 4: every column of the products with ones holds the sums
     __device__ __forceinline__ void clear() {
+        ones = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+        asm volatile("" : "+v"(ones));                        // they stay in registers
+#pragma unroll
+        for (int mi = 0; mi < Order::kSlots; ++mi) {
+            ended[mi] = 0.0;
+#pragma unroll
+            for (int c = 0; c < kChains; ++c) sum[mi][c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+    }
+    __device__ __forceinline__ f32x4 joined(int mi) const {   // (BY_PARITY) of rows 4 (lane / 16) ..
+        f32x4 t;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            t[v] = sum[mi][0][v] + sum[mi][kHalves][v];
+            if constexpr (kHalves == 2) t[v] += sum[mi][1][v] + sum[mi][3][v];
+        }
+        return t;
+    }
+    __device__ __forceinline__ void end_chains(uint32_t lane) {
 #pragma unroll
         for (int mi = 0; mi < Order::kSlots; ++mi)
 #pragma unroll
-            for (int c = 0; c < kChains; ++c) sum[mi][c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int c = 0; c < kChains; ++c) {
+                const f32x4 x = sum[mi][c];
+                const float lower = (lane & 1u) ? x[1] : x[0], upper = (lane & 1u) ? x[3] : x[2];
+                ended[mi] += static_cast<double>((lane & 2u) ? upper : lower);
+                sum[mi][c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            }
     }
-    template <int MI, int HALF>
+    template <int MI, int HALF, bool ODD>
     __device__ __forceinline__ void add(bf16x8 a) {
-        const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
-        if constexpr (MI < Order::kSlots && HALF < kChains) sum[MI][HALF] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, ones), sum[MI][HALF], 0, 0, 0);
+        constexpr int chain = HALF + (BY_PARITY && ODD ? kHalves : 0);
+        if constexpr (MI < Order::kSlots && HALF < kHalves) sum[MI][chain] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, ones), sum[MI][chain], 0, 0, 0);
     }
 };
 
@@ -205,20 +236,24 @@ struct StepFrags {
 
 // A wave's share of the row sums of A to LDS, [team * kParts + part][BM]; without an offset they must not enter the result,
 // whatever they are.
-template <int WN, int BM, int TM>
-__device__ __forceinline__ void publish_row_sums(float *rowsum, const RowSums<WN, TM> &rsum, bool wanted, uint32_t team, uint32_t row0,
+template <int WN, int BM, int TM, bool BY_PARITY>
+__device__ __forceinline__ void publish_row_sums(float *rowsum, RowSums<WN, TM, BY_PARITY> &rsum, bool wanted, uint32_t team, uint32_t row0,
                                                  uint32_t wn, uint32_t lane) {
     typedef RowOrder<WN, TM> Order;
     const Order order(wn);
+    float *to = rowsum + (team * Order::kParts + (Order::kByHalf ? wn & 1u : 0u)) * BM + row0 + 4 * (lane >> 4);
+    if constexpr (BY_PARITY) {
 #pragma unroll
-    for (int mi = 0; mi < Order::kSlots; ++mi) {
-        f32x4 t = rsum.sum[mi][0];                            // every column of the products with ones holds the sums
+        for (int mi = 0; mi < Order::kSlots; ++mi) {
+            f32x4 t = rsum.joined(mi);
+            if (!wanted) t = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            if ((lane & 15u) == 0) *reinterpret_cast<f32x4 *>(to + order.row(mi)) = t;
+        }
+    } else {
+        rsum.end_chains(lane);
 #pragma unroll
-        for (int c = 1; c < RowSums<WN, TM>::kChains; ++c)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) t[v] += rsum.sum[mi][c][v];
-        if (!wanted) t = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if ((lane & 15u) == 0) *reinterpret_cast<f32x4 *>(rowsum + (team * Order::kParts + (Order::kByHalf ? wn & 1u : 0u)) * BM + row0 + order.row(mi) + 4 * (lane >> 4)) = t;
+        for (int mi = 0; mi < Order::kSlots; ++mi)
+            if ((lane & 15u) < 4) to[order.row(mi) + (lane & 3u)] = wanted ? static_cast<float>(rsum.ended[mi]) : 0.0f;
     }
 }
 

@@ -284,6 +284,33 @@ def test_small_products_against_64_bits(shape, bound):
         assert np.linalg.norm(got.astype(np.float64) - want) <= bound * np.linalg.norm(want)
 
 
+# A long contraction for the tiles that can be asked for one: (format, tile, chains) -> size
+LONG_CONTRACTIONS = {((4, 3), 0, 1): (3072, 3072, 8192), ((4, 3), 1, 1): (6144, 3072, 8192), ((4, 3), 2, 1): (1536, 3072, 8192), ((4, 3), 3, 1): (4096, 640, 8192),
+                     ((4, 3), 4, 1): (3072, 640, 8192), ((4, 3), 6, 4): (1024, 1024, 8192), ((4, 3), 7, 4): (256, 128, 8192), ((3, 7), 0, 1): (3072, 3072, 8192),
+                     ((3, 7), 1, 1): (1536, 3072, 8192), ((3, 7), 3, 1): (6144, 640, 8192), ((3, 7), 3, 2): (1536, 1536, 8192), ((3, 7), 4, 1): (8192, 768, 4096),
+                     ((3, 7), 6, 2): (1536, 768, 8192), ((3, 7), 7, 4): (256, 128, 8192)}
+
+
+@pytest.mark.parametrize("kernel", list(LONG_CONTRACTIONS))
+def test_row_sums_against_64_bits(kernel):
+    """Weights of zero and an offset of one: the product is the row sums of A, here of one sign, whose error grows with the length of a chain of fp32 sums.  In two chains
+    they are 11.5e-8 off over 8192 and 6.4e-8 over 4096; in the four and more that a row has, at most 5.2e-8 and 4.1e-8.  The bounds lie between the two."""
+    EM, tile, sums = kernel
+    M, N, K = LONG_CONTRACTIONS[kernel]
+    assert (gemm_tile(EM, M, N, K), gemm_sums(EM, M, N, K)) == (tile, sums)
+    gf = omc.fmt(*EM)
+    A = torch.from_numpy(synth.normal_f32(M * K, 1.0, 5)).cuda().abs().bfloat16().reshape(M, K)
+    want = A.double().sum(1)
+    codes = torch.zeros(omc.omc_packed_bytes(gf, K * N), dtype=torch.uint8, device="cuda")
+    sb = torch.ones(2, device="cuda")
+    ws = torch.empty(omc.omc_dequant_gemm_workspace_bytes(M), dtype=torch.uint8, device="cuda")
+    for product, sizes in ((omc.omc_dequant_gemm, (M, N, K)), (omc.omc_dequant_gemm_dx, (M, K, N))):
+        C = torch.full((M, N), float("nan"), device="cuda")
+        product(A, codes, gf, sb, C, *sizes, ws)
+        assert torch.equal(C, C[:, :1].expand(M, N))
+        assert (C[:, 0].double() - want).norm() <= (7e-8 if K == 8192 else 5.2e-8) * want.norm()
+
+
 @pytest.mark.parametrize("shape", [(4096, 2048, 160), (256, 256, 544)])
 def test_top_codes_in_some_tiles_only(shape):
     """A tile that meets the code that the FP8 conversion reads as NaN is computed again; its neighbours are not."""
