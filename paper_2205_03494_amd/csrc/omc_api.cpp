@@ -978,11 +978,15 @@ size_t omc_transport_meta_bytes(uint32_t nvars) {
     return static_cast<size_t>(align_up(sizeof(TransportHeader) + static_cast<uint64_t>(nvars) * sizeof(TransportVar), kTransportAlign));
 }
 
+// Returns whether the arena is laid out like the payload: in table order, without gaps but for the padding to 16 bytes.
 static bool transport_header_for(const PlanHeader *ph, TransportHeader *th) {
     const PlanVar *pv = plan_vars(ph);
     uint64_t payload = 0;
-    for (uint32_t i = 0; i < ph->nvars; ++i)
+    bool dense = ph->nvars > 0;
+    for (uint32_t i = 0; i < ph->nvars; ++i) {
+        dense = dense && pv[i].data_offset == pv[0].data_offset + payload;
         payload += align_up((pv[i].flags & OMC_VAR_QUANTIZED) ? pv[i].total_dwords * 4 : 4 * pv[i].n, 16);
+    }
     std::memset(th, 0, sizeof *th);
     th->magic = kTransportMagic;
     th->version = kTransportVersion;
@@ -993,7 +997,7 @@ static bool transport_header_for(const PlanHeader *ph, TransportHeader *th) {
     th->payload_bytes = payload;
     th->total_bytes = th->payload_off + payload;
     th->aux_elems = ph->aux_elems;
-    return true;
+    return dense;
 }
 
 uint64_t omc_transport_bytes(const void *plan_host) {
@@ -1011,13 +1015,13 @@ omc_status omc_transport_pack(const void *plan_host, const void *plan_dev, const
     if (!ph) return OMC_ERR_PLAN;
     if (arena_bytes < ph->arena_bytes) return OMC_ERR_SIZE;
     TransportHeader th;
-    transport_header_for(ph, &th);
+    const bool dense = transport_header_for(ph, &th);
     if (msg_bytes < th.total_bytes) return OMC_ERR_SIZE;
     if (!aligned16(plan_dev) || !aligned16(arena) || !aligned16(msg_dev) || (reinterpret_cast<uintptr_t>(sb_table) & 7u))
         return OMC_ERR_ALIGN;
     const uintptr_t a0 = reinterpret_cast<uintptr_t>(arena), m0 = reinterpret_cast<uintptr_t>(msg_dev);
     if (a0 < m0 + th.total_bytes && m0 < a0 + ph->arena_bytes) return OMC_ERR_SIZE;            // message overlaps the arena
-    const int rc = launch_transport_pack(ph, plan_dev, arena, sb_table, msg_dev, th, stream);
+    const int rc = launch_transport_pack(ph, plan_dev, arena, dense, sb_table, msg_dev, th, stream);
     return rc == 0 ? OMC_OK : OMC_ERR_DEVICE;
 }
 

@@ -248,7 +248,7 @@ struct PlanPair {
 };
 int launch_reselect(const void *arena_old, const float *sb_old, void *arena_new, float *sb_new, const PlanPair &to_codes,
                     const PlanPair &to_fp32, const uint32_t *actions_dev, uint32_t nvars, Partial *ws, void *stream);
-int launch_transport_pack(const PlanHeader *ph, const void *plan_dev, const void *arena, const float *sb_table,
+int launch_transport_pack(const PlanHeader *ph, const void *plan_dev, const void *arena, bool dense, const float *sb_table,
                           void *msg_dev, const TransportHeader &th, void *stream);
 int gemm_fp8_tile(uint32_t M, uint32_t N, uint32_t K);
 uint32_t gemm_fp8_sums(uint32_t M, uint32_t N, uint32_t K);

@@ -173,20 +173,13 @@ __global__ __launch_bounds__(kPackThreads) void transport_pack_kernel(const uint
     }
 }
 
-int launch_transport_pack(const PlanHeader *ph, const void *plan_dev, const void *arena, const float *sb_table,
+int launch_transport_pack(const PlanHeader *ph, const void *plan_dev, const void *arena, bool dense, const float *sb_table,
                           void *msg_dev, const TransportHeader &th, void *stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint8_t *plan = static_cast<const uint8_t *>(plan_dev), *from = static_cast<const uint8_t *>(arena);
     uint8_t *msg = static_cast<uint8_t *>(msg_dev);
     const uint64_t run = pack_run(th.payload_bytes), runs = (th.payload_bytes + run - 1) / run;
     if (runs > 0x7ffffffeull) return static_cast<int>(hipErrorInvalidValue);
-    const PlanVar *vars = reinterpret_cast<const PlanVar *>(reinterpret_cast<const uint8_t *>(ph) + ph->var_off);
-    bool dense = ph->nvars > 0;
-    uint64_t next = dense ? vars[0].data_offset : 0;
-    for (uint32_t i = 0; i < ph->nvars && dense; ++i) {
-        dense = vars[i].data_offset == next;
-        next += (vars[i].flags & OMC_VAR_QUANTIZED) ? vars[i].total_dwords * 4 : (4 * vars[i].n + 15) / 16 * 16;
-    }
     if (dense) {
         transport_pack_kernel<true><<<dim3(static_cast<uint32_t>(runs) + 1), dim3(kPackThreads), 0, st>>>(plan, ph->var_off, from, sb_table, msg, th, run);
         return static_cast<int>(hipGetLastError());

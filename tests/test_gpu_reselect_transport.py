@@ -291,7 +291,7 @@ def test_transport_payload_of_many_sizes(count):
     assert np.array_equal(table_sb, np.where(mask[:, None], sb, np.array([1.0, 0.0], np.float32)))
 
 
-@pytest.mark.parametrize("count", [1, 3, 256, 257, 700])
+@pytest.mark.parametrize("count", [1, 3, 256, 257, 700, 1100, 3000])
 def test_transport_is_the_same_with_and_without_gaps(count):
     """An arena without gaps is packed by one launch that takes the places from the plan, one with a gap by two: the same message, whatever
     the arena's first offset, the bytes between the variables, and the sizes (fp32 ones that are no multiple of four among them)."""
