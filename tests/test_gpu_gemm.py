@@ -57,28 +57,41 @@ def test_small_shapes_all_rows(EM, shape):
     check(C, orc.dequant_gemm(A, packed, of, None, M, N, K, threads=8), (0, M))
 
 
+# One size for every kernel of the products, by tile and chains of sums (a test without a GPU holds that); nearly all contractions end on half a step.
+FP8_KERNELS = {(0, 1): (3584, 3584, 2976), (1, 1): (2560, 3328, 224), (2, 1): (5632, 768, 416), (3, 1): (1792, 1792, 224), (4, 1): (9472, 128, 288),
+               (4, 2): (8448, 128, 288), (5, 1): (256, 2048, 32), (5, 2): (256, 2816, 224), (5, 4): (256, 128, 32), (6, 2): (6400, 128, 608),
+               (6, 4): (256, 128, 480), (7, 4): (256, 128, 4000)}
+BITS_KERNELS = {(0, 1): (3328, 3840, 224), (1, 1): (3328, 1920, 672), (2, 1): (1792, 3584, 544), (3, 1): (12544, 256, 160), (3, 2): (1280, 1664, 2592),
+                (4, 1): (1792, 2944, 96), (5, 1): (768, 2176, 32), (5, 2): (256, 128, 32), (6, 2): (256, 128, 96), (6, 4): (256, 128, 160),
+                (7, 4): (256, 128, 672)}
+
+
 @pytest.mark.parametrize("EM", [(2, 3), (5, 2), (2, 3, 2), (5, 2, 14), (3, 4)])
-@pytest.mark.parametrize("shape", [(256, 128, 64), (512, 256, 96), (2048, 2048, 512), (7936, 1024, 1536), (8192, 4096, 1024)])
+@pytest.mark.parametrize("shape", [(256, 128, 64), (512, 256, 96), (2048, 2048, 512), (7936, 1024, 1536), (8192, 4096, 1024)] + list(BITS_KERNELS.values()))
 def test_every_code_is_converted_exactly(EM, shape):
     """Formats that the hardware converts (S1E2M3 with bias 1, S1E5M2 with bias 15, whose top exponent the hardware reads as Inf and NaN) beside others of the same width:
-    with one-hot rows of A the product is the weights' values, every code among them, in both directions and in tiles of 64, 128 and 256 rows."""
+    with one-hot rows of A the product is the weights' values, every code among them, in both directions and in every tile."""
     of, gf = pair(*EM)
     M, N, K = shape
+    for tile, sums in [k for k in BITS_KERNELS if BITS_KERNELS[k] == shape]:
+        assert (gemm_tile(EM, M, N, K), gemm_sums(EM, M, N, K)) == (tile, sums)
     bits = 1 + EM[0] + EM[1]
     rng = np.random.default_rng(bits)
     codes = np.concatenate([np.arange(1 << bits), rng.integers(0, 1 << bits, K * N - (1 << bits))]).astype(np.uint32)
     packed = to_dev(orc.pack(codes, bits))
-    W = to_dev(orc.decode(codes, of)).reshape(K, N)
+    W = to_dev(orc.decode(codes, of))
     ws = torch.empty(omc.omc_dequant_gemm_workspace_bytes(M), dtype=torch.uint8, device="cuda")
     rows = torch.arange(M, device="cuda")
-    for width, product in ((K, omc.omc_dequant_gemm), (N, omc.omc_dequant_gemm_dx)):
-        if width == N and K % 128 != 0:
+    for product, m, n, k in ((omc.omc_dequant_gemm, M, N, K), (omc.omc_dequant_gemm_dx, M, N, K), (omc.omc_dequant_gemm_dx, M, K, N)):
+        transposed = product is omc.omc_dequant_gemm_dx
+        width, columns = (n, k) if transposed else (k, n)
+        if transposed and columns % 128 != 0:
             continue                                          # refused in this direction
-        A = torch.zeros(M, width, dtype=torch.bfloat16, device="cuda")
+        A = torch.zeros(m, width, dtype=torch.bfloat16, device="cuda")
         A[rows, rows % width] = 1.0
-        C = torch.full((M, N + K - width), float("nan"), device="cuda")
-        product(A, packed, gf, None, C, M, N, K, ws)
-        assert torch.equal(C, (W if width == K else W.t())[rows % width])
+        C = torch.full((m, columns), float("nan"), device="cuda")
+        product(A, packed, gf, None, C, m, n, k, ws)
+        assert torch.equal(C, (W.reshape(k, n).t() if transposed else W.reshape(k, n))[rows % width])
 
 
 def test_identity_pattern_pins_the_tile_layout():
@@ -252,15 +265,6 @@ def test_every_tile_size_ends_on_half_a_step(EM, shape):
     tile."""
     M, N, K = shape
     assert both_directions(EM, M, N, K, tile_sample_rows(M, seed=K, per_quarter=4)) < 1e-5
-
-
-# One size for every kernel of the products, by tile and chains of sums (a test without a GPU holds that); nearly all contractions end on half a step.
-FP8_KERNELS = {(0, 1): (3584, 3584, 2976), (1, 1): (2560, 3328, 224), (2, 1): (5632, 768, 416), (3, 1): (1792, 1792, 224), (4, 1): (9472, 128, 288),
-               (4, 2): (8448, 128, 288), (5, 1): (256, 2048, 32), (5, 2): (256, 2816, 224), (5, 4): (256, 128, 32), (6, 2): (6400, 128, 608),
-               (6, 4): (256, 128, 480), (7, 4): (256, 128, 4000)}
-BITS_KERNELS = {(0, 1): (3328, 3840, 224), (1, 1): (3328, 1920, 672), (2, 1): (1792, 3584, 544), (3, 1): (12544, 256, 160), (3, 2): (1280, 1664, 2592),
-                (4, 1): (1792, 2944, 96), (5, 1): (768, 2176, 32), (5, 2): (256, 128, 32), (6, 2): (256, 128, 96), (6, 4): (256, 128, 160),
-                (7, 4): (256, 128, 672)}
 
 
 @pytest.mark.parametrize("EM,kernel", [((4, 3), k) for k in FP8_KERNELS] + [(EM, k) for EM in ((2, 3), (5, 2), (3, 7), (4, 7), (5, 7)) for k in BITS_KERNELS])
