@@ -27,7 +27,7 @@
 // either way.  Looking more often costs up to 9 % where there is none, and so does looking in small tiles (up to 4 %).
 //
 // Measured (us, 8192 x 4096 x 1024 / 8192 x 1024 x 4096, fp32 output, new operands each time): 65 / 59 with matrix instructions of 32 x 32 x 16, row sums by dot products and the
-// compiler's order, 62 / 57 now.  What bounds it: power.  With two waves a SIMD and K = 4096 it ran at 1.77 GHz, the matrix cores busy in 80 % of the cycles (of two tiles a compute unit); now it is 1.88 GHz.  Instructions
+// compiler's order, 62 / 57 now.  What bounds it: power.  With two waves a SIMD and 8192 x 4096 x 4096 it ran at 1.77 GHz, the matrix cores busy in 80 % of the cycles (of two tiles a compute unit); now it is 1.88 GHz, and 1.83 / 1.80 GHz at the first shape (forward / input gradient), of 2.4.  Instructions
 // taken out of the loop make the clock fall again, by and large: without the reads of fragments it is 2.38 GHz, without the loads 2.23.  At a contraction of 1024 also the C stores: a workgroup's take 5 us, in which
 // the other one of the unit has the matrix cores to itself and uses them half as well as two.
 #include <algorithm>
@@ -385,7 +385,7 @@ static constexpr double kFp8Uneven = 0.5;
 // Chains of fp32 sums that a contraction is dealt into, by the result's 64 x 64 tiles and the steps: at least as many as when the choice fell
 // on four or two teams of waves for nearly every small product.  Those are slower than one team or two on most of them, but an error against 64 bits grows
 // with a chain's length: 512 x 512 x 512 3.4e-8 in four chains, 4.0e-8 in one, 512 x 512 x 4096 6.0e-8 in four, 7.2e-8 in two, 5120 x 256 x 1472 5.2e-8 in
-// two, 6.5e-8 in one.  So one team keeps the chains of four: 64 more registers and 48 additions at the end, 4.33 -> 4.45 us for 256 x 384 x 416
+// two, 6.5e-8 in one.  So one team keeps the chains of four: 64 more registers (two waves a SIMD are enough, as results that want four chains have at most one of these tiles a compute unit) and 48 additions at the end, 4.33 -> 4.45 us for 256 x 384 x 416
 // (5.29 with four teams), 9.27 -> 9.7 for 2048 x 512 x 2048 with two teams of two chains (9.8 - 10.0 with four).
 static uint32_t fp8_chains(uint32_t M, uint32_t N, uint32_t K) {
     const uint64_t small_tiles = static_cast<uint64_t>(M / 64) * (N / 64), steps = (static_cast<uint64_t>(K) + 63) / 64;

@@ -1089,8 +1089,8 @@ __device__ __forceinline__ void do_tail(const TileArgs &a, const FmtParams &fp, 
 // ---- finalize: per-variable (s, b) from the partials (paper Sec. 2.3) -----------------------------
 // Called by a whole workgroup of NW <= 16 waves (blockDim.x == 64 * NW).  Sums the variable's partials
 // (a run of `nparts` from the full-tile kernels and, if `tail` is not null, one more from the tail
-// kernel) with compensated additions in an order fixed by (nparts, NW) alone: thread t takes
-// partials t, t + 64 NW, ...; lanes combine by a butterfly; waves combine by a butterfly.  Then the
+// kernel) with compensated additions in an order fixed by (nparts, NW) alone: of W waves, one up to kOneWave
+// partials and NW above, thread t takes partials t, t + 64 W, ...; lanes combine by a butterfly; waves, if several, combine by a butterfly.  Then the
 // closed form in fp64, stored as fp32.  `red` is LDS scratch of NW * 10 doubles.  `exact`: the partials
 // carry error words (formats of 16 or more mantissa bits), which are added as well.
 // What bounds it is a chain of round trips and dependent fp64 additions.  So up to kOneWave partials are one wave's (the others leave at once): up to four in each lane cost
@@ -1154,7 +1154,8 @@ __device__ __forceinline__ void finalize_variable(const Partial *__restrict__ pa
     one = dd_add(one, dd_xor_in_row<4>(one));
     one = dd_add(one, dd_xor_in_row<2>(one));
     one = dd_add(one, dd_xor_in_row<1>(one));
-    // all values equal: the same one in all lanes that have any
+    // All values equal: the same one in all lanes that have any.  (A wave's first lane has a partial if any of its lanes has, and every partial covers at least one
+    // element: an empty one's range, from inf to -inf, would look unequal here.)
     const float inf = __builtin_huge_valf();
     const uint64_t with = __ballot(tid < total);
     const float first = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__float_as_int(tmin), 0));
