@@ -9,8 +9,7 @@
 //
 // 16-byte pieces are XOR-swizzled on their way in (the lane picks the piece, its LDS place is fixed): A pieces by half the row,
 // forward W pieces by the k row as far as a row has pieces, TRANS W pieces by a quarter of the column, so that the 16 pieces of A that one read takes at
-// a time, or the 16 k rows of one piece of W, lie on different ones of the 64 banks.  Forward no bank conflict is counted; TRANS reads half of a 16-byte piece at a time, and these reads conflict,
-// 1.1 - 2.1 million cycles over all compute units in a launch of 60 us at the shapes below.
+// a time, or the 16 k rows of one piece of W, lie on different ones of the 64 banks.  No bank conflict is counted in either direction.
 //
 // The order of the instructions is written down, a column of matrix tiles at a time: its products, and beside them a share of the reads of the next part's fragments, the conversion of
 // the next column, and a share of the loads of a later stage.  Left to itself the compiler puts the reads right before their use, and the address arithmetic of the loads in one run of 100
